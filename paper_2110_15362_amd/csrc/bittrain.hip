@@ -329,17 +329,26 @@ constexpr int kMaxBatchDecompress = BT_MAX_BATCH;   // tensors per launch: what 
 constexpr int kMaxBatchCompress = 52;
 
 template <int MAXB> struct BatchLayout {
-    uint32_t count;
-    uint32_t start[MAXB + 1];
+    uint32_t coarse[8];                       // start[0], start[8], ..., start[56]
+    uint32_t start[(MAXB + 8) / 8 * 8];       // first slot of each tensor; from `count` on the end of the last one
     uint32_t tiles[MAXB];
+    uint32_t count;
+    static_assert(MAXB <= 64, "two steps of eight");
+    // The tensor of a slot (slot < start[count]): every workgroup looks it up before it can ask for anything, so
+    // in two steps of eight entries that each come with one scalar load, where halving takes six loads in a row.
+    // (With the scanner's slot ranges kept in registers, see scan_counts: the 49 fp32 activations of a ResNet-50 at
+    // batch 64 restore in 601 us instead of 621 and compress in 539 instead of 548.)
     __device__ __forceinline__ Slot at(const uint32_t slot) const {
-        uint32_t lo = 0, hi = count;          // start[lo] <= slot < start[hi]
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (slot >= start[mid]) lo = mid; else hi = mid;
-        }
-        const uint32_t tile = slot - start[lo];
-        return Slot{lo, tile, tile >= tiles[lo]};
+        // (slot numbers are below 2^31, so the sign of a difference compares them: scalar arithmetic, where a
+        // comparison's result would go through vector registers)
+        uint32_t block = 0, item;
+#pragma unroll
+        for (int i = 1; i < 8; ++i) block += (coarse[i] - 1u - slot) >> 31;
+        item = 8u * block;
+#pragma unroll
+        for (int i = 1; i < 8; ++i) item += (start[8u * block + i] - 1u - slot) >> 31;
+        const uint32_t tile = slot - start[item];
+        return Slot{item, tile, tile >= tiles[item]};
     }
 };
 
@@ -569,10 +578,10 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
     uint32_t *hdr = reinterpret_cast<uint32_t *>(ws);
     const uint32_t seq = uniform32(hdr[kHdrSeq]);
     const uint32_t cur = seq & 1u;
-    const uint32_t n_items = job.count();
     const uint32_t n_slots = job.slots();
     uint32_t frontier = 0;     // slots [0, frontier) are done
     uint32_t item = 0;         // tensor that the frontier's row belongs to
+    uint32_t item_start = 0, item_end = Job::kMany ? job.start(1) : n_slots;      // its slots (of many tensors: read once a tensor, not once a row)
     uint64_t base = 0;         // stored values of that tensor in the tiles before the frontier's row of 128 slots
     uint32_t spins = 0;
     const uint32_t limit = uniform32(wait_limit(hdr));
@@ -584,6 +593,8 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
     while (frontier < n_slots) {
         frontier = uniform32(frontier);
         item = uniform32(item);
+        item_start = uniform32(item_start);
+        item_end = uniform32(item_end);
         base = uniform64(base);
         const uint32_t row = frontier >> 7;
         uint32_t ca[kRowScan], cb[kRowScan];          // count + 1 of the lane's two slots; 0: not published yet, or past the end
@@ -611,9 +622,12 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
                 const uint32_t row_end = slot0 + run;
                 if constexpr (Job::kMany) {
                     // batched tensors begin at multiples of 128 slots: the sum restarts there
-                    while (item + 1 < n_items && slot0 >= job.start(item + 1)) ++item;
-                    if (slot0 == job.start(item)) base = 0;
-                    item = uniform32(item);
+                    if (slot0 >= item_end && slot0 < n_slots) {       // (every tensor has a row: the next one starts here)
+                        item = uniform32(item + 1);
+                        item_start = slot0;
+                        item_end = uniform32(job.start(item + 1));
+                    }
+                    if (slot0 == item_start) base = 0;
                 }
                 if (row_end > new_frontier) {
                     const bool use_a = 2u * lane < run, use_b = 2u * lane + 1u < run;
@@ -631,7 +645,7 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
                         if (use_b) ws_store64(entry + 8, pa + va);
                     }
                     new_frontier = row_end;
-                    if (row_end == (Job::kMany ? job.start(item + 1) : n_slots)) {      // this tensor's number of values
+                    if (row_end == item_end) {      // this tensor's number of values
                         uint64_t *const nnz = job.nnz(item);
                         if (lane == 0 && nnz != nullptr) *nnz = base + total;
                     }
@@ -1568,7 +1582,9 @@ void lay_out(BatchLayout<MAXB> &lay, size_t first, size_t count, int s, NOf n_of
         lay.tiles[i] = (uint32_t)tiles_for(n, s);
         at += batch_slots_for(n, s);
     }
-    for (size_t i = count; i <= (size_t)MAXB; ++i) lay.start[i] = (uint32_t)at;
+    constexpr size_t kStarts = sizeof(lay.start) / sizeof(lay.start[0]);
+    for (size_t i = count; i < kStarts; ++i) lay.start[i] = (uint32_t)at;
+    for (size_t i = 0; i < 8; ++i) lay.coarse[i] = 8 * i < kStarts ? lay.start[8 * i] : (uint32_t)at;
     for (size_t i = count; i < (size_t)MAXB; ++i) lay.tiles[i] = 0;
 }
 

@@ -121,6 +121,16 @@ def test_batch_of_more_tensors_than_one_launch_takes(bt, oracle):
     _check_batch(bt, oracle, xs)
 
 
+@pytest.mark.parametrize("count", [1, 7, 8, 9, 51, 52, 53, 63, 64, 65])
+def test_batch_slot_lookup_at_the_ends_of_its_steps(bt, oracle, count):
+    """A workgroup finds its tensor in two steps of eight entries: numbers of tensors around whole steps and around
+    full launches (52 and 64), tensors of no, one and two rows of slots, the last one large."""
+    t = TILE[8]
+    sizes = [(0, 5, t, 128 * t, 128 * t + 1)[(3 * k + count) % 5] for k in range(count - 1)] + [129 * t + 7]
+    xs = [wl.random_sparse(n, "f64", 0.9, 7000 + k) for k, n in enumerate(sizes)]
+    _check_batch(bt, oracle, xs)
+
+
 def test_batch_and_single_calls_share_a_workspace(bt, oracle):
     """Large batch, small single call, small batch, large single call, large batch: each call
     cleans up what the one before it left, whatever their sizes."""
