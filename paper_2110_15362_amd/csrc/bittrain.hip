@@ -42,6 +42,9 @@ constexpr int kBlock = kWaveSize * kWaves;
 constexpr int kRows = 8;                  // 16-byte loads per lane per tile
 constexpr int kPhaseRows = 4;             // rows that are compacted / expanded through LDS at a time
 constexpr int kVecBytes = 16;
+// LDS of a compressing workgroup: what eight of them on a compute unit leave each other of its 160 KiB, less the
+// words beside the staging area.
+constexpr int kStageBytes = 160 * 1024 / 8 - 64;
 #ifndef BT_RELU_ROWS
 #define BT_RELU_ROWS 1
 #endif
@@ -85,6 +88,7 @@ constexpr uint32_t kPatience = 1u << 12;  // polls before a workgroup counts wha
 #ifndef BT_TILE_SLEEP
 #define BT_TILE_SLEEP 16
 #endif
+constexpr uint32_t kDenseEarlySlots = 1280;      // launches of up to this many slots store a dense output before the prefix is there
 constexpr int kScannerSleep = BT_SCANNER_SLEEP;   // pause between two polls, in units of 64 clocks
 constexpr int kTileSleep = BT_TILE_SLEEP;
 
@@ -97,9 +101,9 @@ template <int S> struct Geo {
     static constexpr int TILE = kWaves * WAVE;       // elements per tile
     static constexpr int TILE_WORDS = TILE / 32;     // bitmap words per tile
     static constexpr int LANE_WORDS = TILE_WORDS / kWaveSize;   // of which a lane counts this many when a wave counts a tile
-    static constexpr int LDS_WAVE = kPhaseRows * ROW * S + 2 * kVecBytes;  // staging bytes per wave: the rows of a phase, the
-                                                                          // shift to a 16-byte boundary, and a vector nobody reads
-    static constexpr int DUMP = (LDS_WAVE - kVecBytes) / S;             // element index of that vector in a wave's strip
+    static constexpr int LDS_WAVE = kPhaseRows * ROW * S + 2 * kVecBytes;  // restoration's staging bytes per wave: the rows of a phase, the
+                                                                          // shift to a 16-byte boundary, and what a read past the last value may touch
+    static constexpr int STAGE = kStageBytes - kVecBytes;               // compression: bytes of a tile's values that fit LDS together (then a vector nobody reads)
     static constexpr int RPM = 32 / E;               // rows whose E-bit lane masks share one register
     static constexpr int MW = (kRows + RPM - 1) / RPM;   // registers that hold a lane's masks
     static_assert(kRows % kPhaseRows == 0 && kPhaseRows % 2 == 0, "rows are scanned two to a register");
@@ -140,6 +144,13 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The lane's number, computed where it is needed instead of kept in a register up to there.
+__device__ __forceinline__ int lane_number() {
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return lane;
+}
+
 // Order LDS traffic between the lanes of one wave (no block barrier involved).
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -158,6 +169,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 // so compress and the ReLU stream use both hints (their input is dead after the call:
 // Algorithm 1 ends by giving the dense tensor up), decompress only the store hint.
 typedef uint32_t bt_u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t bt_u2 __attribute__((ext_vector_type(2)));
 template <bool NT> __device__ __forceinline__ uint4 stream_load(const uint4 *p) {
     if (NT) {
         const bt_u4 v = __builtin_nontemporal_load(reinterpret_cast<const bt_u4 *>(p));
@@ -215,7 +227,7 @@ __device__ __forceinline__ uint32_t keep_mask(const uint4 v, const float thresho
     if (KEEP == kKeepAboveF64) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            m |= (__longlong_as_double((long long)(((uint64_t)d[2 * i + 1] << 32) | d[2 * i])) > threshold_f64 ? 1u : 0u) << i;
+            m |= (__builtin_bit_cast(double, bt_u2{d[2 * i], d[2 * i + 1]}) > threshold_f64 ? 1u : 0u) << i;
     } else if (KEEP == kKeepAboveF32) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) m |= (__uint_as_float(d[i]) > threshold ? 1u : 0u) << i;
@@ -699,14 +711,16 @@ __device__ __forceinline__ Epoch read_epoch(const char *ws) {
     return Epoch{hdr[kHdrSeq] & 1u, hdr[kHdrPrevTiles]};
 }
 
-// Zero what the previous call left in the other copy of the workspace entries: slots
-// [0, prev_slots), shared out over the threads of this call's `workers` workgroups.
-__device__ __forceinline__ void zero_previous(char *ws, const Epoch ep, const uint32_t worker, const uint32_t workers,
-                                              const uint32_t block = kBlock) {
+// Zero what the previous call left in the other copy of the workspace entries: the blocks of slots
+// [0, prev_slots), shared out over this call's `workers` workgroups; a thread takes one slot of a block.
+__device__ __forceinline__ void zero_previous(char *ws, const Epoch ep, const uint32_t worker, const uint32_t workers) {
+    static_assert(kBlock == kSlotsPerBlock, "a thread per slot of a block");
     const uint32_t other = ep.cur ^ 1u;
-    for (uint64_t i = (uint64_t)worker * block + threadIdx.x; i < ep.prev_slots; i += (uint64_t)workers * block) {
-        ws_store32(ws_count(ws, (uint32_t)i, other), 0);
-        ws_store64(ws_prefix(ws, (uint32_t)i, other), 0);
+    for (uint64_t b = worker; b * kSlotsPerBlock < ep.prev_slots; b += workers) {
+        char *const entries = ws + kHeaderBytes + b * kBlockBytes;
+        // (written out, with the uniform part of the addresses in scalar registers: this runs where vector registers are short)
+        asm volatile("global_store_dword %0, %1, %2 sc1" : : "v"(4u * threadIdx.x), "v"(0u), "s"(entries + 1024u * other) : "memory");
+        asm volatile("global_store_dwordx2 %0, %1, %2 sc1" : : "v"(8u * threadIdx.x), "v"((uint64_t)0), "s"(entries + 2048u + 2048u * other) : "memory");
     }
 }
 
@@ -731,42 +745,88 @@ __device__ __forceinline__ void rank_rows(const uint32_t (&mp)[Geo<S>::MW], uint
 
 // ---- Algorithm 1: dense -> bitmap -------------------------------------------------------
 
-// Write `cnt` elements from a wave's LDS strip to global memory with aligned 16-byte
-// stores.  LDS element `pad + i` corresponds to global element g0 + i, where pad makes
-// LDS byte 0 line up with a 16-byte boundary of the global buffer.  The first and
-// last vector go element by element, so nothing outside [g0, g0 + cnt) is touched.
-// All LDS reads of the inner vectors are issued before the first store and the two edge
-// vectors are left to 2 E lanes at the end: this runs after the tile has received its
-// prefix, where every instruction delays the tile's exit.
-template <int S>
-__device__ __forceinline__ void strip_store(const unsigned char *strip, char *g0_ptr, const uint32_t pad,
-                                            const uint32_t cnt, const int lane) {
+// 16 bytes of LDS at an element-aligned byte offset.  The misalignment is the same in all lanes (it is that of the
+// workgroup's place in the value array).
+template <int S> __device__ __forceinline__ uint4 lds_load_shifted(const unsigned char *p, const bool odd_half) {
+    typedef uint32_t dword4 __attribute__((ext_vector_type(4), aligned(4)));
+    if (S == 2 && odd_half) {
+        const uint32_t *q = reinterpret_cast<const uint32_t *>(p - 2);
+        const dword4 v = *reinterpret_cast<const dword4 *>(q);
+        const uint32_t next = q[4];
+        return make_uint4(__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16),
+                          __builtin_amdgcn_alignbit(v.w, v.z, 16), __builtin_amdgcn_alignbit(next, v.w, 16));
+    }
+    const dword4 v = *reinterpret_cast<const dword4 *>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// Write `cnt` elements to gdst with aligned 16-byte stores of kThreads threads (`t`: this one's number).  kPlaced: they
+// lie in LDS from element `pad` of `run` on, pad being gdst's distance from the 16-byte boundary before it.  Otherwise
+// they lie from the start of `run` on, as they do when they are compacted before the prefix tells what gdst is, and
+// LDS is read at the shift that lines up with gdst.  The first and
+// the last vector go element by element, so nothing outside [gdst, gdst + cnt) is touched.  All LDS reads of the inner
+// vectors are issued before the first store and the two edge vectors are left to 2 E threads at the end: this runs
+// after the tile has received its prefix, where every instruction delays the tile's exit.
+template <int S, int kThreads, int kMaxBytes, bool kPlaced>
+__device__ __forceinline__ void run_store(const unsigned char *run, char *gdst, const uint32_t cnt, const int t) {
     constexpr int E = Geo<S>::E;
-    static_assert(kPhaseRows * Geo<S>::ROW / E + 1 <= 2 + 4 * kWaveSize, "a phase must fit four inner vectors per lane");
+    constexpr int kSteps = (kMaxBytes / kVecBytes + kThreads - 1) / kThreads;      // inner vectors a thread (at most kMaxBytes / 16 - 1 in all)
     if (cnt == 0) return;
-    char *gvec = g0_ptr - (size_t)pad * S;      // 16-byte aligned; may start before g0
+    const uint32_t pad = (uint32_t)(reinterpret_cast<uintptr_t>(gdst) & (kVecBytes - 1)) / S;   // elements
+    char *const gvec = gdst - (size_t)pad * S;  // 16-byte aligned; may start before gdst
     const uint32_t hi_valid = pad + cnt;
     const uint32_t n_vec = (hi_valid + E - 1) / E;
-    // the inner vectors (all but the first and the last: at most 255, wholly inside the range), four to a lane
-    uint4 t[4];
+    const uint32_t shift = kPlaced ? 0u : pad;
+    const bool odd_half = S == 2 && (shift & 1u) != 0;
+    uint4 x[kSteps];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t v = 1u + (uint32_t)lane + (uint32_t)kWaveSize * i;
-        if (v + 1 < n_vec) t[i] = *reinterpret_cast<const uint4 *>(strip + (size_t)v * kVecBytes);
+    for (int i = 0; i < kSteps; ++i) {
+        const uint32_t v = 1u + (uint32_t)t + (uint32_t)kThreads * i;
+        if (v + 1 < n_vec)
+            x[i] = kPlaced ? *reinterpret_cast<const uint4 *>(run + (size_t)v * kVecBytes) : lds_load_shifted<S>(run + (v * E - shift) * S, odd_half);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t v = 1u + (uint32_t)lane + (uint32_t)kWaveSize * i;
-        if (v + 1 < n_vec) stream_store<kCompressNtStore>(reinterpret_cast<uint4 *>(gvec + (size_t)v * kVecBytes), t[i]);
+    for (int i = 0; i < kSteps; ++i) {
+        const uint32_t v = 1u + (uint32_t)t + (uint32_t)kThreads * i;
+        if (v + 1 < n_vec) stream_store<kCompressNtStore>(reinterpret_cast<uint4 *>(gvec + (size_t)v * kVecBytes), x[i]);
     }
-    // the first and the last vector, an element a lane: lane j < E element j of the first, lane E + j element j
+    // the first and the last vector, an element a thread: thread j < E element j of the first, thread E + j element j
     // of the last, each only if it lies inside [pad, pad + cnt)
-    if (lane < 2 * E) {
-        const uint32_t e = lane < E ? (uint32_t)lane : (n_vec - 1) * E + (uint32_t)(lane - E);
-        if (e >= pad && e < hi_valid && (lane < E || n_vec > 1)) {
-            if (S == 8) reinterpret_cast<uint64_t *>(gvec)[e] = reinterpret_cast<const uint64_t *>(strip)[e];
-            else if (S == 4) reinterpret_cast<uint32_t *>(gvec)[e] = reinterpret_cast<const uint32_t *>(strip)[e];
-            else reinterpret_cast<uint16_t *>(gvec)[e] = reinterpret_cast<const uint16_t *>(strip)[e];
+    if (t < 2 * E) {
+        const uint32_t e = t < E ? (uint32_t)t : (n_vec - 1) * E + (uint32_t)(t - E);
+        if (e >= pad && e < hi_valid && (t < E || n_vec > 1)) {
+            if (S == 8) reinterpret_cast<uint64_t *>(gvec)[e] = reinterpret_cast<const uint64_t *>(run)[e - shift];
+            else if (S == 4) reinterpret_cast<uint32_t *>(gvec)[e] = reinterpret_cast<const uint32_t *>(run)[e - shift];
+            else reinterpret_cast<uint16_t *>(gvec)[e] = reinterpret_cast<const uint16_t *>(run)[e - shift];
+        }
+    }
+}
+
+// Put the kept elements of one row of a wave into LDS: lane by lane from byte `rb` before `dump` on, in element order.
+// Every element is written, a dropped one to `dump`, a place nobody reads: a select on the address instead of
+// a branch around the write keeps the execution mask alone.
+template <int S> __device__ __forceinline__ void scatter_row(unsigned char *const dump, int rb, const uint32_t mk, const uint4 x) {
+    const uint32_t d[4] = {x.x, x.y, x.z, x.w};
+    if (S == 8) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int keep = (int)((mk >> j) & 1u);
+            *reinterpret_cast<bt_u2 *>(dump + __mul24(keep, rb)) = bt_u2{d[2 * j], d[2 * j + 1]};
+            rb += keep * S;
+        }
+    } else if (S == 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int keep = (int)((mk >> j) & 1u);
+            *reinterpret_cast<uint32_t *>(dump + __mul24(keep, rb)) = d[j];
+            rb += keep * S;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int keep = (int)((mk >> j) & 1u);
+            *reinterpret_cast<uint16_t *>(dump + __mul24(keep, rb)) = (uint16_t)(d[j >> 1] >> (16 * (j & 1)));
+            rb += keep * S;
         }
     }
 }
@@ -794,10 +854,18 @@ __device__ __forceinline__ uint64_t prefix_from_input(const void *__restrict__ i
 // 2. the test of Algorithm 1 (on the bit pattern), or the pruning test; masks packed RPM rows to a register;
 //    ranks by one DPP wave prefix sum per two rows.
 // 3. bitmap words: G lanes OR their E-bit masks into one 32-bit word.
-// 4. the waves' totals meet in LDS, the tile's count is published, the first wave polls the tile's prefix.
-// 5. values: kPhaseRows rows at a time, the wave compacts its kept elements into its LDS strip at their ranks,
-//    shifted so that LDS byte 0 maps to a 16-byte boundary of the value array, and writes the strip out with
-//    aligned stores; then the dense pruned tensor, if asked for.
+// 4. the waves' totals meet in LDS and the tile's count is published.  While the prefix is on its way the kept elements
+//    are compacted in LDS at their ranks (all of them if the tile's values fit, as they do up to 62 % non-zero elements;
+//    else each wave's first rows) and the waves that do not poll store their bitmap words; then the first wave polls.
+// 5. values: with the prefix known, the compacted run is read back at the shift that lines it up with a 16-byte boundary
+//    of the value array and written with aligned stores, by the whole workgroup; a tile that did not fit goes
+//    kPhaseRows rows at a time, each wave its own.
+// What bounds it: the memory system on large tensors (fp32, 205 M elements: 6.2 TB/s), the chain load, count, scan,
+// prefix, store on ordinary ones, so what follows the prefix is kept short.  Compacting before the wait instead of
+// after it measured, us: configuration 2 (fp32, 25.7 M elements, 50 % zeros) 30.7 -> 29.5, at 90 % zeros 26.5 -> 24.9;
+// bf16 67 M elements at 65 % zeros 37.1 -> 35.2; fp16 206 M elements at 95 % zeros 88.9 -> 83.0, at 5 % 138.1 (does not fit)
+// -> 138.1; fp64 25.7 M 54.9 -> 53.4; the 49 tensors of a ResNet-50 539 -> 524; activation call fp32 5.5 M 13.4 -> 11.5.
+// The staging area is what eight workgroups leave each other of a compute unit's 160 KiB: more would cost occupancy.
 // The workgroup ends with its stores on their way: nothing waits for them to land.  (A persistent version
 // of this kernel -- as many workgroups as are resident, each taking tiles w, w + G, ..., the next tile's loads
 // asked for before the current tile's prefix wait, compacted values parked in rings in LDS -- was built and
@@ -806,7 +874,7 @@ template <int S, int KEEP, bool DENSE, class Job>
 __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Job job, char *ws, const double threshold, const float threshold_f) {
     using G = Geo<S>;
     constexpr int E = G::E;
-    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kWaves * G::LDS_WAVE];
+    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kStageBytes];
     __shared__ uint64_t s_tile_prefix;
     __shared__ uint32_t s_wave_total[kWaves];
     if (workspace_failed(ws)) return;
@@ -894,7 +962,7 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
                 const uint32_t w = group_or<G::G>(BT_MASK(S, mp, k) << (uint32_t)(E * i));
                 if (i == k - r0) word[r0 / G::G] = w;
                 // finish this row's word now: left alone, the compiler sinks the selects below
-                // the wait in (4) and keeps one partial result per row alive across it
+                // the compaction in (4) and keeps one partial result per row alive across it
                 asm volatile("" : "+v"(word[r0 / G::G]));
             }
         }
@@ -909,13 +977,6 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
             if (r0 + i < kRows && widx < n_words) bitmap[widx] = word[r0 / G::G];
         }
     };
-    // Before the wait of (4) or after it?  After is better (a store in flight delays the polling loads, which share
-    // its completion counter: 3 % on fp32), but the words cost registers across the wait, and kernels for 16-bit
-    // elements have none to spare: there a spilled value would come back from memory right behind the value stores
-    // and wait for them (7 %).
-    constexpr bool kWordsEarly = S == 2;
-    if (kWordsEarly) store_words();
-
     // (4)
     // written at the end of the previous call; constant until every slot of this call has published
     const Epoch ep = read_epoch(ws);
@@ -931,98 +992,15 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
         tile_total += c;
     }
     before_wave = uniform32(before_wave);       // the same in every lane: tell the compiler, so that addresses built on it stay scalar
+    tile_total = uniform32(tile_total);
     if (tid == 0) ws_store32(ws_count(ws, slot, cur), tile_total + 1);
     BT_TL(slot, 1);
     zero_previous(ws, Epoch{cur, prev_slots}, slot, n_slots);
-    uint32_t polls = 0;
-    if (wave == 0) {
-        uint64_t v;
-        for (;;) {
-            v = uniform64(ws_load64(ws_prefix(ws, slot, cur)));
-            ++polls;
-            if (v != 0) { v -= 1; break; }
-            if (__builtin_expect((polls & 255u) == 0 && polls > patience_of(hdr), 0)) {
-                // Count for ourselves.  The loop needs registers and the tile's elements fill them: park the elements
-                // in LDS meanwhile (the strips are not in use before the barrier below).
-                static_assert(kRows * kWaveSize * kVecBytes <= kWaves * G::LDS_WAVE, "room to park a wave's elements");
-                uint4 *const park = reinterpret_cast<uint4 *>(s_stage) + lane;
-#pragma unroll
-                for (int k = 0; k < kRows; ++k) park[k * kWaveSize] = x[k];
-                v = prefix_from_input<S, KEEP>(in, tile, threshold_f, threshold, lane);
-#pragma unroll
-                for (int k = 0; k < kRows; ++k) x[k] = park[k * kWaveSize];
-                break;
-            }
-            __builtin_amdgcn_s_sleep(kTileSleep);
-        }
-        if (lane == 0) {
-            s_tile_prefix = v;
-            uint64_t *const index = job.index(sl.item);
-            if (index != nullptr) index[tile] = v;     // Algorithm 2's j at the start of this tile, for bt_decompress_indexed
-        }
-    }
-    lds_barrier();
-    uint64_t g0 = uniform64(s_tile_prefix) + before_wave;          // index in the value array of this wave's next value
-    BT_TL(slot, 2);
-    BT_TL_VALUE(slot, 5, polls);
-    if (!kWordsEarly) store_words();
 
-    // (5)
-    unsigned char *strip = s_stage + wave * G::LDS_WAVE;
-    const uint64_t values_cap = job.cap(sl.item);
-#pragma unroll
-    for (int r0 = 0; r0 < kRows; r0 += kPhaseRows) {
-        char *gdst = static_cast<char *>(job.values(sl.item)) + g0 * S;
-        const uint32_t pad = (uint32_t)(reinterpret_cast<uintptr_t>(gdst) & (kVecBytes - 1)) / S;   // elements
-        if (r0 != 0) wave_lds_sync();   // the previous phase's reads are done before the strip is reused
-        uint32_t row_start = pad;
-#pragma unroll
-        for (int k = r0; k < r0 + kPhaseRows; ++k) {
-            // byte offset of this lane's next kept element from the spare vector (negative: the strip lies before it)
-            int rb = ((int)(row_start + BT_FIELD(rank2, k)) - G::DUMP) * S;
-            unsigned char *const dump = strip + G::DUMP * S;
-            const uint32_t mk = BT_MASK(S, mp, k);
-            const uint32_t d[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
-            // every element is written, a dropped one to a place nobody reads: a select on the address instead of
-            // a branch around the write keeps the execution mask alone
-            if (S == 8) {
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int keep = (int)((mk >> j) & 1u);
-                    *reinterpret_cast<uint64_t *>(dump + __mul24(keep, rb)) = ((uint64_t)d[2 * j + 1] << 32) | d[2 * j];
-                    rb += keep * S;
-                }
-            } else if (S == 4) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int keep = (int)((mk >> j) & 1u);
-                    *reinterpret_cast<uint32_t *>(dump + __mul24(keep, rb)) = d[j];
-                    rb += keep * S;
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int keep = (int)((mk >> j) & 1u);
-                    *reinterpret_cast<uint16_t *>(dump + __mul24(keep, rb)) = (uint16_t)(d[j >> 1] >> (16 * (j & 1)));
-                    rb += keep * S;
-                }
-            }
-            row_start += BT_FIELD(total2, k);
-        }
-        wave_lds_sync();
-        const uint32_t phase_total = row_start - pad;
-        // capacity clamp: never write at or beyond values_cap
-        uint32_t cnt = phase_total;
-        if (g0 >= values_cap) cnt = 0;
-        else if (values_cap - g0 < cnt) cnt = (uint32_t)(values_cap - g0);
-        strip_store<S>(strip, gdst, pad, cnt, lane);
-        g0 += phase_total;
-    }
-
-    // the dense tensor after pruning, if asked for (bt_activation_compress): what survives keeps its bits, the
-    // rest is +0.  Last, so that no store precedes the polling loads of (4); the dense output may be the input
-    // itself (every lane rewrites exactly the vectors it has read).
-    if (DENSE) {
+    // What needs no prefix is done while it is on its way.
+    // The dense tensor after pruning, if asked for (bt_activation_compress): what survives keeps its bits, the
+    // rest is +0.  The dense output may be the input itself (every lane rewrites exactly the vectors it has read).
+    const auto store_dense = [&]() __attribute__((always_inline)) {
         void *const dense = job.dense(sl.item);
 #pragma unroll
         for (int k = 0; k < kRows; ++k) {
@@ -1045,6 +1023,88 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
             if (full) stream_store<kCompressNtStore>(reinterpret_cast<uint4 *>(static_cast<char *>(dense) + e0 * S), o);
             else store_vec_guarded<S>(dense, e0, n, o);
         }
+    };
+    // Before the wait or after it?  Before, the stores use memory that would idle while the prefixes of a small launch are
+    // on their way, but the polling wave waits for its own first; in a launch that keeps the memory busy they only hold
+    // up everybody's polls and values.  Measured, before / after, us: fp32 8 M elements (977 tiles) 14.9 / 16.1, 12 M (1465
+    // tiles) 23.2 / 22.0, 25.7 M 48.2 / 45.1; bf16 16 M (977) 16.4 / 17.9, 24 M (1465) 23.2 / 23.9, 32 M (1954) 30.8 / 28.4.
+    const bool dense_early = DENSE && n_slots <= kDenseEarlySlots;
+    if (dense_early) store_dense();
+    // The bitmap words; the wave that polls keeps its own until afterwards, because a store in flight delays the polling
+    // loads, which share its completion counter.  (For 16-bit elements it has no register to keep them in.)
+    const bool words_early = S == 2 || dense_early || wave != 0;
+    if (words_early) store_words();
+
+    // The values: if the tile's fit LDS together (62 % of its elements: most activations), all of them are compacted into
+    // one run now; if not, each wave's first kPhaseRows rows into a strip of its own.
+    const bool staged = tile_total * S <= (uint32_t)G::STAGE;
+    constexpr int kStrip = kPhaseRows * G::ROW * S + kVecBytes;      // the rows, and the shift to a 16-byte boundary
+    static_assert(kWaves * kStrip <= G::STAGE, "the waves' strips share the staging area");
+    const int run0 = staged ? (int)(before_wave * S) : wave * kStrip;      // byte offset of this wave's first value
+    uint32_t row_start = 0;                                                // kept elements of the wave in the rows before
+    const auto scatter = [&](const int k, const int from) __attribute__((always_inline)) {
+        // byte offset of this lane's next kept element from the spare vector (negative: the values lie before it)
+        const int rb = from + (int)((row_start + BT_FIELD(rank2, k)) * S) - G::STAGE;
+        uint32_t mk = BT_MASK(S, mp, k);
+        asm volatile("" : "+v"(mk));      // (a row's work starts here: nothing of it is done ahead, registers are short)
+        scatter_row<S>(s_stage + G::STAGE, rb, mk, make_uint4(x[k].x, x[k].y, x[k].z, x[k].w));
+        row_start += BT_FIELD(total2, k);
+    };
+#pragma unroll
+    for (int k = 0; k < kPhaseRows; ++k) scatter(k, run0);
+    const uint32_t first_total = row_start;
+    if (staged) {
+#pragma unroll
+        for (int k = kPhaseRows; k < kRows; ++k) scatter(k, run0);
+    }
+
+    // The first wave waits for the tile's prefix.
+    uint32_t polls = 0;
+    if (wave == 0) {
+        uint64_t v;
+        for (;;) {
+            v = uniform64(ws_load64(ws_prefix(ws, slot, cur)));
+            ++polls;
+            if (v != 0) { v -= 1; break; }
+            if (__builtin_expect((polls & 255u) == 0 && polls > patience_of(hdr), 0)) {      // count for ourselves
+                v = prefix_from_input<S, KEEP>(in, tile, threshold_f, threshold, lane_number());
+                break;
+            }
+            __builtin_amdgcn_s_sleep(kTileSleep);
+        }
+        if (lane_number() == 0) {
+            s_tile_prefix = v;
+            uint64_t *const index = job.index(sl.item);
+            if (index != nullptr) index[tile] = v;     // Algorithm 2's j at the start of this tile, for bt_decompress_indexed
+        }
+    }
+    lds_barrier();
+    const uint64_t tile_g0 = uniform64(s_tile_prefix);         // index in the value array of the tile's first value
+    BT_TL(slot, 2);
+    BT_TL_VALUE(slot, 5, polls);
+    if (!words_early) store_words();
+    if (DENSE && !dense_early) store_dense();
+
+    // (5)
+    const uint64_t values_cap = job.cap(sl.item);
+    // capacity clamp: never write at or beyond values_cap
+    const auto room = [&](const uint64_t g0, const uint32_t cnt) {
+        return g0 >= values_cap ? 0u : values_cap - g0 < cnt ? (uint32_t)(values_cap - g0) : cnt;
+    };
+    char *const values = static_cast<char *>(job.values(sl.item));
+    if (staged) {
+        run_store<S, kBlock, G::STAGE, false>(s_stage, values + tile_g0 * S, room(tile_g0, tile_total), wave * kWaveSize + lane_number());
+    } else {
+        unsigned char *const strip = s_stage + wave * kStrip;
+        const uint64_t g0 = tile_g0 + before_wave, g1 = g0 + first_total;
+        run_store<S, kWaveSize, kPhaseRows * G::ROW * S, false>(strip, values + g0 * S, room(g0, first_total), lane_number());
+        wave_lds_sync();                // the first phase's reads are done before the strip is reused
+        row_start = 0;
+        const int pad = (int)(reinterpret_cast<uintptr_t>(values + g1 * S) & (kVecBytes - 1));
+#pragma unroll
+        for (int k = kPhaseRows; k < kRows; ++k) scatter(k, wave * kStrip + pad);
+        wave_lds_sync();
+        run_store<S, kWaveSize, kPhaseRows * G::ROW * S, true>(strip, values + g1 * S, room(g1, row_start), lane_number());
     }
     BT_TL(slot, 3);
 }

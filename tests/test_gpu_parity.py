@@ -291,6 +291,51 @@ def test_repeated_calls_are_identical(gpu, oracle):
         assert torch.equal(out.view(torch.int16), xd.view(torch.int16))
 
 
+@pytest.mark.parametrize("dt", DTYPES)
+def test_compress_tiles_around_the_staging_limit(gpu, oracle, dt):
+    """A tile whose values fit the staging area is compacted into one run before its prefix is known, a fuller one in
+    two phases per wave: numbers of kept elements around that limit, at every alignment of the value array, in front of and
+    behind tiles of the other kind, whole and cut off by the capacity."""
+    width = {"f32": 4, "f16": 2, "bf16": 2, "f64": 8}[dt]
+    tile = 32768 // width
+    limit = (160 * 1024 // 8 - 64 - 16) // width
+    rng = np.random.RandomState(31 + width)
+
+    def one(kept):
+        x = torch.zeros(tile, dtype=wl.DTYPES[dt])
+        at = torch.from_numpy(rng.permutation(tile)[:kept].copy())
+        x[at] = wl.random_sparse(kept, dt, 0.0, seed=kept) if kept else x[at]
+        return x
+    for i, kept in enumerate([(limit,), (limit + 1,), (limit - 1, tile), (tile, limit), (tile - 1, limit + 1, 3, limit), (0, limit + 2)]):
+        x = torch.cat([one(k) for k in kept] + [wl.random_sparse(777, dt, 0.5, seed=i)])
+        nnz = int((torch.from_numpy(wl.bits(x).astype(np.int64)) != 0).sum())
+        for offset in range(16 // width):
+            _check_compress(gpu, oracle, x, values_offset=offset)
+        for cap in (nnz // 2 + 1, nnz - 3, 5):
+            _check_compress(gpu, oracle, x, cap=cap, values_offset=1)
+
+
+@pytest.mark.parametrize("tiles", [1279, 1280, 1281])
+def test_activation_compress_around_the_size_where_the_dense_output_moves(gpu, oracle, tiles):
+    """Launches of up to 1280 tiles store the dense output before the prefixes are there, larger ones after."""
+    import paper_2110_15362_amd.bittrain as bt
+    n = tiles * 4096 - 5
+    x = wl.random_sparse(n, "f64", 0.3, seed=tiles)
+    want = oracle.prune(wl.bits(x), "f64", 0.0)
+    o_bitmap, o_values, o_nnz = oracle.compress(want)
+    for inplace in (False, True):
+        xd = x.cuda()
+        dense = xd if inplace else torch.empty_like(xd)
+        bitmap = torch.empty((n + 31) // 32, dtype=torch.int32, device="cuda")
+        values, nnz = torch.empty_like(xd), torch.zeros(1, dtype=torch.int64, device="cuda")
+        bt.bt_activation_compress(xd, 0.0, dense, bitmap, values, nnz, bt.new_workspace(n, x.dtype))
+        torch.cuda.synchronize()
+        assert int(nnz.item()) == o_nnz
+        assert np.array_equal(wl.bits(dense.cpu()), want)
+        assert np.array_equal(bitmap.cpu().numpy().view(np.uint32), o_bitmap)
+        assert np.array_equal(wl.bits(values[:o_nnz].cpu()), o_values)
+
+
 # ---- activation pruning fused into compression (Section 4.3) ------------------------------
 
 
