@@ -104,7 +104,8 @@ const char *bt_status_str(bt_status status);
  *                           bt_workspace_status).  The outputs of that call are not valid (nnz
  *                           in particular is not written), and later calls on the workspace
  *                           write nothing at all, until bt_workspace_init has been run on it again.
- *   BT_WS_WAIT_LIMIT_WORD   passes of the grid scan after which it gives up; 0 (the initial
+ *   BT_WS_WAIT_LIMIT_WORD   passes of the grid scan after which it gives up (where a call on a small
+ *                           tensor has none: polls of its last tile); 0 (the initial
  *                           state) means the built-in limit of 2^20, far beyond what any
  *                           tensor needs.  Written by the caller only (a device-side store
  *                           or copy ordered before the call); meant for tests of the

@@ -315,6 +315,56 @@ def test_compress_tiles_around_the_staging_limit(gpu, oracle, dt):
             _check_compress(gpu, oracle, x, cap=cap, values_offset=1)
 
 
+def _plan_edges(width):
+    """Numbers of elements around which the library changes how it launches a call on a small tensor: compression at 64 tiles
+    of two rows, 256 of four and 256 of eight (a row is 4 KiB a tile), restoration at 256 of two and of four."""
+    row = 4096 // width
+    return sorted({tiles * rows * row + d for tiles, rows in ((1, 2), (64, 2), (256, 2), (256, 4), (256, 8)) for d in (-1, 0, 1)})
+
+
+@pytest.mark.parametrize("dt", DTYPES)
+def test_small_launches_at_the_edges_of_their_plans(gpu, oracle, dt):
+    """Both directions on either side of every change of plan, all on one workspace and in an order that mixes the plans, so
+    that each finds what another left there; misaligned values; pruning; the calls are counted."""
+    import paper_2110_15362_amd.bittrain as bt
+    sizes = _plan_edges({"f32": 4, "f16": 2, "bf16": 2, "f64": 8}[dt])
+    ws = bt.new_workspace(max(sizes), wl.DTYPES[dt])
+    calls = 0
+    for i, n in enumerate(sizes[::2] + sizes[1::2][::-1]):
+        x = wl.random_sparse(n, dt, (0.5, 0.1, 0.93)[i % 3], seed=600 + i)
+        o_bitmap, o_values, o_nnz = _check_compress(gpu, oracle, x, ws=ws, values_offset=i % 4)
+        _check_decompress(gpu, oracle, o_bitmap, o_values, n, x.dtype, wl.bits(x), ws=ws, values_offset=(i + 1) % 4)
+        p_bitmap, p_values, p_nnz = oracle.compress(oracle.prune(wl.bits(x), dt, 0.2))
+        bitmap, values, nnz, tail_ok = gpu.gpu_compress(x, ws=ws, threshold=0.2, cap=p_nnz // 2)
+        assert tail_ok and nnz == p_nnz and np.array_equal(bitmap, p_bitmap) and np.array_equal(values, p_values[:p_nnz // 2])
+        calls += 3
+    status = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+    bt.bt_workspace_status(ws, status)
+    assert status.tolist() == [0, calls]
+
+
+def test_a_small_launch_whose_wait_runs_out_ends(gpu, oracle):
+    """Forced from the host: one poll for the last tile of a launch without a scanner.  Whether the counts are there by then
+    is up to the machine; the call must end inside its buffers, and either be right or say that it gave up."""
+    import paper_2110_15362_amd.bittrain as bt
+    n = 200 * 8192
+    x = wl.random_sparse(n, "f32", 0.5, seed=77)
+    o_bitmap, o_values, o_nnz = oracle.compress(wl.bits(x))
+    ws = bt.new_workspace(n, torch.float32)
+    words = ws.view(torch.int32)
+    words[bt.BT_WS_WAIT_LIMIT_WORD] = 1
+    bitmap, values, nnz, tail_ok = gpu.gpu_compress(x, ws=ws)
+    assert tail_ok
+    if int(words[bt.BT_WS_ERROR_WORD].item()) == 0:
+        assert nnz == o_nnz and np.array_equal(bitmap, o_bitmap) and np.array_equal(values[:o_nnz], o_values)
+    else:
+        assert nnz == -7, "nnz of a failed call"
+        out, guard_ok = gpu.gpu_decompress(o_bitmap[:1], o_values, 32, torch.float32, ws=ws)
+        assert guard_ok and (out == 0x5A5A5A5A).all(), "a failed workspace takes no work"
+    bt.bt_workspace_init(ws)
+    _check_compress(gpu, oracle, x, ws=ws)
+
+
 @pytest.mark.parametrize("tiles", [1279, 1280, 1281])
 def test_activation_compress_around_the_size_where_the_dense_output_moves(gpu, oracle, tiles):
     """Launches of up to 1280 tiles store the dense output before the prefixes are there, larger ones after."""
