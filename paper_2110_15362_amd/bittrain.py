@@ -1,7 +1,7 @@
 """Thin binding over the C-ABI library ``libbittrain.so``.
 
-Argument marshalling only: every step of the codec runs in the HIP kernels of
-the library.  PyTorch supplies device memory and the stream, nothing else.
+Argument marshalling only (that of the single-tensor calls in C, ``csrc/call.c``): every step of the codec
+runs in the HIP kernels of the library.  PyTorch supplies device memory and the stream, nothing else.
 There is no CPU fallback: if the library is missing, or a call fails, this
 module raises.
 """
@@ -12,6 +12,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbittrain.so")
+CALL_PATH = os.path.join(_HERE, "_call.so")
 
 BT_F32, BT_F16, BT_BF16, BT_F64 = 0, 1, 2, 3
 # 32-bit words of a workspace that a caller may look at (BT_WS_* of the C header)
@@ -25,6 +26,10 @@ BT_MAX_ELEMENTS = 1 << 37
 _DTYPES = {torch.float32: BT_F32, torch.float16: BT_F16, torch.bfloat16: BT_BF16, torch.float64: BT_F64}
 
 _lib = None
+_call = None      # the single-tensor calls, checked and marshalled in C; bound to the library that lib() has loaded
+# the library's functions behind it, in the order of the table in csrc/call.c
+_CALLS = ("bt_compress", "bt_compress_static", "bt_compress_pruned", "bt_activation_compress", "bt_compress_indexed",
+          "bt_decompress", "bt_decompress_indexed", "bt_relu_backward_from_bitmap", "bt_mask_apply", "bt_index_bytes")
 
 
 class BitTrainError(RuntimeError):
@@ -48,10 +53,10 @@ class DecompressItem(ctypes.Structure):
 
 def lib():
     """The loaded library; raises if it has not been built."""
-    global _lib
+    global _lib, _call
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError("libbittrain.so is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
+        if not os.path.exists(LIB_PATH) or not os.path.exists(CALL_PATH):
+            raise RuntimeError("libbittrain.so or _call.so is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
                                "(there is no CPU fallback)")
         L = ctypes.CDLL(LIB_PATH)
         u64, sz, vp, ci = ctypes.c_uint64, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_int
@@ -95,7 +100,11 @@ def lib():
         L.bt_decompress_batch_indexed.argtypes = [ctypes.POINTER(DecompressItem), sz, ci, vp]
         L.bt_workspace_status.restype = ci
         L.bt_workspace_status.argtypes = [vp, vp, vp]
-        _lib = L
+        from . import _call as call
+        call.bind(tuple(ctypes.cast(getattr(L, f), vp).value for f in _CALLS), _DTYPES, dtype_code, BitTrainError, _stream_handle,
+                  getattr(torch._C, "_cuda_getDevice", None),
+                  getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None)
+        _lib, _call = L, call
     return _lib
 
 
@@ -134,10 +143,14 @@ def bt_workspace_bytes(n, dtype):
     return int(lib().bt_workspace_bytes(n, dtype if isinstance(dtype, int) else dtype_code(dtype)))
 
 
-def _stream(stream):
+def _stream_handle(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _stream(stream):
+    return ctypes.c_void_p(_stream_handle(stream))
 
 
 def _ptr(t):
@@ -173,73 +186,34 @@ def bt_compress(x, bitmap, values, nnz, workspace, stream=None):
     """Algorithm 1 on device tensors.  x: dense tensor (any shape, contiguous);
     bitmap: int32[ceil(n/32)]; values: x.dtype[cap]; nnz: int64[1]; all on x's
     device.  Enqueues on the stream and returns; nothing is synchronised."""
-    for t, name in ((x, "x"), (bitmap, "bitmap"), (values, "values"), (nnz, "nnz"), (workspace, "workspace")):
-        _dev(t, name)
-    if values.dtype != x.dtype:
-        raise TypeError("values must have the dtype of x")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(x.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    if nnz.element_size() != 8 or nnz.numel() < 1:
-        raise ValueError("nnz must be one 64-bit integer")
-    _check("bt_compress", lib().bt_compress(
-        _ptr(x), x.numel(), dtype_code(x.dtype), _ptr(bitmap), _ptr(values), values.numel(), _ptr(nnz),
-        _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+    lib()
+    _call.compress(x, bitmap, values, nnz, workspace, stream)
 
 
 def bt_compress_static(x, bitmap, values, nnz, stream=None):
     """bt_compress on the library's own workspace (nothing is allocated by the call); x of at
     most BT_STATIC_MAX_TILES tiles.  Calls on one GPU share that workspace: keep them ordered."""
-    for t, name in ((x, "x"), (bitmap, "bitmap"), (values, "values"), (nnz, "nnz")):
-        _dev(t, name)
-    if values.dtype != x.dtype:
-        raise TypeError("values must have the dtype of x")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(x.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    if nnz.element_size() != 8 or nnz.numel() < 1:
-        raise ValueError("nnz must be one 64-bit integer")
-    _check("bt_compress_static", lib().bt_compress_static(
-        _ptr(x), x.numel(), dtype_code(x.dtype), _ptr(bitmap), _ptr(values), values.numel(), _ptr(nnz), _stream(stream)))
+    lib()
+    _call.compress_static(x, bitmap, values, nnz, stream)
 
 
 def bt_compress_pruned(x, threshold, bitmap, values, nnz, workspace, stream=None):
     """Section 4.3 fused into Algorithm 1: keep x[i] where x[i] > threshold (ReLU for
     threshold 0 on a pre-activation tensor).  Same buffers as bt_compress."""
-    for t, name in ((x, "x"), (bitmap, "bitmap"), (values, "values"), (nnz, "nnz"), (workspace, "workspace")):
-        _dev(t, name)
-    if values.dtype != x.dtype:
-        raise TypeError("values must have the dtype of x")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(x.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    if nnz.element_size() != 8 or nnz.numel() < 1:
-        raise ValueError("nnz must be one 64-bit integer")
-    _check("bt_compress_pruned", lib().bt_compress_pruned(
-        _ptr(x), x.numel(), dtype_code(x.dtype), ctypes.c_double(threshold), _ptr(bitmap), _ptr(values), values.numel(),
-        _ptr(nnz), _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+    lib()
+    _call.compress_pruned(x, bitmap, values, nnz, workspace, threshold, stream)
 
 
 def bt_decompress(bitmap, values, out, workspace, stream=None):
     """Algorithm 2 on device tensors: fills `out` (n = out.numel()) from bitmap + values."""
-    for t, name in ((bitmap, "bitmap"), (values, "values"), (out, "out"), (workspace, "workspace")):
-        _dev(t, name)
-    if values.dtype != out.dtype:
-        raise TypeError("values must have the dtype of out")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(out.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    _check("bt_decompress", lib().bt_decompress(
-        _ptr(bitmap), _ptr(values), out.numel(), dtype_code(out.dtype), _ptr(out),
-        _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+    lib()
+    _call.decompress(bitmap, values, out, workspace, stream)
 
 
 def bt_relu_backward_from_bitmap(bitmap, grad_out, grad_in, stream=None):
     """grad_in[i] = bit(i) ? grad_out[i] : +0; grad_in may be grad_out itself."""
-    for t, name in ((bitmap, "bitmap"), (grad_out, "grad_out"), (grad_in, "grad_in")):
-        _dev(t, name)
-    if grad_in.dtype != grad_out.dtype or grad_in.numel() != grad_out.numel():
-        raise TypeError("grad_in must match grad_out")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(grad_out.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    _check("bt_relu_backward_from_bitmap", lib().bt_relu_backward_from_bitmap(
-        _ptr(bitmap), _ptr(grad_out), grad_out.numel(), dtype_code(grad_out.dtype), _ptr(grad_in), _stream(stream)))
+    lib()
+    _call.relu_backward(bitmap, grad_out, grad_in, stream)
 
 
 def bt_batch_workspace_bytes(ns, dtype):
@@ -360,14 +334,8 @@ def bt_decompress_batch(items, count, dtype, workspace, stream=None):
 
 def bt_mask_apply(bitmap, x, out, stream=None):
     """Double mask: out[i] = bit(i) ? x[i] : +0 with the bitmap of another tensor; out may be x."""
-    for t, name in ((bitmap, "bitmap"), (x, "x"), (out, "out")):
-        _dev(t, name)
-    if out.dtype != x.dtype or out.numel() != x.numel():
-        raise TypeError("out must match x")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(x.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    _check("bt_mask_apply", lib().bt_mask_apply(_ptr(bitmap), _ptr(x), x.numel(), dtype_code(x.dtype), _ptr(out),
-                                                _stream(stream)))
+    lib()
+    _call.mask_apply(bitmap, x, out, stream)
 
 
 def bt_tile_elems(dtype):
@@ -380,49 +348,18 @@ def bt_index_bytes(n, dtype):
 
 def bt_compress_indexed(x, bitmap, values, nnz, index, workspace, stream=None):
     """bt_compress that also leaves the tile index (int64[ceil(n / bt_tile_elems)]) for bt_decompress_indexed."""
-    for t, name in ((x, "x"), (bitmap, "bitmap"), (values, "values"), (nnz, "nnz"), (index, "index"),
-                    (workspace, "workspace")):
-        _dev(t, name)
-    if values.dtype != x.dtype:
-        raise TypeError("values must have the dtype of x")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(x.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    if nnz.element_size() != 8 or nnz.numel() < 1:
-        raise ValueError("nnz must be one 64-bit integer")
-    if index.element_size() != 8 or index.numel() * 8 < bt_index_bytes(x.numel(), x.dtype):
-        raise ValueError("index must hold one 64-bit integer per tile")
-    _check("bt_compress_indexed", lib().bt_compress_indexed(
-        _ptr(x), x.numel(), dtype_code(x.dtype), _ptr(bitmap), _ptr(values), values.numel(), _ptr(nnz), _ptr(index),
-        _ptr(workspace), _bytes(workspace), _stream(stream)))
+    lib()
+    _call.compress_indexed(x, bitmap, values, nnz, index, workspace, stream)
 
 
 def bt_decompress_indexed(bitmap, values, index, out, stream=None):
     """Algorithm 2 started at every tile from the tile index: no workspace, no scan."""
-    for t, name in ((bitmap, "bitmap"), (values, "values"), (index, "index"), (out, "out")):
-        _dev(t, name)
-    if values.dtype != out.dtype:
-        raise TypeError("values must have the dtype of out")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(out.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    if index.element_size() != 8 or index.numel() * 8 < bt_index_bytes(out.numel(), out.dtype):
-        raise ValueError("index must hold one 64-bit integer per tile")
-    _check("bt_decompress_indexed", lib().bt_decompress_indexed(
-        _ptr(bitmap), _ptr(values), values.numel(), _ptr(index), out.numel(), dtype_code(out.dtype), _ptr(out),
-        _stream(stream)))
+    lib()
+    _call.decompress_indexed(bitmap, values, index, out, stream)
 
 
 def bt_activation_compress(x, threshold, dense_out, bitmap, values, nnz, workspace, stream=None):
     """One pass over x: dense_out = x where x > threshold else +0 (ReLU for threshold 0; dense_out may be x
     itself), and bitmap / values / nnz = the compressed form of that dense_out."""
-    for t, name in ((x, "x"), (dense_out, "dense_out"), (bitmap, "bitmap"), (values, "values"), (nnz, "nnz"),
-                    (workspace, "workspace")):
-        _dev(t, name)
-    if values.dtype != x.dtype or dense_out.dtype != x.dtype or dense_out.numel() != x.numel():
-        raise TypeError("values and dense_out must match x")
-    if bitmap.element_size() != 4 or bitmap.numel() * 4 < bt_bitmap_bytes(x.numel()):
-        raise ValueError("bitmap must hold ceil(n/32) 32-bit words")
-    if nnz.element_size() != 8 or nnz.numel() < 1:
-        raise ValueError("nnz must be one 64-bit integer")
-    _check("bt_activation_compress", lib().bt_activation_compress(
-        _ptr(x), x.numel(), dtype_code(x.dtype), ctypes.c_double(threshold), _ptr(dense_out), _ptr(bitmap), _ptr(values),
-        values.numel(), _ptr(nnz), _ptr(workspace), _bytes(workspace), _stream(stream)))
+    lib()
+    _call.activation_compress(x, dense_out, bitmap, values, nnz, workspace, threshold, stream)

@@ -1,6 +1,7 @@
-"""Build libbittrain.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Build libbittrain.so for gfx950 with hipcc (cross-compiles without a GPU), and the binding's call module with gcc."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -9,6 +10,9 @@ LIB = os.path.join(HERE, "libbittrain.so")
 # measurement aids for bench.py: the same kernels with per-tile time stamps compiled in, plus a plain stream
 BENCH_SRC = os.path.join(HERE, "csrc", "bench_aids.hip")
 BENCH_LIB = os.path.join(HERE, "libbittrain_bench.so")
+# the calls on torch tensors, checked and marshalled in C
+CALL_SRC = os.path.join(HERE, "csrc", "call.c")
+CALL_LIB = os.path.join(HERE, "_call.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
@@ -29,11 +33,22 @@ def build(verbose=False, extra_flags=(), lib=LIB, src=SRC):
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
         print(out)
+    if lib == LIB:
+        build_call(verbose)
     return lib
 
 
 def build_bench_aids(verbose=False, extra_flags=()):
     return build(verbose=verbose, extra_flags=extra_flags, lib=BENCH_LIB, src=BENCH_SRC)
+
+
+def build_call(verbose=False):
+    cmd = ["gcc", "-std=c11", "-O2", "-Wall", "-Wextra", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), CALL_SRC, "-o", CALL_LIB]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.check_call(cmd)
+    return CALL_LIB
 
 
 if __name__ == "__main__":

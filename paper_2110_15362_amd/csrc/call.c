@@ -1,0 +1,352 @@
+/*
+ * paper_2110_15362_amd/_call.so: the calls of libbittrain on torch tensors, for bittrain.py.
+ *
+ * What a small call costs is the host's work, not the GPU's: the three calls of a training step on one image's
+ * layer (fp32, 200,704 elements) keep the GPU busy for 10 us, and checking the tensors and marshalling the arguments with
+ * ctypes took 5 to 6 us a call on top of the launch's 3.  This module does the same checks in the same
+ * order through the C API of Python: the attributes of the tensors are read as any caller would read them, so it
+ * depends on neither torch's headers nor its binary interface.  The library itself is loaded by bittrain.py,
+ * which hands over the addresses of the calls (bind).
+ */
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+#include <stdint.h>
+
+#include "bittrain.h"
+
+static struct {
+    bt_status (*compress)(const void *, uint64_t, bt_dtype, uint32_t *, void *, uint64_t, uint64_t *, void *, size_t, bt_stream);
+    bt_status (*compress_static)(const void *, uint64_t, bt_dtype, uint32_t *, void *, uint64_t, uint64_t *, bt_stream);
+    bt_status (*compress_pruned)(const void *, uint64_t, bt_dtype, double, uint32_t *, void *, uint64_t, uint64_t *, void *, size_t,
+                                 bt_stream);
+    bt_status (*activation_compress)(const void *, uint64_t, bt_dtype, double, void *, uint32_t *, void *, uint64_t, uint64_t *, void *,
+                                     size_t, bt_stream);
+    bt_status (*compress_indexed)(const void *, uint64_t, bt_dtype, uint32_t *, void *, uint64_t, uint64_t *, uint64_t *, void *, size_t,
+                                  bt_stream);
+    bt_status (*decompress)(const uint32_t *, const void *, uint64_t, bt_dtype, void *, void *, size_t, bt_stream);
+    bt_status (*decompress_indexed)(const uint32_t *, const void *, uint64_t, const uint64_t *, uint64_t, bt_dtype, void *, bt_stream);
+    bt_status (*relu_backward)(const uint32_t *, const void *, uint64_t, bt_dtype, void *, bt_stream);
+    bt_status (*mask_apply)(const uint32_t *, const void *, uint64_t, bt_dtype, void *, bt_stream);
+    size_t (*index_bytes)(uint64_t, bt_dtype);
+} lib;
+
+/* Python objects handed over by bind: {dtype: code}, the function that refuses other dtypes, the error class, the
+ * function that turns a stream argument into a handle, and torch's functions for the current device and its raw stream. */
+static PyObject *dtypes, *dtype_code, *error_class, *stream_handle, *get_device, *get_raw_stream;
+static PyObject *s_is_cuda, *s_is_contiguous, *s_dtype, *s_numel, *s_element_size, *s_data_ptr;
+
+typedef struct {
+    PyObject *t;        /* borrowed */
+    const void *dtype;  /* which object it is, to compare: dtypes are singletons */
+    int code;           /* bt_dtype, or -1 */
+    uint64_t numel, width;
+    void *ptr;
+} tensor;
+
+static int is_true(PyObject *o) {      /* takes the reference; -1: an error is set */
+    if (o == NULL) return -1;
+    const int r = PyObject_IsTrue(o);
+    Py_DECREF(o);
+    return r;
+}
+
+static int to_u64(PyObject *o, uint64_t *v) {
+    if (o == NULL) return -1;
+    *v = PyLong_AsUnsignedLongLong(o);
+    Py_DECREF(o);
+    return *v == (uint64_t)-1 && PyErr_Occurred() ? -1 : 0;
+}
+
+/* The tensor lives in device memory and is contiguous: the first thing that is checked of every argument. */
+static int on_device(tensor *a, PyObject *t, const char *name) {
+    a->t = t;
+    int ok = is_true(PyObject_GetAttr(t, s_is_cuda));
+    if (ok < 0) return -1;
+    if (!ok) {
+        PyErr_Format(PyExc_ValueError, "%s must live in device memory", name);
+        return -1;
+    }
+    ok = is_true(PyObject_CallMethodNoArgs(t, s_is_contiguous));
+    if (ok < 0) return -1;
+    if (!ok) {
+        PyErr_Format(PyExc_ValueError, "%s must be contiguous", name);
+        return -1;
+    }
+    return 0;
+}
+
+/* What the checks and the call need of it. */
+static int describe(tensor *a) {
+    PyObject *const dtype = PyObject_GetAttr(a->t, s_dtype);
+    if (dtype == NULL) return -1;
+    PyObject *const code = PyDict_GetItemWithError(dtypes, dtype);      /* borrowed */
+    a->dtype = dtype;
+    a->code = code != NULL ? (int)PyLong_AsLong(code) : -1;
+    Py_DECREF(dtype);
+    if (PyErr_Occurred()) return -1;
+    uint64_t p;
+    if (to_u64(PyObject_CallMethodNoArgs(a->t, s_numel), &a->numel) != 0 ||
+        to_u64(PyObject_CallMethodNoArgs(a->t, s_element_size), &a->width) != 0 ||
+        to_u64(PyObject_CallMethodNoArgs(a->t, s_data_ptr), &p) != 0)
+        return -1;
+    a->ptr = (void *)(uintptr_t)p;
+    return 0;
+}
+
+static int take(tensor *a, PyObject *const *args, const char *const *names, const int count) {
+    for (int i = 0; i < count; ++i)
+        if (on_device(&a[i], args[i], names[i]) != 0) return -1;
+    for (int i = 0; i < count; ++i)
+        if (describe(&a[i]) != 0) return -1;
+    return 0;
+}
+
+static int fail(PyObject *type, const char *text) {
+    PyErr_SetString(type, text);
+    return -1;
+}
+
+static int check_bitmap(const tensor *bitmap, const uint64_t n) {
+    if (bitmap->width != 4 || bitmap->numel * 4 < 4 * ((n + 31) / 32)) return fail(PyExc_ValueError, "bitmap must hold ceil(n/32) 32-bit words");
+    return 0;
+}
+
+static int check_nnz(const tensor *nnz) {
+    if (nnz->width != 8 || nnz->numel < 1) return fail(PyExc_ValueError, "nnz must be one 64-bit integer");
+    return 0;
+}
+
+static int code_of(const tensor *a, bt_dtype *code) {
+    if (a->code < 0) {
+        PyObject *const dtype = PyObject_GetAttr(a->t, s_dtype);
+        if (dtype != NULL) {
+            Py_XDECREF(PyObject_CallOneArg(dtype_code, dtype));      /* raises */
+            Py_DECREF(dtype);
+        }
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "dtype");
+        return -1;
+    }
+    *code = (bt_dtype)a->code;
+    return 0;
+}
+
+static int check_index(const tensor *index, const tensor *x) {
+    bt_dtype code = BT_F32;
+    if (index->width == 8 && code_of(x, &code) != 0) return -1;
+    if (index->width != 8 || index->numel * 8 < lib.index_bytes(x->numel, code))
+        return fail(PyExc_ValueError, "index must hold one 64-bit integer per tile");
+    return 0;
+}
+
+/* The stream argument as a handle; None: the current stream of the current device. */
+static int stream_of(PyObject *o, bt_stream *stream) {
+    PyObject *h;
+    if (o == Py_None && get_raw_stream != Py_None) {
+        PyObject *device = PyObject_CallNoArgs(get_device);
+        if (device == NULL) return -1;
+        h = PyObject_CallOneArg(get_raw_stream, device);
+        Py_DECREF(device);
+    } else {
+        h = PyObject_CallOneArg(stream_handle, o);
+    }
+    uint64_t v;
+    if (to_u64(h, &v) != 0) return -1;
+    *stream = (bt_stream)(uintptr_t)v;
+    return 0;
+}
+
+static PyObject *done(const char *call, const bt_status st) {
+    if (st == BT_OK) Py_RETURN_NONE;
+    PyObject *e = PyObject_CallFunction(error_class, "si", call, (int)st);
+    if (e != NULL) {
+        PyErr_SetObject(error_class, e);
+        Py_DECREF(e);
+    }
+    return NULL;
+}
+
+static int expect(const Py_ssize_t got, const Py_ssize_t want) {
+    if (lib.compress == NULL) return fail(PyExc_RuntimeError, "the library is not loaded");
+    return got == want ? 0 : fail(PyExc_TypeError, "wrong number of arguments");
+}
+
+#define CALL(name, expression)              \
+    do {                                    \
+        bt_status st;                       \
+        Py_BEGIN_ALLOW_THREADS              \
+        st = (expression);                  \
+        Py_END_ALLOW_THREADS                \
+        return done(name, st);              \
+    } while (0)
+
+/* (x, bitmap, values, nnz, workspace, stream) */
+static PyObject *py_compress(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"x", "bitmap", "values", "nnz", "workspace"};
+    tensor a[5];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 6) != 0 || take(a, args, names, 5) != 0) return NULL;
+    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), NULL;
+    if (check_bitmap(&a[1], a[0].numel) != 0 || check_nnz(&a[3]) != 0 || code_of(&a[0], &code) != 0 || stream_of(args[5], &stream) != 0)
+        return NULL;
+    CALL("bt_compress", lib.compress(a[0].ptr, a[0].numel, code, a[1].ptr, a[2].ptr, a[2].numel, a[3].ptr, a[4].ptr,
+                                     a[4].numel * a[4].width, stream));
+}
+
+/* (x, bitmap, values, nnz, stream) */
+static PyObject *py_compress_static(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"x", "bitmap", "values", "nnz"};
+    tensor a[4];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 5) != 0 || take(a, args, names, 4) != 0) return NULL;
+    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), NULL;
+    if (check_bitmap(&a[1], a[0].numel) != 0 || check_nnz(&a[3]) != 0 || code_of(&a[0], &code) != 0 || stream_of(args[4], &stream) != 0)
+        return NULL;
+    CALL("bt_compress_static", lib.compress_static(a[0].ptr, a[0].numel, code, a[1].ptr, a[2].ptr, a[2].numel, a[3].ptr, stream));
+}
+
+/* (x, bitmap, values, nnz, workspace, threshold, stream) */
+static PyObject *py_compress_pruned(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"x", "bitmap", "values", "nnz", "workspace"};
+    tensor a[5];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 7) != 0 || take(a, args, names, 5) != 0) return NULL;
+    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), NULL;
+    if (check_bitmap(&a[1], a[0].numel) != 0 || check_nnz(&a[3]) != 0 || code_of(&a[0], &code) != 0) return NULL;
+    const double threshold = PyFloat_AsDouble(args[5]);
+    if ((threshold == -1.0 && PyErr_Occurred()) || stream_of(args[6], &stream) != 0) return NULL;
+    CALL("bt_compress_pruned", lib.compress_pruned(a[0].ptr, a[0].numel, code, threshold, a[1].ptr, a[2].ptr, a[2].numel, a[3].ptr,
+                                                   a[4].ptr, a[4].numel * a[4].width, stream));
+}
+
+/* (x, dense_out, bitmap, values, nnz, workspace, threshold, stream) */
+static PyObject *py_activation_compress(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"x", "dense_out", "bitmap", "values", "nnz", "workspace"};
+    tensor a[6];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 8) != 0 || take(a, args, names, 6) != 0) return NULL;
+    if (a[3].dtype != a[0].dtype || a[1].dtype != a[0].dtype || a[1].numel != a[0].numel)
+        return fail(PyExc_TypeError, "values and dense_out must match x"), NULL;
+    if (check_bitmap(&a[2], a[0].numel) != 0 || check_nnz(&a[4]) != 0 || code_of(&a[0], &code) != 0) return NULL;
+    const double threshold = PyFloat_AsDouble(args[6]);
+    if ((threshold == -1.0 && PyErr_Occurred()) || stream_of(args[7], &stream) != 0) return NULL;
+    CALL("bt_activation_compress", lib.activation_compress(a[0].ptr, a[0].numel, code, threshold, a[1].ptr, a[2].ptr, a[3].ptr, a[3].numel,
+                                                           a[4].ptr, a[5].ptr, a[5].numel * a[5].width, stream));
+}
+
+/* (x, bitmap, values, nnz, index, workspace, stream) */
+static PyObject *py_compress_indexed(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"x", "bitmap", "values", "nnz", "index", "workspace"};
+    tensor a[6];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 7) != 0 || take(a, args, names, 6) != 0) return NULL;
+    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), NULL;
+    if (check_bitmap(&a[1], a[0].numel) != 0 || check_nnz(&a[3]) != 0 || check_index(&a[4], &a[0]) != 0 ||
+        code_of(&a[0], &code) != 0 || stream_of(args[6], &stream) != 0)
+        return NULL;
+    CALL("bt_compress_indexed", lib.compress_indexed(a[0].ptr, a[0].numel, code, a[1].ptr, a[2].ptr, a[2].numel, a[3].ptr, a[4].ptr,
+                                                     a[5].ptr, a[5].numel * a[5].width, stream));
+}
+
+/* (bitmap, values, out, workspace, stream) */
+static PyObject *py_decompress(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"bitmap", "values", "out", "workspace"};
+    tensor a[4];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 5) != 0 || take(a, args, names, 4) != 0) return NULL;
+    if (a[1].dtype != a[2].dtype) return fail(PyExc_TypeError, "values must have the dtype of out"), NULL;
+    if (check_bitmap(&a[0], a[2].numel) != 0 || code_of(&a[2], &code) != 0 || stream_of(args[4], &stream) != 0) return NULL;
+    CALL("bt_decompress", lib.decompress(a[0].ptr, a[1].ptr, a[2].numel, code, a[2].ptr, a[3].ptr, a[3].numel * a[3].width, stream));
+}
+
+/* (bitmap, values, index, out, stream) */
+static PyObject *py_decompress_indexed(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"bitmap", "values", "index", "out"};
+    tensor a[4];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 5) != 0 || take(a, args, names, 4) != 0) return NULL;
+    if (a[1].dtype != a[3].dtype) return fail(PyExc_TypeError, "values must have the dtype of out"), NULL;
+    if (check_bitmap(&a[0], a[3].numel) != 0 || check_index(&a[2], &a[3]) != 0 || code_of(&a[3], &code) != 0 ||
+        stream_of(args[4], &stream) != 0)
+        return NULL;
+    CALL("bt_decompress_indexed", lib.decompress_indexed(a[0].ptr, a[1].ptr, a[1].numel, a[2].ptr, a[3].numel, code, a[3].ptr, stream));
+}
+
+/* (bitmap, grad_out, grad_in, stream) */
+static PyObject *py_relu_backward(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"bitmap", "grad_out", "grad_in"};
+    tensor a[3];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 4) != 0 || take(a, args, names, 3) != 0) return NULL;
+    if (a[2].dtype != a[1].dtype || a[2].numel != a[1].numel) return fail(PyExc_TypeError, "grad_in must match grad_out"), NULL;
+    if (check_bitmap(&a[0], a[1].numel) != 0 || code_of(&a[1], &code) != 0 || stream_of(args[3], &stream) != 0) return NULL;
+    CALL("bt_relu_backward_from_bitmap", lib.relu_backward(a[0].ptr, a[1].ptr, a[1].numel, code, a[2].ptr, stream));
+}
+
+/* (bitmap, x, out, stream) */
+static PyObject *py_mask_apply(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"bitmap", "x", "out"};
+    tensor a[3];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 4) != 0 || take(a, args, names, 3) != 0) return NULL;
+    if (a[2].dtype != a[1].dtype || a[2].numel != a[1].numel) return fail(PyExc_TypeError, "out must match x"), NULL;
+    if (check_bitmap(&a[0], a[1].numel) != 0 || code_of(&a[1], &code) != 0 || stream_of(args[3], &stream) != 0) return NULL;
+    CALL("bt_mask_apply", lib.mask_apply(a[0].ptr, a[1].ptr, a[1].numel, code, a[2].ptr, stream));
+}
+
+/* (addresses of the calls in the order of `lib`, the objects above in their order) */
+static PyObject *py_bind(PyObject *self, PyObject *args) {
+    (void)self;
+    PyObject *addresses, *o[6];
+    if (!PyArg_ParseTuple(args, "O!O!OOOOO", &PyTuple_Type, &addresses, &PyDict_Type, &o[0], &o[1], &o[2], &o[3], &o[4], &o[5])) return NULL;
+    void **const slots = (void **)(void *)&lib;
+    enum { kSlots = sizeof(lib) / sizeof(void *) };
+    uint64_t at[kSlots];
+    if (PyTuple_GET_SIZE(addresses) != kSlots) return fail(PyExc_TypeError, "one address per call"), NULL;
+    for (int i = 0; i < kSlots; ++i) {
+        at[i] = PyLong_AsUnsignedLongLong(PyTuple_GET_ITEM(addresses, i));
+        if (at[i] == (uint64_t)-1 && PyErr_Occurred()) return NULL;
+    }
+    for (int i = 0; i < kSlots; ++i) slots[i] = (void *)(uintptr_t)at[i];
+    PyObject **const keep[6] = {&dtypes, &dtype_code, &error_class, &stream_handle, &get_device, &get_raw_stream};
+    for (int i = 0; i < 6; ++i) {
+        Py_INCREF(o[i]);
+        Py_XSETREF(*keep[i], o[i]);
+    }
+    Py_RETURN_NONE;
+}
+
+#define FAST(name) {#name, (PyCFunction)(void (*)(void))py_##name, METH_FASTCALL, NULL}
+static PyMethodDef methods[] = {
+    FAST(compress), FAST(compress_static), FAST(compress_pruned), FAST(activation_compress), FAST(compress_indexed),
+    FAST(decompress), FAST(decompress_indexed), FAST(relu_backward), FAST(mask_apply),
+    {"bind", py_bind, METH_VARARGS, NULL}, {NULL, NULL, 0, NULL}};
+static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", NULL, -1, methods, NULL, NULL, NULL, NULL};
+
+PyMODINIT_FUNC PyInit__call(void) {
+    s_is_cuda = PyUnicode_InternFromString("is_cuda");
+    s_is_contiguous = PyUnicode_InternFromString("is_contiguous");
+    s_dtype = PyUnicode_InternFromString("dtype");
+    s_numel = PyUnicode_InternFromString("numel");
+    s_element_size = PyUnicode_InternFromString("element_size");
+    s_data_ptr = PyUnicode_InternFromString("data_ptr");
+    if (!s_is_cuda || !s_is_contiguous || !s_dtype || !s_numel || !s_element_size || !s_data_ptr) return NULL;
+    return PyModule_Create(&module);
+}

@@ -348,3 +348,118 @@ def test_workspace_bytes_cover_every_tile(bt):
             n = tiles * elems_per_tile
             assert bt.bt_workspace_bytes(n, code) == 256 + 6144 * ((tiles + 255) // 256)
             assert bt.bt_workspace_bytes(n + 1, code) == 256 + 6144 * ((tiles + 1 + 255) // 256)
+
+
+class _FakeTensor:
+    """What the binding reads of a tensor; no memory behind it, so a call must be refused before anything is launched."""
+
+    def __init__(self, numel, dtype, is_cuda=True, contiguous=True, ptr=0x1000):
+        self.is_cuda, self.dtype, self._n, self._c, self._p = is_cuda, dtype, numel, contiguous, ptr
+
+    def is_contiguous(self):
+        return self._c
+
+    def numel(self):
+        return self._n
+
+    def element_size(self):
+        return self.dtype.itemsize
+
+    def data_ptr(self):
+        return self._p
+
+
+def _binding_calls():
+    """name -> (argument names in order, the extra positional arguments) of the calls that are marshalled in C."""
+    xs = ("x", "bitmap", "values", "nnz")
+    return {"bt_compress": (xs + ("workspace",), None), "bt_compress_static": (xs, None),
+            "bt_compress_pruned": (("x", 0.5, "bitmap", "values", "nnz", "workspace"), None),
+            "bt_activation_compress": (("x", 0.5, "dense_out", "bitmap", "values", "nnz", "workspace"), None),
+            "bt_compress_indexed": (xs + ("index", "workspace"), None),
+            "bt_decompress": (("bitmap", "values", "out", "workspace"), None),
+            "bt_decompress_indexed": (("bitmap", "values", "index", "out"), None),
+            "bt_relu_backward_from_bitmap": (("bitmap", "grad_out", "grad_in"), None),
+            "bt_mask_apply": (("bitmap", "x", "out"), None)}
+
+
+@pytest.mark.parametrize("name", sorted(_binding_calls()))
+def test_binding_refuses_what_does_not_fit(bt, name):
+    import torch
+    n = 100000
+
+    def good():
+        f = torch.float32
+        t = {k: _FakeTensor(n, f) for k in ("x", "values", "dense_out", "out", "grad_out", "grad_in")}
+        t.update(bitmap=_FakeTensor(n // 32, torch.int32), nnz=_FakeTensor(1, torch.int64),
+                 index=_FakeTensor(-(-n // 8192), torch.int64), workspace=_FakeTensor(1 << 16, torch.uint8))
+        return t
+    order = _binding_calls()[name][0]
+
+    def call(t, stream=0):
+        return getattr(bt, name)(*[t[a] if isinstance(a, str) else a for a in order], stream=stream)
+    tensors = [a for a in order if isinstance(a, str)]
+    # in front of everything else, in argument order: device memory, contiguous (all but the first bad one are not looked at)
+    for i, a in enumerate(sorted(tensors, key=order.index)):
+        for kw, text in (({"is_cuda": False}, "%s must live in device memory"), ({"contiguous": False}, "%s must be contiguous")):
+            t = good()
+            t[a] = _FakeTensor(3, torch.int8, **kw)
+            with pytest.raises(ValueError, match=text % a):
+                call(t)
+    first = "x" if "x" in order and name != "bt_mask_apply" else {"bt_mask_apply": "x", "bt_relu_backward_from_bitmap": "grad_out"}.get(name, "out")
+    bad = [("bitmap", _FakeTensor(n // 32 - 1, torch.int32), ValueError, "bitmap must hold"),
+           ("bitmap", _FakeTensor(n // 32, torch.int64), ValueError, "bitmap must hold"),
+           ("nnz", _FakeTensor(0, torch.int64), ValueError, "nnz must be one 64-bit"),
+           ("nnz", _FakeTensor(1, torch.int32), ValueError, "nnz must be one 64-bit"),
+           ("index", _FakeTensor(-(-n // 8192) - 1, torch.int64), ValueError, "index must hold"),
+           ("index", _FakeTensor(n, torch.int32), ValueError, "index must hold"),
+           ("values", _FakeTensor(n, torch.float16), TypeError, "values"),
+           ("dense_out", _FakeTensor(n - 1, torch.float32), TypeError, "must match x"),
+           ("dense_out", _FakeTensor(n, torch.float16), TypeError, "must match x"),
+           ("grad_in", _FakeTensor(n - 1, torch.float32), TypeError, "grad_in must match"),
+           ("grad_in", _FakeTensor(n, torch.bfloat16), TypeError, "grad_in must match")]
+    if name == "bt_mask_apply":
+        bad += [("out", _FakeTensor(n - 1, torch.float32), TypeError, "out must match x"),
+                ("out", _FakeTensor(n, torch.float16), TypeError, "out must match x")]
+    for a, t_bad, error, text in bad:
+        if a in tensors:
+            t = good()
+            t[a] = t_bad
+            with pytest.raises(error, match=text):
+                call(t)
+    # a dtype the library does not take, everywhere it would have to agree
+    t = good()
+    for a in tensors:
+        if t[a].dtype == torch.float32:
+            t[a] = _FakeTensor(n, torch.int32)
+    with pytest.raises(TypeError, match="handles float64, float32, float16 and bfloat16, not torch.int32"):
+        call(t)
+    # what the library itself refuses, by its status: a misaligned tensor (the call on the library's own workspace, which it
+    # looks up first, is given more tiles than that holds instead)
+    t, status = good(), 3
+    t[first]._p = 0x1004
+    if name == "bt_compress_static":
+        big, status = 16385 * 8192, 6
+        t.update(x=_FakeTensor(big, torch.float32), bitmap=_FakeTensor(big, torch.int32))
+    with pytest.raises(bt.BitTrainError, match=r"%s failed: %s" % (name, bt.STATUS_NAMES[status])) as e:
+        call(t)
+    assert e.value.status == status
+    # a stream that is none, and a missing attribute
+    with pytest.raises((TypeError, ValueError)):
+        call(good(), stream="no stream")
+    t = good()
+    t[tensors[0]] = object()
+    with pytest.raises(AttributeError):
+        call(t)
+    if "x" in order and 0.5 in order:
+        with pytest.raises(TypeError):
+            getattr(bt, name)(*[good()[a] if isinstance(a, str) else "much" for a in order], stream=0)
+
+
+def test_binding_takes_empty_tensors_and_keywords(bt):
+    """No element: every check is made, nothing is launched (restoration and the streams do nothing at all)."""
+    import torch
+    f, w = _FakeTensor(0, torch.float32, ptr=0), _FakeTensor(0, torch.int32, ptr=0)
+    assert bt.bt_decompress(bitmap=w, values=f, out=f, workspace=_FakeTensor(1 << 16, torch.uint8), stream=0) is None
+    assert bt.bt_relu_backward_from_bitmap(w, grad_out=f, grad_in=f, stream=0) is None
+    assert bt.bt_mask_apply(w, f, f, stream=0) is None
+    assert bt.bt_decompress_indexed(w, f, _FakeTensor(0, torch.int64, ptr=0), f, stream=0) is None
