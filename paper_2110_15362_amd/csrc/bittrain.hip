@@ -70,7 +70,6 @@ constexpr int kHdrSpinLimit = BT_WS_WAIT_LIMIT_WORD;  // scanner passes before i
 constexpr int kHdrWide = BT_WS_WIDE_WORD;             // non-zero: the one-tensor scanner writes 8-byte entries only
 constexpr int kHdrPatience = BT_WS_PATIENCE_WORD;     // polls before a workgroup counts what precedes its tile itself; 0: kPatience
 constexpr size_t kHeaderBytes = 256;
-constexpr size_t kHdrSpare = 128;      // bytes [128, 256) of the header take stores that mean nothing (see the scanner)
 // Block of 256 slots, two copies c = 0, 1 of everything:
 //   [1024*c, 1024*c + 1024)            uint32 count + 1 of each slot, written by the slot's workgroup
 //   [2048 + 2048*c, 2048*c + 4096)     uint64 prefix + 1 of each slot, written by the scanner
@@ -85,12 +84,8 @@ constexpr uint32_t kPatience = 1u << 12;  // polls before a workgroup counts wha
 #ifndef BT_SCANNER_SLEEP
 #define BT_SCANNER_SLEEP 1
 #endif
-#ifndef BT_TILE_SLEEP
-#define BT_TILE_SLEEP 16
-#endif
 constexpr uint32_t kDenseEarlySlots = 1280;      // launches of up to this many slots store a dense output before the prefix is there
 constexpr int kScannerSleep = BT_SCANNER_SLEEP;   // pause between two polls, in units of 64 clocks
-constexpr int kTileSleep = BT_TILE_SLEEP;
 
 // S: element bytes; R: rows (16-byte loads) per lane per tile.
 template <int S, int R = kRows> struct Geo {
@@ -102,7 +97,8 @@ template <int S, int R = kRows> struct Geo {
     static constexpr int PHASE = R < 4 ? R : 4;      // rows that are compacted / expanded through LDS at a time
     static constexpr int TILE = kWaves * WAVE;       // elements per tile
     static constexpr int TILE_WORDS = TILE / 32;     // bitmap words per tile
-    static constexpr int LANE_WORDS = TILE_WORDS / kWaveSize;   // of which a lane counts this many when a wave counts a tile
+    static constexpr int WAVE_WORDS = TILE_WORDS / kWaves;      // of which a wave's quarter of the tile has this many
+    static constexpr int WPL = WAVE_WORDS > kWaveSize ? WAVE_WORDS / kWaveSize : 1;   // and a lane reads this many
     static constexpr int LDS_WAVE = PHASE * ROW * S + 2 * kVecBytes;  // restoration's staging bytes per wave: the rows of a phase, the
                                                                           // shift to a 16-byte boundary, and what a read past the last value may touch
     static constexpr int STAGE = TILE * S <= kStageBytes - kVecBytes ? TILE * S : kStageBytes - kVecBytes;   // compression: bytes of a tile's
@@ -760,16 +756,29 @@ __device__ __forceinline__ bool sum_counts(char *ws, const uint32_t slot, const 
     return true;
 }
 
+// Pause between two polls of a tile for its prefix.  A launch that the GPU swallows in one go wants the answer soon; where
+// thousands of workgroups come and go, the polls of the two thousand resident ones stand in the way of the scanner's
+// and of the values'.  Measured with pauses of 4 / 16 / 32 x 64 clocks, us: fp32 at 50 % zeros, restore 2 M elements (245
+// tiles) 6.5 / 6.8 / 7.0, 4 M 8.0 / 8.1 / 8.4, 25.7 M (3136 tiles) 26.8 / 26.7 / 26.8; compress 25.7 M 28.3 / 28.3 / 28.8, 4 M
+// 8.6 / 8.9 / 9.0; restore fp16 206 M (12,544 tiles, 5 % zeros) - / 141.4 / 140.7, fp32 206 M - / 211.3 / 209.7; the 49 tensors of
+// a ResNet-50 (79,488 slots) restore - / 610 / 572, compress - / 519 / 514 (48: 568 / 515; 100: 581 / 518).
+__device__ __forceinline__ void poll_pause(const uint32_t n_slots) {
+    if (n_slots >= 8192) __builtin_amdgcn_s_sleep(32);
+    else if (n_slots > 1536) __builtin_amdgcn_s_sleep(16);
+    else __builtin_amdgcn_s_sleep(4);
+}
+
 // The wait of a tile's first wave for the scanner: the number of values before its slot.  `itself` counts what precedes the
 // tile from the call's input, for a wave that stops waiting.
 template <class Itself>
-__device__ __forceinline__ uint64_t wait_for_prefix(char *ws, const uint32_t slot, const uint32_t cur, uint32_t &polls, const Itself &itself) {
+__device__ __forceinline__ uint64_t wait_for_prefix(char *ws, const uint32_t slot, const uint32_t n_slots, const uint32_t cur, uint32_t &polls,
+                                                    const Itself &itself) {
     for (;;) {
         const uint64_t v = uniform64(ws_load64(ws_prefix(ws, slot, cur)));
         ++polls;
         if (v != 0) return v - 1;
         if (__builtin_expect((polls & 255u) == 0 && polls > patience_of(reinterpret_cast<const uint32_t *>(ws)), 0)) return itself();
-        __builtin_amdgcn_s_sleep(kTileSleep);
+        poll_pause(n_slots);
     }
 }
 
@@ -1151,7 +1160,7 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
     if (wave == 0) {
         const auto itself = [&]() { return prefix_from_input<S, R, KEEP>(in, tile, threshold_f, threshold, lane_number()); };
         const uint64_t v = DIRECT ? wait_for_counts(ws, job, slot, n_slots, ep, tile_total, polls, itself)
-                                  : wait_for_prefix(ws, slot, ep.cur, polls, itself);
+                                  : wait_for_prefix(ws, slot, n_slots, ep.cur, polls, itself);
         if (lane_number() == 0) {
             s_tile_prefix = v;
             uint64_t *const index = job.index(sl.item);
@@ -1253,106 +1262,130 @@ __device__ __forceinline__ void strip_commit(unsigned char *strip, const uint32_
     }
 }
 
-// Restoration of one wave's quarter of a tile goes in three steps, so that a wave can have the
-// steps of consecutive tiles overlap:
-//   ahead_load      asks for the bitmap words the wave needs (always the same number of loads,
-//                   from somewhere harmless if there is no such tile);
-//   restore_fetch   turns them into the lane's masks and ranks (Algorithm 2's counter j inside the
-//                   tile) and, given j at the start of the tile, asks for the wave's values;
+// Restoration of one wave's quarter of a tile:
+//   quarter_load    asks for the bitmap words of the quarter, each once (lane l: words l * WPL ...);
+//   restore_ranks   counts them, running sum over the lanes, and hands every lane the words and ranks of its rows
+//                   (Algorithm 2's counter j inside the quarter) through LDS;
+//   restore_fetch   given j at the start of the tile, asks for the wave's values;
 //   restore_store   puts the values into the LDS strip, expands them by rank (a value where
 //                   the bit is set, +0 where it is clear) and stores the dense quarter tile.
-// The waves of a workgroup do not talk to each other: each counts what the waves before it hold
-// from the bitmap itself.
-template <int S, int R> struct Ahead {
-    uint32_t rows[R];                      // the bitmap word that holds this lane's bits of row k
-    uint32_t mine[Geo<S, R>::LANE_WORDS];         // this lane's share of the tile's words (lane l: words l * LANE_WORDS ...)
+// (Read once per row by the lanes that share a word, and ranked by row sums, they cost a wave eight loads of 32 bytes,
+// which keep the address units busy before anything else can start, and four times the DPP steps.  Measured, before /
+// after, us: restore from the index fp32 25.7 M elements 24.8 / 24.2, the ResNet-50 set 585 / 563;
+// with the scan fp32 25.7 M 27.0 / 26.7, 206 M 214 / 212, fp16 206 M at 5 % 142.8 / 141.7.)
+template <int S, int R> struct Quarter { uint32_t w[Geo<S, R>::WPL]; };
+
+// Words at or beyond the bitmap's end read as 0, bits at or beyond n are cleared (Algorithm 2 visits n bits).
+template <int S, int R>
+__device__ __forceinline__ Quarter<S, R> quarter_load(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane, const int wave) {
+    using G = Geo<S, R>;
+    static_assert(G::WPL <= 2, "one load");
+    typedef uint32_t word2 __attribute__((ext_vector_type(2), aligned(4)));      // (the bitmap is 4-byte aligned)
+    const uint64_t first = (uint64_t)tile * G::TILE_WORDS + (uint64_t)wave * G::WAVE_WORDS;
+    const bool full = (uint64_t)(tile + 1) * G::TILE <= n;
+    Quarter<S, R> q;
+#pragma unroll
+    for (int j = 0; j < G::WPL; ++j) q.w[j] = 0;
+    if (__builtin_expect(full, 1)) {
+        if (G::WPL == 2) {
+            const word2 v = *reinterpret_cast<const word2 *>(bitmap + first + 2 * lane);
+            q.w[0] = v.x;
+            q.w[G::WPL - 1] = v.y;
+        } else if (G::WAVE_WORDS >= kWaveSize || lane < G::WAVE_WORDS) {
+            q.w[0] = bitmap[first + lane];
+        }
+    } else {
+        const uint64_t n_words = (n + 31) >> 5;
+#pragma unroll
+        for (int j = 0; j < G::WPL; ++j) {
+            const uint64_t wi = first + (uint32_t)(lane * G::WPL + j);
+            if (lane * G::WPL + j < G::WAVE_WORDS && wi < n_words) q.w[j] = bitmap[wi];
+            if (wi + 1 == n_words && (n & 31) != 0) q.w[j] &= (1u << (uint32_t)(n & 31)) - 1u;
+        }
+    }
+    return q;
+}
+
+template <int S, int R> struct Restoring {            // a quarter tile between restore_ranks and restore_store
+    static constexpr int PHASES = R / Geo<S, R>::PHASE;
+    uint32_t mp[Geo<S, R>::MW], rank2[R / 2];          // ranks inside the quarter, two rows to a register
+    uint32_t before[PHASES + 1];                       // set bits of the quarter before each phase, and all of them
+    Fetched<S, R> fetched[PHASES];
+    uint32_t pads[PHASES], cnts[PHASES];
 };
 
-// `bitmap` == nullptr: there is no tile; everything is read from `harmless` (4-byte aligned, readable).
+// (1) this lane's bits of the bitmap (G lanes take E bits each of one word), and Algorithm 2's counter j as ranks.  Returns the
+//     set bits of this wave's quarter of the tile.  `strip`: the wave's LDS, free until the values are put into it.
 template <int S, int R>
-__device__ __forceinline__ void rows_load(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane,
-                                          const int wave, const uint32_t *harmless, uint32_t (&rows)[R]) {
+__device__ __forceinline__ uint32_t restore_ranks(const Quarter<S, R> &q, unsigned char *strip, const int lane, Restoring<S, R> &r) {
     using G = Geo<S, R>;
-    const bool real = bitmap != nullptr;
-    const uint32_t *const base = real ? bitmap : harmless;
-    const uint64_t last = real ? ((n + 31) >> 5) - 1 : 0;         // a real tile has n >= 1
-    const uint64_t row_w0 = (real ? (uint64_t)tile * G::TILE_WORDS : 0) + (uint64_t)wave * (G::TILE_WORDS / kWaves) + (uint32_t)(lane / G::G);
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const uint64_t wi = row_w0 + (uint64_t)k * G::WPR;
-        rows[k] = base[wi < last ? wi : last];
-    }
-}
-
-template <int S, int R>
-__device__ __forceinline__ void words_load(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane,
-                                           const uint32_t *harmless, uint32_t (&words)[Geo<S, R>::LANE_WORDS]) {
-    using G = Geo<S, R>;
-    const bool real = bitmap != nullptr;
-    const uint32_t *const base = real ? bitmap : harmless;
-    const uint64_t last = real ? ((n + 31) >> 5) - 1 : 0;
-    const uint64_t w0 = real ? (uint64_t)tile * G::TILE_WORDS + (uint64_t)lane * G::LANE_WORDS : 0;
-#pragma unroll
-    for (int j = 0; j < G::LANE_WORDS; ++j) words[j] = base[w0 + j < last ? w0 + j : last];
-}
-
-template <int S, int R>
-__device__ __forceinline__ void ahead_load(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane,
-                                           const int wave, const uint32_t *harmless, Ahead<S, R> &a) {
-    rows_load<S, R>(bitmap, n, tile, lane, wave, harmless, a.rows);
-    words_load<S, R>(bitmap, n, tile, lane, harmless, a.mine);
-}
-
-// The set bits of a whole tile from the words words_load has brought, as a running sum over the lanes: lane l
-// holds LANE_WORDS consecutive words, so the 16 lanes [16 v, 16 v + 16) hold the words of the tile's v-th wave,
-// lane 63 ends up with the tile's total and lane 16 v - 1 with the set bits of the waves before v.  Words at or
-// beyond the bitmap's end count as 0 and so do bits at or beyond n (Algorithm 2 visits n bits).
-template <int S, int R>
-__device__ __forceinline__ uint32_t tile_inclusive(const uint32_t (&words)[Geo<S, R>::LANE_WORDS], const uint64_t n, const uint32_t tile,
-                                                   const int lane) {
-    using G = Geo<S, R>;
-    const uint64_t n_words = (n + 31) >> 5;
-    const uint64_t w0 = (uint64_t)tile * G::TILE_WORDS + (uint64_t)lane * G::LANE_WORDS;
-    const bool full = (uint64_t)(tile + 1) * G::TILE <= n;
+    constexpr int E = G::E;
+    static_assert(8 * G::WAVE_WORDS <= G::LDS_WAVE && G::WAVE < 65536, "a word and its rank per entry; ranks in 16 bits");
     uint32_t mine = 0;
 #pragma unroll
-    for (int j = 0; j < G::LANE_WORDS; ++j) {
-        uint32_t word = words[j];
-        if (!full) {
-            const uint64_t wi = w0 + j;
-            if (wi >= n_words) word = 0;
-            if (wi + 1 == n_words && (n & 31) != 0) word &= (1u << (uint32_t)(n & 31)) - 1u;
+    for (int j = 0; j < G::WPL; ++j) mine += (uint32_t)__popc(q.w[j]);
+    const uint32_t incl = wave_inclusive_sum(mine);
+    uint32_t rank = incl - mine;
+#pragma unroll
+    for (int ph = 0; ph < Restoring<S, R>::PHASES; ++ph)       // the lane that holds the phase's first word
+        r.before[ph] = (uint32_t)__builtin_amdgcn_readlane((int)rank, ph * G::PHASE * G::WPR / G::WPL);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    r.before[Restoring<S, R>::PHASES] = total;
+    bt_u2 *const entries = reinterpret_cast<bt_u2 *>(strip);
+    if (G::WAVE_WORDS >= kWaveSize || lane < G::WAVE_WORDS) {
+#pragma unroll
+        for (int j = 0; j < G::WPL; ++j) {
+            entries[lane * G::WPL + j] = bt_u2{q.w[j], rank};
+            rank += (uint32_t)__popc(q.w[j]);
         }
-        mine += (uint32_t)__popc(word);
     }
-    return wave_inclusive_sum(mine);
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < G::MW; ++i) r.mp[i] = 0;
+    const uint32_t shift = (uint32_t)E * (uint32_t)(lane % G::G);
+    const uint32_t below = (1u << shift) - 1u;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const bt_u2 e = entries[k * G::WPR + lane / G::G];
+        r.mp[k / G::RPM] |= ((e.x >> shift) & ((1u << E) - 1u)) << (E * (k % G::RPM));
+        const uint32_t at = e.y + (uint32_t)__popc(e.x & below);
+        r.rank2[k / 2] = (k & 1) == 0 ? at : r.rank2[k / 2] | (at << 16);
+    }
+    wave_lds_sync();                    // the entries are read before the strip is used for values
+    return total;
 }
 
-// Returns the tile's total, and in `before` the set bits of the waves before `wave`.
+// (1) in the form that the restoration of one 16-bit tensor from its index keeps: the word of each row read by the lanes that
+// share it, ranks from row sums, and the waves before this one counted from the whole tile's words.  More work, but those
+// kernels are bound by their stores, and a workgroup that is later with its own writes sparse tensors faster (fp16, 206 M
+// elements, 95 % zeros: 69 us; with restore_ranks 77, or 70 with LDS reserved for five workgroups a compute unit).
+// Returns the set bits of the waves before `wave`.
 template <int S, int R>
-__device__ __forceinline__ uint32_t count_words(const uint32_t (&words)[Geo<S, R>::LANE_WORDS], const uint64_t n, const uint32_t tile,
-                                                const int lane, const int wave, uint32_t &before) {
-    const uint32_t incl = tile_inclusive<S, R>(words, n, tile, lane);
-    before = wave == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)uniform32(16u * (uint32_t)wave - 1u));
-    return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-}
-
-template <int S, int R> struct Restoring {            // a quarter tile between restore_fetch and restore_store
-    uint32_t mp[Geo<S, R>::MW], rank2[R / 2], total2[R / 2];
-    Fetched<S, R> fetched[R / Geo<S, R>::PHASE];
-    uint32_t pads[R / Geo<S, R>::PHASE], cnts[R / Geo<S, R>::PHASE];
-};
-
-// (1) this lane's bits of the bitmap (G lanes read the same word and take E bits each), and Algorithm 2's
-//     counter j as ranks.  Returns the set bits of this wave's quarter of the tile.
-template <int S, int R>
-__device__ __forceinline__ uint32_t restore_ranks(const uint32_t (&rows)[R], const uint64_t n, const uint32_t tile, const int lane,
-                                                  const int wave, Restoring<S, R> &r) {
+__device__ __forceinline__ uint32_t restore_ranks_by_row(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane, const int wave,
+                                                     Restoring<S, R> &r) {
     using G = Geo<S, R>;
     constexpr int E = G::E;
     const uint64_t n_words = (n + 31) >> 5;
     const uint64_t wave_e0 = (uint64_t)tile * G::TILE + (uint64_t)wave * G::WAVE;
     const bool full = (uint64_t)(tile + 1) * G::TILE <= n;
+    uint32_t rows[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const uint64_t wi = (wave_e0 >> 5) + (uint64_t)(k * G::WPR + lane / G::G);
+        rows[k] = bitmap[wi < n_words ? wi : n_words - 1];
+    }
+    constexpr int kShare = G::TILE_WORDS / kWaveSize;           // lane l counts words l * kShare ... of the tile: 16 lanes a quarter
+    const uint64_t w0 = (uint64_t)tile * G::TILE_WORDS + (uint64_t)lane * kShare;
+    uint32_t words[kShare], mine = 0;
+#pragma unroll
+    for (int j = 0; j < kShare; ++j) words[j] = bitmap[w0 + j < n_words ? w0 + j : n_words - 1];
+#pragma unroll
+    for (int j = 0; j < kShare; ++j) {
+        if (!full && w0 + j >= n_words) words[j] = 0;
+        if (!full && w0 + j + 1 == n_words && (n & 31) != 0) words[j] &= (1u << (uint32_t)(n & 31)) - 1u;
+        mine += (uint32_t)__popc(words[j]);
+    }
+    const uint32_t incl = wave_inclusive_sum(mine);
 #pragma unroll
     for (int i = 0; i < G::MW; ++i) r.mp[i] = 0;
 #pragma unroll
@@ -1365,11 +1398,17 @@ __device__ __forceinline__ uint32_t restore_ranks(const uint32_t (&rows)[R], con
         }
         r.mp[k / G::RPM] |= m << (E * (k % G::RPM));
     }
-    rank_rows<S, R>(r.mp, r.rank2, r.total2);
-    uint32_t wave_total = 0;
+    uint32_t total2[R / 2];
+    rank_rows<S, R>(r.mp, r.rank2, total2);
+    uint32_t row_start = 0;
 #pragma unroll
-    for (int k = 0; k < R; ++k) wave_total += BT_FIELD(r.total2, k);
-    return wave_total;
+    for (int k = 0; k < R; ++k) {
+        if (k % G::PHASE == 0) r.before[k / G::PHASE] = row_start;
+        r.rank2[k / 2] += row_start << (16 * (k & 1));
+        row_start += BT_FIELD(total2, k);
+    }
+    r.before[Restoring<S, R>::PHASES] = row_start;
+    return wave == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)uniform32(16u * (uint32_t)wave - 1u));
 }
 
 // (2) ask for the values of every phase (PHASE rows each), so that all of them are in flight together
@@ -1380,9 +1419,7 @@ __device__ __forceinline__ void restore_fetch(const void *__restrict__ values, c
     uint64_t g0 = tile_j + before_wave;                                   // Algorithm 2's j for this wave
 #pragma unroll
     for (int ph = 0; ph < R / G::PHASE; ++ph) {
-        r.cnts[ph] = 0;
-#pragma unroll
-        for (int k = ph * G::PHASE; k < (ph + 1) * G::PHASE; ++k) r.cnts[ph] += BT_FIELD(r.total2, k);
+        r.cnts[ph] = r.before[ph + 1] - r.before[ph];
         const char *gsrc = static_cast<const char *>(values) + g0 * S;
         r.pads[ph] = (uint32_t)(reinterpret_cast<uintptr_t>(gsrc) & (kVecBytes - 1)) / S;
         const uint32_t phase_total = r.cnts[ph];
@@ -1406,10 +1443,10 @@ __device__ __forceinline__ void restore_store(const Restoring<S, R> &r, const ui
         if (ph != 0) wave_lds_sync();   // the previous phase's reads are done before the strip is reused
         strip_commit<S, R>(strip, r.pads[ph], r.cnts[ph], lane, r.fetched[ph]);
         wave_lds_sync();
-        uint32_t row_start = r.pads[ph];
+        const uint32_t base = r.pads[ph] - r.before[ph];
 #pragma unroll
         for (int k = ph * G::PHASE; k < (ph + 1) * G::PHASE; ++k) {
-            uint32_t at = row_start + BT_FIELD(r.rank2, k);
+            uint32_t at = base + BT_FIELD(r.rank2, k);
             const uint32_t mk = BT_MASK(S, r.mp, k);
             uint32_t d[4] = {0, 0, 0, 0};
             // every lane reads at its running rank whether the bit is set or not (the index stays inside the strip)
@@ -1447,13 +1484,8 @@ __device__ __forceinline__ void restore_store(const Restoring<S, R> &r, const ui
             const uint4 o = make_uint4(d[0], d[1], d[2], d[3]);
             if (full) stream_store<kDecompressNtStore>(reinterpret_cast<uint4 *>(static_cast<char *>(out) + e0 * S), o);
             else store_vec_guarded<S>(out, e0, n, o);
-            row_start += BT_FIELD(r.total2, k);
         }
     }
-    wave_lds_sync();                    // this tile's reads are done before the next tile's values are committed
-    // a ragged tile's stores are element by element, as many as it takes: let them finish here, so that what is
-    // outstanding after a tile does not depend on the tile (see the kernel)
-    if (!full) __builtin_amdgcn_s_waitcnt(0x0f70);                        // vmcnt(0)
 }
 
 // What a restoring wave does when the scanner's answer for its tile does not come: it counts the set
@@ -1538,8 +1570,8 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
     // the bitmap words first: everything else waits for them
     const uint32_t *const bitmap = sl.idle ? nullptr : job.bitmap(sl.item);
     const uint64_t n = sl.idle ? 0 : job.n(sl.item);
-    uint32_t rows[R];
-    rows_load<S, R>(bitmap, n, sl.tile, lane, wave, reinterpret_cast<const uint32_t *>(ws + kHdrSpare), rows);
+    Quarter<S, R> quarter = {};
+    if (!sl.idle) quarter = quarter_load<S, R>(bitmap, n, sl.tile, lane, wave);
     BT_TL(slot, 0);
     uint32_t calls = 0, before_share = 0;
     if (SELF) {
@@ -1548,7 +1580,8 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
     }
     // masks and ranks; what they add up to is this wave's share of the tile's count
     Restoring<S, R> r;
-    const uint32_t wave_total = sl.idle ? 0u : restore_ranks<S, R>(rows, n, sl.tile, lane, wave, r);
+    unsigned char *const strip = s_stage + wave * G::LDS_WAVE;
+    const uint32_t wave_total = sl.idle ? 0u : restore_ranks<S, R>(quarter, strip, lane, r);
     const Epoch ep = epoch_of(header);
     if (SELF) {
         const uint32_t incl = wave_inclusive_sum(before_share);
@@ -1581,7 +1614,7 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
         // Algorithm 2's counter j at the start of the tile: the first wave asks (one poller a tile keeps the
         // traffic on the workspace's few lines low) and passes the answer on through LDS
         if (wave == 0) {
-            const uint64_t v = wait_for_prefix(ws, slot, ep.cur, polls, [&]() { return prefix_from_bitmap<S, R>(bitmap, sl.tile, lane); });
+            const uint64_t v = wait_for_prefix(ws, slot, n_slots, ep.cur, polls, [&]() { return prefix_from_bitmap<S, R>(bitmap, sl.tile, lane); });
             if (lane == 0) s_tile_j = v;
         }
         lds_barrier();
@@ -1589,18 +1622,30 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
     }
     BT_TL(slot, 2);
     restore_fetch<S, R>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
-    restore_store<S, R>(r, n, job.out(sl.item), sl.tile, s_stage + wave * G::LDS_WAVE, lane, wave);
+    restore_store<S, R>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
     BT_TL(slot, 3);
     BT_TL_VALUE(slot, 5, polls);
 }
 
 // bt_decompress_indexed and its batched form: one workgroup per slot and nothing else.  Algorithm 2's
 // j at the start of the tile comes from the tile index.
+//
+// Two thirds of the traffic and more are stores, and nothing holds a workgroup back: with all eight workgroups that fit a
+// compute unit, the more the tensor's values thin out, the more the stores of too many tiles mix.  So LDS is reserved for
+// fewer where that measured better (us; 8 / 6 / 5 workgroups): the 49 fp32 tensors of a ResNet-50, 70 % zeros 563 / 547 / 552:
+// six for batches; fp32 103 M elements, 5 % 137.7 / 139.8 / 140.6, 50 % 106.2 / 104.8 / 104.5, 95 % 76.4 / 74.6 / 71.1: eight.
+// What the waves before a wave hold, it counts itself; for one tensor of fp32 or fp64 an exchange behind a barrier is better
+// (103 M and 51 M elements, 50 % zeros: 104.5 instead of 106.2 and 103 instead of 106).
+template <class Job> constexpr int kIndexedOcc = Job::kMany ? 6 : 8;
 template <int S, class Job>
-__global__ __launch_bounds__(kBlock, 8) void decompress_indexed_kernel(const Job job) {
+__global__ __launch_bounds__(kBlock, kIndexedOcc<Job>) void decompress_indexed_kernel(const Job job) {
     constexpr int R = kRows;
     using G = Geo<S, R>;
-    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kWaves * G::LDS_WAVE];
+    constexpr int kShare = 160 * 1024 / kIndexedOcc<Job> - 256;
+    constexpr bool kByRow = S == 2 && !Job::kMany;
+    constexpr bool kExchange = S != 2 && !Job::kMany;
+    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kShare > kWaves * G::LDS_WAVE ? kShare : kWaves * G::LDS_WAVE];
+    __shared__ uint32_t s_wave_total[kWaves];
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Slot sl = job.at(blockIdx.x);
@@ -1608,14 +1653,39 @@ __global__ __launch_bounds__(kBlock, 8) void decompress_indexed_kernel(const Job
     const uint64_t tile_j = job.tile_index(sl.item)[sl.tile];             // asked for first, needed last
     const uint32_t *const bitmap = job.bitmap(sl.item);
     const uint64_t n = job.n(sl.item);
-    Ahead<S, R> ahead;
-    ahead_load<S, R>(bitmap, n, sl.tile, lane, wave, bitmap, ahead);
-    uint32_t before_wave;
-    count_words<S, R>(ahead.mine, n, sl.tile, lane, wave, before_wave);
+    const Quarter<S, R> quarter = quarter_load<S, R>(bitmap, n, sl.tile, lane, wave);
+    // What the waves before this one hold, each wave counts itself: a barrier in their place made the workgroup's stores
+    // come in one burst (fp16, 206 M elements, 95 % zeros: 77 us instead of 72).
     Restoring<S, R> r;
-    restore_ranks<S, R>(ahead.rows, n, sl.tile, lane, wave, r);
+    unsigned char *const strip = s_stage + wave * G::LDS_WAVE;
+    uint32_t before_wave = 0;
+    if (kExchange) {
+        const uint32_t wave_total = restore_ranks<S, R>(quarter, strip, lane, r);
+        if (lane == 0) s_wave_total[wave] = wave_total;
+        lds_barrier();
+#pragma unroll
+        for (int w = 0; w < kWaves - 1; ++w) {
+            const uint32_t c = s_wave_total[w];
+            if (w < wave) before_wave += c;
+        }
+        before_wave = uniform32(before_wave);
+    } else if (kByRow) {
+        before_wave = restore_ranks_by_row<S, R>(bitmap, n, sl.tile, lane, wave, r);
+    } else {
+        uint32_t before = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves - 1; ++w) {
+            if (w < wave) {
+                const Quarter<S, R> q = quarter_load<S, R>(bitmap, n, sl.tile, lane, w);
+#pragma unroll
+                for (int j = 0; j < G::WPL; ++j) before += (uint32_t)__popc(q.w[j]);
+            }
+        }
+        restore_ranks<S, R>(quarter, strip, lane, r);
+        before_wave = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(before), 63);
+    }
     restore_fetch<S, R>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
-    restore_store<S, R>(r, n, job.out(sl.item), sl.tile, s_stage + wave * G::LDS_WAVE, lane, wave);
+    restore_store<S, R>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
 }
 
 // ---- ReLU backward from the bitmap -----------------------------------------------------------
