@@ -104,7 +104,8 @@ def lib():
         call.bind(tuple(ctypes.cast(getattr(L, f), vp).value for f in _CALLS), _DTYPES, dtype_code, BitTrainError, _stream_handle,
                   getattr(torch._C, "_cuda_getDevice", None),
                   getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None)
-        _lib, _call = L, call
+        _call = call      # first: other threads go by _lib
+        _lib = L
     return _lib
 
 

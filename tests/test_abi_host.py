@@ -350,6 +350,31 @@ def test_workspace_bytes_cover_every_tile(bt):
             assert bt.bt_workspace_bytes(n + 1, code) == 256 + 6144 * ((tiles + 1 + 255) // 256)
 
 
+def test_the_first_use_from_several_threads_never_meets_half_a_binding(bt):
+    """What other threads ask is whether the library is there; the calls behind it must be there by then: looked at after
+    every step of the interpreter through the first use."""
+    import sys
+    before = bt._lib, bt._call
+    halves = []
+
+    def look(frame, event, arg):
+        if frame.f_code is not bt.lib.__code__:
+            return None
+        frame.f_trace_opcodes = True
+        if bt._lib is not None and bt._call is None:
+            halves.append(frame.f_lineno)
+        return look
+    tracer = sys.gettrace()
+    bt._lib = bt._call = None
+    try:
+        sys.settrace(look)
+        bt.lib()
+    finally:
+        sys.settrace(tracer)
+        bt._lib, bt._call = before if bt._lib is None else (bt._lib, bt._call)
+    assert not halves
+
+
 class _FakeTensor:
     """What the binding reads of a tensor; no memory behind it, so a call must be refused before anything is launched."""
 
