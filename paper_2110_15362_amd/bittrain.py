@@ -147,7 +147,7 @@ def bt_workspace_bytes(n, dtype):
 def _stream_handle(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)).value or 0
 
 
 def _stream(stream):

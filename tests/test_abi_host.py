@@ -488,3 +488,17 @@ def test_binding_takes_empty_tensors_and_keywords(bt):
     assert bt.bt_relu_backward_from_bitmap(w, grad_out=f, grad_in=f, stream=0) is None
     assert bt.bt_mask_apply(w, f, f, stream=0) is None
     assert bt.bt_decompress_indexed(w, f, _FakeTensor(0, torch.int64, ptr=0), f, stream=0) is None
+
+
+@pytest.mark.parametrize("handle", [0, 2, True, "3", -1, 1 << 63, (1 << 64) + 2, None])
+def test_binding_takes_every_stream_that_makes_a_pointer(bt, handle):
+    """A stream is an object with a handle (which may be None, the default stream) or a number; single-tensor and batched
+    calls make a pointer of it alike.  Nothing is launched: the tensors are empty."""
+    import torch
+
+    class Stream:
+        cuda_stream = handle if not isinstance(handle, str) else int(handle)
+    f, w = _FakeTensor(0, torch.float32, ptr=0), _FakeTensor(0, torch.int32, ptr=0)
+    for stream in (Stream(),) if handle is None else (Stream(), handle):
+        assert bt.bt_relu_backward_from_bitmap(w, f, f, stream=stream) is None
+        assert bt.bt_decompress_batch((bt.DecompressItem * 1)(), 0, torch.float32, _FakeTensor(64, torch.uint8), stream=stream) is None
