@@ -84,7 +84,8 @@ constexpr uint32_t kPatience = 1u << 12;  // polls before a workgroup counts wha
 #ifndef BT_SCANNER_SLEEP
 #define BT_SCANNER_SLEEP 1
 #endif
-constexpr uint32_t kDenseEarlySlots = 1280;      // launches of up to this many slots store a dense output before the prefix is there
+// Launches of up to this many slots store a dense output before the prefix is there (element bytes S; see compress_kernel).
+template <int S> constexpr uint32_t kDenseEarlySlots = S == 2 ? 1024 : 768;
 constexpr int kScannerSleep = BT_SCANNER_SLEEP;   // pause between two polls, in units of 64 clocks
 
 // S: element bytes; R: rows (16-byte loads) per lane per tile.
@@ -124,6 +125,13 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
     x += BT_DPP(0, x, 0x142, 0xa, false);  // row_bcast:15 into rows 1 and 3
     x += BT_DPP(0, x, 0x143, 0xc, false);  // row_bcast:31 into rows 2 and 3
     return x;
+}
+
+// The lanes' numbers added up, in 64 bits.  (By DPP, in two halves: shuffles would keep an address per step in a register.)
+__device__ __forceinline__ uint64_t wave_total_of(uint32_t x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(x & 0xffffu), 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(x >> 16), 63);
+    return ((uint64_t)hi << 16) + lo;
 }
 
 // OR over each aligned group of G lanes (G = 4, 8 or 16); every lane gets the result.
@@ -934,12 +942,11 @@ __device__ __forceinline__ uint64_t prefix_from_input(const void *__restrict__ i
                                                    const double threshold, const int lane) {
     const uint64_t vectors = (uint64_t)tile * (Geo<S, R>::TILE / Geo<S, R>::E);      // all of them whole and inside the tensor
     const uint4 *const end = static_cast<const uint4 *>(in) + vectors;
-    uint64_t mine = 0;
+    uint32_t share = 0;      // at most BT_MAX_ELEMENTS / 64
+#pragma unroll 1
     for (const uint4 *q = static_cast<const uint4 *>(in) + lane; q < end; q += kWaveSize)
-        mine += (uint32_t)__popc(keep_mask<S, KEEP>(*q, threshold_f, threshold));
-#pragma unroll
-    for (int d = 1; d < kWaveSize; d <<= 1) mine += __shfl_xor((unsigned long long)mine, d, kWaveSize);
-    return uniform64(mine);
+        share += (uint32_t)__popc(keep_mask<S, KEEP>(*q, threshold_f, threshold));
+    return wave_total_of(share);
 }
 
 // bt_compress and its relatives (pruning, dense output, tile index, batches): workgroup 0 is the scanner
@@ -1100,31 +1107,36 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
         void *const dense = job.dense(sl.item);
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-            const uint32_t mk = BT_MASK(S, mp, k);
-            uint32_t d[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
-            // masks by arithmetic (0 - bit is all ones or zero), not by compares: see nonzero_mask
+            uint32_t mk = BT_MASK(S, mp, k);
+            if (S == 2 && !DIRECT) asm volatile("" : "+v"(mk));      // (a row's work starts here, as in the compaction below)
+            // Masks by arithmetic (0 - bit is all ones or zero), not by compares: see nonzero_mask.  In place, and with the row's
+            // address in scalar registers, because vector registers are short: of a dropped element nothing is looked at any
+            // more.  (A row's masked copy put 8 to 9 registers of the eight-row kernels into scratch: fp64 5 M elements 18.7 us,
+            // now 15.2, 103 M 347 / 340; fp32 12 M 19.8 / 18.1.)
+            uint32_t *const d[4] = {&x[k].x, &x[k].y, &x[k].z, &x[k].w};
             if (S == 8) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) d[j] &= 0u - ((mk >> (j >> 1)) & 1u);
+                for (int j = 0; j < 4; ++j) *d[j] &= 0u - ((mk >> (j >> 1)) & 1u);
             } else if (S == 4) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) d[j] &= 0u - ((mk >> j) & 1u);
+                for (int j = 0; j < 4; ++j) *d[j] &= 0u - ((mk >> j) & 1u);
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    d[j] &= (((mk >> (2 * j)) & 1u) * 0x0000ffffu) | (((mk >> (2 * j + 1)) & 1u) * 0xffff0000u);
+                    *d[j] &= (((mk >> (2 * j)) & 1u) * 0x0000ffffu) | (((mk >> (2 * j + 1)) & 1u) * 0xffff0000u);
             }
-            const uint64_t e0 = wave_e0 + (uint64_t)k * G::ROW + (uint64_t)lane * E;
-            const uint4 o = make_uint4(d[0], d[1], d[2], d[3]);
-            if (full) stream_store<kCompressNtStore>(reinterpret_cast<uint4 *>(static_cast<char *>(dense) + e0 * S), o);
-            else store_vec_guarded<S>(dense, e0, n, o);
+            const uint64_t row_e0 = wave_e0 + (uint64_t)k * G::ROW;
+            if (full) stream_store<kCompressNtStore>(reinterpret_cast<uint4 *>(static_cast<char *>(dense) + row_e0 * S) + lane, x[k]);
+            else store_vec_guarded<S>(dense, row_e0 + (uint64_t)(lane * E), n, x[k]);
         }
     };
     // Before the wait or after it?  Before, the stores use memory that would idle while the prefixes of a small launch are
     // on their way, but the polling wave waits for its own first; in a launch that keeps the memory busy they only hold
-    // up everybody's polls and values.  Measured, before / after, us: fp32 8 M elements (977 tiles) 14.9 / 16.1, 12 M (1465
-    // tiles) 23.2 / 22.0, 25.7 M 48.2 / 45.1; bf16 16 M (977) 16.4 / 17.9, 24 M (1465) 23.2 / 23.9, 32 M (1954) 30.8 / 28.4.
-    const bool dense_early = DENSE && n_slots <= kDenseEarlySlots;
+    // up everybody's polls and values.  Measured, before / after, us, at 0, 50 and 95 % zeros beside what the ReLU clears: fp32
+    // 6 M elements (733 tiles) 11.1 / 12.3, 10.9 / 11.6, 10.6 / 11.1, 8 M (977) 15.6 / 15.0, 15.3 / 13.6, 14.8 / 12.7; fp64 3 M (733)
+    // 10.9 / 12.3, 10.5 / 11.1, 10.6 / 10.8, 3.5 M (855) 14.2 / 13.4, 14.0 / 12.4, 13.3 / 11.6; bf16 16 M (977) 16.6 / 17.2,
+    // 15.9 / 16.1, 15.5 / 15.5, 20 M (1221) 19.6 / 19.8, 18.5 / 18.4, 18.3 / 17.4.
+    const bool dense_early = DENSE && n_slots <= kDenseEarlySlots<S>;
     if (dense_early) store_dense();
     // The bitmap words; the wave that polls keeps its own until afterwards, because a store in flight delays the polling
     // loads, which share its completion counter.  (For 16-bit elements it has no register to keep them in.)
@@ -1494,11 +1506,9 @@ __device__ __forceinline__ void restore_store(const Restoring<S, R> &r, const ui
 template <int S, int R>
 __device__ __noinline__ uint64_t prefix_from_bitmap(const uint32_t *__restrict__ bitmap, const uint32_t tile, const int lane) {
     const uint64_t words = (uint64_t)tile * Geo<S, R>::TILE_WORDS;
-    uint64_t mine = 0;
-    for (uint64_t w = (uint32_t)lane; w < words; w += kWaveSize) mine += (uint32_t)__popc(bitmap[w]);
-#pragma unroll
-    for (int d = 1; d < kWaveSize; d <<= 1) mine += __shfl_xor((unsigned long long)mine, d, kWaveSize);
-    return uniform64(mine);
+    uint32_t share = 0;      // at most BT_MAX_ELEMENTS / 64
+    for (uint64_t w = (uint32_t)lane; w < words; w += kWaveSize) share += (uint32_t)__popc(bitmap[w]);
+    return wave_total_of(share);
 }
 
 // One thread's share of the set bits in the first `words` words of the bitmap (a whole number of 16-byte vectors), the

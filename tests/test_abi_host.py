@@ -39,6 +39,14 @@ def test_every_declared_symbol_is_exported(bt):
     assert not hasattr(raw, "bt_stream_probe") and not hasattr(raw, "bt_timeline_set")
 
 
+def test_no_kernel_keeps_values_in_scratch(bt):
+    """A value that comes back from scratch behind a kernel's stores waits for them: what the compiler wrote into the
+    kernels' metadata as their private memory (a small MessagePack number) is nothing."""
+    data = open(bt.LIB_PATH, "rb").read()
+    sizes = re.findall(rb"\.private_segment_fixed_size(.)", data, flags=re.S)
+    assert len(sizes) > 70 and set(sizes) == {b"\0"}, sizes
+
+
 def test_binding_constants_are_the_headers(bt):
     text = open(os.path.join(os.path.dirname(__file__), "..", "include", "bittrain.h")).read()
     for name in ("BT_WS_ERROR_WORD", "BT_WS_WAIT_LIMIT_WORD", "BT_WS_PATIENCE_WORD", "BT_WS_WIDE_WORD", "BT_STATIC_MAX_TILES"):

@@ -365,13 +365,22 @@ def test_a_small_launch_whose_wait_runs_out_ends(gpu, oracle):
     _check_compress(gpu, oracle, x, ws=ws)
 
 
-@pytest.mark.parametrize("tiles", [1279, 1280, 1281])
-def test_activation_compress_around_the_size_where_the_dense_output_moves(gpu, oracle, tiles):
-    """Launches of up to 1280 tiles store the dense output before the prefixes are there, larger ones after."""
+def _dense_moves():
+    """(dtype, number of tiles) around the sizes where the dense output moves, and well beyond them."""
+    edges = {"f32": 768, "f64": 768, "f16": 1024, "bf16": 1024}
+    return [(dt, e + d) for dt, e in edges.items() for d in (-1, 0, 1)] + [("f64", 1279), ("f64", 1280), ("f64", 1281), ("f32", 1500)]
+
+
+@pytest.mark.parametrize("dt,tiles", _dense_moves())
+def test_activation_compress_around_the_size_where_the_dense_output_moves(gpu, oracle, dt, tiles):
+    """Launches of up to 768 tiles (16-bit elements: 1024) store the dense output before the prefixes are there, larger ones
+    after: every type on both sides, with tiles that fit the staging area and tiles that don't."""
     import paper_2110_15362_amd.bittrain as bt
-    n = tiles * 4096 - 5
-    x = wl.random_sparse(n, "f64", 0.3, seed=tiles)
-    want = oracle.prune(wl.bits(x), "f64", 0.0)
+    tile = bt.bt_tile_elems(wl.DTYPES[dt])
+    n = tiles * tile - 5
+    x = wl.random_sparse(n, dt, 0.3, seed=tiles)
+    x[5 * tile:9 * tile].abs_()                      # all of it survives: more than the staging area holds
+    want = oracle.prune(wl.bits(x), dt, 0.0)
     o_bitmap, o_values, o_nnz = oracle.compress(want)
     for inplace in (False, True):
         xd = x.cuda()
