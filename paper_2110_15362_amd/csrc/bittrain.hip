@@ -1370,7 +1370,7 @@ __device__ __forceinline__ uint32_t restore_ranks(const Quarter<S, R> &q, unsign
 // (1) in the form that the restoration of one 16-bit tensor from its index keeps: the word of each row read by the lanes that
 // share it, ranks from row sums, and the waves before this one counted from the whole tile's words.  More work, but those
 // kernels are bound by their stores, and a workgroup that is later with its own writes sparse tensors faster (fp16, 206 M
-// elements, 95 % zeros: 69 us; with restore_ranks 77, or 70 with LDS reserved for five workgroups a compute unit).
+// elements, 95 % zeros: 69 us; with restore_ranks 77, or 70 with LDS reserved for four workgroups a compute unit).
 // Returns the set bits of the waves before `wave`.
 template <int S, int R>
 __device__ __forceinline__ uint32_t restore_ranks_by_row(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane, const int wave,
@@ -1641,58 +1641,80 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
 // j at the start of the tile comes from the tile index.
 //
 // Two thirds of the traffic and more are stores, and nothing holds a workgroup back: with all eight workgroups that fit a
-// compute unit, the more the tensor's values thin out, the more the stores of too many tiles mix.  So LDS is reserved for
-// fewer where that measured better (us; 8 / 6 / 5 workgroups): the 49 fp32 tensors of a ResNet-50, 70 % zeros 563 / 547 / 552:
-// six for batches; fp32 103 M elements, 5 % 137.7 / 139.8 / 140.6, 50 % 106.2 / 104.8 / 104.5, 95 % 76.4 / 74.6 / 71.1: eight.
-// What the waves before a wave hold, it counts itself; for one tensor of fp32 or fp64 an exchange behind a barrier is better
-// (103 M and 51 M elements, 50 % zeros: 104.5 instead of 106.2 and 103 instead of 106).
-template <class Job> constexpr int kIndexedOcc = Job::kMany ? 6 : 8;
-template <int S, class Job>
+// compute unit, the stores of too many tiles mix; with few, the chain from bitmap to values shows.  So a batch reserves LDS
+// for five (LDS is allocated in steps of kLdsStep bytes: a share that is no whole number of steps makes room for one less).
+// Measured with 8 / 6 / 5 / 4 workgroups, us: the 49 tensors of a ResNet-50, fp32 at batch 64, 30 % zeros 748 / 748 / 758 / 761, 50 %
+// 659 / 644 / 643 / 637, 70 % 566 / 553 / 550 / 554; at batch 16, 95 %, 117 / 116 / 113 / 110; bf16 at batch 16, 95 %, 59 / 57 / 52 / 52, at batch 64,
+// 50 %, 335 / 324 / 319 / 319; fp64 at batch 4, 95 %, 59 / 58 / 55 / 50, at batch 1, 50 %, 20.0 / 20.4 / 20.6 / 20.9.  One tensor: fp32 103 M
+// elements, 5 % zeros 137.7 with eight, 50 % 106.2 (at 95 % fewer would be better, at 5 % worse).
+//
+// What the waves before a wave hold (see the three ways below):
+//   batches            counted by every wave from the bitmap itself, so that the waves need not meet: fp32 at batch 64, 50 % zeros,
+//                      643 us instead of 680 with an exchange through LDS, bf16 at batch 16, 95 %, 51 instead of 56;
+//   one fp32 or fp64   exchanged through LDS behind a barrier (fp32 103 M elements, 50 %: 104.5 us instead of 106.2);
+//   one of 16 bits     restore_ranks_by_row, which says why.
+//
+// LARGE (a batch of kLargeSlots slots and more): where a tile is a quarter full or less, which its index entry and the next one
+// tell, the waves meet all the same before they ask for their values, so that the tile's stores leave together.  Measured, without /
+// with, us: batch 64 in fp32 at 85 % zeros 525 / 502, at 95 % 568 / 545, in bf16 279 / 269 and 255 / 246; batch 32 in fp64 570 / 489 and
+// 545 / 486 (eight workgroups and row-by-row ranks: 526 and 489).  Below, it is as often worse as better (20 k slots: fp32 85 %
+// 114.6 / 114.9, 95 % 113 / 115.2; bf16 148 / 138 and 113 / 114.8).
+constexpr int kLdsBytes = 160 * 1024, kLdsStep = 1280;      // of a compute unit
+constexpr uint32_t kLargeSlots = 30000;
+template <class Job> constexpr int kIndexedOcc = Job::kMany ? 5 : 8;
+template <int S, class Job, bool LARGE>
 __global__ __launch_bounds__(kBlock, kIndexedOcc<Job>) void decompress_indexed_kernel(const Job job) {
     constexpr int R = kRows;
     using G = Geo<S, R>;
-    constexpr int kShare = 160 * 1024 / kIndexedOcc<Job> - 256;
+    constexpr int kShare = kLdsBytes / kIndexedOcc<Job> / kLdsStep * kLdsStep;
+    constexpr int kTotals = kWaves * (int)sizeof(uint32_t);      // of the share, for the waves' totals
+    static_assert(kShare * kIndexedOcc<Job> <= kLdsBytes && kShare - kTotals >= kWaves * G::LDS_WAVE, "the workgroups and their strips fit");
     constexpr bool kByRow = S == 2 && !Job::kMany;
     constexpr bool kExchange = S != 2 && !Job::kMany;
-    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kShare > kWaves * G::LDS_WAVE ? kShare : kWaves * G::LDS_WAVE];
+    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kShare - kTotals];
     __shared__ uint32_t s_wave_total[kWaves];
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Slot sl = job.at(blockIdx.x);
     if (sl.idle) return;
-    const uint64_t tile_j = job.tile_index(sl.item)[sl.tile];             // asked for first, needed last
+    const uint64_t *const index = job.tile_index(sl.item) + sl.tile;
+    const uint64_t tile_j = index[0];             // asked for first, needed last
+    bool together = false;                        // (the same in all waves: it depends on the index alone)
+    if (LARGE && sl.tile + 1 < job.tiles(sl.item)) together = index[1] - tile_j < (uint64_t)(G::TILE / 4);
     const uint32_t *const bitmap = job.bitmap(sl.item);
     const uint64_t n = job.n(sl.item);
-    const Quarter<S, R> quarter = quarter_load<S, R>(bitmap, n, sl.tile, lane, wave);
-    // What the waves before this one hold, each wave counts itself: a barrier in their place made the workgroup's stores
-    // come in one burst (fp16, 206 M elements, 95 % zeros: 77 us instead of 72).
     Restoring<S, R> r;
     unsigned char *const strip = s_stage + wave * G::LDS_WAVE;
     uint32_t before_wave = 0;
-    if (kExchange) {
-        const uint32_t wave_total = restore_ranks<S, R>(quarter, strip, lane, r);
-        if (lane == 0) s_wave_total[wave] = wave_total;
-        lds_barrier();
-#pragma unroll
-        for (int w = 0; w < kWaves - 1; ++w) {
-            const uint32_t c = s_wave_total[w];
-            if (w < wave) before_wave += c;
-        }
-        before_wave = uniform32(before_wave);
-    } else if (kByRow) {
+    if constexpr (kByRow) {
         before_wave = restore_ranks_by_row<S, R>(bitmap, n, sl.tile, lane, wave, r);
     } else {
+        const Quarter<S, R> quarter = quarter_load<S, R>(bitmap, n, sl.tile, lane, wave);
         uint32_t before = 0;
+        if (!kExchange) {
 #pragma unroll
-        for (int w = 0; w < kWaves - 1; ++w) {
-            if (w < wave) {
-                const Quarter<S, R> q = quarter_load<S, R>(bitmap, n, sl.tile, lane, w);
+            for (int w = 0; w < kWaves - 1; ++w) {
+                if (w < wave) {
+                    const Quarter<S, R> q = quarter_load<S, R>(bitmap, n, sl.tile, lane, w);
 #pragma unroll
-                for (int j = 0; j < G::WPL; ++j) before += (uint32_t)__popc(q.w[j]);
+                    for (int j = 0; j < G::WPL; ++j) before += (uint32_t)__popc(q.w[j]);
+                }
             }
         }
-        restore_ranks<S, R>(quarter, strip, lane, r);
-        before_wave = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(before), 63);
+        const uint32_t wave_total = restore_ranks<S, R>(quarter, strip, lane, r);
+        if (kExchange) {
+            if (lane == 0) s_wave_total[wave] = wave_total;
+            lds_barrier();
+#pragma unroll
+            for (int w = 0; w < kWaves - 1; ++w) {
+                const uint32_t c = s_wave_total[w];
+                if (w < wave) before_wave += c;
+            }
+            before_wave = uniform32(before_wave);
+        } else {
+            before_wave = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(before), 63);
+            if (LARGE && together) lds_barrier();
+        }
     }
     restore_fetch<S, R>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
     restore_store<S, R>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
@@ -1913,12 +1935,12 @@ bt_status launch_decompress(const Job &job, uint64_t slots, int s, char *ws, hip
     return launched();
 }
 
-template <class Job>
+template <bool LARGE, class Job>
 bt_status launch_decompress_indexed(const Job &job, uint64_t slots, int s, hipStream_t hs) {
     const dim3 grid((unsigned)slots), block(kBlock);
-    if (s == 8) decompress_indexed_kernel<8, Job><<<grid, block, 0, hs>>>(job);
-    else if (s == 4) decompress_indexed_kernel<4, Job><<<grid, block, 0, hs>>>(job);
-    else decompress_indexed_kernel<2, Job><<<grid, block, 0, hs>>>(job);
+    if (s == 8) decompress_indexed_kernel<8, Job, LARGE><<<grid, block, 0, hs>>>(job);
+    else if (s == 4) decompress_indexed_kernel<4, Job, LARGE><<<grid, block, 0, hs>>>(job);
+    else decompress_indexed_kernel<2, Job, LARGE><<<grid, block, 0, hs>>>(job);
     return launched();
 }
 
@@ -2118,7 +2140,7 @@ bt_status bt_decompress_indexed(const uint32_t *d_bitmap, const void *d_values, 
         return BT_ERR_ALIGN;
     const uint32_t n_tiles = (uint32_t)tiles_for(n, s);
     const DecompressOne job{d_bitmap, d_values, values_cap, d_index, n, d_out, n_tiles};
-    return launch_decompress_indexed(job, n_tiles, s, (hipStream_t)stream);
+    return launch_decompress_indexed<false>(job, n_tiles, s, (hipStream_t)stream);
 }
 
 bt_status bt_decompress(const uint32_t *d_bitmap, const void *d_values, uint64_t n, bt_dtype dtype, void *d_out,
@@ -2306,7 +2328,8 @@ bt_status bt_decompress_batch_indexed(const bt_decompress_item *items, size_t co
             b.n_[i] = it.n;
             b.out_[i] = it.d_out;
         }
-        const bt_status ls = launch_decompress_indexed(b, b.lay.start[c], s, hs);
+        const uint64_t slots = b.lay.start[c];
+        const bt_status ls = slots >= kLargeSlots ? launch_decompress_indexed<true>(b, slots, s, hs) : launch_decompress_indexed<false>(b, slots, s, hs);
         if (ls != BT_OK) return ls;
     }
     return BT_OK;

@@ -125,3 +125,39 @@ def test_indexed_config2_full_size(bt, oracle):
     assert np.array_equal(index, oracle.tile_index(o_bitmap, n, tile))
     out = _decompress_indexed(bt, bitmap, values, index, n, torch.float32)
     assert np.array_equal(out, wl.bits(x))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
+def test_large_batch_from_indexes_with_tiles_around_a_quarter_full(bt, dt):
+    """A batch of 30,000 slots and more lets a tile's waves meet where the tile is a quarter full or less: tiles on both sides of
+    that, empty and full ones, a ragged last tile (whose index entry is the last) and tensors of one tile, against the tensors
+    that were compressed."""
+    dtype = wl.DTYPES[dt]
+    tile = bt.bt_tile_elems(dtype)
+    g = torch.Generator(device="cuda").manual_seed(77)
+    ns = [385 * tile - 3 - k for k in range(60)] + [1, tile, 2 * tile + 1, 5]      # 385 tiles: 512 slots
+    assert sum(-(-max(-(-n // tile), 1) // 128) * 128 for n in ns) >= 30000
+    kept = torch.tensor([0, 1, tile // 4 - 1, tile // 4, tile // 4 + 1, tile // 2, tile - 1, tile], device="cuda")
+    xs = []
+    for k, n in enumerate(ns):
+        tiles = -(-n // tile)
+        x = torch.randint(1, 1 << 15, (tiles, tile), generator=g, device="cuda", dtype=torch.int16)
+        want = kept[torch.randint(0, len(kept), (tiles,), generator=g, device="cuda")]
+        offset = torch.randint(0, tile, (tiles,), generator=g, device="cuda")      # a run of `want` elements, wrapped round
+        at = (torch.arange(tile, device="cuda")[None, :] - offset[:, None]) % tile
+        x.masked_fill_(at >= want[:, None], 0)
+        wide = {2: torch.int16, 4: torch.int32, 8: torch.int64}[dtype.itemsize]
+        xs.append(x.reshape(-1)[:n].to(wide).view(dtype))
+    bms = [torch.empty((n + 31) // 32, dtype=torch.int32, device="cuda") for n in ns]
+    vals = [torch.empty(n, dtype=dtype, device="cuda") for n in ns]
+    idx = [torch.empty(bt.bt_index_bytes(n, dtype) // 8, dtype=torch.int64, device="cuda") for n in ns]
+    nnz = torch.zeros(len(ns), dtype=torch.int64, device="cuda")
+    bt.bt_compress_batch(bt.compress_items(xs, bms, vals, nnz, indexes=idx), len(ns), dtype, bt.new_batch_workspace(ns, dtype))
+    outs = [_sentinel(n + 8, dtype) for n in ns]
+    items = bt.decompress_items(bms, vals, [o[:n] for o, n in zip(outs, ns)], indexes=idx)
+    bt.bt_decompress_batch_indexed(items, len(ns), dtype)
+    torch.cuda.synchronize()
+    for k, (n, x, o) in enumerate(zip(ns, xs, outs)):
+        assert int(nnz[k].item()) == int((x.view(torch.uint8).view(n, -1) != 0).any(1).sum()), k
+        assert torch.equal(o[:n].view(torch.uint8), x.view(torch.uint8)), k
+        assert bool((o[n:].view(torch.uint8) == SENT).all()), k
