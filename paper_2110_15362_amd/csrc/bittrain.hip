@@ -1176,7 +1176,9 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
         if (lane_number() == 0) {
             s_tile_prefix = v;
             uint64_t *const index = job.index(sl.item);
-            if (index != nullptr) index[tile] = v;     // Algorithm 2's j at the start of this tile, for bt_decompress_indexed
+            // Algorithm 2's j at the start of this tile, for bt_decompress_indexed; the index has the tiles of kRows rows
+            constexpr uint32_t kPerEntry = kRows / R;
+            if (index != nullptr && tile % kPerEntry == 0) index[tile / kPerEntry] = v;
         }
     }
     lds_barrier();
@@ -2053,12 +2055,14 @@ static bt_status compress_common(const void *d_in, uint64_t n, bt_dtype dtype, b
     // Small tensors.  With few tiles a launch is the chain kernel start, load, count, wait, store, each step at the latency of
     // a wave that has its SIMD nearly to itself, so a tile of two or four rows a lane instead of eight is through sooner,
     // as long as no more than kDirectSlots workgroups poll each other's counts; two rows only up to 64 tiles, beyond which
-    // the polling costs more than they save.  A tile index has the tiles of eight rows.  Measured, us per call on the GPU,
-    // before / after: fp32 5 k elements 6.1 / 3.6, 50 k 5.9 / 4.1, 201 k 6.5 / 4.5 (with two rows 4.7), 500 k 6.3 / 4.9,
-    // 1 M 6.6 / 5.2, 2 M (eight rows) 7.3 / 6.2, 3 M (scanner) 8.7 / 8.3; bf16 2 M 7.0 / 5.3.
+    // the polling costs more than they save.  An index entry comes from every second or fourth of these tiles.  Measured,
+    // us per call on the GPU, before / after: fp32 5 k elements 6.1 / 3.6, 50 k 5.9 / 4.1, 201 k 6.5 / 4.5 (with two rows 4.7), 500 k
+    // 6.3 / 4.9, 1 M 6.6 / 5.2, 2 M (eight rows) 7.3 / 6.2, 3 M (scanner) 8.7 / 8.3; bf16 2 M 7.0 / 5.3.  With an index: bf16 100 k elements
+    // with the scanner 7.2, without it but in tiles of eight rows 7.3 (by the workspace's place up to 7.6), of two rows 4.8; 800 k,
+    // 5 % zeros, 8.7 / 9.2 / 6.3 (four rows); fp32 201 k 6.9 / 6.6 / 4.8.
     using std::integral_constant;
-    if (d_index == nullptr && tiles_for(n, s, 2) <= 64) return launch(integral_constant<int, 2>{}, std::true_type{});
-    if (d_index == nullptr && tiles_for(n, s, 4) <= kDirectSlots) return launch(integral_constant<int, 4>{}, std::true_type{});
+    if (tiles_for(n, s, 2) <= 64) return launch(integral_constant<int, 2>{}, std::true_type{});
+    if (tiles_for(n, s, 4) <= kDirectSlots) return launch(integral_constant<int, 4>{}, std::true_type{});
     if (tiles_for(n, s) <= kDirectSlots) return launch(integral_constant<int, kRows>{}, std::true_type{});
     return launch(integral_constant<int, kRows>{}, std::false_type{});
 }

@@ -80,6 +80,23 @@ def test_index_and_indexed_decompress_sizes_and_tails(bt, oracle, dt):
         assert np.array_equal(out, xb), n
 
 
+@pytest.mark.parametrize("dt", DTYPES)
+def test_index_at_the_edges_of_the_small_launches(bt, oracle, dt):
+    """Small tensors are compressed in tiles of two or four rows, of which every fourth or second leaves an entry: numbers of
+    elements around the changes of plan (64 tiles of two rows, 256 of four, 256 of eight; a row is 4 KiB a tile) and last
+    tiles that begin or don't begin an entry, on one workspace."""
+    row = 4096 // wl.DTYPES[dt].itemsize
+    tile = 8 * row
+    ws = bt.new_workspace(257 * tile, wl.DTYPES[dt])
+    sizes = sorted({k * row + d for k in (2, 4, 6, 8, 10, 128, 130, 134, 136, 1024, 1028, 1032, 2048, 2056) for d in (-1, 0, 1)})
+    for i, n in enumerate(sizes):
+        x = wl.random_sparse(n, dt, [0.5, 0.05, 0.97][i % 3], seed=7300 + i)
+        o_bitmap, o_values, o_nnz = oracle.compress(wl.bits(x))
+        bitmap, values, nnz, index = _compress_indexed(bt, x, ws)
+        assert nnz == o_nnz and np.array_equal(bitmap, o_bitmap) and np.array_equal(values, o_values), n
+        assert np.array_equal(index, oracle.tile_index(o_bitmap, n, tile)), n
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_indexed_special_patterns_and_extremes(bt, oracle, dt):
     tile = bt.bt_tile_elems(wl.DTYPES[dt])
