@@ -85,7 +85,7 @@ constexpr uint32_t kPatience = 1u << 12;  // polls before a workgroup counts wha
 #define BT_SCANNER_SLEEP 1
 #endif
 // Launches of up to this many slots store a dense output before the prefix is there (element bytes S; see compress_kernel).
-template <int S> constexpr uint32_t kDenseEarlySlots = S == 2 ? 1024 : 768;
+template <int S> constexpr uint32_t kDenseEarlySlots = S == 2 ? 1280 : 1000;
 constexpr int kScannerSleep = BT_SCANNER_SLEEP;   // pause between two polls, in units of 64 clocks
 
 // S: element bytes; R: rows (16-byte loads) per lane per tile.
@@ -1130,14 +1130,13 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
             else store_vec_guarded<S>(dense, row_e0 + (uint64_t)(lane * E), n, x[k]);
         }
     };
-    // Before the wait or after it?  Before, the stores use memory that would idle while the prefixes of a small launch are
-    // on their way, but the polling wave waits for its own first; in a launch that keeps the memory busy they only hold
-    // up everybody's polls and values.  Measured, before / after, us, at 0, 50 and 95 % zeros beside what the ReLU clears: fp32
-    // 6 M elements (733 tiles) 11.1 / 12.3, 10.9 / 11.6, 10.6 / 11.1, 8 M (977) 15.6 / 15.0, 15.3 / 13.6, 14.8 / 12.7; fp64 3 M (733)
-    // 10.9 / 12.3, 10.5 / 11.1, 10.6 / 10.8, 3.5 M (855) 14.2 / 13.4, 14.0 / 12.4, 13.3 / 11.6; bf16 16 M (977) 16.6 / 17.2,
-    // 15.9 / 16.1, 15.5 / 15.5, 20 M (1221) 19.6 / 19.8, 18.5 / 18.4, 18.3 / 17.4.
+    // Before the wait or after it?  Before (but behind the compaction, which has the values in registers too), the stores use
+    // memory that would idle while the prefixes of a small launch are on their way, but the polling wave waits for its own
+    // first; in a launch that keeps the memory busy they only hold up everybody's polls and values.  Measured, before / after, us,
+    // pre-activations without zeros and with half zeros: fp32 6.5 M elements (794 tiles) 12.4 / 13.2 and 12.1 / 12.6, 8 M (977)
+    // 14.4 / 14.8 and 13.9 / 13.4, 9 M (1099) 18.3 / 16.3 and 17.4 / 14.8; fp64 3.7 M (904) 13.1 / 13.7 and 12.9 / 12.5, 4.5 M (1099)
+    // 18.3 / 15.8 and 17.4 / 14.3; bf16 18 M (1099) 18.3 / 18.9 and 17.4 / 17.7, 20 M (1221) 19.0 / 19.5 and 17.9 / 18.0.
     const bool dense_early = DENSE && n_slots <= kDenseEarlySlots<S>;
-    if (dense_early) store_dense();
     // The bitmap words; the wave that polls keeps its own until afterwards, because a store in flight delays the polling
     // loads, which share its completion counter.  (For 16-bit elements it has no register to keep them in.)
     const bool words_early = S == 2 || dense_early || wave != 0;
@@ -1166,6 +1165,8 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
 #pragma unroll
         for (int k = G::PHASE; k < R; ++k) scatter(k, run0);
     }
+
+    if (dense_early) store_dense();
 
     // The first wave waits for the tile's prefix.
     uint32_t polls = 0;

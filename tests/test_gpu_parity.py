@@ -367,13 +367,13 @@ def test_a_small_launch_whose_wait_runs_out_ends(gpu, oracle):
 
 def _dense_moves():
     """(dtype, number of tiles) around the sizes where the dense output moves, and well beyond them."""
-    edges = {"f32": 768, "f64": 768, "f16": 1024, "bf16": 1024}
+    edges = {"f32": 1000, "f64": 1000, "f16": 1280, "bf16": 1280}
     return [(dt, e + d) for dt, e in edges.items() for d in (-1, 0, 1)] + [("f64", 1279), ("f64", 1280), ("f64", 1281), ("f32", 1500)]
 
 
 @pytest.mark.parametrize("dt,tiles", _dense_moves())
 def test_activation_compress_around_the_size_where_the_dense_output_moves(gpu, oracle, dt, tiles):
-    """Launches of up to 768 tiles (16-bit elements: 1024) store the dense output before the prefixes are there, larger ones
+    """Launches of up to 1000 tiles (16-bit elements: 1280) store the dense output before the prefixes are there, larger ones
     after: every type on both sides, with tiles that fit the staging area and tiles that don't."""
     import paper_2110_15362_amd.bittrain as bt
     tile = bt.bt_tile_elems(wl.DTYPES[dt])
