@@ -69,6 +69,7 @@ constexpr int kHdrError = BT_WS_ERROR_WORD;           // set if a wait was given
 constexpr int kHdrSpinLimit = BT_WS_WAIT_LIMIT_WORD;  // scanner passes before its wait is given up; 0: kSpinLimit
 constexpr int kHdrWide = BT_WS_WIDE_WORD;             // non-zero: the one-tensor scanner writes 8-byte entries only
 constexpr int kHdrPatience = BT_WS_PATIENCE_WORD;     // polls before a workgroup counts what precedes its tile itself; 0: kPatience
+constexpr int kHdrMute = BT_WS_MUTE_WORD;             // non-zero: tiles are not told their prefixes
 constexpr size_t kHeaderBytes = 256;
 // Block of 256 slots, two copies c = 0, 1 of everything:
 //   [1024*c, 1024*c + 1024)            uint32 count + 1 of each slot, written by the slot's workgroup
@@ -610,7 +611,8 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
     uint64_t base = 0;         // stored values of that tensor in the tiles before the frontier's row of 128 slots
     uint32_t spins = 0;
     const uint32_t limit = uniform32(wait_limit(hdr));
-    const bool wide = uniform32(hdr[kHdrWide]) != 0;      // never written by a kernel
+    const uint32_t mute = uniform32(hdr[kHdrMute]);       // these two: never written by a kernel
+    const bool wide = uniform32(hdr[kHdrWide]) != 0 || mute != 0;
 #ifdef BT_TIMELINE
     uint64_t *const timeline = g_timeline;      // read once: a load in the loop would join the scanner's waits
     uint32_t timeline_pass = 0;
@@ -666,8 +668,8 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
                         else if (use_a) ws_store32(entry, pa);
                     } else {
                         const uint64_t pa = (base + 1) + (incl - va - vb);
-                        if (use_a) ws_store64(entry, pa);
-                        if (use_b) ws_store64(entry + 8, pa + va);
+                        if (use_a && mute == 0) ws_store64(entry, pa);
+                        if (use_b && mute == 0) ws_store64(entry + 8, pa + va);
                     }
                     new_frontier = row_end;
                     if (row_end == item_end) {      // this tensor's number of values
@@ -796,8 +798,13 @@ __device__ __forceinline__ uint64_t wait_for_counts(char *ws, const Job &job, co
                                                     const uint32_t own, uint32_t &polls, const Itself &itself) {
     uint32_t *const hdr = reinterpret_cast<uint32_t *>(ws);
     const bool last = slot + 1 == n_slots;
+#ifdef BT_TIMELINE
+    const bool deaf = uniform32(hdr[kHdrMute]) > (last ? 1u : 0u);
+#else
+    constexpr bool deaf = false;      // (to look costs these launches, which are short of everything but registers, 1 to 2 %)
+#endif
     uint64_t v = 0;
-    while (!sum_counts(ws, slot, ep.cur, v)) {
+    while (deaf || !sum_counts(ws, slot, ep.cur, v)) {
         ++polls;
         if (!last && (polls & 255u) == 0 && polls > patience_of(hdr)) return itself();
         if (last && polls >= wait_limit(hdr)) {      // its wait is bounded like the scanner's

@@ -131,6 +131,22 @@ def test_batch_slot_lookup_at_the_ends_of_its_steps(bt, oracle, count):
     _check_batch(bt, oracle, xs)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
+def test_batch_whose_tiles_stop_waiting(bt, oracle, dt):
+    """Forced from the host: no tile of a batch is told its offset, so each counts what precedes it in its own tensor, from the
+    input or the bitmap; sums still go to every nnz, and the workspace serves the next call."""
+    t = TILE[wl.DTYPES[dt].itemsize]
+    xs = [wl.random_sparse(n, dt, 0.6, 7600 + k) for k, n in enumerate((3 * t + 5, 0, 129 * t + 1, 7, 40 * t))]
+    ns = [x.numel() for x in xs]
+    ws = bt.new_batch_workspace(ns, xs[0].dtype)
+    words = ws.view(torch.int32)
+    words[bt.BT_WS_MUTE_WORD], words[bt.BT_WS_PATIENCE_WORD] = 1, 1
+    _check_batch(bt, oracle, xs, ws)
+    words[bt.BT_WS_MUTE_WORD] = 0
+    _check_batch(bt, oracle, xs, ws)
+    assert int(words[bt.BT_WS_ERROR_WORD].item()) == 0
+
+
 def test_batch_and_single_calls_share_a_workspace(bt, oracle):
     """Large batch, small single call, small batch, large single call, large batch: each call
     cleans up what the one before it left, whatever their sizes."""

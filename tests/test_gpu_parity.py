@@ -2,6 +2,8 @@
 
 Integer / bit work throughout, so the bar is exact equality of the bitmap, the
 value array [0, nnz), nnz, the restored tensor and the ReLU-backward output."""
+import contextlib
+
 import numpy as np
 import pytest
 import torch
@@ -343,26 +345,62 @@ def test_small_launches_at_the_edges_of_their_plans(gpu, oracle, dt):
     assert status.tolist() == [0, calls]
 
 
-def test_a_small_launch_whose_wait_runs_out_ends(gpu, oracle):
-    """Forced from the host: one poll for the last tile of a launch without a scanner.  Whether the counts are there by then
-    is up to the machine; the call must end inside its buffers, and either be right or say that it gave up."""
+@contextlib.contextmanager
+def _instrumented():
+    """The binding on the instrumented build (the same kernels with time stamps): the one that looks at the mute word in
+    launches without a scanner.  Workspaces must not go from one build to the other."""
     import paper_2110_15362_amd.bittrain as bt
-    n = 200 * 8192
-    x = wl.random_sparse(n, "f32", 0.5, seed=77)
-    o_bitmap, o_values, o_nnz = oracle.compress(wl.bits(x))
-    ws = bt.new_workspace(n, torch.float32)
+    from paper_2110_15362_amd import bench_aids
+    path = bt.LIB_PATH
+    bt._lib, bt.LIB_PATH = None, bench_aids.LIB_PATH
+    try:
+        bt.lib()
+        yield
+    finally:
+        bt._lib, bt.LIB_PATH = None, path
+        bt.lib()
+
+
+def _small_plans(dt):
+    """name -> a number of elements that takes it: the launches of compression without a scanner, and one with it."""
+    row = 4096 // wl.DTYPES[dt].itemsize
+    return {"two_rows": 40 * 2 * row - 5, "four_rows": 100 * 4 * row + 77, "eight_rows": 200 * 8 * row + 1, "scanner": 300 * 8 * row + 4321}
+
+
+def _refused(gpu, x, o_bitmap, o_values, ws):
+    """Both directions on a workspace that has failed: every output keeps the fill pattern."""
+    n = x.numel()
+    bitmap, values, nnz, _ = gpu.gpu_compress(x, ws=ws)
+    assert nnz == -7 and (bitmap == 0x5A5A5A5A).all() and (values.view(np.uint8) == 0x5A).all(), n
+    out, guard_ok = gpu.gpu_decompress(o_bitmap, o_values, n, x.dtype, ws=ws)
+    assert guard_ok and (out.view(np.uint8) == 0x5A).all(), n
+
+
+@pytest.mark.parametrize("dt", DTYPES)
+@pytest.mark.parametrize("plan", ["two_rows", "four_rows", "eight_rows"])
+def test_a_small_launch_whose_wait_runs_out_ends(gpu, oracle, dt, plan):
+    """Forced from the host: the last tile of a launch without a scanner is told nothing and has one poll.  The call must end
+    inside its buffers and say that it gave up; until bt_workspace_init nothing on that workspace writes anything, in either
+    direction and at any size; afterwards it works again."""
+    import paper_2110_15362_amd.bittrain as bt
+    n = _small_plans(dt)[plan]
+    x = wl.random_sparse(n, dt, 0.5, seed=77)
+    ws = bt.new_workspace(max(_small_plans(dt).values()), x.dtype)
     words = ws.view(torch.int32)
-    words[bt.BT_WS_WAIT_LIMIT_WORD] = 1
-    bitmap, values, nnz, tail_ok = gpu.gpu_compress(x, ws=ws)
-    assert tail_ok
-    if int(words[bt.BT_WS_ERROR_WORD].item()) == 0:
-        assert nnz == o_nnz and np.array_equal(bitmap, o_bitmap) and np.array_equal(values[:o_nnz], o_values)
-    else:
-        assert nnz == -7, "nnz of a failed call"
-        out, guard_ok = gpu.gpu_decompress(o_bitmap[:1], o_values, 32, torch.float32, ws=ws)
-        assert guard_ok and (out == 0x5A5A5A5A).all(), "a failed workspace takes no work"
+    words[bt.BT_WS_MUTE_WORD], words[bt.BT_WS_WAIT_LIMIT_WORD], words[bt.BT_WS_PATIENCE_WORD] = 2, 1, 1
+    with _instrumented():
+        bitmap, values, nnz, tail_ok = gpu.gpu_compress(x, ws=ws)
+    assert tail_ok and nnz == -7, "nnz of a failed call is not written"
+    assert int(words[bt.BT_WS_ERROR_WORD].item()) == 1
+    # (the error word is all that a refused call looks at: from here on the library's own build)
+    for m in _small_plans(dt).values():
+        y = wl.random_sparse(m, dt, 0.5, seed=78)
+        o_bitmap, o_values, _ = oracle.compress(wl.bits(y))
+        _refused(gpu, y, o_bitmap, o_values, ws)
     bt.bt_workspace_init(ws)
-    _check_compress(gpu, oracle, x, ws=ws)
+    assert not bool(words.any())
+    o_bitmap, o_values, _ = _check_compress(gpu, oracle, x, ws=ws)
+    _check_decompress(gpu, oracle, o_bitmap, o_values, n, x.dtype, wl.bits(x), ws=ws)
 
 
 def _dense_moves():
@@ -497,38 +535,62 @@ def test_a_wait_that_runs_out_ends_the_kernel_and_raises_the_flag(gpu, oracle):
 
 
 @pytest.mark.parametrize("dt", DTYPES)
-def test_compression_that_stops_waiting_counts_the_input_itself(gpu, oracle, dt):
-    """Forced from the host: with the patience word at one poll a compressing workgroup does not wait for the
-    scanner but counts the kept elements before its tile itself.  Every output must be right all the same,
-    with and without pruning, and nothing has failed."""
+@pytest.mark.parametrize("plan", ["two_rows", "four_rows", "eight_rows", "scanner"])
+def test_compression_that_stops_waiting_counts_the_input_itself(gpu, oracle, dt, plan):
+    """Forced from the host: no tile but the one that ends the call is told anything and their patience is a poll (looked at
+    every 256th), so every workgroup stops waiting and counts the kept elements before its tile itself, with its values already
+    compacted: in launches with and without a scanner, in tiles that fit the staging area and tiles that don't, with pruning and
+    with a dense output on top of the input.  Every output must be right all the same, and nothing has failed."""
+    with contextlib.nullcontext() if plan == "scanner" else _instrumented():
+        _stops_waiting(gpu, oracle, dt, plan)
+
+
+def _stops_waiting(gpu, oracle, dt, plan):
     import paper_2110_15362_amd.bittrain as bt
-    n = 70 * bt.bt_tile_elems(wl.DTYPES[dt]) + 4321
+    n = _small_plans(dt)[plan]
+    tile = bt.bt_tile_elems(wl.DTYPES[dt])
     x = wl.random_sparse(n, dt, 0.6, seed=98)
+    full = slice(n // 3, n // 3 + min(3 * tile, n // 3))
+    x[full] = wl.random_sparse(full.stop - full.start, dt, 0.0, seed=97).abs()
     ws = bt.new_workspace(n, x.dtype)
-    ws.view(torch.int32)[bt.BT_WS_PATIENCE_WORD] = 1
+    words = ws.view(torch.int32)
+    words[bt.BT_WS_MUTE_WORD], words[bt.BT_WS_PATIENCE_WORD] = 1, 1
     _check_compress(gpu, oracle, x, ws=ws)
-    o_bitmap, o_values, o_nnz = oracle.compress(oracle.prune(wl.bits(x), dt, 0.25))
+    want = oracle.prune(wl.bits(x), dt, 0.25)
+    o_bitmap, o_values, o_nnz = oracle.compress(want)
     bitmap, values, nnz, tail_ok = gpu.gpu_compress(x, ws=ws, threshold=0.25)
     assert tail_ok and nnz == o_nnz
     assert np.array_equal(bitmap, o_bitmap) and np.array_equal(values[:o_nnz], o_values)
-    assert int(ws.view(torch.int32)[bt.BT_WS_ERROR_WORD].item()) == 0
+    for inplace in (False, True):
+        xd = x.cuda()
+        dense = xd if inplace else torch.empty_like(xd)
+        bitmap, values = torch.empty((n + 31) // 32, dtype=torch.int32, device="cuda"), torch.empty_like(xd)
+        nnz = torch.zeros(1, dtype=torch.int64, device="cuda")
+        bt.bt_activation_compress(xd, 0.25, dense, bitmap, values, nnz, ws)
+        assert int(nnz.item()) == o_nnz and np.array_equal(wl.bits(dense.cpu()), want)
+        assert np.array_equal(bitmap.cpu().numpy().view(np.uint32), o_bitmap)
+        assert np.array_equal(wl.bits(values[:o_nnz].cpu()), o_values)
+    assert int(words[bt.BT_WS_ERROR_WORD].item()) == 0 and int(words[0].item()) == 4
+    assert words[[bt.BT_WS_MUTE_WORD, bt.BT_WS_PATIENCE_WORD]].tolist() == [1, 1]      # the kernels leave the caller's words alone
 
 
 @pytest.mark.parametrize("dt", DTYPES)
 def test_restoration_that_stops_waiting_counts_the_bitmap_itself(gpu, oracle, dt):
-    """Forced from the host: with the patience word at one poll a restoring workgroup does not wait for the scanner
-    but counts the set bits before its tile itself.  The output must be right all the same, and nothing has failed."""
+    """Forced from the host: no tile is told its offset and their patience is a poll (looked at every 256th), so every restoring
+    workgroup stops waiting and counts the set bits before its tile itself.  The output must be right all the same, and nothing
+    has failed.  (More than 256 tiles of four rows: smaller tensors are restored without waiting for anything.)"""
     import paper_2110_15362_amd.bittrain as bt
     n = 150 * bt.bt_tile_elems(wl.DTYPES[dt]) + 4321
     x = wl.random_sparse(n, dt, 0.6, seed=99)
     o_bitmap, o_values, o_nnz = oracle.compress(wl.bits(x))
     ws = bt.new_workspace(n, x.dtype)
-    ws.view(torch.int32)[bt.BT_WS_PATIENCE_WORD] = 1
+    words = ws.view(torch.int32)
+    words[bt.BT_WS_MUTE_WORD], words[bt.BT_WS_PATIENCE_WORD] = 1, 1
     for _ in range(2):
         out, guard_ok = gpu.gpu_decompress(o_bitmap, o_values, n, x.dtype, ws=ws)
         assert guard_ok
         assert np.array_equal(out, wl.bits(x))
-    assert int(ws.view(torch.int32)[bt.BT_WS_ERROR_WORD].item()) == 0
+    assert int(words[bt.BT_WS_ERROR_WORD].item()) == 0 and int(words[0].item()) == 2
 
 
 @pytest.mark.parametrize("dt", DTYPES)
