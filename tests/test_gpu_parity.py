@@ -13,7 +13,8 @@ from paper_2110_15362_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 DTYPES = ["f32", "f16", "bf16", "f64"]
-# tile = 8192 fp32 / 16384 16-bit / 4096 fp64 elements; wave strip = a quarter of it; row = 256 / 512 / 128
+# tile of eight rows = 8192 fp32 / 16384 16-bit / 4096 fp64 elements (small tensors: of two or four); wave strip = a quarter of it;
+# row = 256 / 512 / 128
 SIZES = [1, 3, 4, 5, 7, 8, 9, 31, 32, 33, 63, 64, 65, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2049,
          4095, 4096, 4097, 8191, 8192, 8193, 12305, 16384, 3 * 8192 + 17, 100003, 5 * 8192, 1000000 + 37]
 
@@ -139,11 +140,11 @@ def test_workspace_reuse_across_calls_and_sizes(gpu, oracle):
 
 @pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
 def test_tile_record_and_scan_window_boundaries(gpu, oracle, dt):
-    """Sizes around the bookkeeping granularities: a tile (8192 fp32 / 16384 16-bit elements), a
-    workspace record (32 tiles), a scanner row (64 tiles) and a scanner pass (448 tiles; 384 and 512 in earlier builds)."""
+    """Sizes around the bookkeeping granularities: a tile (8192 fp32 / 16384 16-bit / 4096 fp64 elements), a scanner row (128
+    tiles), the workspace's blocks and the launches without a scanner (256), the scanner's passes (256 and 384), and some between."""
     tile = {"f32": 8192, "bf16": 16384, "f64": 4096}[dt]
     sizes = []
-    for tiles in (1, 31, 32, 33, 63, 64, 65, 383, 384, 385, 447, 448, 449, 511, 512, 513, 897, 1025):
+    for tiles in (1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 383, 384, 385, 447, 448, 449, 511, 512, 513, 897, 1025):
         sizes += [tiles * tile - 1, tiles * tile, tiles * tile + 1]
     for i, n in enumerate(sizes):
         x = wl.random_sparse(n, dt, 0.5 if i % 3 else 0.97, seed=6000 + i)
@@ -683,7 +684,8 @@ def test_bitmap_bits_beyond_n_are_ignored(gpu, oracle, dt):
     """A bitmap whose last word carries set bits at positions >= n (not what bt_compress writes, but allowed
     on input): Algorithm 2 and the select run over the n valid bits only."""
     import paper_2110_15362_amd.bittrain as bt
-    for n in (5, 33, 8191, 3 * 16384 + 7, 100001):
+    # the last two: restored in tiles of four rows, and of eight behind the scanner
+    for n in (5, 33, 8191, 3 * 16384 + 7, 100001, 70 * bt.bt_tile_elems(wl.DTYPES[dt]) + 9, 300 * bt.bt_tile_elems(wl.DTYPES[dt]) + 7):
         x = wl.random_sparse(n, dt, 0.5, seed=9100 + n % 97)
         o_bitmap, o_values, o_nnz = oracle.compress(wl.bits(x))
         dirty = o_bitmap.copy()
@@ -740,13 +742,14 @@ def test_two_streams_with_their_own_workspaces(gpu, oracle):
 
 def _pattern_masks(n, tile):
     """Zero / non-zero layouts whose run lengths sit on, just before and just after the sizes the kernels
-    work in: a 16-byte vector, a bitmap word, a wave row, a wave strip, a tile."""
+    work in: a 16-byte vector, a bitmap word, a wave row, a wave's strip and a tile of eight rows, and those of two
+    (a sixteenth and a quarter of the large tile, the latter also the strip of eight rows)."""
     i = np.arange(n)
-    row, strip = tile // 32, tile // 4
+    row, small_strip, strip = tile // 32, tile // 16, tile // 4
     masks = {"alternate": i % 2 == 0, "every_32nd": i % 32 == 31, "every_33rd": i % 33 == 0,
              "first_of_each_word_missing": i % 32 != 0, "dense_then_empty": i < n // 2, "empty_then_dense": i >= n // 2,
              "only_the_last_tile": i >= (n // tile) * tile, "only_the_last_element": i == n - 1}
-    for name, period in (("row", row), ("strip", strip), ("tile", tile)):
+    for name, period in (("row", row), ("small_strip", small_strip), ("strip", strip), ("tile", tile)):
         masks["every_other_%s" % name] = (i // period) % 2 == 0
         masks["runs_of_%s_minus_1" % name] = (i // (period - 1)) % 2 == 1
         masks["runs_of_%s_plus_1" % name] = (i // (period + 1)) % 2 == 1
@@ -757,13 +760,16 @@ def _pattern_masks(n, tile):
     return masks
 
 
+@pytest.mark.parametrize("tiles", [3, 70, 200, 260])
 @pytest.mark.parametrize("dt", ["f32", "f16", "f64"])
-def test_structured_zero_patterns(gpu, oracle, dt):
+def test_structured_zero_patterns(gpu, oracle, dt, tiles):
     """The ranks, the scatter through LDS and the tile offsets depend on where the zeros are, not
-    only on how many there are: run lengths on and around every internal size."""
+    only on how many there are: run lengths on and around every internal size, in tensors that are compressed in tiles of two, four
+    and eight rows and in eight with the scanner, and restored in two, four and (twice) in eight."""
     tile = {"f32": 8192, "f16": 16384, "f64": 4096}[dt]
-    n = 3 * tile + tile // 4 + 37
+    n = tiles * tile + tile // 4 + 37
     base = wl.random_sparse(n, dt, 0.0, 23)                    # no zeros: every kept element is distinct enough
+    base[base == 0] = 0.5                                      # (a draw can be too small for a half)
     g = wl.random_sparse(n, dt, 0.0, 24)
     assert int((wl.bits(base) == 0).sum()) == 0
     for name, keep in _pattern_masks(n, tile).items():
