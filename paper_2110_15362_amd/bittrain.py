@@ -144,14 +144,14 @@ def bt_workspace_bytes(n, dtype):
     return int(lib().bt_workspace_bytes(n, dtype if isinstance(dtype, int) else dtype_code(dtype)))
 
 
-def _stream_handle(stream):
+def _stream(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)).value or 0
+    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
-def _stream(stream):
-    return ctypes.c_void_p(_stream_handle(stream))
+def _stream_handle(stream):
+    return _stream(stream).value or 0
 
 
 def _ptr(t):
@@ -294,7 +294,7 @@ def decompress_items(bitmaps, values, outs, indexes=None):
 
 
 def bt_compress_batch(items, count, dtype, workspace, stream=None):
-    """Algorithm 1 on every tensor of `items` (from compress_items) in one launch per 64 tensors."""
+    """Algorithm 1 on every tensor of `items` (from compress_items) in one launch per 52 tensors."""
     _dev(workspace, "workspace")
     _check("bt_compress_batch", lib().bt_compress_batch(
         items, count, dtype if isinstance(dtype, int) else dtype_code(dtype), _ptr(workspace), _bytes(workspace),

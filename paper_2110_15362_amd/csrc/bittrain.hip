@@ -15,12 +15,13 @@
 //   grid    per-tile counts published in the workspace; one extra wave turns them
 //           into per-tile prefixes; a wave polls only the prefix of its own tile
 //
-// A codec launch has one workgroup per 32 KiB tile (plus one, whose first wave is the
-// scanner; launches on small tensors have smaller tiles and do without).  No workgroup depends on another for progress: a workgroup whose prefix has
-// not come after a bounded number of polls counts the elements before its tile itself,
-// from the input (compression) or from the bitmap (restoration), so the order in which
-// the hardware starts the workgroups does not matter.  A workgroup ends with its stores
-// on their way; it never waits for them to land.
+// A codec launch has one workgroup per 32 KiB tile, plus one, whose first wave is the
+// scanner; launches on small tensors have no scanner, and smaller tiles.  No workgroup
+// depends on another for progress: a workgroup whose prefix has not come after a bounded
+// number of polls counts the elements before its tile itself, from the input (compression)
+// or from the bitmap (restoration), so the order in which the hardware starts the workgroups
+// does not matter.  A workgroup ends with its stores on their way; it never waits for them
+// to land.
 //
 // There is no matrix contraction anywhere, so no MFMA: the path is bound by HBM
 // bandwidth and everything here is about moving each byte once, coalesced, and
@@ -39,7 +40,7 @@ namespace {
 constexpr int kWaveSize = 64;
 constexpr int kWaves = 4;                 // waves per block
 constexpr int kBlock = kWaveSize * kWaves;
-constexpr int kRows = 8;                  // 16-byte loads per lane per tile (of the tile index, of batches and of all but small tensors)
+constexpr int kRows = 8;                  // 16-byte loads per lane per tile: of the tile index, of batches and of all but small tensors
 constexpr int kVecBytes = 16;
 // LDS of a compressing workgroup: what eight of them on a compute unit leave each other of its 160 KiB, less the
 // words beside the staging area.
@@ -705,8 +706,8 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
     }
 }
 
-// What a workgroup reads from the header before it publishes anything, once its tile's loads are on their way.  The
-// header is rewritten once every slot of the call has published, so no wave may read it after any wave of its
+// What a workgroup reads from the header before it publishes anything (in compression once its tile's loads are on their
+// way).  The header is rewritten once every slot of the call has published, so no wave may read it after any wave of its
 // workgroup has published a count.
 // A workspace on which a wait was given up is in no defined state: later calls on it do nothing (and stay away from its
 // stale entries) until bt_workspace_init has been run.  The error word may be set while a workgroup's waves read
@@ -956,16 +957,18 @@ __device__ __forceinline__ uint64_t prefix_from_input(const void *__restrict__ i
     return wave_total_of(share);
 }
 
-// bt_compress and its relatives (pruning, dense output, tile index, batches): workgroup 0 is the scanner
-// (one wave of it), workgroup 1 + t compresses slot t.
+// bt_compress and its relatives (pruning, dense output, tile index, batches).  Tiles of R rows a lane; without DIRECT
+// workgroup 0 is the scanner (one wave of it) and workgroup 1 + t compresses slot t, with it (small tensors, see
+// compress_common) workgroup t does and sums the counts before its tile itself.
 // 1. load: lane l of row k owns elements wave_e0 + k * ROW + l * E ... + E - 1 of its wave's quarter of the
-//    tile; all eight rows are asked for at once.
+//    tile; all R rows are asked for at once.
 // 2. the test of Algorithm 1 (on the bit pattern), or the pruning test; masks packed RPM rows to a register;
 //    ranks by one DPP wave prefix sum per two rows.
 // 3. bitmap words: G lanes OR their E-bit masks into one 32-bit word.
 // 4. the waves' totals meet in LDS and the tile's count is published.  While the prefix is on its way the kept elements
-//    are compacted in LDS at their ranks (all of them if the tile's values fit, as they do up to 62 % non-zero elements;
-//    else each wave's first rows) and the waves that do not poll store their bitmap words; then the first wave polls.
+//    are compacted in LDS at their ranks (all of them if the tile's values fit, as they do up to 62 % non-zero elements of
+//    eight rows and always of fewer; else each wave's first rows) and the waves that do not poll store their bitmap words;
+//    then the first wave polls.
 // 5. values: with the prefix known, the compacted run is read back at the shift that lines it up with a 16-byte boundary
 //    of the value array and written with aligned stores, by the whole workgroup; a tile that did not fit goes
 //    PHASE rows at a time, each wave its own.
@@ -973,7 +976,8 @@ __device__ __forceinline__ uint64_t prefix_from_input(const void *__restrict__ i
 // prefix, store on ordinary ones, so what follows the prefix is kept short.  Compacting before the wait instead of
 // after it measured, us: configuration 2 (fp32, 25.7 M elements, 50 % zeros) 30.7 -> 29.5, at 90 % zeros 26.5 -> 24.9;
 // bf16 67 M elements at 65 % zeros 37.1 -> 35.2; fp16 206 M elements at 95 % zeros 88.9 -> 83.0, at 5 % 138.1 (does not fit)
-// -> 138.1; fp64 25.7 M 54.9 -> 53.4; the 49 tensors of a ResNet-50 539 -> 524; activation call fp32 5.5 M 13.4 -> 11.5.
+// -> 138.1; fp64 25.7 M 54.9 -> 53.4; the 49 tensors of a ResNet-50 539 -> 524; activation call fp32 5.5 M 13.4 -> 11.5 (10.6 since
+// it keeps nothing in scratch).  No kernel may: a value that comes back from scratch behind the stores waits for them.
 // The staging area is what eight workgroups leave each other of a compute unit's 160 KiB: more would cost occupancy.
 // The workgroup ends with its stores on their way: nothing waits for them to land.  (A persistent version
 // of this kernel -- as many workgroups as are resident, each taking tiles w, w + G, ..., the next tile's loads
@@ -1222,12 +1226,12 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
 
 // ---- Algorithm 2: bitmap -> dense ---------------------------------------------------------
 
-// The reverse of ring_flush in two steps, so that the loads of several phases can be in
+// The reverse of run_store in two steps, so that the loads of several phases can be in
 // flight together: strip_fetch issues the loads of values[g0, g0 + cnt) into
 // registers, strip_commit later writes them into the wave's LDS strip, LDS element
 // pad + i being global element g0 + i (pad lines LDS byte 0 up with a 16-byte boundary
-// of the global buffer).  A phase holds at most PHASE * ROW elements, i.e. 257 aligned
-// vectors: the inner ones (at most 255, all fully inside the range) go PHASE (four) to a
+// of the global buffer).  A phase of four rows holds at most PHASE * ROW elements, i.e. 257 aligned
+// vectors: the inner ones (at most 255, all fully inside the range) go PHASE to a
 // lane; of the first and the last vector, lane j < E takes element j of the first
 // and lane E + j element j of the last, each only if it lies inside the range.
 template <int S, int R> struct Fetched {
@@ -1543,12 +1547,12 @@ __device__ __forceinline__ uint32_t count_share(const uint32_t *__restrict__ bit
 }
 
 // bt_decompress and bt_decompress_batch: workgroup 0 is the scanner (one wave of it), workgroup 1 + t
-// restores slot t.  A tile's count depends on the bitmap alone: every wave turns its bitmap words into
-// masks and ranks, whose totals are the wave's share of the count; the workgroup adds the shares up
-// and publishes the count; then the first wave waits for the tile's prefix, every wave fetches its
+// restores slot t (with SELF, see below, there is no scanner and workgroup t does).  A tile's count depends
+// on the bitmap alone: every wave turns its bitmap words into masks and ranks, whose totals are the
+// wave's share of the count; the workgroup adds the shares up and publishes the count; then the first wave waits for the tile's prefix, every wave fetches its
 // values, expands and stores them, and the workgroup ends.
 //
-// Why a workgroup per tile and no loop over tiles as in compression.  A wave that has issued its stores
+// Why a workgroup per tile and no loop over tiles.  A wave that has issued its stores
 // is gone (nothing waits for them to land) and the next workgroup takes its place, whereas a wave that
 // went on to a next tile would, on this hardware, wait for its own stores whenever it waits for that
 // tile's loads (one counter tracks both, in order).  Two thirds of a restoration's traffic are stores;
@@ -1655,8 +1659,9 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
 // for five (LDS is allocated in steps of kLdsStep bytes: a share that is no whole number of steps makes room for one less).
 // Measured with 8 / 6 / 5 / 4 workgroups, us: the 49 tensors of a ResNet-50, fp32 at batch 64, 30 % zeros 748 / 748 / 758 / 761, 50 %
 // 659 / 644 / 643 / 637, 70 % 566 / 553 / 550 / 554; at batch 16, 95 %, 117 / 116 / 113 / 110; bf16 at batch 16, 95 %, 59 / 57 / 52 / 52, at batch 64,
-// 50 %, 335 / 324 / 319 / 319; fp64 at batch 4, 95 %, 59 / 58 / 55 / 50, at batch 1, 50 %, 20.0 / 20.4 / 20.6 / 20.9.  One tensor: fp32 103 M
-// elements, 5 % zeros 137.7 with eight, 50 % 106.2 (at 95 % fewer would be better, at 5 % worse).
+// 50 %, 335 / 324 / 319 / 319; fp64 at batch 4, 95 %, 59 / 58 / 55 / 50, at batch 1, 50 %, 20.0 / 20.4 / 20.6 / 20.9.  One tensor
+// keeps eight: fp32 103 M elements, 8 / 5 / 4, 5 % zeros 137.7 / 139.8 / 140.6, 50 % 106.2 / 104.8 / 104.5, 95 % 76.4 / 74.6 / 71.1; the
+// call does not know how many values there are, and dense tensors would lose.
 //
 // What the waves before a wave hold (see the three ways below):
 //   batches            counted by every wave from the bitmap itself, so that the waves need not meet: fp32 at batch 64, 50 % zeros,
