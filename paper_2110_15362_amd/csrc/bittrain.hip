@@ -1549,8 +1549,9 @@ __device__ __forceinline__ uint32_t count_share(const uint32_t *__restrict__ bit
 // bt_decompress and bt_decompress_batch: workgroup 0 is the scanner (one wave of it), workgroup 1 + t
 // restores slot t (with SELF, see below, there is no scanner and workgroup t does).  A tile's count depends
 // on the bitmap alone: every wave turns its bitmap words into masks and ranks, whose totals are the
-// wave's share of the count; the workgroup adds the shares up and publishes the count; then the first wave waits for the tile's prefix, every wave fetches its
-// values, expands and stores them, and the workgroup ends.
+// wave's share of the count; the workgroup adds the shares up and publishes the count; then the first
+// wave waits for the tile's prefix, every wave fetches its values, expands and stores them, and the
+// workgroup ends.
 //
 // Why a workgroup per tile and no loop over tiles.  A wave that has issued its stores
 // is gone (nothing waits for them to land) and the next workgroup takes its place, whereas a wave that
