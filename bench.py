@@ -10,7 +10,7 @@ several independent buffer sets, so that no buffer is touched again while it cou
 still sit in the 256 MB last-level cache ("cold"); the same-buffer ("warm") times are
 reported beside them.
 
-Prints ONE JSON line: metric/value/unit as the driver expects, plus
+Prints ONE JSON line: metric, value and unit, plus
   roofline      HBM roofline of the dominant kernel from its algorithmic bytes
   cpu_baseline  the CPU oracle (single thread) timed on the same tensor
   ops           per-op, per-sparsity times, GB/s, roofline fractions, compression ratio
@@ -357,7 +357,7 @@ def other_configs(bt, wl, torch, dev, timed, args):
 def main():
     args = parse()
     if args.gpus != 1:
-        print("bench.py: this build is single-GPU (the codec has no cross-GPU step); run with --gpus 1", file=sys.stderr)
+        print("bench.py: single-GPU only (the codec has no cross-GPU step); run with --gpus 1", file=sys.stderr)
         sys.exit(2)
 
     import numpy as np
@@ -523,7 +523,7 @@ def main():
                                    "profiles/hbm_traffic_config2_z50.txt: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE of this "
                                    "kernel on this workload, each scaled by the same counter's reading for a plain copy of "
                                    "known size (a committed summary, not measured by this run)"),
-                "north_star": {"target_frac": 0.70, "what": "bt_compress and bt_decompress on configuration 2 at 50 % zeros, cold",
+                "target": {"target_frac": 0.70, "what": "bt_compress and bt_decompress on configuration 2 at 50 % zeros, cold",
                                "compress_frac": row["compress"]["roofline_frac_cold"],
                                "decompress_frac": row["decompress"]["roofline_frac_cold"],
                                "met": bool(min(row["compress"]["roofline_frac_cold"], row["decompress"]["roofline_frac_cold"]) >= 0.70)},

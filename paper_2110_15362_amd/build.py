@@ -16,7 +16,7 @@ CALL_LIB = os.path.join(HERE, "_call.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
-    # packed fp32 VALU forms are kept out of the device code on the test machines
+    # packed fp32 VALU forms are kept out of the device code: some of them have given wrong results
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
