@@ -120,11 +120,11 @@ const char *bt_status_str(bt_status status);
  *                           offsets reach 2^32 (below that it writes two neighbours' lower
  *                           halves in one store).  Same results; written by the caller only;
  *                           meant for tests of the wide path on tensors of ordinary size.
- *   BT_WS_MUTE_WORD         non-zero: the grid scan counts and ends the call as always but writes no
- *                           offset, so that every tile runs out of patience.  Calls on small tensors have no
- *                           grid scan; in the instrumented build of the library (-DBT_TIMELINE) 1 keeps all counts
- *                           from their tiles but the last, 2 from the last one too, whose wait then runs
- *                           out.  Written by the caller only; meant for tests of the paths behind the waits. */
+ *   BT_WS_MUTE_WORD         looked at in the instrumented build of the library only (-DBT_TIMELINE).  Non-zero:
+ *                           the grid scan counts and ends the call as always but writes no offset, so that
+ *                           every tile runs out of patience; in calls on small tensors, which have no grid scan,
+ *                           1 keeps all counts from the tiles but the last, 2 from the last one too, whose wait
+ *                           then runs out.  Written by the caller only; meant for tests of the paths behind the waits. */
 #define BT_WS_ERROR_WORD 2
 #define BT_WS_WAIT_LIMIT_WORD 3
 #define BT_WS_PATIENCE_WORD 4

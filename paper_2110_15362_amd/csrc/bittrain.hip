@@ -70,7 +70,7 @@ constexpr int kHdrError = BT_WS_ERROR_WORD;           // set if a wait was given
 constexpr int kHdrSpinLimit = BT_WS_WAIT_LIMIT_WORD;  // scanner passes before its wait is given up; 0: kSpinLimit
 constexpr int kHdrWide = BT_WS_WIDE_WORD;             // non-zero: the one-tensor scanner writes 8-byte entries only
 constexpr int kHdrPatience = BT_WS_PATIENCE_WORD;     // polls before a workgroup counts what precedes its tile itself; 0: kPatience
-constexpr int kHdrMute = BT_WS_MUTE_WORD;             // non-zero: tiles are not told their prefixes
+[[maybe_unused]] constexpr int kHdrMute = BT_WS_MUTE_WORD;      // instrumented build; non-zero: tiles are not told their prefixes
 constexpr size_t kHeaderBytes = 256;
 // Block of 256 slots, two copies c = 0, 1 of everything:
 //   [1024*c, 1024*c + 1024)            uint32 count + 1 of each slot, written by the slot's workgroup
@@ -129,7 +129,8 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
     return x;
 }
 
-// The lanes' numbers added up, in 64 bits.  (By DPP, in two halves: shuffles would keep an address per step in a register.)
+// The lanes' numbers added up, in 64 bits.  (By DPP, in two halves: shuffles would keep an address per step in a register,
+// which compression cannot spare.)
 __device__ __forceinline__ uint64_t wave_total_of(uint32_t x) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(x & 0xffffu), 63);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(x >> 16), 63);
@@ -563,6 +564,17 @@ __device__ __forceinline__ uint32_t patience_of(const uint32_t *hdr) {
     return asked != 0 ? asked : kPatience;
 }
 
+// Whether the header's mute word, which is for tests, reaches `level`.  Looked at in the instrumented build only: a look costs
+// launches without a scanner 1 to 2 % and batches 0.5 to 1 %.
+__device__ __forceinline__ bool told_nothing(const uint32_t *hdr, const uint32_t level) {
+#ifdef BT_TIMELINE
+    return uniform32(hdr[kHdrMute]) >= level;
+#else
+    (void)hdr, (void)level;
+    return false;
+#endif
+}
+
 // A call is over as far as the header is concerned (one lane, once every slot's workgroup has published its count and
 // hence has read the header): count it, and leave the entries to the next call.
 __device__ __forceinline__ void header_finish(uint32_t *hdr, const uint32_t n_slots, const uint32_t cur) {
@@ -612,8 +624,8 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
     uint64_t base = 0;         // stored values of that tensor in the tiles before the frontier's row of 128 slots
     uint32_t spins = 0;
     const uint32_t limit = uniform32(wait_limit(hdr));
-    const uint32_t mute = uniform32(hdr[kHdrMute]);       // these two: never written by a kernel
-    const bool wide = uniform32(hdr[kHdrWide]) != 0 || mute != 0;
+    const bool mute = told_nothing(hdr, 1);
+    const bool wide = uniform32(hdr[kHdrWide]) != 0 || mute;      // never written by a kernel
 #ifdef BT_TIMELINE
     uint64_t *const timeline = g_timeline;      // read once: a load in the loop would join the scanner's waits
     uint32_t timeline_pass = 0;
@@ -669,8 +681,8 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
                         else if (use_a) ws_store32(entry, pa);
                     } else {
                         const uint64_t pa = (base + 1) + (incl - va - vb);
-                        if (use_a && mute == 0) ws_store64(entry, pa);
-                        if (use_b && mute == 0) ws_store64(entry + 8, pa + va);
+                        if (use_a && !mute) ws_store64(entry, pa);
+                        if (use_b && !mute) ws_store64(entry + 8, pa + va);
                     }
                     new_frontier = row_end;
                     if (row_end == item_end) {      // this tensor's number of values
@@ -799,11 +811,7 @@ __device__ __forceinline__ uint64_t wait_for_counts(char *ws, const Job &job, co
                                                     const uint32_t own, uint32_t &polls, const Itself &itself) {
     uint32_t *const hdr = reinterpret_cast<uint32_t *>(ws);
     const bool last = slot + 1 == n_slots;
-#ifdef BT_TIMELINE
-    const bool deaf = uniform32(hdr[kHdrMute]) > (last ? 1u : 0u);
-#else
-    constexpr bool deaf = false;      // (to look costs these launches, which are short of everything but registers, 1 to 2 %)
-#endif
+    const bool deaf = told_nothing(hdr, last ? 2 : 1);
     uint64_t v = 0;
     while (deaf || !sum_counts(ws, slot, ep.cur, v)) {
         ++polls;
@@ -1520,9 +1528,11 @@ __device__ __forceinline__ void restore_store(const Restoring<S, R> &r, const ui
 template <int S, int R>
 __device__ __noinline__ uint64_t prefix_from_bitmap(const uint32_t *__restrict__ bitmap, const uint32_t tile, const int lane) {
     const uint64_t words = (uint64_t)tile * Geo<S, R>::TILE_WORDS;
-    uint32_t share = 0;      // at most BT_MAX_ELEMENTS / 64
-    for (uint64_t w = (uint32_t)lane; w < words; w += kWaveSize) share += (uint32_t)__popc(bitmap[w]);
-    return wave_total_of(share);
+    uint64_t mine = 0;
+    for (uint64_t w = (uint32_t)lane; w < words; w += kWaveSize) mine += (uint32_t)__popc(bitmap[w]);
+#pragma unroll
+    for (int d = 1; d < kWaveSize; d <<= 1) mine += __shfl_xor((unsigned long long)mine, d, kWaveSize);
+    return uniform64(mine);
 }
 
 // One thread's share of the set bits in the first `words` words of the bitmap (a whole number of 16-byte vectors), the

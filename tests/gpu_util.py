@@ -1,5 +1,7 @@
 """Helpers for the GPU parity tests: run the library on a CPU tensor's bytes and
 hand the outputs back as numpy bit arrays.  Calls go through the C ABI binding."""
+import contextlib
+
 import numpy as np
 import torch
 
@@ -13,6 +15,21 @@ def _sentinel(numel, dtype, dev):
     t = torch.empty(numel, dtype=dtype, device=dev)
     t.view(torch.uint8).fill_(SENTINEL)
     return t
+
+
+@contextlib.contextmanager
+def instrumented():
+    """The binding on the instrumented build (the same kernels with time stamps), the one that looks at the workspace's
+    mute word.  A workspace that is in use must not go from one build to the other."""
+    from paper_2110_15362_amd import bench_aids
+    path = bt.LIB_PATH
+    bt._lib, bt.LIB_PATH = None, bench_aids.LIB_PATH
+    try:
+        bt.lib()
+        yield
+    finally:
+        bt._lib, bt.LIB_PATH = None, path
+        bt.lib()
 
 
 def gpu_compress(x, cap=None, ws=None, values_offset=0, dev="cuda", threshold=None):

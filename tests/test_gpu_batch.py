@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2110_15362_amd import workloads as wl
+from tests import gpu_util
 
 pytestmark = pytest.mark.gpu
 
@@ -141,9 +142,10 @@ def test_batch_whose_tiles_stop_waiting(bt, oracle, dt):
     ws = bt.new_batch_workspace(ns, xs[0].dtype)
     words = ws.view(torch.int32)
     words[bt.BT_WS_MUTE_WORD], words[bt.BT_WS_PATIENCE_WORD] = 1, 1
-    _check_batch(bt, oracle, xs, ws)
-    words[bt.BT_WS_MUTE_WORD] = 0
-    _check_batch(bt, oracle, xs, ws)
+    with gpu_util.instrumented():
+        _check_batch(bt, oracle, xs, ws)
+        words[bt.BT_WS_MUTE_WORD] = 0
+        _check_batch(bt, oracle, xs, ws)
     assert int(words[bt.BT_WS_ERROR_WORD].item()) == 0
 
 

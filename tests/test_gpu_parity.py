@@ -2,8 +2,6 @@
 
 Integer / bit work throughout, so the bar is exact equality of the bitmap, the
 value array [0, nnz), nnz, the restored tensor and the ReLU-backward output."""
-import contextlib
-
 import numpy as np
 import pytest
 import torch
@@ -346,22 +344,6 @@ def test_small_launches_at_the_edges_of_their_plans(gpu, oracle, dt):
     assert status.tolist() == [0, calls]
 
 
-@contextlib.contextmanager
-def _instrumented():
-    """The binding on the instrumented build (the same kernels with time stamps): the one that looks at the mute word in
-    launches without a scanner.  Workspaces must not go from one build to the other."""
-    import paper_2110_15362_amd.bittrain as bt
-    from paper_2110_15362_amd import bench_aids
-    path = bt.LIB_PATH
-    bt._lib, bt.LIB_PATH = None, bench_aids.LIB_PATH
-    try:
-        bt.lib()
-        yield
-    finally:
-        bt._lib, bt.LIB_PATH = None, path
-        bt.lib()
-
-
 def _small_plans(dt):
     """name -> a number of elements that takes it: the launches of compression without a scanner, and one with it."""
     row = 4096 // wl.DTYPES[dt].itemsize
@@ -389,7 +371,7 @@ def test_a_small_launch_whose_wait_runs_out_ends(gpu, oracle, dt, plan):
     ws = bt.new_workspace(max(_small_plans(dt).values()), x.dtype)
     words = ws.view(torch.int32)
     words[bt.BT_WS_MUTE_WORD], words[bt.BT_WS_WAIT_LIMIT_WORD], words[bt.BT_WS_PATIENCE_WORD] = 2, 1, 1
-    with _instrumented():
+    with gpu.instrumented():
         bitmap, values, nnz, tail_ok = gpu.gpu_compress(x, ws=ws)
     assert tail_ok and nnz == -7, "nnz of a failed call is not written"
     assert int(words[bt.BT_WS_ERROR_WORD].item()) == 1
@@ -542,7 +524,7 @@ def test_compression_that_stops_waiting_counts_the_input_itself(gpu, oracle, dt,
     every 256th), so every workgroup stops waiting and counts the kept elements before its tile itself, with its values already
     compacted: in launches with and without a scanner, in tiles that fit the staging area and tiles that don't, with pruning and
     with a dense output on top of the input.  Every output must be right all the same, and nothing has failed."""
-    with contextlib.nullcontext() if plan == "scanner" else _instrumented():
+    with gpu.instrumented():
         _stops_waiting(gpu, oracle, dt, plan)
 
 
@@ -587,10 +569,11 @@ def test_restoration_that_stops_waiting_counts_the_bitmap_itself(gpu, oracle, dt
     ws = bt.new_workspace(n, x.dtype)
     words = ws.view(torch.int32)
     words[bt.BT_WS_MUTE_WORD], words[bt.BT_WS_PATIENCE_WORD] = 1, 1
-    for _ in range(2):
-        out, guard_ok = gpu.gpu_decompress(o_bitmap, o_values, n, x.dtype, ws=ws)
-        assert guard_ok
-        assert np.array_equal(out, wl.bits(x))
+    with gpu.instrumented():
+        for _ in range(2):
+            out, guard_ok = gpu.gpu_decompress(o_bitmap, o_values, n, x.dtype, ws=ws)
+            assert guard_ok
+            assert np.array_equal(out, wl.bits(x))
     assert int(words[bt.BT_WS_ERROR_WORD].item()) == 0 and int(words[0].item()) == 2
 
 
