@@ -132,6 +132,24 @@ def test_batch_slot_lookup_at_the_ends_of_its_steps(bt, oracle, count):
     _check_batch(bt, oracle, xs)
 
 
+@pytest.mark.parametrize("wide", [0, 1])
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
+def test_batch_of_tensors_that_begin_inside_a_row_of_the_scan(bt, oracle, dt, wide):
+    """The scan takes rows of 128 slots and a tensor begins behind the one before it: at even and odd slots, several in a
+    row, at a row's first and last slot, with empty tensors between them and at both ends, all zero ones (whose start has the
+    sum of the one before), and a launch of empty tensors only in front.  wide: entries in 8-byte stores."""
+    t = TILE[wl.DTYPES[dt].itemsize]
+    tiles = [0, 1, 2, 0, 0, 3, 1, 119, 1, 1, 1, 127, 129, 1, 0, 2, 128, 0]
+    sizes = [0] * 52 + [max(k * t - (7 * i) % 29, 0) for i, k in enumerate(tiles)] + [0] * 3
+    xs = [wl.random_sparse(n, dt, 1.0 if k % 5 == 3 else 0.5, 8000 + k) for k, n in enumerate(sizes)]
+    ws = bt.new_batch_workspace(sizes, xs[0].dtype)
+    words = ws.view(torch.int32)
+    words[bt.BT_WS_WIDE_WORD] = wide
+    for _ in range(3):
+        _check_batch(bt, oracle, xs, ws)
+    assert int(words[bt.BT_WS_ERROR_WORD].item()) == 0
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
 def test_batch_whose_tiles_stop_waiting(bt, oracle, dt):
     """Forced from the host: no tile of a batch is told its offset, so each counts what precedes it in its own tensor, from the
