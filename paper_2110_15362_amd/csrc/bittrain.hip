@@ -101,9 +101,11 @@ template <int S, int R = kRows> struct Geo {
     static constexpr int TILE = kWaves * WAVE;       // elements per tile
     static constexpr int TILE_WORDS = TILE / 32;     // bitmap words per tile
     static constexpr int WAVE_WORDS = TILE_WORDS / kWaves;      // of which a wave's quarter of the tile has this many
-    static constexpr int WPL = WAVE_WORDS > kWaveSize ? WAVE_WORDS / kWaveSize : 1;   // and a lane reads this many
+    static constexpr int QPL = WAVE_WORDS > kWaveSize ? WAVE_WORDS / kWaveSize : 1;   // and a lane reads this many (of a quarter)
+    static constexpr int WPL = TILE_WORDS > kWaveSize ? TILE_WORDS / kWaveSize : 1;   // or this many (of the whole tile)
     static constexpr int LDS_WAVE = PHASE * ROW * S + 2 * kVecBytes;  // restoration's staging bytes per wave: the rows of a phase, the
                                                                           // shift to a 16-byte boundary, and what a read past the last value may touch
+    static constexpr int LDS_TILE = PHASE * kBlock * kVecBytes + 2 * kVecBytes;      // and per workgroup, where its waves stage together
     static constexpr int STAGE = TILE * S <= kStageBytes - kVecBytes ? TILE * S : kStageBytes - kVecBytes;   // compression: bytes of a tile's
                                                                           // values that fit LDS together (then a vector nobody reads)
     static constexpr int RPM = 32 / E;               // rows whose E-bit lane masks share one register
@@ -1325,8 +1327,8 @@ __device__ __forceinline__ void strip_commit(unsigned char *strip, const uint32_
     }
 }
 
-// Restoration of one wave's quarter of a tile:
-//   quarter_load    asks for the bitmap words of the quarter, each once (lane l: words l * WPL ...);
+// Restoration of one wave's quarter of a tile, where the scan tells the tile's place (without it: load_bits and what follows it):
+//   quarter_load    asks for the bitmap words of the quarter, each once (lane l: words l * QPL ...);
 //   restore_ranks   counts them, running sum over the lanes, and hands every lane the words and ranks of its rows
 //                   (Algorithm 2's counter j inside the quarter) through LDS;
 //   restore_fetch   given j at the start of the tile, asks for the wave's values;
@@ -1334,35 +1336,34 @@ __device__ __forceinline__ void strip_commit(unsigned char *strip, const uint32_
 //                   the bit is set, +0 where it is clear) and stores the dense quarter tile.
 // (Read once per row by the lanes that share a word, and ranked by row sums, they cost a wave eight loads of 32 bytes,
 // which keep the address units busy before anything else can start, and four times the DPP steps.  Measured, before /
-// after, us: restore from the index fp32 25.7 M elements 24.8 / 24.2, the ResNet-50 set 585 / 563;
-// with the scan fp32 25.7 M 27.0 / 26.7, 206 M 214 / 212, fp16 206 M at 5 % 142.8 / 141.7.)
-template <int S, int R> struct Quarter { uint32_t w[Geo<S, R>::WPL]; };
+// after, us: fp32 25.7 M 27.0 / 26.7, 206 M 214 / 212, fp16 206 M at 5 % 142.8 / 141.7.)
+template <int S, int R> struct Quarter { uint32_t w[Geo<S, R>::QPL]; };
 
 // Words at or beyond the bitmap's end read as 0, bits at or beyond n are cleared (Algorithm 2 visits n bits).
 template <int S, int R>
 __device__ __forceinline__ Quarter<S, R> quarter_load(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane, const int wave) {
     using G = Geo<S, R>;
-    static_assert(G::WPL <= 2, "one load");
+    static_assert(G::QPL <= 2, "one load");
     typedef uint32_t word2 __attribute__((ext_vector_type(2), aligned(4)));      // (the bitmap is 4-byte aligned)
     const uint64_t first = (uint64_t)tile * G::TILE_WORDS + (uint64_t)wave * G::WAVE_WORDS;
     const bool full = (uint64_t)(tile + 1) * G::TILE <= n;
     Quarter<S, R> q;
 #pragma unroll
-    for (int j = 0; j < G::WPL; ++j) q.w[j] = 0;
+    for (int j = 0; j < G::QPL; ++j) q.w[j] = 0;
     if (__builtin_expect(full, 1)) {
-        if (G::WPL == 2) {
+        if (G::QPL == 2) {
             const word2 v = *reinterpret_cast<const word2 *>(bitmap + first + 2 * lane);
             q.w[0] = v.x;
-            q.w[G::WPL - 1] = v.y;
+            q.w[G::QPL - 1] = v.y;
         } else if (G::WAVE_WORDS >= kWaveSize || lane < G::WAVE_WORDS) {
             q.w[0] = bitmap[first + lane];
         }
     } else {
         const uint64_t n_words = (n + 31) >> 5;
 #pragma unroll
-        for (int j = 0; j < G::WPL; ++j) {
-            const uint64_t wi = first + (uint32_t)(lane * G::WPL + j);
-            if (lane * G::WPL + j < G::WAVE_WORDS && wi < n_words) q.w[j] = bitmap[wi];
+        for (int j = 0; j < G::QPL; ++j) {
+            const uint64_t wi = first + (uint32_t)(lane * G::QPL + j);
+            if (lane * G::QPL + j < G::WAVE_WORDS && wi < n_words) q.w[j] = bitmap[wi];
             if (wi + 1 == n_words && (n & 31) != 0) q.w[j] &= (1u << (uint32_t)(n & 31)) - 1u;
         }
     }
@@ -1386,19 +1387,19 @@ __device__ __forceinline__ uint32_t restore_ranks(const Quarter<S, R> &q, unsign
     static_assert(8 * G::WAVE_WORDS <= G::LDS_WAVE && G::WAVE < 65536, "a word and its rank per entry; ranks in 16 bits");
     uint32_t mine = 0;
 #pragma unroll
-    for (int j = 0; j < G::WPL; ++j) mine += (uint32_t)__popc(q.w[j]);
+    for (int j = 0; j < G::QPL; ++j) mine += (uint32_t)__popc(q.w[j]);
     const uint32_t incl = wave_inclusive_sum(mine);
     uint32_t rank = incl - mine;
 #pragma unroll
     for (int ph = 0; ph < Restoring<S, R>::PHASES; ++ph)       // the lane that holds the phase's first word
-        r.before[ph] = (uint32_t)__builtin_amdgcn_readlane((int)rank, ph * G::PHASE * G::WPR / G::WPL);
+        r.before[ph] = (uint32_t)__builtin_amdgcn_readlane((int)rank, ph * G::PHASE * G::WPR / G::QPL);
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     r.before[Restoring<S, R>::PHASES] = total;
     bt_u2 *const entries = reinterpret_cast<bt_u2 *>(strip);
     if (G::WAVE_WORDS >= kWaveSize || lane < G::WAVE_WORDS) {
 #pragma unroll
-        for (int j = 0; j < G::WPL; ++j) {
-            entries[lane * G::WPL + j] = bt_u2{q.w[j], rank};
+        for (int j = 0; j < G::QPL; ++j) {
+            entries[lane * G::QPL + j] = bt_u2{q.w[j], rank};
             rank += (uint32_t)__popc(q.w[j]);
         }
     }
@@ -1416,62 +1417,6 @@ __device__ __forceinline__ uint32_t restore_ranks(const Quarter<S, R> &q, unsign
     }
     wave_lds_sync();                    // the entries are read before the strip is used for values
     return total;
-}
-
-// (1) in the form that the restoration of one 16-bit tensor from its index keeps: the word of each row read by the lanes that
-// share it, ranks from row sums, and the waves before this one counted from the whole tile's words.  More work, but those
-// kernels are bound by their stores, and a workgroup that is later with its own writes sparse tensors faster (fp16, 206 M
-// elements, 95 % zeros: 69 us; with restore_ranks 77, or 70 with LDS reserved for four workgroups a compute unit).
-// Returns the set bits of the waves before `wave`.
-template <int S, int R>
-__device__ __forceinline__ uint32_t restore_ranks_by_row(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane, const int wave,
-                                                     Restoring<S, R> &r) {
-    using G = Geo<S, R>;
-    constexpr int E = G::E;
-    const uint64_t n_words = (n + 31) >> 5;
-    const uint64_t wave_e0 = (uint64_t)tile * G::TILE + (uint64_t)wave * G::WAVE;
-    const bool full = (uint64_t)(tile + 1) * G::TILE <= n;
-    uint32_t rows[R];
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const uint64_t wi = (wave_e0 >> 5) + (uint64_t)(k * G::WPR + lane / G::G);
-        rows[k] = bitmap[wi < n_words ? wi : n_words - 1];
-    }
-    constexpr int kShare = G::TILE_WORDS / kWaveSize;           // lane l counts words l * kShare ... of the tile: 16 lanes a quarter
-    const uint64_t w0 = (uint64_t)tile * G::TILE_WORDS + (uint64_t)lane * kShare;
-    uint32_t words[kShare], mine = 0;
-#pragma unroll
-    for (int j = 0; j < kShare; ++j) words[j] = bitmap[w0 + j < n_words ? w0 + j : n_words - 1];
-#pragma unroll
-    for (int j = 0; j < kShare; ++j) {
-        if (!full && w0 + j >= n_words) words[j] = 0;
-        if (!full && w0 + j + 1 == n_words && (n & 31) != 0) words[j] &= (1u << (uint32_t)(n & 31)) - 1u;
-        mine += (uint32_t)__popc(words[j]);
-    }
-    const uint32_t incl = wave_inclusive_sum(mine);
-#pragma unroll
-    for (int i = 0; i < G::MW; ++i) r.mp[i] = 0;
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const uint64_t e0 = wave_e0 + (uint64_t)k * G::ROW + (uint64_t)lane * E;
-        uint32_t m = (rows[k] >> (uint32_t)(e0 & 31)) & ((1u << E) - 1u);
-        if (!full) {                       // words beyond the bitmap read as 0, bits at or beyond n are cleared
-            if ((e0 >> 5) >= n_words) m = 0;
-            if (e0 + E > n) m &= (e0 < n) ? ((1u << (uint32_t)(n - e0)) - 1u) : 0u;
-        }
-        r.mp[k / G::RPM] |= m << (E * (k % G::RPM));
-    }
-    uint32_t total2[R / 2];
-    rank_rows<S, R>(r.mp, r.rank2, total2);
-    uint32_t row_start = 0;
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        if (k % G::PHASE == 0) r.before[k / G::PHASE] = row_start;
-        r.rank2[k / 2] += row_start << (16 * (k & 1));
-        row_start += BT_FIELD(total2, k);
-    }
-    r.before[Restoring<S, R>::PHASES] = row_start;
-    return wave == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)uniform32(16u * (uint32_t)wave - 1u));
 }
 
 // (2) ask for the values of every phase (PHASE rows each), so that all of them are in flight together
@@ -1564,6 +1509,316 @@ __device__ __noinline__ uint64_t prefix_from_bitmap(const uint32_t *__restrict__
     return uniform64(mine);
 }
 
+// bt_decompress and bt_decompress_batch: workgroup 0 is the scanner (one wave of it), workgroup 1 + t
+// restores slot t.  A tile's count depends
+// on the bitmap alone: every wave turns its bitmap words into masks and ranks, whose totals are the
+// wave's share of the count; the workgroup adds the shares up and publishes the count; then the first
+// wave waits for the tile's prefix, every wave fetches its values, expands and stores them, and the
+// workgroup ends.
+//
+// Why a workgroup per tile and no loop over tiles.  A wave that has issued its stores
+// is gone (nothing waits for them to land) and the next workgroup takes its place, whereas a wave that
+// went on to a next tile would, on this hardware, wait for its own stores whenever it waits for that
+// tile's loads (one counter tracks both, in order).  Two thirds of a restoration's traffic are stores;
+// kernels that loop measured 10 to 25 % slower, with or without the next tile's loads in flight.
+//
+// Forward progress does not rest on the order in which workgroups are started.  A workgroup publishes
+// its count before it waits for anything, and one whose prefix has not come after kPatience polls
+// stops waiting and counts the bitmap itself (prefix_from_bitmap): so every workgroup that has been
+// started ends, whatever the others do, and every workgroup is started in the end.
+template <int S, class Job>
+__global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(const Job job, char *ws) {
+    constexpr int R = kRows;
+    using G = Geo<S, R>;
+    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kWaves * G::LDS_WAVE];
+    __shared__ uint64_t s_tile_j;
+    __shared__ uint32_t s_wave_total[kWaves];
+    const uint32_t n_slots = gridDim.x - 1u;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < kWaveSize && !epoch_of(read_header(ws)).failed) scan_counts<2>(ws, job);
+        return;
+    }
+    BT_TL_INIT;
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t slot = blockIdx.x - 1u;
+    // (Compression looks at the header while its tile is on its way.  Here that made batches 1 % slower: the counts are out
+    // long before the values' turn comes, and a workgroup that starts sooner only adds to what the stores compete with.)
+    const HeaderWords header = read_header(ws);
+    if (__builtin_expect(epoch_of(header).failed, 0)) {
+        if (lane == 0) s_wave_total[wave] = kWaveFailed;
+        lds_barrier();
+        return;
+    }
+    const Slot sl = job.at(slot);
+    // the bitmap words first: everything else waits for them
+    const uint32_t *const bitmap = job.bitmap(sl.item);
+    const uint64_t n = job.n(sl.item);
+    const Quarter<S, R> quarter = quarter_load<S, R>(bitmap, n, sl.tile, lane, wave);
+    BT_TL(slot, 0);
+    // masks and ranks; what they add up to is this wave's share of the tile's count
+    Restoring<S, R> r;
+    unsigned char *const strip = s_stage + wave * G::LDS_WAVE;
+    const uint32_t wave_total = restore_ranks<S, R>(quarter, strip, lane, r);
+    const Epoch ep = epoch_of(header);
+    if (lane == 0) s_wave_total[wave] = ep.failed ? kWaveFailed : wave_total;
+    lds_barrier();                      // also: every wave has read the header before the first wave publishes anything
+    if (any_wave_failed(s_wave_total)) return;
+    uint32_t before_wave = 0, tile_total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = s_wave_total[w];
+        if (w < wave) before_wave += c;
+        tile_total += c;
+    }
+    before_wave = uniform32(before_wave);       // the same in every lane: tell the compiler, so that addresses built on it stay scalar
+    uint32_t polls = 0;
+    if (tid == 0) ws_store32(ws_count(ws, slot, ep.cur), (tile_total + 1) | (Job::kMany && sl.tile == 0 ? kFirstTile : 0u));
+    BT_TL(slot, 1);
+    zero_previous(ws, ep, slot, n_slots);
+    // Algorithm 2's counter j at the start of the tile: the first wave asks (one poller a tile keeps the
+    // traffic on the workspace's few lines low) and passes the answer on through LDS
+    if (wave == 0) {
+        const uint64_t v = wait_for_prefix(ws, slot, n_slots, ep.cur, polls, [&]() { return prefix_from_bitmap<S, R>(bitmap, sl.tile, lane); });
+        if (lane == 0) s_tile_j = v;
+    }
+    lds_barrier();
+    const uint64_t tile_j = uniform64(s_tile_j);
+    BT_TL(slot, 2);
+    restore_fetch<S, R>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
+    restore_store<S, R>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
+    BT_TL(slot, 3);
+    BT_TL_VALUE(slot, 5, polls);
+}
+
+// ---- restoration without the scan ------------------------------------------------------------
+//
+// Restoration of a tile by a workgroup whose tile's place is known without a wait:
+//   load_bits     a wave asks for the bitmap words of the whole tile, each once (lane l: words l * WPL ...);
+//   rank_words    counts them, running sum over the lanes: every wave knows the rank of every word, so the waves need
+//                 not meet for it;
+//   rows_of       hands the lanes the words and ranks of the wave's rows (Algorithm 2's counter j inside the tile) through LDS;
+//   fetch_values  given j at the start of the tile, asks for the values of one phase (PHASE rows of every wave), a contiguous run;
+//   commit_values puts them into LDS, where all waves find them;
+//   expand_row    a value where the bit is set, +0 where it is clear, by rank; 16-byte dense stores.
+// The waves take the tile's rows in turn (wave w rows w, w + 4, ...): a phase is one contiguous piece of the tensor and of the
+// values, and it is written from front to back.  When every wave had a quarter of the tile with a strip of LDS of its own, a phase
+// was eight pieces, each with element-wise edges and partial cache lines of its own, written at four places at once.
+// (With the scan it is the other way round: quarters publish their counts from a fourth of the loads, and the waves of a tile that
+// has its prefix do not wait for each other.  Measured, us, quarters / this: fp32 3 M elements 7.5 / 7.7, 25.7 M 26.6 / 26.9, bf16 3 M
+// 7.9 / 8.3, fp64 25.7 M 58.2 / 63.5.)
+
+// Bits of words at or beyond the bitmap's end, and bits at or beyond n, are 0 (Algorithm 2 visits n bits).
+template <int S, int R> struct TileBits { uint32_t w[Geo<S, R>::WPL]; };
+
+template <int S, int R>
+__device__ __forceinline__ TileBits<S, R> load_bits(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane) {
+    using G = Geo<S, R>;
+    constexpr int WPL = G::WPL;
+    typedef uint32_t words __attribute__((ext_vector_type(WPL), aligned(4)));      // (the bitmap is 4-byte aligned)
+    const uint64_t first = (uint64_t)tile * G::TILE_WORDS;
+    TileBits<S, R> b;
+#pragma unroll
+    for (int j = 0; j < WPL; ++j) b.w[j] = 0;
+    if (__builtin_expect((uint64_t)(tile + 1) * G::TILE <= n, 1)) {
+        if (G::TILE_WORDS >= kWaveSize || lane < G::TILE_WORDS) {
+            const words v = *reinterpret_cast<const words *>(bitmap + first + lane * WPL);
+#pragma unroll
+            for (int j = 0; j < WPL; ++j) b.w[j] = v[j];
+        }
+    } else {
+        // a tensor's last tile (n > tile * TILE): all loads at once, from clamped addresses
+        const uint64_t left = ((n + 31) >> 5) - first;
+        const uint32_t there = left < (uint64_t)G::TILE_WORDS ? (uint32_t)left : (uint32_t)G::TILE_WORDS;
+        const uint32_t tail = left <= (uint64_t)G::TILE_WORDS && (n & 31) != 0 ? (1u << (uint32_t)(n & 31)) - 1u : ~0u;
+#pragma unroll
+        for (int j = 0; j < WPL; ++j) b.w[j] = bitmap[first + min((uint32_t)(lane * WPL + j), there - 1u)];
+#pragma unroll
+        for (int j = 0; j < WPL; ++j) {
+            const uint32_t i = (uint32_t)(lane * WPL + j);
+            b.w[j] &= i + 1u < there ? ~0u : i + 1u == there ? tail : 0u;
+        }
+    }
+    return b;
+}
+
+// Set bits of the tile before the lane's first word, and before each phase and after the last one.
+template <int S, int R> struct TileRanks {
+    static constexpr int PHASES = R / Geo<S, R>::PHASE;
+    uint32_t mine;
+    uint32_t before[PHASES + 1];
+};
+
+template <int S, int R> __device__ __forceinline__ TileRanks<S, R> rank_words(const TileBits<S, R> &b) {
+    using G = Geo<S, R>;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < G::WPL; ++j) sum += (uint32_t)__popc(b.w[j]);
+    const uint32_t incl = wave_inclusive_sum(sum);
+    TileRanks<S, R> r;
+    r.mine = incl - sum;
+#pragma unroll
+    for (int ph = 0; ph < TileRanks<S, R>::PHASES; ++ph)       // (the lane that holds the phase's first word)
+        r.before[ph] = (uint32_t)__builtin_amdgcn_readlane((int)r.mine, ph * kWaves * G::PHASE * G::WPR / G::WPL);
+    r.before[TileRanks<S, R>::PHASES] = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    return r;
+}
+
+// The lane's bits of K rows of its wave (G lanes take E bits each of one word), and Algorithm 2's j as ranks in the tile.
+template <int S, int K> struct Rows {
+    uint32_t mp[Geo<S, K>::MW], rank2[K / 2];          // two rows' ranks to a register
+};
+
+// The wave's rows among the tile's rows [first, first + 4 K).  `entries`: room for their words, a pair each; a wave writes and reads
+// those of its own rows only.
+template <int S, int R, int K>
+__device__ __forceinline__ Rows<S, K> rows_of(const TileBits<S, R> &b, const TileRanks<S, R> &r, const int first, bt_u2 *entries, const int lane, const int wave) {
+    using G = Geo<S, R>;
+    constexpr int E = G::E;
+    static_assert(G::TILE < 65536, "ranks in 16 bits");
+    uint32_t rank = r.mine;
+#pragma unroll
+    for (int j = 0; j < G::WPL; ++j) {
+        const int i = lane * G::WPL + j;
+        const int row = i / G::WPR;
+        const bool asked = K == R || (unsigned)(row - first) < (unsigned)(kWaves * K);
+        if (asked && row % kWaves == wave && (G::TILE_WORDS >= kWaveSize || lane < G::TILE_WORDS)) entries[i - first * G::WPR] = bt_u2{b.w[j], rank};
+        rank += (uint32_t)__popc(b.w[j]);
+    }
+    wave_lds_sync();
+    Rows<S, K> rows;
+#pragma unroll
+    for (int i = 0; i < Geo<S, K>::MW; ++i) rows.mp[i] = 0;
+    const uint32_t shift = (uint32_t)E * (uint32_t)(lane % G::G);
+    const uint32_t below = (1u << shift) - 1u;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const bt_u2 e = entries[(k * kWaves + wave) * G::WPR + lane / G::G];
+        rows.mp[k / G::RPM] |= ((e.x >> shift) & ((1u << E) - 1u)) << (E * (k % G::RPM));
+        const uint32_t at = e.y + (uint32_t)__popc(e.x & below);
+        rows.rank2[k / 2] = (k & 1) == 0 ? at : rows.rank2[k / 2] | (at << 16);
+    }
+    return rows;
+}
+
+// The values of one phase on their way to LDS, whose element pad + i is the phase's i-th (pad lines LDS byte 0 up with a 16-byte
+// boundary of the value array).  They are at most PHASE * kBlock + 1 aligned vectors: the inner ones, all fully inside the
+// range, go PHASE to a thread; of the first and the last vector, thread j < E takes element j of the first and thread
+// E + j element j of the last, each only if it lies inside the range.
+template <int S, int R> struct TileValues {
+    uint4 inner[Geo<S, R>::PHASE];
+    typename std::conditional<S == 8, uint64_t, uint32_t>::type edge;
+    uint32_t pad, end;      // elements of LDS [pad, end) are values
+};
+
+// Is there an edge element for thread `tid`, and which?
+template <int S, int R> __device__ __forceinline__ bool edge_of(const TileValues<S, R> &f, const int tid, uint32_t &at) {
+    constexpr int E = Geo<S, R>::E;
+    const uint32_t vecs = (f.end + E - 1) / E;
+    at = tid < E ? (uint32_t)tid : (vecs - 1) * E + (uint32_t)(tid - E);
+    return tid < 2 * E && f.end != f.pad && at >= f.pad && at < f.end && (tid < E || vecs > 1);
+}
+
+// j: position of the phase's first value; nothing at or beyond the capacity is read (an index that does not belong to the
+// bitmap, a wait that ran out).
+template <int S, int R>
+__device__ __forceinline__ TileValues<S, R> fetch_values(const void *__restrict__ values, const uint64_t values_cap, const uint64_t j, uint32_t count, const int tid) {
+    using G = Geo<S, R>;
+    constexpr int E = G::E;
+    if (j >= values_cap) count = 0;
+    else if (values_cap - j < count) count = (uint32_t)(values_cap - j);
+    const char *const src = static_cast<const char *>(values) + j * S;
+    TileValues<S, R> f;
+    f.pad = (uint32_t)(reinterpret_cast<uintptr_t>(src) & (kVecBytes - 1)) / S;
+    f.end = f.pad + count;
+    const char *const vec = src - (size_t)f.pad * S;
+#pragma unroll
+    for (int i = 0; i < G::PHASE; ++i) {
+        const uint32_t v = 1u + (uint32_t)tid + (uint32_t)kBlock * i;
+        f.inner[i] = make_uint4(0, 0, 0, 0);
+        if ((v + 1) * E < f.end) f.inner[i] = stream_load<kDecompressNtLoad>(reinterpret_cast<const uint4 *>(vec + (size_t)v * kVecBytes));
+    }
+    f.edge = 0;
+    uint32_t at;
+    if (edge_of<S, R>(f, tid, at)) {
+        if (S == 8) f.edge = reinterpret_cast<const uint64_t *>(vec)[at];
+        else if (S == 4) f.edge = reinterpret_cast<const uint32_t *>(vec)[at];
+        else f.edge = reinterpret_cast<const uint16_t *>(vec)[at];
+    }
+    return f;
+}
+
+template <int S, int R>
+__device__ __forceinline__ void commit_values(unsigned char *stage, const TileValues<S, R> &f, const int tid) {
+    using G = Geo<S, R>;
+    constexpr int E = G::E;
+#pragma unroll
+    for (int i = 0; i < G::PHASE; ++i) {
+        const uint32_t v = 1u + (uint32_t)tid + (uint32_t)kBlock * i;
+        if ((v + 1) * E < f.end) *reinterpret_cast<uint4 *>(stage + (size_t)v * kVecBytes) = f.inner[i];
+    }
+    uint32_t at;
+    if (edge_of<S, R>(f, tid, at)) {
+        if (S == 8) reinterpret_cast<uint64_t *>(stage)[at] = f.edge;
+        else if (S == 4) reinterpret_cast<uint32_t *>(stage)[at] = (uint32_t)f.edge;
+        else reinterpret_cast<uint16_t *>(stage)[at] = (uint16_t)f.edge;
+    }
+}
+
+// 16 bytes of the dense tensor.  The lane reads at its running rank whether a bit is set or not (the place stays inside
+// the staging area) and a select drops what a cleared bit read.
+template <int S> __device__ __forceinline__ uint4 expand_row(const unsigned char *stage, uint32_t at, const uint32_t mk) {
+    uint32_t d[4] = {0, 0, 0, 0};
+    if (S == 8) {
+        const uint64_t *l = reinterpret_cast<const uint64_t *>(stage);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t keep = (mk >> j) & 1u;
+            const uint64_t v = l[at];
+            d[2 * j] = keep ? (uint32_t)v : 0u;
+            d[2 * j + 1] = keep ? (uint32_t)(v >> 32) : 0u;
+            at += keep;
+        }
+    } else if (S == 4) {
+        const uint32_t *l = reinterpret_cast<const uint32_t *>(stage);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t keep = (mk >> j) & 1u;
+            const uint32_t v = l[at];
+            d[j] = keep ? v : 0u;
+            at += keep;
+        }
+    } else {
+        const uint16_t *l = reinterpret_cast<const uint16_t *>(stage);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t keep = (mk >> j) & 1u;
+            const uint32_t v = l[at];
+            d[j >> 1] |= (keep ? v : 0u) << (16 * (j & 1));
+            at += keep;
+        }
+    }
+    return make_uint4(d[0], d[1], d[2], d[3]);
+}
+
+// The wave's rows [k0, k0 + PHASE) of `rows`, which are rows first + k * 4 + wave of the tile; `before`: set bits of the tile before the phase.
+template <int S, int R, int K>
+__device__ __forceinline__ void expand_phase(const Rows<S, K> &rows, const int k0, const int first, const TileValues<S, R> &f, const uint32_t before,
+                                             const unsigned char *stage, void *__restrict__ out, const uint64_t n, const uint32_t tile, const int lane,
+                                             const int wave) {
+    using G = Geo<S, R>;
+    const uint64_t tile_e0 = (uint64_t)tile * G::TILE;
+    const bool full = tile_e0 + G::TILE <= n;
+#pragma unroll
+    for (int k = k0; k < k0 + G::PHASE; ++k) {
+        const uint4 o = expand_row<S>(stage, f.pad - before + BT_FIELD(rows.rank2, k), BT_MASK(S, rows.mp, k));
+        const uint64_t e0 = tile_e0 + (uint64_t)((uint32_t)(first + k * kWaves + wave) * G::ROW + (uint32_t)lane * G::E);
+        if (full) stream_store<kDecompressNtStore>(reinterpret_cast<uint4 *>(static_cast<char *>(out) + e0 * S), o);
+        else store_vec_guarded<S>(out, e0, n, o);
+    }
+}
+
 // One thread's share of the set bits in the first `words` words of the bitmap (a whole number of 16-byte vectors), the
 // workgroup's threads taking a vector each in turn.  kAhead loads are in flight together.
 __device__ __forceinline__ uint32_t count_share(const uint32_t *__restrict__ bitmap, const uint32_t words, const int tid) {
@@ -1585,191 +1840,82 @@ __device__ __forceinline__ uint32_t count_share(const uint32_t *__restrict__ bit
     return count;
 }
 
-// bt_decompress and bt_decompress_batch: workgroup 0 is the scanner (one wave of it), workgroup 1 + t
-// restores slot t (with SELF, see below, there is no scanner and workgroup t does).  A tile's count depends
-// on the bitmap alone: every wave turns its bitmap words into masks and ranks, whose totals are the
-// wave's share of the count; the workgroup adds the shares up and publishes the count; then the first
-// wave waits for the tile's prefix, every wave fetches its values, expands and stores them, and the
-// workgroup ends.
-//
-// Why a workgroup per tile and no loop over tiles.  A wave that has issued its stores
-// is gone (nothing waits for them to land) and the next workgroup takes its place, whereas a wave that
-// went on to a next tile would, on this hardware, wait for its own stores whenever it waits for that
-// tile's loads (one counter tracks both, in order).  Two thirds of a restoration's traffic are stores;
-// kernels that loop measured 10 to 25 % slower, with or without the next tile's loads in flight.
-//
-// Forward progress does not rest on the order in which workgroups are started.  A workgroup publishes
-// its count before it waits for anything, and one whose prefix has not come after kPatience polls
-// stops waiting and counts the bitmap itself (prefix_from_bitmap): so every workgroup that has been
-// started ends, whatever the others do, and every workgroup is started in the end.
-//
-// SELF (small tensors, see bt_decompress): no scanner and nothing published.  Every workgroup counts the bitmap before
+
+// Small tensors (see bt_decompress): no scanner and nothing published.  Every workgroup counts the bitmap before
 // its tile itself, all its threads together while its own words are on their way: a few KiB that sit in the caches, against
-// four hops through memory.  The call leaves the workspace's entries alone.
-template <int S, int R, bool SELF, class Job>
-__global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(const Job job, char *ws) {
+// four hops through memory.  The call leaves the workspace's entries alone.  (With each wave restoring a quarter of the tile,
+// us: fp32 30 k elements 3.1, 201 k 3.1, 700 k 4.5, bf16 201 k 3.2; now 2.9, 2.9, 4.3, 3.1.)
+template <int S, int R>
+__global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_small_kernel(const DecompressOne job, char *ws) {
     using G = Geo<S, R>;
-    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kWaves * G::LDS_WAVE];
-    __shared__ uint64_t s_tile_j;
-    __shared__ uint32_t s_wave_total[kWaves], s_wave_before[kWaves];
-    const uint32_t n_slots = gridDim.x - (SELF ? 0u : 1u);
-    if (!SELF && blockIdx.x == 0) {
-        if (threadIdx.x < kWaveSize && !epoch_of(read_header(ws)).failed) scan_counts<2>(ws, job);
-        return;
-    }
-    BT_TL_INIT;
+    static_assert(TileRanks<S, R>::PHASES == 1, "one phase");
+    __shared__ __attribute__((aligned(16))) unsigned char s_stage[G::LDS_TILE];
+    __shared__ bt_u2 s_entries[G::TILE_WORDS];
+    __shared__ uint32_t s_wave_before[kWaves], s_wave_total[kWaves];
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t slot = blockIdx.x - (SELF ? 0u : 1u);
-    // (Compression looks at the header while its tile is on its way.  Here that made batches 1 % slower: the counts are out
-    // long before the values' turn comes, and a workgroup that starts sooner only adds to what the stores compete with.)
-    const HeaderWords header = read_header(ws);
-    if (!SELF && __builtin_expect(epoch_of(header).failed, 0)) {
-        if (lane == 0) s_wave_total[wave] = kWaveFailed;
-        lds_barrier();
-        return;
-    }
-    const Slot sl = job.at(slot);
-    // the bitmap words first: everything else waits for them
-    const uint32_t *const bitmap = job.bitmap(sl.item);
-    const uint64_t n = job.n(sl.item);
-    const Quarter<S, R> quarter = quarter_load<S, R>(bitmap, n, sl.tile, lane, wave);
-    BT_TL(slot, 0);
-    uint32_t calls = 0, before_share = 0;
-    if (SELF) {
-        calls = reinterpret_cast<const uint32_t *>(ws)[kHdrCalls];
-        before_share = count_share(bitmap, sl.tile * G::TILE_WORDS, tid);
-    }
-    // masks and ranks; what they add up to is this wave's share of the tile's count
-    Restoring<S, R> r;
-    unsigned char *const strip = s_stage + wave * G::LDS_WAVE;
-    const uint32_t wave_total = restore_ranks<S, R>(quarter, strip, lane, r);
-    const Epoch ep = epoch_of(header);
-    if (SELF) {
-        const uint32_t incl = wave_inclusive_sum(before_share);
-        if (lane == kWaveSize - 1) s_wave_before[wave] = incl;
-    }
-    if (lane == 0) s_wave_total[wave] = ep.failed ? kWaveFailed : wave_total;
-    lds_barrier();                      // also: every wave has read the header before the first wave publishes anything
+    const uint32_t tile = blockIdx.x;
+    uint32_t *const hdr = reinterpret_cast<uint32_t *>(ws);
+    const uint32_t calls = hdr[kHdrCalls], error = hdr[kHdrError];
+    const uint32_t *const bitmap = job.bitmap(0);
+    const uint64_t n = job.n(0);
+    const TileBits<S, R> bits = load_bits<S, R>(bitmap, n, tile, lane);
+    const uint32_t before_share = count_share(bitmap, tile * G::TILE_WORDS, tid);
+    const TileRanks<S, R> ranks = rank_words<S, R>(bits);
+    const Rows<S, R> rows = rows_of<S, R, R>(bits, ranks, 0, s_entries, lane, wave);
+    const uint32_t incl = wave_inclusive_sum(before_share);
+    if (lane == kWaveSize - 1) s_wave_before[wave] = incl;
+    if (lane == 0) s_wave_total[wave] = uniform32(error) != 0 ? kWaveFailed : 0u;
+    lds_barrier();                      // also: every wave has read the header before the first workgroup's first wave counts the call
     if (any_wave_failed(s_wave_total)) return;
-    uint32_t before_wave = 0, tile_total = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const uint32_t c = s_wave_total[w];
-        if (w < wave) before_wave += c;
-        tile_total += c;
-    }
-    before_wave = uniform32(before_wave);       // the same in every lane: tell the compiler, so that addresses built on it stay scalar
     uint64_t tile_j = 0;
-    uint32_t polls = 0;
-    if (SELF) {
-        BT_TL(slot, 1);
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) tile_j += s_wave_before[w];
-        tile_j = uniform64(tile_j);
-        if (slot == 0 && tid == 0) reinterpret_cast<uint32_t *>(ws)[kHdrCalls] = calls + 1u;
-    } else {
-        if (tid == 0) ws_store32(ws_count(ws, slot, ep.cur), (tile_total + 1) | (Job::kMany && sl.tile == 0 ? kFirstTile : 0u));
-        BT_TL(slot, 1);
-        zero_previous(ws, ep, slot, n_slots);
-        // Algorithm 2's counter j at the start of the tile: the first wave asks (one poller a tile keeps the
-        // traffic on the workspace's few lines low) and passes the answer on through LDS
-        if (wave == 0) {
-            const uint64_t v = wait_for_prefix(ws, slot, n_slots, ep.cur, polls, [&]() { return prefix_from_bitmap<S, R>(bitmap, sl.tile, lane); });
-            if (lane == 0) s_tile_j = v;
-        }
-        lds_barrier();
-        tile_j = uniform64(s_tile_j);
-    }
-    BT_TL(slot, 2);
-    restore_fetch<S, R>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
-    restore_store<S, R>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
-    BT_TL(slot, 3);
-    BT_TL_VALUE(slot, 5, polls);
+    for (int w = 0; w < kWaves; ++w) tile_j += s_wave_before[w];
+    tile_j = uniform64(tile_j);
+    if (tile == 0 && tid == 0) hdr[kHdrCalls] = calls + 1u;
+    const TileValues<S, R> f = fetch_values<S, R>(job.values(0), job.cap(0), tile_j, ranks.before[1], tid);
+    commit_values<S, R>(s_stage, f, tid);
+    lds_barrier();
+    expand_phase<S, R, R>(rows, 0, 0, f, 0, s_stage, job.out(0), n, tile, lane, wave);
 }
 
-// bt_decompress_indexed and its batched form: one workgroup per slot and nothing else.  Algorithm 2's
-// j at the start of the tile comes from the tile index.
+// bt_decompress_indexed and its batched form: two workgroups per slot, one for each phase of its tile, and nothing else.
+// Algorithm 2's j at the start of the tile comes from the tile index; what the tile's first half holds a wave of the second
+// counts from the same words.
 //
-// Two thirds of the traffic and more are stores, and nothing holds a workgroup back: with all eight workgroups that fit a
-// compute unit, the stores of too many tiles mix; with few, the chain from bitmap to values shows.  So a batch reserves LDS
-// for five (LDS is allocated in steps of kLdsStep bytes: a share that is no whole number of steps makes room for one less).
-// Measured with 8 / 6 / 5 / 4 workgroups, us: the 49 tensors of a ResNet-50, fp32 at batch 64, 30 % zeros 748 / 748 / 758 / 761, 50 %
-// 659 / 644 / 643 / 637, 70 % 566 / 553 / 550 / 554; at batch 16, 95 %, 117 / 116 / 113 / 110; bf16 at batch 16, 95 %, 59 / 57 / 52 / 52, at batch 64,
-// 50 %, 335 / 324 / 319 / 319; fp64 at batch 4, 95 %, 59 / 58 / 55 / 50, at batch 1, 50 %, 20.0 / 20.4 / 20.6 / 20.9.  One tensor
-// keeps eight: fp32 103 M elements, 8 / 5 / 4, 5 % zeros 137.7 / 139.8 / 140.6, 50 % 106.2 / 104.8 / 104.5, 95 % 76.4 / 74.6 / 71.1; the
-// call does not know how many values there are, and dense tensors would lose.
-//
-// What the waves before a wave hold (see the three ways below):
-//   batches            counted by every wave from the bitmap itself, so that the waves need not meet: fp32 at batch 64, 50 % zeros,
-//                      643 us instead of 680 with an exchange through LDS, bf16 at batch 16, 95 %, 51 instead of 56;
-//   one fp32 or fp64   exchanged through LDS behind a barrier (fp32 103 M elements, 50 %: 104.5 us instead of 106.2);
-//   one of 16 bits     restore_ranks_by_row, which says why.
-//
-// LARGE (a batch of kLargeSlots slots and more): where a tile is a quarter full or less, which its index entry and the next one
-// tell, the waves meet all the same before they ask for their values, so that the tile's stores leave together.  Measured, without /
-// with, us: batch 64 in fp32 at 85 % zeros 525 / 502, at 95 % 568 / 545, in bf16 279 / 269 and 255 / 246; batch 32 in fp64 570 / 489 and
-// 545 / 486 (eight workgroups and row-by-row ranks: 526 and 489).  Below, it is as often worse as better (20 k slots: fp32 85 %
-// 114.6 / 114.9, 95 % 113 / 115.2; bf16 148 / 138 and 113 / 114.8).
-constexpr int kLdsBytes = 160 * 1024, kLdsStep = 1280;      // of a compute unit
-constexpr uint32_t kLargeSlots = 30000;
-template <class Job> constexpr int kIndexedOcc = Job::kMany ? 5 : 8;
-template <int S, class Job, bool LARGE>
-__global__ __launch_bounds__(kBlock, kIndexedOcc<Job>) void decompress_indexed_kernel(const Job job) {
+// What bounds it: the memory system on large tensors, the chain index and words, values, stores on small ones, so the less a workgroup
+// has to do one after the other the better: half a tile, rows of all waves written front to back.  Measured, a workgroup per tile
+// whose waves restore a quarter each / this, us: one tensor, fp32 3 M elements at 50 % zeros 4.3 / 3.8, 100 M 101.6 / 98.9, at 95 %
+// 74.8 / 70.0; bf16 1 M 5.9 / 3.8, 25.7 M 16.2 / 13.2, 100 M 57.2 / 51.9, fp16 206 M at 95 % 71.8 / 65.6; fp64 100 M 200.9 / 195.9; the
+// 49 tensors of a ResNet-50, fp32 at 1 / 4 / 64 images, 50 %, 12.9 / 10.9, 43.2 / 38.1, 641.7 / 613.9, at 64 images and 95 % 526 / 474, bf16 at
+// 1 image 13.1 / 7.3.  Tiles of two rows instead of four: fp32 100 M at 95 % 60.1, but 106 at 50 %; six workgroups a compute unit
+// instead of eight: 612.6 instead of 624.5 on the fp32 set at 50 %, 527 instead of 484 at 85 %.
+template <int S, class Job>
+__global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_indexed_kernel(const Job job, const uint32_t first_slot) {
     constexpr int R = kRows;
     using G = Geo<S, R>;
-    constexpr int kShare = kLdsBytes / kIndexedOcc<Job> / kLdsStep * kLdsStep;
-    constexpr int kTotals = kWaves * (int)sizeof(uint32_t);      // of the share, for the waves' totals
-    static_assert(kShare * kIndexedOcc<Job> <= kLdsBytes && kShare - kTotals >= kWaves * G::LDS_WAVE, "the workgroups and their strips fit");
-    constexpr bool kByRow = S == 2 && !Job::kMany;
-    constexpr bool kExchange = S != 2 && !Job::kMany;
-    __shared__ __attribute__((aligned(16))) unsigned char s_stage[kShare - kTotals];
-    __shared__ uint32_t s_wave_total[kWaves];
-    const int lane = threadIdx.x & (kWaveSize - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const Slot sl = job.at(blockIdx.x);
-    const uint64_t *const index = job.tile_index(sl.item) + sl.tile;
-    const uint64_t tile_j = index[0];             // asked for first, needed last
-    bool together = false;                        // (the same in all waves: it depends on the index alone)
-    if (LARGE && sl.tile + 1 < job.tiles(sl.item)) together = index[1] - tile_j < (uint64_t)(G::TILE / 4);
-    const uint32_t *const bitmap = job.bitmap(sl.item);
+    static_assert(TileRanks<S, R>::PHASES == 2, "a workgroup per phase");
+    __shared__ __attribute__((aligned(16))) unsigned char s_stage[G::LDS_TILE];
+    __shared__ bt_u2 s_entries[G::TILE_WORDS / 2];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const Slot sl = job.at(first_slot + blockIdx.x / 2);
+    const uint32_t half = blockIdx.x % 2;
     const uint64_t n = job.n(sl.item);
-    Restoring<S, R> r;
-    unsigned char *const strip = s_stage + wave * G::LDS_WAVE;
-    uint32_t before_wave = 0;
-    if constexpr (kByRow) {
-        before_wave = restore_ranks_by_row<S, R>(bitmap, n, sl.tile, lane, wave, r);
-    } else {
-        const Quarter<S, R> quarter = quarter_load<S, R>(bitmap, n, sl.tile, lane, wave);
-        uint32_t before = 0;
-        if (!kExchange) {
-#pragma unroll
-            for (int w = 0; w < kWaves - 1; ++w) {
-                if (w < wave) {
-                    const Quarter<S, R> q = quarter_load<S, R>(bitmap, n, sl.tile, lane, w);
-#pragma unroll
-                    for (int j = 0; j < G::WPL; ++j) before += (uint32_t)__popc(q.w[j]);
-                }
-            }
-        }
-        const uint32_t wave_total = restore_ranks<S, R>(quarter, strip, lane, r);
-        if (kExchange) {
-            if (lane == 0) s_wave_total[wave] = wave_total;
-            lds_barrier();
-#pragma unroll
-            for (int w = 0; w < kWaves - 1; ++w) {
-                const uint32_t c = s_wave_total[w];
-                if (w < wave) before_wave += c;
-            }
-            before_wave = uniform32(before_wave);
-        } else {
-            before_wave = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(before), 63);
-            if (LARGE && together) lds_barrier();
-        }
-    }
-    restore_fetch<S, R>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
-    restore_store<S, R>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
+    if ((uint64_t)sl.tile * G::TILE + half * (G::TILE / 2) >= n) return;
+    const uint64_t tile_j = job.tile_index(sl.item)[sl.tile];
+    const TileBits<S, R> bits = load_bits<S, R>(job.bitmap(sl.item), n, sl.tile, lane);
+    const TileRanks<S, R> ranks = rank_words<S, R>(bits);
+    const uint32_t before = half != 0 ? ranks.before[1] : 0u;
+    const uint32_t count = half != 0 ? ranks.before[2] - ranks.before[1] : ranks.before[1];
+    const TileValues<S, R> f = fetch_values<S, R>(job.values(sl.item), job.cap(sl.item), tile_j + before, count, tid);
+    const int first_row = (int)half * (kWaves * G::PHASE);
+    const Rows<S, G::PHASE> rows = rows_of<S, R, G::PHASE>(bits, ranks, first_row, s_entries, lane, wave);
+    commit_values<S, R>(s_stage, f, tid);
+    lds_barrier();
+    expand_phase<S, R, G::PHASE>(rows, 0, first_row, f, before, s_stage, job.out(sl.item), n, sl.tile, lane, wave);
 }
 
 // ---- ReLU backward from the bitmap -----------------------------------------------------------
@@ -1968,29 +2114,34 @@ bt_status launch_compress(const Job &job, uint64_t slots, bt_dtype dtype, bool p
     return launched();
 }
 
-template <int R, bool SELF, class Job>
-bt_status launch_decompress(const Job &job, uint64_t slots, int s, char *ws, hipStream_t hs) {
-    const dim3 block(kBlock);
-    const unsigned grid = (unsigned)slots + (SELF ? 0u : 1u);      // with or without a scanner
-#define BT_LAUNCH_DECOMPRESS(S_)                                                                \
-    do {                                                                                        \
-        auto kernel = decompress_kernel<S_, R, SELF, Job>;                                      \
-        kernel<<<dim3(grid), block, 0, hs>>>(job, ws);                                          \
-    } while (0)
-    if (s == 8) BT_LAUNCH_DECOMPRESS(8);
-    else if (s == 4) BT_LAUNCH_DECOMPRESS(4);
-    else BT_LAUNCH_DECOMPRESS(2);
-#undef BT_LAUNCH_DECOMPRESS
+template <class Job> bt_status launch_decompress(const Job &job, uint64_t slots, int s, char *ws, hipStream_t hs) {
+    const dim3 grid((unsigned)slots + 1u), block(kBlock);      // and the scanner
+    if (s == 8) decompress_kernel<8, Job><<<grid, block, 0, hs>>>(job, ws);
+    else if (s == 4) decompress_kernel<4, Job><<<grid, block, 0, hs>>>(job, ws);
+    else decompress_kernel<2, Job><<<grid, block, 0, hs>>>(job, ws);
     return launched();
 }
 
-template <bool LARGE, class Job>
-bt_status launch_decompress_indexed(const Job &job, uint64_t slots, int s, hipStream_t hs) {
-    const dim3 grid((unsigned)slots), block(kBlock);
-    if (s == 8) decompress_indexed_kernel<8, Job, LARGE><<<grid, block, 0, hs>>>(job);
-    else if (s == 4) decompress_indexed_kernel<4, Job, LARGE><<<grid, block, 0, hs>>>(job);
-    else decompress_indexed_kernel<2, Job, LARGE><<<grid, block, 0, hs>>>(job);
+template <int R> bt_status launch_decompress_small(const DecompressOne &job, uint64_t tiles, int s, char *ws, hipStream_t hs) {
+    const dim3 grid((unsigned)tiles), block(kBlock);
+    if (s == 8) decompress_small_kernel<8, R><<<grid, block, 0, hs>>>(job, ws);
+    else if (s == 4) decompress_small_kernel<4, R><<<grid, block, 0, hs>>>(job, ws);
+    else decompress_small_kernel<2, R><<<grid, block, 0, hs>>>(job, ws);
     return launched();
+}
+
+template <class Job>
+bt_status launch_decompress_indexed(const Job &job, uint64_t slots, int s, hipStream_t hs) {
+    constexpr uint64_t kMost = 1u << 22;      // slots a launch: a grid holds less than 2^32 threads
+    for (uint64_t first = 0; first < slots; first += kMost) {
+        const dim3 grid((unsigned)(2 * (slots - first < kMost ? slots - first : kMost))), block(kBlock);
+        if (s == 8) decompress_indexed_kernel<8, Job><<<grid, block, 0, hs>>>(job, (uint32_t)first);
+        else if (s == 4) decompress_indexed_kernel<4, Job><<<grid, block, 0, hs>>>(job, (uint32_t)first);
+        else decompress_indexed_kernel<2, Job><<<grid, block, 0, hs>>>(job, (uint32_t)first);
+        const bt_status st = launched();
+        if (st != BT_OK) return st;
+    }
+    return BT_OK;
 }
 
 // ---- a workspace that belongs to the library -------------------------------------------------
@@ -2191,7 +2342,7 @@ bt_status bt_decompress_indexed(const uint32_t *d_bitmap, const void *d_values, 
         return BT_ERR_ALIGN;
     const uint32_t n_tiles = (uint32_t)tiles_for(n, s);
     const DecompressOne job{d_bitmap, d_values, values_cap, d_index, n, d_out, n_tiles};
-    return launch_decompress_indexed<false>(job, n_tiles, s, (hipStream_t)stream);
+    return launch_decompress_indexed(job, n_tiles, s, (hipStream_t)stream);
 }
 
 bt_status bt_decompress(const uint32_t *d_bitmap, const void *d_values, uint64_t n, bt_dtype dtype, void *d_out,
@@ -2204,21 +2355,16 @@ bt_status bt_decompress(const uint32_t *d_bitmap, const void *d_values, uint64_t
     if (misaligned(d_out, 16) || misaligned(d_bitmap, 4) || misaligned(d_values, (size_t)s)) return BT_ERR_ALIGN;
     char *const ws = static_cast<char *>(d_workspace);
     hipStream_t hs = (hipStream_t)stream;
-    const auto launch = [&](auto rows, auto self) {
-        constexpr int R = decltype(rows)::value;
-        const uint32_t n_tiles = (uint32_t)tiles_for(n, s, R);
-        const DecompressOne job{d_bitmap, d_values, ~(uint64_t)0, nullptr, n, d_out, n_tiles};
-        return launch_decompress<R, decltype(self)::value>(job, n_tiles, s, ws, hs);
-    };
-    // Small tensors: every workgroup counts the bitmap before its tile itself (SELF), in tiles of two or four rows a lane.
+    const auto job = [&](uint64_t tiles) { return DecompressOne{d_bitmap, d_values, ~(uint64_t)0, nullptr, n, d_out, (uint32_t)tiles}; };
+    const uint64_t tiles2 = tiles_for(n, s, 2), tiles4 = tiles_for(n, s, 4), tiles = tiles_for(n, s);
+    // Small tensors: every workgroup counts the bitmap before its tile itself, in tiles of two or four rows a lane.
     // What it reads grows with the tensor: with 256 tiles of four rows 128 KiB at the end of an fp32 tensor, 256 KiB of a
     // 16-bit one, which is where the scanner is as fast.  Measured, us per call on the GPU, before / after: fp32 5 k elements
     // 6.0 / 2.9, 201 k 6.5 / 3.2, 500 k 6.7 / 3.8, 1 M 6.6 / 5.2 (1.5 M with eight rows 6.9 / 7.6: not done); bf16 1 M 7.9 / 5.0,
     // 2 M 7.9 / 7.6.
-    using std::integral_constant;
-    if (tiles_for(n, s, 2) <= 256) return launch(integral_constant<int, 2>{}, std::true_type{});
-    if (tiles_for(n, s, 4) <= 256) return launch(integral_constant<int, 4>{}, std::true_type{});
-    return launch(integral_constant<int, kRows>{}, std::false_type{});
+    if (tiles2 <= 256) return launch_decompress_small<2>(job(tiles2), tiles2, s, ws, hs);
+    if (tiles4 <= 256) return launch_decompress_small<4>(job(tiles4), tiles4, s, ws, hs);
+    return launch_decompress(job(tiles), tiles, s, ws, hs);
 }
 
 bt_status bt_relu_backward_from_bitmap(const uint32_t *d_bitmap, const void *d_grad_out, uint64_t n, bt_dtype dtype,
@@ -2344,7 +2490,7 @@ bt_status bt_decompress_batch(const bt_decompress_item *items, size_t count, bt_
             b.n_[i] = it.n;
             b.out_[i] = it.d_out;
         }
-        const bt_status ls = launch_decompress<kRows, false>(b, b.lay.start[c], s, ws, hs);
+        const bt_status ls = launch_decompress(b, b.lay.start[c], s, ws, hs);
         if (ls != BT_OK) return ls;
     }
     return BT_OK;
@@ -2379,9 +2525,7 @@ bt_status bt_decompress_batch_indexed(const bt_decompress_item *items, size_t co
             b.n_[i] = it.n;
             b.out_[i] = it.d_out;
         }
-        const uint64_t slots = b.lay.start[c];
-        if (slots == 0) continue;      // empty tensors only
-        const bt_status ls = slots >= kLargeSlots ? launch_decompress_indexed<true>(b, slots, s, hs) : launch_decompress_indexed<false>(b, slots, s, hs);
+        const bt_status ls = launch_decompress_indexed(b, b.lay.start[c], s, hs);      // (nothing for empty tensors only)
         if (ls != BT_OK) return ls;
     }
     return BT_OK;

@@ -112,6 +112,38 @@ def test_indexed_special_patterns_and_extremes(bt, oracle, dt):
         assert np.array_equal(out, wl.bits(x))
 
 
+@pytest.mark.parametrize("dt", DTYPES)
+def test_restoration_without_the_scan_at_the_edges_of_halves_and_rows(bt, oracle, dt):
+    """From an index a workgroup restores half a tile, a small tensor's one tile of two or four rows; waves take rows (1 KiB) in
+    turn: sizes around rows, halves, tiles and the last small plan, a last tile with and without a second half, empty, full and
+    mixed, with bitmaps and values at every alignment they may have."""
+    dtype = wl.DTYPES[dt]
+    tile = bt.bt_tile_elems(dtype)
+    row, half = tile // 32, tile // 2
+    sizes = sorted({k + d for k in (row, 4 * row, half, half + row, tile, tile + half, 2 * tile, 64 * tile, 128 * tile) for d in (-33, -1, 0, 1, 32)})
+    for i, n in enumerate(sizes):
+        x = wl.random_sparse(n, dt, [0.5, 0.0, 0.98, 1.0][i % 4], seed=7400 + i)
+        o_bitmap, o_values, o_nnz = oracle.compress(wl.bits(x))
+        shift = i % 4      # words
+        bbuf = _sentinel(o_bitmap.size + 4, torch.int32)
+        bitmap = bbuf[shift:shift + o_bitmap.size]
+        bitmap.copy_(torch.from_numpy(o_bitmap.view(np.int32)))
+        vbuf = _sentinel(o_nnz + 16, dtype)
+        values = vbuf[i % 7:i % 7 + o_nnz]
+        values.copy_(_values_tensor(o_values[:o_nnz], dtype))
+        index = torch.from_numpy(oracle.tile_index(o_bitmap, n, tile).view(np.int64).copy()).cuda()
+        ws = bt.new_workspace(n, dtype)
+        for indexed in (True, False):
+            out = _sentinel(n + 8, dtype)
+            if indexed:
+                bt.bt_decompress_indexed(bitmap, values, index, out[:n])
+            else:
+                bt.bt_decompress(bitmap, values, out[:n], ws)
+            torch.cuda.synchronize()
+            assert np.array_equal(wl.bits(out[:n].cpu()), wl.bits(x)), (n, indexed)
+            assert bool((out[n:].view(torch.uint8) == SENT).all()), (n, indexed)
+
+
 def test_indexed_decompress_never_reads_beyond_the_values_it_was_given(bt, oracle):
     """An index that does not belong to the bitmap gives a wrong tensor, but the call stays inside its
     buffers: with the capacity cut to half the values, everything restored from the first half is right."""
