@@ -189,7 +189,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 //   compress    plain 38.1/31.3   nt loads 34.2/32.8   nt stores 35.0/30.0   both 33.3/31.3
 //   decompress  plain 35.6/27.6   nt loads 36.3/32.8   nt stores 34.4/27.3   both 35.0/34.2
 //   relu bwd    plain 37.2        nt loads 36.6        nt stores 35.4        both 34.7
-// so compress and the ReLU stream use both hints (their input is dead after the call:
+// so compress and the ReLU stream of large gradients use both hints (their input is dead after the call:
 // Algorithm 1 ends by giving the dense tensor up), decompress only the store hint.
 typedef uint32_t bt_u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t bt_u2 __attribute__((ext_vector_type(2)));
@@ -211,7 +211,7 @@ template <bool NT> __device__ __forceinline__ void stream_store(uint4 *p, const 
 }
 constexpr bool kCompressNtLoad = true, kCompressNtStore = true;
 constexpr bool kDecompressNtLoad = false, kDecompressNtStore = true;
-constexpr bool kReluNtLoad = true, kReluNtStore = true;
+constexpr bool kReluNtStore = true;
 
 // Bit j set <=> element j of the 16-byte vector has a non-zero bit pattern.
 // min(bits, 1) instead of a compare: a compare result lives in a scalar register
@@ -1921,8 +1921,9 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_indexed_ker
 // ---- ReLU backward from the bitmap -----------------------------------------------------------
 
 // grad_in[i] = bit(i) ? grad_out[i] : +0.  Pure streaming: no scan, no LDS.  Each
-// lane selects per element with the E bits that cover its 16-byte vector.
-template <int S>
+// lane selects per element with the E bits that cover its 16-byte vector.  Bound by memory; NT: gradients are read past the
+// caches (see bt_relu_backward_from_bitmap).
+template <int S, bool NT>
 __global__ __launch_bounds__(kBlock) void relu_backward_kernel(const uint32_t *__restrict__ bitmap,
                                                                const void *grad_out, const uint64_t n,
                                                                void *grad_in) {
@@ -1942,7 +1943,7 @@ __global__ __launch_bounds__(kBlock) void relu_backward_kernel(const uint32_t *_
     for (int k = 0; k < kR; ++k) {
         const uint64_t e0 = wave_e0 + (uint64_t)k * G::ROW + (uint64_t)lane * E;
         if (full) {
-            g[k] = stream_load<kReluNtLoad>(reinterpret_cast<const uint4 *>(static_cast<const char *>(grad_out) + e0 * S));
+            g[k] = stream_load<NT>(reinterpret_cast<const uint4 *>(static_cast<const char *>(grad_out) + e0 * S));
             m[k] = (bitmap[e0 >> 5] >> (uint32_t)(e0 & 31)) & ((1u << E) - 1u);
         } else {
             g[k] = load_vec_guarded<S>(grad_out, e0, n);
@@ -2006,6 +2007,8 @@ uint64_t tiles_for(uint64_t n, int s, int rows = kRows) {
     const uint64_t t = tile_elems(s, rows);
     return (n + t - 1) / t;
 }
+
+constexpr uint64_t kReluCachedBytes = (uint64_t)64 << 20;      // largest gradient that is read through the caches
 
 uint64_t relu_blocks_for(uint64_t n, int s) {
     const uint64_t t = (uint64_t)kBlock * kReluRows * (kVecBytes / s);
@@ -2376,13 +2379,18 @@ bt_status bt_relu_backward_from_bitmap(const uint32_t *d_bitmap, const void *d_g
     if (d_bitmap == nullptr || d_grad_out == nullptr || d_grad_in == nullptr) return BT_ERR_NULL;
     if (misaligned(d_grad_out, 16) || misaligned(d_grad_in, 16) || misaligned(d_bitmap, 4)) return BT_ERR_ALIGN;
     hipStream_t hs = (hipStream_t)stream;
-    const uint32_t blocks = (uint32_t)relu_blocks_for(n, s);
-    if (s == 8)
-        relu_backward_kernel<8><<<dim3(blocks), dim3(kBlock), 0, hs>>>(d_bitmap, d_grad_out, n, d_grad_in);
-    else if (s == 4)
-        relu_backward_kernel<4><<<dim3(blocks), dim3(kBlock), 0, hs>>>(d_bitmap, d_grad_out, n, d_grad_in);
-    else
-        relu_backward_kernel<2><<<dim3(blocks), dim3(kBlock), 0, hs>>>(d_bitmap, d_grad_out, n, d_grad_in);
+    // The gradient was written just before, so while it fits the 256 MB cache beside what else was written since, it is read
+    // from there with plain loads; the hint sends them past it.  Measured, us, with the hint / plain, three sets of buffers in
+    // turn: fp32 1 M elements 2.8 / 2.3, 2 M 3.9 / 2.7, 5.5 M 9.2 / 7.8, 12 M 17.5 / 15.2, 20 M 27.3 / 23.8, 25.7 M 34.2 / 35.1; bf16 5.5 M
+    // 5.3 / 4.3, 25.7 M 18.6 / 16.1, 60 M 39.5 / 41.1.  With eight sets, which push each other out of it: fp32 5.5 M 9.4 / 7.9, 9 M 13.9 /
+    // 13.5, 16 M 22.5 / 23.0, 25.7 M 34.4 / 35.2.  So up to a quarter of the cache.
+    const bool cached = n * (uint64_t)s <= kReluCachedBytes;
+    const auto launch = [&](auto kernel) {
+        kernel<<<dim3((unsigned)relu_blocks_for(n, s)), dim3(kBlock), 0, hs>>>(d_bitmap, d_grad_out, n, d_grad_in);
+    };
+    if (s == 8) launch(cached ? relu_backward_kernel<8, false> : relu_backward_kernel<8, true>);
+    else if (s == 4) launch(cached ? relu_backward_kernel<4, false> : relu_backward_kernel<4, true>);
+    else launch(cached ? relu_backward_kernel<2, false> : relu_backward_kernel<2, true>);
     return launched();
 }
 

@@ -763,3 +763,22 @@ def test_structured_zero_patterns(gpu, oracle, dt, tiles):
         _check_decompress(gpu, oracle, o_bitmap, o_values, n, x.dtype, wl.bits(x))
         out, guard_ok = gpu.gpu_relu_backward(o_bitmap, g)
         assert np.array_equal(out, oracle.relu_backward(o_bitmap, wl.bits(g))) and guard_ok, name
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
+def test_relu_backward_around_the_largest_gradient_read_through_the_caches(gpu, dt):
+    """Gradients of up to 64 MiB are read with plain loads, larger ones past the caches: the last of the one kind and the first
+    of the other, with ragged ends, against torch on the device."""
+    from paper_2110_15362_amd import bittrain as bt
+    dtype = wl.DTYPES[dt]
+    wide = {2: torch.int16, 4: torch.int32, 8: torch.int64}[dtype.itemsize]
+    last = (64 << 20) // dtype.itemsize
+    g = torch.Generator(device="cuda").manual_seed(9)
+    words = torch.randint(-(1 << 31), 1 << 31, ((last + 5) // 32 + 1,), generator=g, device="cuda").to(torch.int32)
+    grad = torch.randint(-(1 << 15), 1 << 15, (last + 5,), generator=g, device="cuda").to(wide)
+    keep = ((words[:, None] >> torch.arange(32, device="cuda", dtype=torch.int32)) & 1).reshape(-1).bool()
+    for n in (last - 3, last, last + 1, last + 5):
+        out = torch.full((n + 4,), 0x5A, dtype=wide, device="cuda")
+        bt.bt_relu_backward_from_bitmap(words, grad[:n].view(dtype), out[:n].view(dtype))
+        assert torch.equal(out[:n], torch.where(keep[:n], grad[:n], 0)), n
+        assert bool((out[n:] == 0x5A).all()), n
