@@ -2008,7 +2008,7 @@ uint64_t tiles_for(uint64_t n, int s, int rows = kRows) {
     return (n + t - 1) / t;
 }
 
-constexpr uint64_t kReluCachedBytes = (uint64_t)64 << 20;      // largest gradient that is read through the caches
+constexpr uint64_t kReluCachedBytes = (uint64_t)48 << 20;      // largest gradient that is read through the caches
 
 uint64_t relu_blocks_for(uint64_t n, int s) {
     const uint64_t t = (uint64_t)kBlock * kReluRows * (kVecBytes / s);
@@ -2383,7 +2383,7 @@ bt_status bt_relu_backward_from_bitmap(const uint32_t *d_bitmap, const void *d_g
     // from there with plain loads; the hint sends them past it.  Measured, us, with the hint / plain, three sets of buffers in
     // turn: fp32 1 M elements 2.8 / 2.3, 2 M 3.9 / 2.7, 5.5 M 9.2 / 7.8, 12 M 17.5 / 15.2, 20 M 27.3 / 23.8, 25.7 M 34.2 / 35.1; bf16 5.5 M
     // 5.3 / 4.3, 25.7 M 18.6 / 16.1, 60 M 39.5 / 41.1.  With eight sets, which push each other out of it: fp32 5.5 M 9.4 / 7.9, 9 M 13.9 /
-    // 13.5, 16 M 22.5 / 23.0, 25.7 M 34.4 / 35.2.  So up to a quarter of the cache.
+    // 13.5, 16 M 22.5 / 23.0, 25.7 M 34.4 / 35.2.  In a step (compress, restore, this) fp32 5.5 M 32.4 / 30.7, 12 M 51.3 / 49.7, bf16 32.2 M 66.4 / 68.4.
     const bool cached = n * (uint64_t)s <= kReluCachedBytes;
     const auto launch = [&](auto kernel) {
         kernel<<<dim3((unsigned)relu_blocks_for(n, s)), dim3(kBlock), 0, hs>>>(d_bitmap, d_grad_out, n, d_grad_in);

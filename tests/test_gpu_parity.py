@@ -767,12 +767,12 @@ def test_structured_zero_patterns(gpu, oracle, dt, tiles):
 
 @pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
 def test_relu_backward_around_the_largest_gradient_read_through_the_caches(gpu, dt):
-    """Gradients of up to 64 MiB are read with plain loads, larger ones past the caches: the last of the one kind and the first
+    """Gradients of up to 48 MiB are read with plain loads, larger ones past the caches: the last of the one kind and the first
     of the other, with ragged ends, against torch on the device."""
     from paper_2110_15362_amd import bittrain as bt
     dtype = wl.DTYPES[dt]
     wide = {2: torch.int16, 4: torch.int32, 8: torch.int64}[dtype.itemsize]
-    last = (64 << 20) // dtype.itemsize
+    last = (48 << 20) // dtype.itemsize
     g = torch.Generator(device="cuda").manual_seed(9)
     words = torch.randint(-(1 << 31), 1 << 31, ((last + 5) // 32 + 1,), generator=g, device="cuda").to(torch.int32)
     grad = torch.randint(-(1 << 15), 1 << 15, (last + 5,), generator=g, device="cuda").to(wide)
