@@ -1,6 +1,6 @@
 """Thin binding over the C-ABI library ``libbittrain.so``.
 
-Argument marshalling only (that of the single-tensor calls in C, ``csrc/call.c``): every step of the codec
+Argument marshalling only (that of the single-tensor calls in C++, ``csrc/call.cpp``): every step of the codec
 runs in the HIP kernels of the library.  PyTorch supplies device memory and the stream, nothing else.
 There is no CPU fallback: if the library is missing, or a call fails, this
 module raises.
@@ -26,8 +26,8 @@ BT_MAX_ELEMENTS = 1 << 37
 _DTYPES = {torch.float32: BT_F32, torch.float16: BT_F16, torch.bfloat16: BT_BF16, torch.float64: BT_F64}
 
 _lib = None
-_call = None      # the single-tensor calls, checked and marshalled in C; bound to the library that lib() has loaded
-# the library's functions behind it, in the order of the table in csrc/call.c
+_call = None      # the single-tensor calls, checked and marshalled in C++; bound to the library that lib() has loaded
+# the library's functions behind it, in the order of the table in csrc/call.cpp
 _CALLS = ("bt_compress", "bt_compress_static", "bt_compress_pruned", "bt_activation_compress", "bt_compress_indexed",
           "bt_decompress", "bt_decompress_indexed", "bt_relu_backward_from_bitmap", "bt_mask_apply", "bt_index_bytes")
 
@@ -102,8 +102,7 @@ def lib():
         L.bt_workspace_status.argtypes = [vp, vp, vp]
         from . import _call as call
         call.bind(tuple(ctypes.cast(getattr(L, f), vp).value for f in _CALLS), _DTYPES, dtype_code, BitTrainError, _stream_handle,
-                  getattr(torch._C, "_cuda_getDevice", None),
-                  getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None)
+                  hasattr(torch._C, "_cuda_getCurrentRawStream"))
         _call = call      # first: other threads go by _lib
         _lib = L
     return _lib
@@ -187,33 +186,38 @@ def bt_compress(x, bitmap, values, nnz, workspace, stream=None):
     """Algorithm 1 on device tensors.  x: dense tensor (any shape, contiguous);
     bitmap: int32[ceil(n/32)]; values: x.dtype[cap]; nnz: int64[1]; all on x's
     device.  Enqueues on the stream and returns; nothing is synchronised."""
-    lib()
+    if _lib is None:
+        lib()
     _call.compress(x, bitmap, values, nnz, workspace, stream)
 
 
 def bt_compress_static(x, bitmap, values, nnz, stream=None):
     """bt_compress on the library's own workspace (nothing is allocated by the call); x of at
     most BT_STATIC_MAX_TILES tiles.  Calls on one GPU share that workspace: keep them ordered."""
-    lib()
+    if _lib is None:
+        lib()
     _call.compress_static(x, bitmap, values, nnz, stream)
 
 
 def bt_compress_pruned(x, threshold, bitmap, values, nnz, workspace, stream=None):
     """Section 4.3 fused into Algorithm 1: keep x[i] where x[i] > threshold (ReLU for
     threshold 0 on a pre-activation tensor).  Same buffers as bt_compress."""
-    lib()
+    if _lib is None:
+        lib()
     _call.compress_pruned(x, bitmap, values, nnz, workspace, threshold, stream)
 
 
 def bt_decompress(bitmap, values, out, workspace, stream=None):
     """Algorithm 2 on device tensors: fills `out` (n = out.numel()) from bitmap + values."""
-    lib()
+    if _lib is None:
+        lib()
     _call.decompress(bitmap, values, out, workspace, stream)
 
 
 def bt_relu_backward_from_bitmap(bitmap, grad_out, grad_in, stream=None):
     """grad_in[i] = bit(i) ? grad_out[i] : +0; grad_in may be grad_out itself."""
-    lib()
+    if _lib is None:
+        lib()
     _call.relu_backward(bitmap, grad_out, grad_in, stream)
 
 
@@ -335,7 +339,8 @@ def bt_decompress_batch(items, count, dtype, workspace, stream=None):
 
 def bt_mask_apply(bitmap, x, out, stream=None):
     """Double mask: out[i] = bit(i) ? x[i] : +0 with the bitmap of another tensor; out may be x."""
-    lib()
+    if _lib is None:
+        lib()
     _call.mask_apply(bitmap, x, out, stream)
 
 
@@ -349,18 +354,21 @@ def bt_index_bytes(n, dtype):
 
 def bt_compress_indexed(x, bitmap, values, nnz, index, workspace, stream=None):
     """bt_compress that also leaves the tile index (int64[ceil(n / bt_tile_elems)]) for bt_decompress_indexed."""
-    lib()
+    if _lib is None:
+        lib()
     _call.compress_indexed(x, bitmap, values, nnz, index, workspace, stream)
 
 
 def bt_decompress_indexed(bitmap, values, index, out, stream=None):
     """Algorithm 2 started at every tile from the tile index: no workspace, no scan."""
-    lib()
+    if _lib is None:
+        lib()
     _call.decompress_indexed(bitmap, values, index, out, stream)
 
 
 def bt_activation_compress(x, threshold, dense_out, bitmap, values, nnz, workspace, stream=None):
     """One pass over x: dense_out = x where x > threshold else +0 (ReLU for threshold 0; dense_out may be x
     itself), and bitmap / values / nnz = the compressed form of that dense_out."""
-    lib()
+    if _lib is None:
+        lib()
     _call.activation_compress(x, dense_out, bitmap, values, nnz, workspace, threshold, stream)

@@ -1,4 +1,5 @@
-"""Build libbittrain.so for gfx950 with hipcc (cross-compiles without a GPU), and the binding's call module with gcc."""
+"""Build libbittrain.so for gfx950 with hipcc (cross-compiles without a GPU), and the binding's call module with g++."""
+import importlib.util
 import os
 import subprocess
 import sysconfig
@@ -10,8 +11,8 @@ LIB = os.path.join(HERE, "libbittrain.so")
 # measurement aids for bench.py: the same kernels with per-tile time stamps compiled in, plus a plain stream
 BENCH_SRC = os.path.join(HERE, "csrc", "bench_aids.hip")
 BENCH_LIB = os.path.join(HERE, "libbittrain_bench.so")
-# the calls on torch tensors, checked and marshalled in C
-CALL_SRC = os.path.join(HERE, "csrc", "call.c")
+# the calls on torch tensors, checked and marshalled in C++
+CALL_SRC = os.path.join(HERE, "csrc", "call.cpp")
 CALL_LIB = os.path.join(HERE, "_call.so")
 
 HIPCC_FLAGS = [
@@ -43,8 +44,12 @@ def build_bench_aids(verbose=False, extra_flags=()):
 
 
 def build_call(verbose=False):
-    cmd = ["gcc", "-std=c11", "-O2", "-Wall", "-Wextra", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"],
-           "-I", os.path.join(ROOT, "include"), CALL_SRC, "-o", CALL_LIB]
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(torch, "include"),
+           "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+           CALL_SRC, "-o", CALL_LIB, "-L", os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     if verbose:
         print(" ".join(cmd))
     subprocess.check_call(cmd)

@@ -3,14 +3,22 @@
  *
  * What a small call costs is the host's work, not the GPU's: the three calls of a training step on one image's
  * layer (fp32, 200,704 elements) keep the GPU busy for 10 us, and checking the tensors and marshalling the arguments with
- * ctypes took 5 to 6 us a call on top of the launch's 3.  This module does the same checks in the same
- * order through the C API of Python: the attributes of the tensors are read as any caller would read them, so it
- * depends on neither torch's headers nor its binary interface.  The library itself is loaded by bittrain.py,
- * which hands over the addresses of the calls (bind).
+ * ctypes took 5 to 6 us a call on top of the launch's 2.4.  There are two ways in here, with the same checks in the same order:
+ *   plain   all tensors are torch.Tensor or Parameter themselves, dense on a device, and no torch function mode is on: what
+ *           the checks need is read from the tensor object through torch's C++ interface (0.2 us a call);
+ *   any     else: the attributes of the tensors are read as any Python caller would read them (1.1 to 1.5 us a call), so
+ *           subclasses, wrappers and modes see what they have always seen.  Whatever is wrong with a tensor is
+ *           reported from here.
+ * The library itself is loaded by bittrain.py, which hands over the addresses of the calls (bind).
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
+
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/core/Tensor.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
 
 #include "bittrain.h"
 
@@ -31,16 +39,23 @@ static struct {
 } lib;
 
 /* Python objects handed over by bind: {dtype: code}, the function that refuses other dtypes, the error class, the
- * function that turns a stream argument into a handle, and torch's functions for the current device and its raw stream. */
-static PyObject *dtypes, *dtype_code, *error_class, *stream_handle, *get_device, *get_raw_stream;
+ * function that turns a stream argument into a handle; and whether this torch has devices. */
+static PyObject *dtypes, *dtype_code, *error_class, *stream_handle;
+static bool has_device;
 static PyObject *s_is_cuda, *s_is_contiguous, *s_dtype, *s_numel, *s_element_size, *s_data_ptr;
+
+/* A device pointer, of whatever type a call takes. */
+struct address {
+    void *p;
+    template <class T> operator T *() const { return static_cast<T *>(p); }
+};
 
 typedef struct {
     PyObject *t;        /* borrowed */
     const void *dtype;  /* which object it is, to compare: dtypes are singletons */
     int code;           /* bt_dtype, or -1 */
     uint64_t numel, width;
-    void *ptr;
+    address ptr;
 } tensor;
 
 static int is_true(PyObject *o) {      /* takes the reference; -1: an error is set */
@@ -89,11 +104,43 @@ static int describe(tensor *a) {
         to_u64(PyObject_CallMethodNoArgs(a->t, s_element_size), &a->width) != 0 ||
         to_u64(PyObject_CallMethodNoArgs(a->t, s_data_ptr), &p) != 0)
         return -1;
-    a->ptr = (void *)(uintptr_t)p;
+    a->ptr.p = (void *)(uintptr_t)p;
     return 0;
 }
 
+/* The plain way: what `describe` reads, without Python; false if there is anything about the tensor that the other way has to
+ * look at.  (The dispatch keys of an ordinary dense tensor on a device, and nothing else: no subclass, wrapper, lazy or
+ * conjugate view.) */
+static bool plain(tensor *a, PyObject *o) {
+    if (!THPVariable_CheckExact(o)) return false;
+    const at::Tensor &t = THPVariable_Unpack(o);
+    if (!t.defined()) return false;
+    static const c10::DispatchKeySet ordinary = c10::DispatchKeySet(c10::DispatchKey::CUDA) | c10::DispatchKeySet(c10::DispatchKey::AutogradCUDA) |
+                                                c10::DispatchKeySet(c10::DispatchKey::AutocastCUDA) | c10::DispatchKeySet(c10::DispatchKey::ADInplaceOrView);
+    if ((t.key_set() | ordinary) != ordinary || !t.is_cuda() || !t.is_contiguous()) return false;
+    const at::ScalarType type = t.scalar_type();
+    a->t = o;
+    a->dtype = reinterpret_cast<const void *>(static_cast<uintptr_t>(type) + 1);      /* compared among plain tensors only */
+    a->code = type == at::kFloat ? BT_F32 : type == at::kHalf ? BT_F16 : type == at::kBFloat16 ? BT_BF16 : type == at::kDouble ? BT_F64 : -1;
+    a->numel = static_cast<uint64_t>(t.numel());
+    a->width = t.element_size();
+    a->ptr.p = t.data_ptr();
+    return true;
+}
+
+static bool all_plain(tensor *a, PyObject *const *args, const int count) {
+    try {
+        if (at::impl::torch_function_mode_enabled()) return false;
+        for (int i = 0; i < count; ++i)
+            if (!plain(&a[i], args[i])) return false;
+        return true;
+    } catch (...) {
+        return false;      /* the other way reports it */
+    }
+}
+
 static int take(tensor *a, PyObject *const *args, const char *const *names, const int count) {
+    if (all_plain(a, args, count)) return 0;
     for (int i = 0; i < count; ++i)
         if (on_device(&a[i], args[i], names[i]) != 0) return -1;
     for (int i = 0; i < count; ++i)
@@ -140,17 +187,17 @@ static int check_index(const tensor *index, const tensor *x) {
 
 /* The stream argument as a handle; None: the current stream of the current device. */
 static int stream_of(PyObject *o, bt_stream *stream) {
-    PyObject *h;
-    if (o == Py_None && get_raw_stream != Py_None) {
-        PyObject *device = PyObject_CallNoArgs(get_device);
-        if (device == NULL) return -1;
-        h = PyObject_CallOneArg(get_raw_stream, device);
-        Py_DECREF(device);
-    } else {
-        h = PyObject_CallOneArg(stream_handle, o);
-    }
     uint64_t v;
-    if (to_u64(h, &v) != 0) return -1;
+    if (o == Py_None && has_device) {
+        try {
+            *stream = (bt_stream)c10::hip::getCurrentHIPStream().stream();
+            return 0;
+        } catch (const std::exception &e) {
+            PyErr_SetString(PyExc_RuntimeError, e.what());
+            return -1;
+        }
+    }
+    if (to_u64(PyObject_CallOneArg(stream_handle, o), &v) != 0) return -1;
     *stream = (bt_stream)(uintptr_t)v;
     return 0;
 }
@@ -187,7 +234,7 @@ static PyObject *py_compress(PyObject *self, PyObject *const *args, Py_ssize_t n
     bt_dtype code = BT_F32;
     bt_stream stream = NULL;
     if (expect(nargs, 6) != 0 || take(a, args, names, 5) != 0) return NULL;
-    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), NULL;
+    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), nullptr;
     if (check_bitmap(&a[1], a[0].numel) != 0 || check_nnz(&a[3]) != 0 || code_of(&a[0], &code) != 0 || stream_of(args[5], &stream) != 0)
         return NULL;
     CALL("bt_compress", lib.compress(a[0].ptr, a[0].numel, code, a[1].ptr, a[2].ptr, a[2].numel, a[3].ptr, a[4].ptr,
@@ -202,7 +249,7 @@ static PyObject *py_compress_static(PyObject *self, PyObject *const *args, Py_ss
     bt_dtype code = BT_F32;
     bt_stream stream = NULL;
     if (expect(nargs, 5) != 0 || take(a, args, names, 4) != 0) return NULL;
-    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), NULL;
+    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), nullptr;
     if (check_bitmap(&a[1], a[0].numel) != 0 || check_nnz(&a[3]) != 0 || code_of(&a[0], &code) != 0 || stream_of(args[4], &stream) != 0)
         return NULL;
     CALL("bt_compress_static", lib.compress_static(a[0].ptr, a[0].numel, code, a[1].ptr, a[2].ptr, a[2].numel, a[3].ptr, stream));
@@ -216,7 +263,7 @@ static PyObject *py_compress_pruned(PyObject *self, PyObject *const *args, Py_ss
     bt_dtype code = BT_F32;
     bt_stream stream = NULL;
     if (expect(nargs, 7) != 0 || take(a, args, names, 5) != 0) return NULL;
-    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), NULL;
+    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), nullptr;
     if (check_bitmap(&a[1], a[0].numel) != 0 || check_nnz(&a[3]) != 0 || code_of(&a[0], &code) != 0) return NULL;
     const double threshold = PyFloat_AsDouble(args[5]);
     if ((threshold == -1.0 && PyErr_Occurred()) || stream_of(args[6], &stream) != 0) return NULL;
@@ -233,7 +280,7 @@ static PyObject *py_activation_compress(PyObject *self, PyObject *const *args, P
     bt_stream stream = NULL;
     if (expect(nargs, 8) != 0 || take(a, args, names, 6) != 0) return NULL;
     if (a[3].dtype != a[0].dtype || a[1].dtype != a[0].dtype || a[1].numel != a[0].numel)
-        return fail(PyExc_TypeError, "values and dense_out must match x"), NULL;
+        return fail(PyExc_TypeError, "values and dense_out must match x"), nullptr;
     if (check_bitmap(&a[2], a[0].numel) != 0 || check_nnz(&a[4]) != 0 || code_of(&a[0], &code) != 0) return NULL;
     const double threshold = PyFloat_AsDouble(args[6]);
     if ((threshold == -1.0 && PyErr_Occurred()) || stream_of(args[7], &stream) != 0) return NULL;
@@ -249,7 +296,7 @@ static PyObject *py_compress_indexed(PyObject *self, PyObject *const *args, Py_s
     bt_dtype code = BT_F32;
     bt_stream stream = NULL;
     if (expect(nargs, 7) != 0 || take(a, args, names, 6) != 0) return NULL;
-    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), NULL;
+    if (a[2].dtype != a[0].dtype) return fail(PyExc_TypeError, "values must have the dtype of x"), nullptr;
     if (check_bitmap(&a[1], a[0].numel) != 0 || check_nnz(&a[3]) != 0 || check_index(&a[4], &a[0]) != 0 ||
         code_of(&a[0], &code) != 0 || stream_of(args[6], &stream) != 0)
         return NULL;
@@ -265,7 +312,7 @@ static PyObject *py_decompress(PyObject *self, PyObject *const *args, Py_ssize_t
     bt_dtype code = BT_F32;
     bt_stream stream = NULL;
     if (expect(nargs, 5) != 0 || take(a, args, names, 4) != 0) return NULL;
-    if (a[1].dtype != a[2].dtype) return fail(PyExc_TypeError, "values must have the dtype of out"), NULL;
+    if (a[1].dtype != a[2].dtype) return fail(PyExc_TypeError, "values must have the dtype of out"), nullptr;
     if (check_bitmap(&a[0], a[2].numel) != 0 || code_of(&a[2], &code) != 0 || stream_of(args[4], &stream) != 0) return NULL;
     CALL("bt_decompress", lib.decompress(a[0].ptr, a[1].ptr, a[2].numel, code, a[2].ptr, a[3].ptr, a[3].numel * a[3].width, stream));
 }
@@ -278,7 +325,7 @@ static PyObject *py_decompress_indexed(PyObject *self, PyObject *const *args, Py
     bt_dtype code = BT_F32;
     bt_stream stream = NULL;
     if (expect(nargs, 5) != 0 || take(a, args, names, 4) != 0) return NULL;
-    if (a[1].dtype != a[3].dtype) return fail(PyExc_TypeError, "values must have the dtype of out"), NULL;
+    if (a[1].dtype != a[3].dtype) return fail(PyExc_TypeError, "values must have the dtype of out"), nullptr;
     if (check_bitmap(&a[0], a[3].numel) != 0 || check_index(&a[2], &a[3]) != 0 || code_of(&a[3], &code) != 0 ||
         stream_of(args[4], &stream) != 0)
         return NULL;
@@ -293,7 +340,7 @@ static PyObject *py_relu_backward(PyObject *self, PyObject *const *args, Py_ssiz
     bt_dtype code = BT_F32;
     bt_stream stream = NULL;
     if (expect(nargs, 4) != 0 || take(a, args, names, 3) != 0) return NULL;
-    if (a[2].dtype != a[1].dtype || a[2].numel != a[1].numel) return fail(PyExc_TypeError, "grad_in must match grad_out"), NULL;
+    if (a[2].dtype != a[1].dtype || a[2].numel != a[1].numel) return fail(PyExc_TypeError, "grad_in must match grad_out"), nullptr;
     if (check_bitmap(&a[0], a[1].numel) != 0 || code_of(&a[1], &code) != 0 || stream_of(args[3], &stream) != 0) return NULL;
     CALL("bt_relu_backward_from_bitmap", lib.relu_backward(a[0].ptr, a[1].ptr, a[1].numel, code, a[2].ptr, stream));
 }
@@ -306,7 +353,7 @@ static PyObject *py_mask_apply(PyObject *self, PyObject *const *args, Py_ssize_t
     bt_dtype code = BT_F32;
     bt_stream stream = NULL;
     if (expect(nargs, 4) != 0 || take(a, args, names, 3) != 0) return NULL;
-    if (a[2].dtype != a[1].dtype || a[2].numel != a[1].numel) return fail(PyExc_TypeError, "out must match x"), NULL;
+    if (a[2].dtype != a[1].dtype || a[2].numel != a[1].numel) return fail(PyExc_TypeError, "out must match x"), nullptr;
     if (check_bitmap(&a[0], a[1].numel) != 0 || code_of(&a[1], &code) != 0 || stream_of(args[3], &stream) != 0) return NULL;
     CALL("bt_mask_apply", lib.mask_apply(a[0].ptr, a[1].ptr, a[1].numel, code, a[2].ptr, stream));
 }
@@ -314,22 +361,24 @@ static PyObject *py_mask_apply(PyObject *self, PyObject *const *args, Py_ssize_t
 /* (addresses of the calls in the order of `lib`, the objects above in their order) */
 static PyObject *py_bind(PyObject *self, PyObject *args) {
     (void)self;
-    PyObject *addresses, *o[6];
-    if (!PyArg_ParseTuple(args, "O!O!OOOOO", &PyTuple_Type, &addresses, &PyDict_Type, &o[0], &o[1], &o[2], &o[3], &o[4], &o[5])) return NULL;
+    PyObject *addresses, *o[4];
+    int devices;
+    if (!PyArg_ParseTuple(args, "O!O!OOOp", &PyTuple_Type, &addresses, &PyDict_Type, &o[0], &o[1], &o[2], &o[3], &devices)) return NULL;
     void **const slots = (void **)(void *)&lib;
     enum { kSlots = sizeof(lib) / sizeof(void *) };
     uint64_t at[kSlots];
-    if (PyTuple_GET_SIZE(addresses) != kSlots) return fail(PyExc_TypeError, "one address per call"), NULL;
+    if (PyTuple_GET_SIZE(addresses) != kSlots) return fail(PyExc_TypeError, "one address per call"), nullptr;
     for (int i = 0; i < kSlots; ++i) {
         at[i] = PyLong_AsUnsignedLongLong(PyTuple_GET_ITEM(addresses, i));
         if (at[i] == (uint64_t)-1 && PyErr_Occurred()) return NULL;
     }
     for (int i = 0; i < kSlots; ++i) slots[i] = (void *)(uintptr_t)at[i];
-    PyObject **const keep[6] = {&dtypes, &dtype_code, &error_class, &stream_handle, &get_device, &get_raw_stream};
-    for (int i = 0; i < 6; ++i) {
+    PyObject **const keep[4] = {&dtypes, &dtype_code, &error_class, &stream_handle};
+    for (int i = 0; i < 4; ++i) {
         Py_INCREF(o[i]);
         Py_XSETREF(*keep[i], o[i]);
     }
+    has_device = devices != 0;
     Py_RETURN_NONE;
 }
 

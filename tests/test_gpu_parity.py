@@ -782,3 +782,59 @@ def test_relu_backward_around_the_largest_gradient_read_through_the_caches(gpu, 
         bt.bt_relu_backward_from_bitmap(words, grad[:n].view(dtype), out[:n].view(dtype))
         assert torch.equal(out[:n], torch.where(keep[:n], grad[:n], 0)), n
         assert bool((out[n:] == 0x5A).all()), n
+
+
+def test_binding_sees_the_same_in_every_kind_of_tensor(gpu, oracle):
+    """Ordinary tensors and parameters are read through the tensor object, everything else through Python: the same results on
+    the same stream, the same refusals, and a function mode still sees what is asked of the tensors."""
+    from torch.overrides import TorchFunctionMode
+
+    from paper_2110_15362_amd import bittrain as bt
+
+    class Sub(torch.Tensor):
+        pass
+
+    class Mode(TorchFunctionMode):
+        def __init__(self):
+            super().__init__()
+            self.seen = 0
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.seen += 1
+            return func(*args, **(kwargs or {}))
+    n = 70001
+    x = wl.random_sparse(n, "f32", 0.5, 77).cuda()
+    o_bitmap, o_values, o_nnz = oracle.compress(wl.bits(x.cpu()))
+    bitmap = torch.empty((n + 31) // 32, dtype=torch.int32, device="cuda")
+    values, out = torch.empty_like(x), torch.empty_like(x)
+    nnz = torch.zeros(1, dtype=torch.int64, device="cuda")
+    ws = bt.new_workspace(n, x.dtype)
+    side, mode = torch.cuda.Stream(), Mode()
+
+    def both(t, o, stream=None):
+        bitmap.zero_(), values.zero_(), out.zero_(), nnz.zero_()
+        torch.cuda.synchronize()
+        bt.bt_compress(t, bitmap, values, nnz, ws, stream=stream)
+        bt.bt_decompress(bitmap, values, o, ws, stream=stream)
+        torch.cuda.synchronize()
+        assert int(nnz.item()) == o_nnz and np.array_equal(bitmap.cpu().numpy().view(np.uint32), o_bitmap)
+        assert np.array_equal(wl.bits(values.cpu())[:o_nnz], o_values) and torch.equal(out, x)
+    both(x, out)
+    both(torch.nn.Parameter(x), out)
+    both(x.as_subclass(Sub), out.as_subclass(Sub))
+    both(x, out, side)
+    with torch.cuda.stream(side):
+        both(x, out)
+    with torch.inference_mode():
+        both(x.clone(), out)
+    with mode:
+        bt.bt_relu_backward_from_bitmap(bitmap, x, out)
+    assert mode.seen >= 18      # six looks at each of three tensors
+    for kind in (lambda t: t, lambda t: t.as_subclass(Sub)):
+        for bad, error in ((x[::2], "contiguous"), (x.cpu(), "device memory"), (x.half(), "dtype"), (x.to(torch.int32), "dtype")):
+            with pytest.raises((ValueError, TypeError), match=error):
+                bt.bt_decompress(bitmap, values, kind(bad), ws)
+        with pytest.raises(TypeError, match="not torch.int32"):
+            bt.bt_compress(kind(x.to(torch.int32)), bitmap, kind(values.to(torch.int32)), nnz, ws)
+    with pytest.raises(RuntimeError):      # a batched tensor has no address
+        torch.func.vmap(lambda t: (bt.bt_relu_backward_from_bitmap(bitmap, t, t), t)[1])(x.reshape(1, -1))
