@@ -63,7 +63,7 @@ bt_status bt_stream_probe(const void *d_in, void *d_out, uint64_t tiles, int rea
     else if (read_rows == 8 && write_rows == 0) stream_probe_kernel<8, 0><<<grid, block, 0, hs>>>(in, out, t);
     else if (read_rows == 0 && write_rows == 8) stream_probe_kernel<0, 8><<<grid, block, 0, hs>>>(in, out, t);
     else return BT_ERR_SIZE;
-    return launched();
+    return hipGetLastError() == hipSuccess ? BT_OK : BT_ERR_HIP;
 }
 
 bt_status bt_timeline_set(uint64_t *d_buf, uint64_t buf_words, uint32_t tiles, uint32_t max_passes) {

@@ -2017,7 +2017,16 @@ uint64_t relu_blocks_for(uint64_t n, int s) {
 
 bool misaligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
 
-bt_status launched() { return hipGetLastError() == hipSuccess ? BT_OK : BT_ERR_HIP; }
+// A launch is most of what a small call costs.  hipLaunchKernel itself, whose status is this launch's own: the triple brackets
+// go through it too, after putting the configuration aside and taking it up again, and then need hipGetLastError to learn how it
+// went (measured 2.45 us a launch, now 2.2).
+template <class... P>
+bt_status launch(void (*kernel)(P...), uint64_t grid, int block, hipStream_t hs, const std::common_type_t<P> &...args) {
+    void *where[] = {const_cast<void *>(static_cast<const void *>(&args))...};
+    if (hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)grid), dim3((unsigned)block), where, 0, hs) == hipSuccess) return BT_OK;
+    (void)hipGetLastError();
+    return BT_ERR_HIP;
+}
 
 constexpr int kMaxDevices = 64;          // devices the static workspace keeps an address for
 
@@ -2085,63 +2094,46 @@ bt_status check_batch_common(const void *items, size_t count, bt_dtype dt, const
 template <int R, bool DIRECT, class Job>
 bt_status launch_compress(const Job &job, uint64_t slots, bt_dtype dtype, bool prune, bool dense, double threshold,
                           char *ws, hipStream_t hs) {
-    const dim3 block(kBlock);
-    const unsigned grid = (unsigned)slots + (DIRECT ? 0u : 1u);      // with or without a scanner
+    const uint64_t grid = slots + (DIRECT ? 0u : 1u);      // with or without a scanner
     // Elements narrower than a double are compared in single precision.  For a single x, x > threshold exactly when
     // x > the largest single at or below the threshold, so that is what the kernel gets (a NaN stays one: nothing
     // exceeds it).
     float threshold_f = (float)threshold;
     if ((double)threshold_f > threshold) threshold_f = std::nextafterf(threshold_f, -INFINITY);
-#define BT_LAUNCH_COMPRESS(S_, KEEP_, DENSE_)                                                   \
-    do {                                                                                        \
-        auto kernel = compress_kernel<S_, R, DIRECT, KEEP_, DENSE_, Job>;                       \
-        kernel<<<dim3(grid), block, 0, hs>>>(job, ws, threshold, threshold_f);                     \
-    } while (0)
+    const auto go = [&](auto kernel) { return launch(kernel, grid, kBlock, hs, job, ws, threshold, threshold_f); };
     const int s = elem_size(dtype);
     if (!prune) {
-        if (s == 8) BT_LAUNCH_COMPRESS(8, kKeepNonZero, false);
-        else if (s == 4) BT_LAUNCH_COMPRESS(4, kKeepNonZero, false);
-        else BT_LAUNCH_COMPRESS(2, kKeepNonZero, false);
-    } else if (!dense) {
-        if (dtype == BT_F64) BT_LAUNCH_COMPRESS(8, kKeepAboveF64, false);
-        else if (dtype == BT_F32) BT_LAUNCH_COMPRESS(4, kKeepAboveF32, false);
-        else if (dtype == BT_F16) BT_LAUNCH_COMPRESS(2, kKeepAboveF16, false);
-        else BT_LAUNCH_COMPRESS(2, kKeepAboveBF16, false);
-    } else {
-        if (dtype == BT_F64) BT_LAUNCH_COMPRESS(8, kKeepAboveF64, true);
-        else if (dtype == BT_F32) BT_LAUNCH_COMPRESS(4, kKeepAboveF32, true);
-        else if (dtype == BT_F16) BT_LAUNCH_COMPRESS(2, kKeepAboveF16, true);
-        else BT_LAUNCH_COMPRESS(2, kKeepAboveBF16, true);
+        if (s == 8) return go(compress_kernel<8, R, DIRECT, kKeepNonZero, false, Job>);
+        if (s == 4) return go(compress_kernel<4, R, DIRECT, kKeepNonZero, false, Job>);
+        return go(compress_kernel<2, R, DIRECT, kKeepNonZero, false, Job>);
     }
-#undef BT_LAUNCH_COMPRESS
-    return launched();
+    if (!dense) {
+        if (dtype == BT_F64) return go(compress_kernel<8, R, DIRECT, kKeepAboveF64, false, Job>);
+        if (dtype == BT_F32) return go(compress_kernel<4, R, DIRECT, kKeepAboveF32, false, Job>);
+        if (dtype == BT_F16) return go(compress_kernel<2, R, DIRECT, kKeepAboveF16, false, Job>);
+        return go(compress_kernel<2, R, DIRECT, kKeepAboveBF16, false, Job>);
+    }
+    if (dtype == BT_F64) return go(compress_kernel<8, R, DIRECT, kKeepAboveF64, true, Job>);
+    if (dtype == BT_F32) return go(compress_kernel<4, R, DIRECT, kKeepAboveF32, true, Job>);
+    if (dtype == BT_F16) return go(compress_kernel<2, R, DIRECT, kKeepAboveF16, true, Job>);
+    return go(compress_kernel<2, R, DIRECT, kKeepAboveBF16, true, Job>);
 }
 
 template <class Job> bt_status launch_decompress(const Job &job, uint64_t slots, int s, char *ws, hipStream_t hs) {
-    const dim3 grid((unsigned)slots + 1u), block(kBlock);      // and the scanner
-    if (s == 8) decompress_kernel<8, Job><<<grid, block, 0, hs>>>(job, ws);
-    else if (s == 4) decompress_kernel<4, Job><<<grid, block, 0, hs>>>(job, ws);
-    else decompress_kernel<2, Job><<<grid, block, 0, hs>>>(job, ws);
-    return launched();
+    const auto go = [&](auto kernel) { return launch(kernel, slots + 1, kBlock, hs, job, ws); };      // and the scanner
+    return s == 8 ? go(decompress_kernel<8, Job>) : s == 4 ? go(decompress_kernel<4, Job>) : go(decompress_kernel<2, Job>);
 }
 
 template <int R> bt_status launch_decompress_small(const DecompressOne &job, uint64_t tiles, int s, char *ws, hipStream_t hs) {
-    const dim3 grid((unsigned)tiles), block(kBlock);
-    if (s == 8) decompress_small_kernel<8, R><<<grid, block, 0, hs>>>(job, ws);
-    else if (s == 4) decompress_small_kernel<4, R><<<grid, block, 0, hs>>>(job, ws);
-    else decompress_small_kernel<2, R><<<grid, block, 0, hs>>>(job, ws);
-    return launched();
+    const auto go = [&](auto kernel) { return launch(kernel, tiles, kBlock, hs, job, ws); };
+    return s == 8 ? go(decompress_small_kernel<8, R>) : s == 4 ? go(decompress_small_kernel<4, R>) : go(decompress_small_kernel<2, R>);
 }
 
-template <class Job>
-bt_status launch_decompress_indexed(const Job &job, uint64_t slots, int s, hipStream_t hs) {
+template <class Job> bt_status launch_decompress_indexed(const Job &job, uint64_t slots, int s, hipStream_t hs) {
     constexpr uint64_t kMost = 1u << 22;      // slots a launch: a grid holds less than 2^32 threads
     for (uint64_t first = 0; first < slots; first += kMost) {
-        const dim3 grid((unsigned)(2 * (slots - first < kMost ? slots - first : kMost))), block(kBlock);
-        if (s == 8) decompress_indexed_kernel<8, Job><<<grid, block, 0, hs>>>(job, (uint32_t)first);
-        else if (s == 4) decompress_indexed_kernel<4, Job><<<grid, block, 0, hs>>>(job, (uint32_t)first);
-        else decompress_indexed_kernel<2, Job><<<grid, block, 0, hs>>>(job, (uint32_t)first);
-        const bt_status st = launched();
+        const auto go = [&](auto kernel) { return launch(kernel, 2 * (slots - first < kMost ? slots - first : kMost), kBlock, hs, job, (uint32_t)first); };
+        const bt_status st = s == 8 ? go(decompress_indexed_kernel<8, Job>) : s == 4 ? go(decompress_indexed_kernel<4, Job>) : go(decompress_indexed_kernel<2, Job>);
         if (st != BT_OK) return st;
     }
     return BT_OK;
@@ -2223,9 +2215,7 @@ bt_status bt_workspace_init(void *d_workspace, size_t workspace_bytes, bt_stream
     if (misaligned(d_workspace, 128)) return BT_ERR_ALIGN;
     const uint64_t count = workspace_bytes / 8;
     if (count == 0) return BT_OK;
-    const unsigned blocks = (unsigned)((count + 255) / 256);
-    fill_u64_kernel<<<dim3(blocks), dim3(256), 0, (hipStream_t)stream>>>((uint64_t *)d_workspace, count, 0);
-    return launched();
+    return launch(fill_u64_kernel, (count + 255) / 256, 256, (hipStream_t)stream, (uint64_t *)d_workspace, count, (uint64_t)0);
 }
 
 static bt_status compress_common(const void *d_in, uint64_t n, bt_dtype dtype, bool prune, double threshold,
@@ -2239,15 +2229,14 @@ static bt_status compress_common(const void *d_in, uint64_t n, bt_dtype dtype, b
     const int s = elem_size(dtype);
     hipStream_t hs = (hipStream_t)stream;
     if (n == 0) {
-        fill_u64_kernel<<<dim3(1), dim3(64), 0, hs>>>(d_nnz, 1, 0);
-        return launched();
+        return launch(fill_u64_kernel, 1, 64, hs, d_nnz, (uint64_t)1, (uint64_t)0);
     }
     if (d_in == nullptr || d_bitmap == nullptr) return BT_ERR_NULL;
     if (d_values == nullptr && values_cap != 0) return BT_ERR_NULL;
     if (misaligned(d_in, 16) || misaligned(d_bitmap, 4) || misaligned(d_values, (size_t)s)) return BT_ERR_ALIGN;
 
     char *const ws = static_cast<char *>(d_workspace);
-    const auto launch = [&](auto rows, auto direct) {
+    const auto go = [&](auto rows, auto direct) {
         constexpr int R = decltype(rows)::value;
         const uint32_t n_tiles = (uint32_t)tiles_for(n, s, R);
         const CompressOne job{d_in, n, d_bitmap, d_values, values_cap, d_nnz, d_index, d_dense, n_tiles};
@@ -2262,10 +2251,10 @@ static bt_status compress_common(const void *d_in, uint64_t n, bt_dtype dtype, b
     // with the scanner 7.2, without it but in tiles of eight rows 7.3 (by the workspace's place up to 7.6), of two rows 4.8; 800 k,
     // 5 % zeros, 8.7 / 9.2 / 6.3 (four rows); fp32 201 k 6.9 / 6.6 / 4.8.
     using std::integral_constant;
-    if (tiles_for(n, s, 2) <= 64) return launch(integral_constant<int, 2>{}, std::true_type{});
-    if (tiles_for(n, s, 4) <= kDirectSlots) return launch(integral_constant<int, 4>{}, std::true_type{});
-    if (tiles_for(n, s) <= kDirectSlots) return launch(integral_constant<int, kRows>{}, std::true_type{});
-    return launch(integral_constant<int, kRows>{}, std::false_type{});
+    if (tiles_for(n, s, 2) <= 64) return go(integral_constant<int, 2>{}, std::true_type{});
+    if (tiles_for(n, s, 4) <= kDirectSlots) return go(integral_constant<int, 4>{}, std::true_type{});
+    if (tiles_for(n, s) <= kDirectSlots) return go(integral_constant<int, kRows>{}, std::true_type{});
+    return go(integral_constant<int, kRows>{}, std::false_type{});
 }
 
 bt_status bt_compress(const void *d_in, uint64_t n, bt_dtype dtype, uint32_t *d_bitmap, void *d_values,
@@ -2286,9 +2275,7 @@ bt_status bt_compress_static(const void *d_in, uint64_t n, bt_dtype dtype, uint3
     // The array keeps what the last call left, possibly a call that gave up a wait: start from a clean workspace
     // every time (a fill kernel rather than a memset, which callers that record the stream could not replay).
     const uint64_t words = kStaticBytes / 8;
-    fill_u64_kernel<<<dim3((unsigned)((words + 255) / 256)), dim3(256), 0, (hipStream_t)stream>>>(
-        reinterpret_cast<uint64_t *>(ws), words, 0);
-    const bt_status fs = launched();
+    const bt_status fs = launch(fill_u64_kernel, (words + 255) / 256, 256, (hipStream_t)stream, reinterpret_cast<uint64_t *>(ws), words, (uint64_t)0);
     if (fs != BT_OK) return fs;
     return compress_common(d_in, n, dtype, false, 0.0, d_bitmap, d_values, values_cap, d_nnz, nullptr, nullptr, ws,
                            kStaticBytes, stream);
@@ -2385,13 +2372,10 @@ bt_status bt_relu_backward_from_bitmap(const uint32_t *d_bitmap, const void *d_g
     // 5.3 / 4.3, 25.7 M 18.6 / 16.1, 60 M 39.5 / 41.1.  With eight sets, which push each other out of it: fp32 5.5 M 9.4 / 7.9, 9 M 13.9 /
     // 13.5, 16 M 22.5 / 23.0, 25.7 M 34.4 / 35.2.  In a step (compress, restore, this) fp32 5.5 M 32.4 / 30.7, 12 M 51.3 / 49.7, bf16 32.2 M 66.4 / 68.4.
     const bool cached = n * (uint64_t)s <= kReluCachedBytes;
-    const auto launch = [&](auto kernel) {
-        kernel<<<dim3((unsigned)relu_blocks_for(n, s)), dim3(kBlock), 0, hs>>>(d_bitmap, d_grad_out, n, d_grad_in);
-    };
-    if (s == 8) launch(cached ? relu_backward_kernel<8, false> : relu_backward_kernel<8, true>);
-    else if (s == 4) launch(cached ? relu_backward_kernel<4, false> : relu_backward_kernel<4, true>);
-    else launch(cached ? relu_backward_kernel<2, false> : relu_backward_kernel<2, true>);
-    return launched();
+    const auto go = [&](auto kernel) { return launch(kernel, relu_blocks_for(n, s), kBlock, hs, d_bitmap, d_grad_out, n, d_grad_in); };
+    if (s == 8) return go(cached ? relu_backward_kernel<8, false> : relu_backward_kernel<8, true>);
+    if (s == 4) return go(cached ? relu_backward_kernel<4, false> : relu_backward_kernel<4, true>);
+    return go(cached ? relu_backward_kernel<2, false> : relu_backward_kernel<2, true>);
 }
 
 bt_status bt_mask_apply(const uint32_t *d_bitmap, const void *d_in, uint64_t n, bt_dtype dtype, void *d_out,
@@ -2544,8 +2528,7 @@ bt_status bt_decompress_batch_indexed(const bt_decompress_item *items, size_t co
 bt_status bt_workspace_status(const void *d_workspace, uint32_t *d_status, bt_stream stream) {
     if (d_workspace == nullptr || d_status == nullptr) return BT_ERR_NULL;
     if (misaligned(d_workspace, 128) || misaligned(d_status, 4)) return BT_ERR_ALIGN;
-    copy_status_kernel<<<dim3(1), dim3(64), 0, (hipStream_t)stream>>>(static_cast<const uint32_t *>(d_workspace), d_status);
-    return launched();
+    return launch(copy_status_kernel, 1, 64, (hipStream_t)stream, static_cast<const uint32_t *>(d_workspace), d_status);
 }
 
 }  // extern "C"
