@@ -276,6 +276,15 @@ bt_status bt_relu_backward_from_bitmap(const uint32_t *d_bitmap, const void *d_g
                                        uint64_t n, bt_dtype dtype, void *d_grad_in,
                                        bt_stream stream);
 
+/* The forward pass that the backward above belongs to, where nothing but the bitmap is kept: y = ReLU(x) and the
+ * bitmap of y from one read of x, no values, no nnz, no workspace:
+ *   out[i] = x[i] where x[i] > 0 or x[i] is a NaN (bit pattern kept), else +0;  bit(i) = out[i] != 0.
+ *   d_in, d_out   n elements each, 16-byte aligned; they may be the same buffer but must not partly overlap.
+ *   d_bitmap      ceil(n/32) words, bits at or beyond n are written as 0.
+ * Errors: as bt_relu_backward_from_bitmap. */
+bt_status bt_relu_forward(const void *d_in, uint64_t n, bt_dtype dtype, void *d_out, uint32_t *d_bitmap,
+                          bt_stream stream);
+
 /* Double-mask batch normalisation (Section 3.1, "Exploiting Sparsity"): the sparsity
  * pattern of a normalisation layer's input is applied to its output, so that the
  * output compresses as well as the input did.  d_bitmap is the bitmap of that input

@@ -29,7 +29,7 @@ _lib = None
 _call = None      # the single-tensor calls, checked and marshalled in C++; bound to the library that lib() has loaded
 # the library's functions behind it, in the order of the table in csrc/call.cpp
 _CALLS = ("bt_compress", "bt_compress_static", "bt_compress_pruned", "bt_activation_compress", "bt_compress_indexed",
-          "bt_decompress", "bt_decompress_indexed", "bt_relu_backward_from_bitmap", "bt_mask_apply", "bt_index_bytes")
+          "bt_decompress", "bt_decompress_indexed", "bt_relu_backward_from_bitmap", "bt_mask_apply", "bt_relu_forward", "bt_index_bytes")
 
 
 class BitTrainError(RuntimeError):
@@ -82,6 +82,8 @@ def lib():
         L.bt_coo_size.restype, L.bt_coo_size.argtypes = sz, [u64, ctypes.c_uint32, ctypes.c_uint32, ci]
         L.bt_mask_apply.restype = ci
         L.bt_mask_apply.argtypes = [vp, vp, u64, ci, vp, vp]
+        L.bt_relu_forward.restype = ci
+        L.bt_relu_forward.argtypes = [vp, u64, ci, vp, vp, vp]
         L.bt_tile_elems.restype, L.bt_tile_elems.argtypes = sz, [ci]
         L.bt_index_bytes.restype, L.bt_index_bytes.argtypes = sz, [u64, ci]
         L.bt_compress_indexed.restype = ci
@@ -342,6 +344,13 @@ def bt_mask_apply(bitmap, x, out, stream=None):
     if _lib is None:
         lib()
     _call.mask_apply(bitmap, x, out, stream)
+
+
+def bt_relu_forward(x, out, bitmap, stream=None):
+    """out = ReLU(x) (a NaN stays one) and the bitmap of out, one pass; out may be x itself."""
+    if _lib is None:
+        lib()
+    _call.relu_forward(x, out, bitmap, stream)
 
 
 def bt_tile_elems(dtype):

@@ -1982,6 +1982,62 @@ __global__ __launch_bounds__(kBlock) void relu_backward_kernel(const uint32_t *_
     }
 }
 
+// ---- ReLU and its bitmap ---------------------------------------------------------------------
+
+// Which elements of the 16-byte vector ReLU keeps: the positive ones and NaNs, told from the bit pattern (as a signed number
+// above 0, or as an unsigned one above that of minus infinity).
+template <int S, int KEEP> __device__ __forceinline__ uint32_t relu_mask(const uint4 v) {
+    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+    uint32_t m = 0;
+    if (S == 8) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint64_t b = ((uint64_t)d[2 * i + 1] << 32) | d[2 * i];
+            m |= ((int64_t)b > 0 || b > 0xfff0000000000000ull ? 1u : 0u) << i;
+        }
+    } else if (S == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m |= ((int32_t)d[i] > 0 || d[i] > 0xff800000u ? 1u : 0u) << i;
+    } else {
+        constexpr uint32_t kMinusInf = KEEP == kKeepAboveBF16 ? 0xff80u : 0xfc00u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t lo = d[i] & 0xffffu, hi = d[i] >> 16;
+            m |= ((int16_t)lo > 0 || lo > kMinusInf ? 1u : 0u) << (2 * i);
+            m |= ((int16_t)hi > 0 || hi > kMinusInf ? 1u : 0u) << (2 * i + 1);
+        }
+    }
+    return m;
+}
+
+// out = ReLU(in), bit i of the bitmap set where out[i] is stored by Algorithm 1.  A stream like relu_backward_kernel, a vector a
+// lane and 4 KiB a workgroup; G lanes make a bitmap word.  Bound by memory: fp32 8.4 M elements in 11.0 us, where torch.relu and a
+// compression without values (which reads that output again and scans it) took 10.9 + 9.9.
+template <int S, int KEEP, bool NT>
+__global__ __launch_bounds__(kBlock) void relu_forward_kernel(const void *in, const uint64_t n, void *out, uint32_t *__restrict__ bitmap) {
+    using G = Geo<S>;
+    constexpr int E = G::E;
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const uint64_t block_e0 = (uint64_t)blockIdx.x * (kBlock * E), e0 = block_e0 + (uint64_t)threadIdx.x * E;
+    const bool full = block_e0 + kBlock * E <= n;
+    uint4 v;
+    if (full) v = stream_load<NT>(reinterpret_cast<const uint4 *>(static_cast<const char *>(in) + e0 * S));
+    else v = load_vec_guarded<S>(in, e0, n);      // (0 beyond n: not kept)
+    const uint32_t mk = relu_mask<S, KEEP>(v);
+    uint32_t d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (S == 8) d[j] &= 0u - ((mk >> (j >> 1)) & 1u);
+        else if (S == 4) d[j] &= 0u - ((mk >> j) & 1u);
+        else d[j] &= (((mk >> (2 * j)) & 1u) * 0x0000ffffu) | (((mk >> (2 * j + 1)) & 1u) * 0xffff0000u);
+    }
+    const uint4 o = make_uint4(d[0], d[1], d[2], d[3]);
+    if (full) stream_store<kReluNtStore>(reinterpret_cast<uint4 *>(static_cast<char *>(out) + e0 * S), o);
+    else store_vec_guarded<S>(out, e0, n, o);
+    const uint32_t word = group_or<G::G>(mk << (uint32_t)(E * (lane % G::G)));
+    if (lane % G::G == 0 && e0 < n) bitmap[e0 >> 5] = word;
+}
+
 // ---- small fills ---------------------------------------------------------------------------
 
 __global__ void fill_u64_kernel(uint64_t *p, uint64_t count, uint64_t value) {
@@ -2384,6 +2440,23 @@ bt_status bt_relu_backward_from_bitmap(const uint32_t *d_bitmap, const void *d_g
     if (s == 8) return go(cached ? relu_backward_kernel<8, false> : relu_backward_kernel<8, true>);
     if (s == 4) return go(cached ? relu_backward_kernel<4, false> : relu_backward_kernel<4, true>);
     return go(cached ? relu_backward_kernel<2, false> : relu_backward_kernel<2, true>);
+}
+
+bt_status bt_relu_forward(const void *d_in, uint64_t n, bt_dtype dtype, void *d_out, uint32_t *d_bitmap, bt_stream stream) {
+    const int s = elem_size(dtype);
+    if (s == 0) return BT_ERR_DTYPE;
+    if (n > BT_MAX_ELEMENTS) return BT_ERR_SIZE;
+    if (n == 0) return BT_OK;
+    if (d_in == nullptr || d_out == nullptr || d_bitmap == nullptr) return BT_ERR_NULL;
+    if (misaligned(d_in, 16) || misaligned(d_out, 16) || misaligned(d_bitmap, 4)) return BT_ERR_ALIGN;
+    hipStream_t hs = (hipStream_t)stream;
+    const uint64_t per_block = (uint64_t)kBlock * (kVecBytes / s);
+    const bool cached = n * (uint64_t)s <= kReluCachedBytes;      // written just before, like a gradient
+    const auto go = [&](auto kernel) { return launch(kernel, (n + per_block - 1) / per_block, kBlock, hs, d_in, n, d_out, d_bitmap); };
+    if (dtype == BT_F64) return go(cached ? relu_forward_kernel<8, kKeepAboveF64, false> : relu_forward_kernel<8, kKeepAboveF64, true>);
+    if (dtype == BT_F32) return go(cached ? relu_forward_kernel<4, kKeepAboveF32, false> : relu_forward_kernel<4, kKeepAboveF32, true>);
+    if (dtype == BT_F16) return go(cached ? relu_forward_kernel<2, kKeepAboveF16, false> : relu_forward_kernel<2, kKeepAboveF16, true>);
+    return go(cached ? relu_forward_kernel<2, kKeepAboveBF16, false> : relu_forward_kernel<2, kKeepAboveBF16, true>);
 }
 
 bt_status bt_mask_apply(const uint32_t *d_bitmap, const void *d_in, uint64_t n, bt_dtype dtype, void *d_out,

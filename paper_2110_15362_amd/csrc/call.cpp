@@ -35,6 +35,7 @@ static struct {
     bt_status (*decompress_indexed)(const uint32_t *, const void *, uint64_t, const uint64_t *, uint64_t, bt_dtype, void *, bt_stream);
     bt_status (*relu_backward)(const uint32_t *, const void *, uint64_t, bt_dtype, void *, bt_stream);
     bt_status (*mask_apply)(const uint32_t *, const void *, uint64_t, bt_dtype, void *, bt_stream);
+    bt_status (*relu_forward)(const void *, uint64_t, bt_dtype, void *, uint32_t *, bt_stream);
     size_t (*index_bytes)(uint64_t, bt_dtype);
 } lib;
 
@@ -358,6 +359,19 @@ static PyObject *py_mask_apply(PyObject *self, PyObject *const *args, Py_ssize_t
     CALL("bt_mask_apply", lib.mask_apply(a[0].ptr, a[1].ptr, a[1].numel, code, a[2].ptr, stream));
 }
 
+/* (x, out, bitmap, stream) */
+static PyObject *py_relu_forward(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    (void)self;
+    static const char *const names[] = {"x", "out", "bitmap"};
+    tensor a[3];
+    bt_dtype code = BT_F32;
+    bt_stream stream = NULL;
+    if (expect(nargs, 4) != 0 || take(a, args, names, 3) != 0) return NULL;
+    if (a[1].dtype != a[0].dtype || a[1].numel != a[0].numel) return fail(PyExc_TypeError, "out must match x"), nullptr;
+    if (check_bitmap(&a[2], a[0].numel) != 0 || code_of(&a[0], &code) != 0 || stream_of(args[3], &stream) != 0) return NULL;
+    CALL("bt_relu_forward", lib.relu_forward(a[0].ptr, a[0].numel, code, a[1].ptr, a[2].ptr, stream));
+}
+
 /* (addresses of the calls in the order of `lib`, the objects above in their order) */
 static PyObject *py_bind(PyObject *self, PyObject *args) {
     (void)self;
@@ -385,7 +399,7 @@ static PyObject *py_bind(PyObject *self, PyObject *args) {
 #define FAST(name) {#name, (PyCFunction)(void (*)(void))py_##name, METH_FASTCALL, NULL}
 static PyMethodDef methods[] = {
     FAST(compress), FAST(compress_static), FAST(compress_pruned), FAST(activation_compress), FAST(compress_indexed),
-    FAST(decompress), FAST(decompress_indexed), FAST(relu_backward), FAST(mask_apply),
+    FAST(decompress), FAST(decompress_indexed), FAST(relu_backward), FAST(mask_apply), FAST(relu_forward),
     {"bind", py_bind, METH_VARARGS, NULL}, {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", NULL, -1, methods, NULL, NULL, NULL, NULL};
 

@@ -108,3 +108,79 @@ def test_deferred_stash_gives_the_same_gradients_without_waiting_for_the_device(
     assert stats["stored_bytes"] < 0.75 * stats["dense_bytes"]        # (the dense input and the weights pass through too)
     for a, b in zip(grads_on, grads_off):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16, torch.float16, torch.float64])
+def test_relu_forward_is_torch_relu_with_its_bitmap(ag, dt):
+    """Every 16-bit pattern, and for wider elements the borders between kinds of numbers and random bits: torch's ReLU bit by
+    bit (NaNs keep theirs, -0 becomes +0); sizes around words, vectors and workgroups (4 KiB) and on both sides of the change to
+    loads past the caches (48 MiB); in place and not; nothing beyond the ends."""
+    from paper_2110_15362_amd import bittrain as bt
+    width = dt.itemsize
+    iv = {2: torch.int16, 4: torch.int32, 8: torch.int64}[width]
+    last = (48 << 20) // width
+    g = torch.Generator(device="cuda").manual_seed(4)
+    if width == 2:
+        special = torch.arange(-(1 << 15), 1 << 15, device="cuda").to(iv)
+    else:
+        inf = {4: 0x7F800000, 8: 0x7FF0000000000000}[width]
+        top = -(1 << (8 * width - 1))      # the sign
+        special = torch.tensor([0, 1, inf - 1, inf, inf + 1, top - 1 & 0x7FFFFFFF, top, top + 1, top + inf - 1, top + inf, top + inf + 1, -1],
+                               dtype=torch.int64, device="cuda").to(iv)
+    bits = torch.randint(torch.iinfo(iv).min, torch.iinfo(iv).max, (last + 5,), generator=g, device="cuda", dtype=iv)
+    bits[:special.numel()] = special
+    block = 4096 // width
+    for n in (1, 31, 33, block - 1, block, block + 1, 65 * block + 7, 70000, last, last + 5):
+        words = (n + 31) // 32
+        for inplace in (False, True):
+            x = bits[:n + 16].clone()
+            out = x if inplace else torch.full_like(x, 0x5A)
+            guard = out[n:].clone()
+            bitmap = torch.full((words + 2,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+            want = torch.relu(x[:n].clone().view(dt)).view(iv)
+            bt.bt_relu_forward(x[:n].view(dt), out[:n].view(dt), bitmap[:words])
+            assert torch.equal(out[:n], want), (n, inplace)
+            assert torch.equal(out[n:], guard) and bool((bitmap[words:] == 0x5A5A5A5A).all()), (n, inplace)
+            kept = torch.zeros(words * 32, dtype=torch.int64, device="cuda")
+            kept[:n] = want != 0
+            packed = (kept.view(-1, 32) << torch.arange(32, device="cuda")).sum(1)
+            assert torch.equal(bitmap[:words].to(torch.int64) & 0xFFFFFFFF, packed), (n, inplace)
+
+
+def test_bitmap_relu_takes_views_off_a_16_byte_boundary_and_empty_tensors(ag):
+    base = torch.randn(4097, device="cuda")
+    for x in (base[1:], base[:0], base[:1]):
+        x = x.clone().detach() if x.numel() < 2 else x.detach()
+        x.requires_grad_()
+        y = ag.bitmap_relu(x)
+        assert torch.equal(y, torch.relu(x.detach()))
+        y.sum().backward()
+        assert torch.equal(x.grad, (x.detach() > 0).float())
+
+
+@pytest.mark.parametrize("deferred", [False, True])
+def test_stash_keeps_what_a_failed_compression_was_given(ag, deferred, monkeypatch):
+    """The grid scan of every compression gives up at once (a limit of one pass): no nnz reaches the host, the tensors are kept
+    dense with a warning, the workspace serves the next step, and no place on the host is lost."""
+    from paper_2110_15362_amd import bittrain as bt
+    n = 300 * bt.bt_tile_elems(torch.float32)
+    w = torch.ones(n, device="cuda", requires_grad=True)
+    h = torch.relu(torch.randn(n, device="cuda"))
+    st = ag._state(h.device)
+    words = st.workspace(n, h.dtype).view(torch.int32)
+
+    def step(limit):
+        words[bt.BT_WS_WAIT_LIMIT_WORD] = limit
+        stash = ag.BitmapStash(deferred=deferred)
+        with stash:
+            loss = (h * w).sum()
+        loss.backward()
+        assert torch.equal(w.grad, h)
+        w.grad = None
+        return stash.stats
+    assert step(0)["compressed"] == 1
+    places = len(st.places)
+    with pytest.warns(UserWarning, match="gave up"):
+        assert step(1)["failed"] == 1
+    stats = step(0)
+    assert stats["compressed"] == 1 and stats["failed"] == 0 and len(st.places) == places
