@@ -311,6 +311,7 @@ template <int S> __device__ __forceinline__ void store_vec_guarded(void *base, u
         *reinterpret_cast<uint4 *>(static_cast<char *>(base) + e0 * S) = v;
         return;
     }
+    if (e0 >= n) return;      // (of a whole wave but one lane at most: what follows is skipped as one)
     const uint32_t d[4] = {v.x, v.y, v.z, v.w};
     if (S == 8) {
         uint64_t *p = static_cast<uint64_t *>(base);
@@ -1080,18 +1081,36 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
             mp[k / G::RPM] |= mk << (E * (k % G::RPM));
         }
     } else {
-        // A tensor's ragged last tile, element by element and one row after the other: each row's addresses are
-        // made to depend on the row before having arrived (`after`, which is 0), because with the loads of all
-        // rows in flight together the addresses alone would need more registers than there are.
-        uint32_t after = 0;
+        // A tensor's ragged last tile: what is there of it in whole vectors, all rows at once, then the elements of the
+        // vector in which the tensor ends.  Elements beyond n are 0, which no test keeps.  (Row after row, element by element, the
+        // tile had its values a microsecond or two after the others, with every tensor whose size is no multiple of a tile.
+        // Together with store_vec_guarded's early return, us: bf16 5.9 M elements compress 9.3 -> 8.3, activation call 12.3 -> 9.6, 320 k 4.9 ->
+        // 4.5 and 6.4 -> 5.5; fp32 160 k 4.6 -> 4.3 and 5.3 -> 4.7; the 49 tensors of a ResNet-50 at one image, bf16, 13.2 -> 10.9.)
+        const uint32_t left = n <= wave_e0 ? 0u : n - wave_e0 < (uint64_t)G::WAVE ? (uint32_t)(n - wave_e0) : (uint32_t)G::WAVE;      // elements of this wave
+        const char *const quarter = static_cast<const char *>(in) + wave_e0 * S;
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-            const uint64_t e0 = wave_e0 + (uint64_t)k * G::ROW + (uint64_t)lane * E + after;
-            x[k] = load_vec_guarded<S>(in, e0, n);
-            asm volatile("" : "+v"(after), "+v"(x[k].x), "+v"(x[k].y), "+v"(x[k].z), "+v"(x[k].w));
-            // elements at or beyond n read as 0, which a negative threshold would keep: mask them
-            const uint32_t in_range = e0 >= n ? 0u : (n - e0 >= (uint64_t)E ? (1u << E) - 1u : (1u << (uint32_t)(n - e0)) - 1u);
-            mp[k / G::RPM] |= (keep_mask<S, KEEP>(x[k], threshold_f, threshold) & in_range) << (E * (k % G::RPM));
+            const uint32_t at = (uint32_t)(k * G::ROW + lane * E);
+            x[k] = make_uint4(0, 0, 0, 0);
+            if (at + E <= left) x[k] = stream_load<kCompressNtLoad>(reinterpret_cast<const uint4 *>(quarter + at * S));
+        }
+        const uint32_t whole = left / E * E;
+        if (whole != left) {
+            const uint4 v = load_vec_guarded<S>(in, wave_e0 + whole, n);
+            const uint32_t d[4] = {uniform32(v.x), uniform32(v.y), uniform32(v.z), uniform32(v.w)};
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                if ((uint32_t)(k * G::ROW + lane * E) == whole) x[k] = make_uint4(d[0], d[1], d[2], d[3]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            // (A loop of its own: where both kinds of tile meet before it, the wait for row 0 becomes one for all rows.  And nothing of
+            // a row's test before its turn: halves widened ahead take registers there are not.)
+            asm volatile("" : "+v"(x[k].x), "+v"(x[k].y), "+v"(x[k].z), "+v"(x[k].w));
+            uint32_t mk = keep_mask<S, KEEP>(x[k], threshold_f, threshold);
+            asm volatile("" : "+v"(mk));
+            mp[k / G::RPM] |= mk << (E * (k % G::RPM));
         }
     }
     // Keep the masks as values of their own: otherwise the compiler keeps one compare
@@ -1367,11 +1386,16 @@ __device__ __forceinline__ Quarter<S, R> quarter_load(const uint32_t *bitmap, co
             q.w[0] = bitmap[first + lane];
         }
     } else {
-        const uint64_t n_words = (n + 31) >> 5;
+        const uint64_t n_words = (n + 31) >> 5;      // (at least one)
 #pragma unroll
         for (int j = 0; j < G::QPL; ++j) {
             const uint64_t wi = first + (uint32_t)(lane * G::QPL + j);
-            if (lane * G::QPL + j < G::WAVE_WORDS && wi < n_words) q.w[j] = bitmap[wi];
+            q.w[j] = bitmap[wi < n_words ? wi : n_words - 1];
+        }
+#pragma unroll
+        for (int j = 0; j < G::QPL; ++j) {
+            const uint64_t wi = first + (uint32_t)(lane * G::QPL + j);
+            if (lane * G::QPL + j >= G::WAVE_WORDS || wi >= n_words) q.w[j] = 0;
             if (wi + 1 == n_words && (n & 31) != 0) q.w[j] &= (1u << (uint32_t)(n & 31)) - 1u;
         }
     }
