@@ -40,9 +40,11 @@ class _StreamState:
 
     def place(self):
         """A place for one compression's nnz, holding -1; back to `places` when that compression is over."""
-        if not self.places:
-            self.places += [_Place(self) for _ in range(8)]
-        p = self.places.pop()
+        try:
+            p = self.places.pop()
+        except IndexError:                # (not asked before: another thread may take the last one)
+            self.places += [_Place(self) for _ in range(7)]
+            p = _Place(self)
         p.word[0] = -1
         return p
 
@@ -228,10 +230,10 @@ class _BitmapReLU(torch.autograd.Function):
             y = torch.empty_like(x)
             st = _state(x.device)
             bt.bt_activation_compress(x, 0.0, y, bitmap, torch.empty(0, dtype=x.dtype, device=x.device), st.nnz, st.workspace(n, x.dtype))
-        elif x.data_ptr() % 16 == 0:
+        elif not (x.is_neg() or x._is_zerotensor()) and x.data_ptr() % 16 == 0:
             y = torch.empty_like(x)
             bt.bt_relu_forward(x, y, bitmap)
-        else:                             # (a view that starts off a 16-byte boundary is not what the library takes; y does not)
+        else:                             # (a view off a 16-byte boundary, or whose memory does not hold its values; y is neither)
             y = torch.relu(x)
             bt.bt_relu_forward(y, y, bitmap)
         ctx.bitmap = bitmap

@@ -149,7 +149,7 @@ def test_relu_forward_is_torch_relu_with_its_bitmap(ag, dt):
 
 def test_bitmap_relu_takes_views_off_a_16_byte_boundary_and_empty_tensors(ag):
     base = torch.randn(4097, device="cuda")
-    for x in (base[1:], base[:0], base[:1]):
+    for x in (base[1:], base[:0], base[:1], torch._neg_view(base)):      # (the last one's memory holds what it is not)
         x = x.clone().detach() if x.numel() < 2 else x.detach()
         x.requires_grad_()
         y = ag.bitmap_relu(x)
