@@ -349,8 +349,8 @@ def other_configs(bt, wl, torch, dev, timed, args):
                  "peak_MiB_without_stash": round(res[False][1]), "peak_MiB_with_stash": round(res[True][1]),
                  "peak_MiB_with_deferred_stash": round(res["deferred"][1]),
                  "saved_dense_MiB": round(res[True][2]["dense_bytes"] / 2**20), "saved_stored_MiB": round(res[True][2]["stored_bytes"] / 2**20),
-                 "note": "packing reads nnz and the workspace status back to right-size the value buffer: one host synchronisation per saved "
-                         "tensor; the deferred stash lets them arrive behind an event and cuts the buffer to size later"})
+                 "note": "packing waits for nnz, which the compression writes to pinned host memory, to right-size the value buffer: one host "
+                         "synchronisation per saved tensor; the deferred stash asks an event and cuts the buffer to size later"})
     return rows
 
 
@@ -517,7 +517,7 @@ def main():
     # dominant kernel of the step: the slower of the two codec kernels (the ReLU kernel is a plain stream)
     dom = max(("compress", "decompress"), key=lambda k: row[k]["us_cold"])
     achieved = row[dom]["algorithmic_bytes"] / row[dom]["us_cold"] / 1e3
-    roofline = {"bound": "hbm", "kernel": {"compress": "compress_kernel<4, 8, false, 0, false, CompressOne>", "decompress": "decompress_kernel<4, 8, false, DecompressOne>"}[dom], "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
+    roofline = {"bound": "hbm", "kernel": {"compress": "compress_kernel<4, 8, false, 0, false, CompressOne>", "decompress": "decompress_kernel<4, DecompressOne>"}[dom], "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": measured_traffic(dom),
                 "traffic_source": (None if measured_traffic(dom) is None else
                                    "profiles/hbm_traffic_config2_z50.txt: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE of this "
