@@ -17,6 +17,7 @@ Two pieces, both thin: every byte of codec work is done by libbittrain's kernels
   (1/32 of an fp32 activation): output and bitmap from one pass, bt_relu_forward.
 """
 import math
+import threading
 import warnings
 
 import torch
@@ -74,9 +75,11 @@ class _Place:
 
     def read(self):
         """nnz, or -1 from a compression that failed; only after the compression is over."""
-        nnz = int(self.word[0])
+        return int(self.word[0])
+
+    def give_back(self):
+        """After the compression is over, and once: whoever takes the place next shares it with nobody."""
         self.state.places.append(self)
-        return nnz
 
 
 _states = {}
@@ -104,10 +107,11 @@ class _Packed:
 class _Pending:
     """What a deferred packing still waits for: nnz on its way to pinned host memory, the event behind the
     compression, and the dense tensor, kept until the result is known to be good."""
-    __slots__ = ("packed", "dense", "place", "event", "ws")
+    __slots__ = ("packed", "dense", "place", "event", "ws", "lock", "taken")
 
     def __init__(self, packed, dense, place, event, ws):
         self.packed, self.dense, self.place, self.event, self.ws = packed, dense, place, event, ws
+        self.lock, self.taken = threading.RLock(), False       # one thread may pack while another unpacks: the first settles it
 
 
 class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
@@ -143,23 +147,38 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
         if gave_up or stored >= n * width:
             self.stats["stored_bytes"] += n * width
             return False                                           # too dense (the bitmap form would be larger), or no good
+        p.values = values_full[:nnz].clone()
         self.stats["compressed"] += 1
         self.stats["stored_bytes"] += stored
-        p.values = values_full[:nnz].clone()
         return True
 
-    def _finish_waiting(self, only=None, block=False):
-        """Deferred mode: settle every packing whose result has arrived; wait for `only`'s (for all, if `block`)."""
-        still = []
-        for w in self._waiting:
-            if not (block or w.packed is only or w.event.query()):
-                still.append(w)
-                continue
-            w.event.synchronize()
-            if not self._settle(w.packed, w.place.read(), w.packed.values, w.ws):
-                w.packed.dense, w.packed.bitmap, w.packed.values, w.packed.index = w.dense, None, None, None
-            w.packed.pending = None
-        self._waiting = still
+    def _finish_waiting(self, only=None, block=False, most=None):
+        """Deferred mode: settle every packing whose result has arrived; wait for `only`'s (for all, if `block`; for the oldest
+        of more than `most`)."""
+        for w in list(self._waiting):
+            if block or w.packed is only or w.event.query():
+                self._finish(w)
+        if most is not None:
+            for w in self._waiting[:max(0, len(self._waiting) - most)]:
+                self._finish(w)
+
+    def _finish(self, w):
+        """Wait for the packing `w` (a _Pending) and settle it, once, whatever becomes of that; if it fails, the tensor stays dense."""
+        with w.lock:
+            if w.taken:
+                return
+            w.taken = True
+            kept = False
+            try:
+                w.event.synchronize()
+                nnz = w.place.read()
+                w.place.give_back()
+                kept = self._settle(w.packed, nnz, w.packed.values, w.ws)
+            finally:
+                if not kept:
+                    w.packed.dense, w.packed.bitmap, w.packed.values, w.packed.index = w.dense, None, None, None
+                w.packed.pending = None
+                self._waiting.remove(w)
 
     def __exit__(self, *exc):
         self._finish_waiting(block=True)      # leaves nothing behind that still holds a dense tensor
@@ -179,9 +198,7 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
         stream = torch.cuda.current_stream()
         packed = _Packed(bitmap, None, index, t.shape, t.dtype, t.device)
         if self.deferred:
-            self._finish_waiting()
-            while len(self._waiting) >= self.max_waiting:          # bounds what the unsettled packings hold
-                self._finish_waiting(only=self._waiting[0].packed)
+            self._finish_waiting(most=self.max_waiting - 1)        # bounds what the unsettled packings hold
             packed.values = torch.empty(n, dtype=t.dtype, device=t.device)     # its own: it outlives this call
             place = self._compress(t, packed, packed.values, st, ws, stream)
             event = torch.cuda.Event()
@@ -192,7 +209,9 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
         scratch = st.value_scratch(n, t.dtype)
         place = self._compress(t, packed, scratch, st, ws, stream)
         stream.synchronize()                                       # nnz is needed to right-size
-        return packed if self._settle(packed, place.read(), scratch, ws) else t
+        nnz = place.read()
+        place.give_back()
+        return packed if self._settle(packed, nnz, scratch, ws) else t
 
     @staticmethod
     def _compress(t, packed, values, st, ws, stream):

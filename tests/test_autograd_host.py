@@ -1,0 +1,104 @@
+"""What BitmapStash does on the host around its compressions, without a GPU: the compressions, the events behind them and
+pinned memory are stand-ins, so every order of events and every failure can be had."""
+import threading
+
+import pytest
+import torch
+
+N = 4096
+NNZ = 100
+
+
+@pytest.fixture
+def ag(monkeypatch):
+    """The module, with ordinary host memory for pinned memory."""
+    from paper_2110_15362_amd import autograd, bittrain
+    bittrain.lib()
+    empty = torch.empty
+    monkeypatch.setattr(torch, "empty", lambda *a, pin_memory=False, **k: empty(*a, **k))
+    return autograd
+
+
+class _Event:
+    """A compression that is over once somebody waits for it."""
+
+    def __init__(self, wait=None):
+        self.wait = wait
+
+    def query(self):
+        return False
+
+    def synchronize(self):
+        if self.wait is not None:
+            self.wait()
+
+
+class _Values:
+    """The worst-case buffer of a packing, which is cut to size by a copy."""
+
+    def __init__(self, failures=0):
+        self.failures = failures
+
+    def __getitem__(self, cut):
+        self.length = cut.stop
+        return self
+
+    def clone(self):
+        if self.failures:
+            self.failures -= 1
+            raise torch.OutOfMemoryError("out of memory")
+        return torch.zeros(self.length)
+
+
+def _waiting(ag, stash, st, values, event=None):
+    """A packing of N elements, of which NNZ are stored, that `stash` has not settled yet."""
+    p = ag._Packed(torch.zeros(N // 32, dtype=torch.int32), values, torch.zeros(1, dtype=torch.int64), torch.Size([N]), torch.float32, st.device)
+    p.pending = True
+    place = st.place()
+    place.word[0] = NNZ
+    stash._waiting.append(ag._Pending(p, torch.ones(N), place, event or _Event(), None))
+    return p
+
+
+def _distinct(places):
+    return len({id(p) for p in places}) == len(places)
+
+
+def test_a_place_is_given_back_once_though_settling_failed(ag):
+    """The copy that cuts a packing to size runs out of memory: the tensor stays dense, the packings after it are settled as
+    ever, and no two of the compressions that follow write their nnz to the same word."""
+    st = ag._StreamState(torch.device("cpu"))
+    stash = ag.BitmapStash(deferred=True)
+    first = _waiting(ag, stash, st, _Values(failures=1))
+    second = _waiting(ag, stash, st, _Values())
+    with pytest.raises(torch.OutOfMemoryError):
+        stash._finish_waiting(block=True)
+    stash._finish_waiting(block=True)
+    assert len(st.places) == 8 and _distinct(st.places)
+    taken = [st.place() for _ in range(12)]
+    assert _distinct(taken) and len({p.address for p in taken}) == 12
+    assert not first.pending and torch.equal(stash._unpack(first), torch.ones(N))
+    assert not second.pending and second.dense is None and second.values.numel() == NNZ
+    assert stash.stats["compressed"] == 1
+
+
+def test_two_threads_settle_a_packing_once(ag):
+    """One thread packs and another unpacks: the second comes while the first waits for the event."""
+    st = ag._StreamState(torch.device("cpu"))
+    stash = ag.BitmapStash(deferred=True)
+    waits, both = [], threading.Event()
+
+    def wait():      # up to half a second for the other thread to get here too
+        waits.append(threading.get_ident())
+        if len(waits) > 1:
+            both.set()
+        both.wait(0.5)
+    p = _waiting(ag, stash, st, _Values(), _Event(wait))
+    threads = [threading.Thread(target=stash._finish_waiting, kwargs={"only": p}) for _ in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(10)
+    assert len(waits) == 1 and stash._waiting == []
+    assert not p.pending and p.values.numel() == NNZ and stash.stats["compressed"] == 1
+    assert len(st.places) == 8 and _distinct(st.places)
