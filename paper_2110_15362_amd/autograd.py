@@ -181,8 +181,10 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
                 self._waiting.remove(w)
 
     def __exit__(self, *exc):
-        self._finish_waiting(block=True)      # leaves nothing behind that still holds a dense tensor
-        return super().__exit__(*exc)
+        try:
+            self._finish_waiting(block=True)  # leaves nothing behind that still holds a dense tensor
+        finally:
+            super().__exit__(*exc)
 
     def _pack(self, t):
         if (not t.is_cuda or t.dtype not in _SUPPORTED or t.numel() < self.min_numel or not t.is_contiguous()

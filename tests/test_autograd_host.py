@@ -102,3 +102,25 @@ def test_two_threads_settle_a_packing_once(ag):
     assert len(waits) == 1 and stash._waiting == []
     assert not p.pending and p.values.numel() == NNZ and stash.stats["compressed"] == 1
     assert len(st.places) == 8 and _distinct(st.places)
+
+
+def test_leaving_the_stash_takes_its_hooks_off_though_settling_failed(ag):
+    class Stash(ag.BitmapStash):
+        packed = 0
+
+        def _pack(self, t):
+            Stash.packed += 1
+            return t
+    x = torch.ones(4, requires_grad=True)
+    stash = Stash(deferred=True)
+    with pytest.raises(torch.OutOfMemoryError):
+        with stash:
+            (x * x).sum()
+            _waiting(ag, stash, ag._StreamState(torch.device("cpu")), _Values(failures=1))
+    inside = Stash.packed
+    try:
+        (x * x).sum()
+        assert inside > 0 and Stash.packed == inside
+    finally:
+        if Stash.packed != inside:      # (not for the tests after this one)
+            torch.autograd.graph.saved_tensors_hooks.__exit__(stash)
