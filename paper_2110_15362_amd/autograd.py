@@ -37,7 +37,9 @@ class _StreamState:
         self.ws = None
         self.scratch = {}
         self.nnz = torch.zeros(1, dtype=torch.int64, device=device)
-        self.places = []      # free ones; the memory is kept, so that a kernel never writes to what is something else by then
+        self.places = []      # free ones
+        self.words = []       # the memory of all, kept: a place that is never given back (the host was interrupted in its wait)
+                              # may still be written to, and not be something else by then
 
     def place(self):
         """A place for one compression's nnz, holding -1; back to `places` when that compression is over."""
@@ -72,6 +74,7 @@ class _Place:
         self.state = state
         self.memory = torch.empty(1, dtype=torch.int64, pin_memory=True)
         self.word, self.address = self.memory.numpy(), self.memory.data_ptr()
+        state.words.append(self.memory)
 
     def read(self):
         """nnz, or -1 from a compression that failed; only after the compression is over."""

@@ -1,6 +1,8 @@
 """What BitmapStash does on the host around its compressions, without a GPU: the compressions, the events behind them and
 pinned memory are stand-ins, so every order of events and every failure can be had."""
+import gc
 import threading
+import weakref
 
 import pytest
 import torch
@@ -124,3 +126,15 @@ def test_leaving_the_stash_takes_its_hooks_off_though_settling_failed(ag):
     finally:
         if Stash.packed != inside:      # (not for the tests after this one)
             torch.autograd.graph.saved_tensors_hooks.__exit__(stash)
+
+
+def test_a_place_that_nobody_gives_back_keeps_its_memory(ag):
+    """Its compression may still be on the way (the host was interrupted while it waited, a packing was let go of unsettled),
+    and what it writes to must not have become something else's memory by then."""
+    st = ag._StreamState(torch.device("cpu"))
+    place = st.place()
+    address, memory = place.address, weakref.ref(place.memory)
+    del place
+    gc.collect()
+    assert memory() is not None and memory().data_ptr() == address
+    assert all(p.address != address for p in [st.place() for _ in range(20)])
