@@ -30,7 +30,8 @@ _SUPPORTED = (torch.float32, torch.float16, torch.bfloat16, torch.float64)
 class _StreamState:
     """Reusable buffers of one (device, stream): workspace, worst-case value scratch, and places in pinned host memory
     that compressions write their nnz to (a call that gave up a wait, or found a workspace on which one was given up, writes
-    none).  Work on different streams must not share them: a workspace serves one call at a time."""
+    none).  Work on different streams must not share them: a workspace serves one call at a time.  Threads on one stream may: their
+    calls are in its order, and a value scratch and a place are one packing's until it gives them back."""
 
     def __init__(self, device):
         self.device = device
@@ -58,12 +59,19 @@ class _StreamState:
             bt.bt_workspace_init(self.ws)
         return self.ws
 
-    def value_scratch(self, n, dtype):
-        buf = self.scratch.get(dtype)
+    def take_scratch(self, n, dtype):
+        """A value buffer for n elements that is nobody else's until it comes back: another thread that packs on this stream takes
+        another one, or its values would land in this one before they are copied out of it."""
+        buf = self.scratch.pop(dtype, None)
         if buf is None or buf.numel() < n:
             buf = torch.empty(n, dtype=dtype, device=self.device)
-            self.scratch[dtype] = buf
-        return buf[:n]
+        return buf
+
+    def give_scratch(self, buf):
+        """Back, once its last use is on the stream; the largest is kept."""
+        other = self.scratch.get(buf.dtype)
+        if other is None or other.numel() < buf.numel():
+            self.scratch[buf.dtype] = buf
 
 
 class _Place:
@@ -211,12 +219,15 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
             packed.pending = True
             self._waiting.append(_Pending(packed, t.detach(), place, event, ws))
             return packed
-        scratch = st.value_scratch(n, t.dtype)
-        place = self._compress(t, packed, scratch, st, ws, stream)
-        stream.synchronize()                                       # nnz is needed to right-size
-        nnz = place.read()
-        place.give_back()
-        return packed if self._settle(packed, nnz, scratch, ws) else t
+        scratch = st.take_scratch(n, t.dtype)
+        try:
+            place = self._compress(t, packed, scratch[:n], st, ws, stream)
+            stream.synchronize()                                   # nnz is needed to right-size
+            nnz = place.read()
+            place.give_back()
+            return packed if self._settle(packed, nnz, scratch, ws) else t
+        finally:
+            st.give_scratch(scratch)
 
     @staticmethod
     def _compress(t, packed, values, st, ws, stream):

@@ -138,3 +138,56 @@ def test_a_place_that_nobody_gives_back_keeps_its_memory(ag):
     gc.collect()
     assert memory() is not None and memory().data_ptr() == address
     assert all(p.address != address for p in [st.place() for _ in range(20)])
+
+
+class _OnDevice(torch.Tensor):
+    is_cuda = True
+
+
+@pytest.fixture
+def packing(ag, monkeypatch):
+    """`packing(values)` has a new stash pack a tensor of them as if it were on a device; the compression is done by torch at
+    once.  `packing.wait`: called while the host waits for the stream."""
+    st = ag._StreamState(torch.device("cpu"))
+
+    def compress(t, packed, values, st, ws, stream):
+        kept = t[t != 0].as_subclass(torch.Tensor)
+        values[:kept.numel()] = kept
+        place = st.place()
+        place.word[0] = kept.numel()
+        return place
+
+    class Stream:
+        cuda_stream = 0
+
+        def synchronize(self):
+            wait, pack.wait = pack.wait, None
+            if wait is not None:
+                wait()
+
+    def pack(values):
+        return ag.BitmapStash()._pack(values.as_subclass(_OnDevice))
+    pack.wait, pack.state = None, st
+    monkeypatch.setattr(ag, "_state", lambda device: st)
+    monkeypatch.setattr(ag.bt, "bt_workspace_init", lambda ws: None)
+    monkeypatch.setattr(ag.BitmapStash, "_compress", staticmethod(compress))
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Stream())
+    return pack
+
+
+def _sparse(n, seed):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randn(n, generator=g).relu()
+
+
+def test_another_thread_packs_on_the_same_stream_before_the_values_are_copied(ag, packing):
+    """The second compression is queued between the end of the first and the copy that cuts it to size: larger, smaller and of
+    the same size."""
+    x = _sparse(N, 1)
+    for n in (N // 2 + 4096, N, 2 * N):
+        y, inner = _sparse(n, n), []
+        packing.wait = lambda: inner.append(packing(y))
+        p = packing(x)
+        assert torch.equal(p.values, x[x != 0])
+        assert torch.equal(inner[0].values, y[y != 0])
+    assert packing.state.scratch[torch.float32].numel() == 2 * N      # the larger one is kept
