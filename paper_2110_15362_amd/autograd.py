@@ -54,10 +54,12 @@ class _StreamState:
 
     def workspace(self, n, dtype):
         need = bt.bt_workspace_bytes(n, dtype)
-        if self.ws is None or self.ws.numel() < need:
-            self.ws = torch.empty(max(need, 1 << 16), dtype=torch.uint8, device=self.device)
-            bt.bt_workspace_init(self.ws)
-        return self.ws
+        ws = self.ws
+        if ws is None or ws.numel() < need:
+            ws = torch.empty(max(need, 1 << 16), dtype=torch.uint8, device=self.device)
+            bt.bt_workspace_init(ws)
+            self.ws = ws                      # (only now: another thread on this stream may look for one in between)
+        return ws
 
     def take_scratch(self, n, dtype):
         """A value buffer for n elements that is nobody else's until it comes back: another thread that packs on this stream takes

@@ -191,3 +191,11 @@ def test_another_thread_packs_on_the_same_stream_before_the_values_are_copied(ag
         assert torch.equal(p.values, x[x != 0])
         assert torch.equal(inner[0].values, y[y != 0])
     assert packing.state.scratch[torch.float32].numel() == 2 * N      # the larger one is kept
+
+
+def test_a_new_workspace_is_seen_by_others_only_once_it_is_initialised(ag, packing, monkeypatch):
+    st, seen = packing.state, []
+    monkeypatch.setattr(ag.bt, "bt_workspace_init", lambda ws: seen.append(st.ws is ws))
+    st.workspace(N, torch.float32)
+    st.workspace(1 << 30, torch.float32)
+    assert seen == [False, False]
