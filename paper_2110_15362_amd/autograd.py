@@ -279,6 +279,8 @@ class _BitmapReLU(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_out):
         grad_out = grad_out.contiguous()
+        if grad_out.data_ptr() % 16 != 0:      # (a part of a concatenation's gradient)
+            grad_out = grad_out.clone()
         grad_in = torch.empty_like(grad_out)
         bt.bt_relu_backward_from_bitmap(ctx.bitmap, grad_out, grad_in)
         return grad_in, None

@@ -199,3 +199,29 @@ def test_a_new_workspace_is_seen_by_others_only_once_it_is_initialised(ag, packi
     st.workspace(N, torch.float32)
     st.workspace(1 << 30, torch.float32)
     assert seen == [False, False]
+
+
+@pytest.fixture
+def relu_backward(ag, monkeypatch):
+    """bitmap_relu's backward with the kernel's work done by torch on what it is handed: the memory at an address."""
+    import ctypes
+    import types
+
+    def kernel(bitmap, grad_out, grad_in):
+        n = grad_out.numel()
+        assert grad_out.is_contiguous() and grad_out.data_ptr() % 16 == 0 and grad_in.data_ptr() % 16 == 0
+        held = (ctypes.c_float * n).from_address(grad_out.data_ptr())
+        kept = (bitmap.repeat_interleave(32) >> torch.arange(32).repeat(bitmap.numel()))[:n] & 1
+        grad_in.copy_(torch.where(kept.bool(), torch.frombuffer(held, dtype=torch.float32), torch.zeros(n)))
+    monkeypatch.setattr(ag.bt, "bt_relu_backward_from_bitmap", kernel)
+    ctx = types.SimpleNamespace(bitmap=torch.tensor([0x35A5A5A5], dtype=torch.int32))
+    kept = (ctx.bitmap >> torch.arange(32)) & 1
+    return lambda grad: (ag._BitmapReLU.backward(ctx, grad)[0], kept)
+
+
+@pytest.mark.parametrize("start", [0, 1, 2, 3, 4])
+def test_relu_backward_takes_gradients_off_a_16_byte_boundary(relu_backward, start):
+    """What a concatenation hands back to its parts: a contiguous view that begins anywhere."""
+    grad = torch.randn(40)[start:start + 32]
+    got, kept = relu_backward(grad)
+    assert torch.equal(got, grad * kept)

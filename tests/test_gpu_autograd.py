@@ -184,3 +184,11 @@ def test_stash_keeps_what_a_failed_compression_was_given(ag, deferred, monkeypat
         assert step(1)["failed"] == 1
     stats = step(0)
     assert stats["compressed"] == 1 and stats["failed"] == 0 and len(st.places) == places
+
+
+def test_bitmap_relu_in_a_concatenation(ag):
+    """Its gradient is a view that begins where the other part ends, off every 16-byte boundary."""
+    x = torch.randn(4099, device="cuda", requires_grad=True)
+    w = torch.randn(3 + 4099, device="cuda")
+    (torch.cat([torch.ones(3, device="cuda"), ag.bitmap_relu(x)]) * w).sum().backward()
+    assert torch.equal(x.grad, torch.where(x.detach() > 0, w[3:], 0))
