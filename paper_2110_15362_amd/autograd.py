@@ -201,8 +201,8 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
 
     def _pack(self, t):
         if (not t.is_cuda or t.dtype not in _SUPPORTED or t.numel() < self.min_numel or not t.is_contiguous()
-                or isinstance(t, torch.nn.Parameter) or t.data_ptr() % 16 != 0):
-            return t                      # (a view that starts off a 16-byte boundary is not what the library takes)
+                or isinstance(t, torch.nn.Parameter) or t.is_neg() or t._is_zerotensor() or t.data_ptr() % 16 != 0):
+            return t                      # (the library takes memory from a 16-byte boundary on that holds the values)
         st = _state(t.device)
         n = t.numel()
         self.stats["tensors"] += 1
@@ -255,6 +255,11 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
         return out
 
 
+def _held(t):
+    """`t`, or a copy of it if its memory does not hold its values (a negated view, a zero tensor)."""
+    return torch.zeros_like(t) if t._is_zerotensor() else t.resolve_neg()
+
+
 class _BitmapReLU(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, fused):
@@ -264,6 +269,7 @@ class _BitmapReLU(torch.autograd.Function):
         bitmap = torch.empty((n + 31) // 32, dtype=torch.int32, device=x.device)
         if fused:
             # y = x where x > 0 else +0 (a NaN input gives 0 here, NaN in torch.relu); capacity 0: no value is written
+            x = _held(x)
             y = torch.empty_like(x)
             st = _state(x.device)
             bt.bt_activation_compress(x, 0.0, y, bitmap, torch.empty(0, dtype=x.dtype, device=x.device), st.nnz, st.workspace(n, x.dtype))
@@ -278,7 +284,7 @@ class _BitmapReLU(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, grad_out):
-        grad_out = grad_out.contiguous()
+        grad_out = _held(grad_out.contiguous())
         if grad_out.data_ptr() % 16 != 0:      # (a part of a concatenation's gradient)
             grad_out = grad_out.clone()
         grad_in = torch.empty_like(grad_out)

@@ -225,3 +225,22 @@ def test_relu_backward_takes_gradients_off_a_16_byte_boundary(relu_backward, sta
     grad = torch.randn(40)[start:start + 32]
     got, kept = relu_backward(grad)
     assert torch.equal(got, grad * kept)
+
+
+def test_tensors_whose_memory_does_not_hold_their_values(ag, packing, relu_backward, monkeypatch):
+    """Negated views and zero tensors (which have no memory at all): the stash leaves them alone, and bitmap_relu hands the
+    kernels memory that holds what they are, also in one pass with the compression and as gradients."""
+    for t in (torch._neg_view(_sparse(N, 1)), torch._efficientzerotensor(N)):
+        t = t.as_subclass(_OnDevice)
+        assert ag.BitmapStash()._pack(t) is t
+    grad = torch.randn(33)
+    for g, want in ((torch._neg_view(grad[:32]), -grad[:32]), (torch._neg_view(grad[1:]), -grad[1:]),
+                    (torch._efficientzerotensor(32), torch.zeros(32))):
+        got, kept = relu_backward(g)
+        assert torch.equal(got, want * kept)
+
+    handed = []
+    monkeypatch.setattr(ag.bt, "bt_activation_compress", lambda x, *rest: handed.append(x))
+    x = torch._neg_view(grad[:32])
+    ag._BitmapReLU.forward(torch.autograd.function.FunctionCtx(), x.as_subclass(_OnDevice), True)
+    assert not handed[0].is_neg() and torch.equal(handed[0], -grad[:32])

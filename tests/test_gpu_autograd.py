@@ -192,3 +192,19 @@ def test_bitmap_relu_in_a_concatenation(ag):
     w = torch.randn(3 + 4099, device="cuda")
     (torch.cat([torch.ones(3, device="cuda"), ag.bitmap_relu(x)]) * w).sum().backward()
     assert torch.equal(x.grad, torch.where(x.detach() > 0, w[3:], 0))
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_negated_views_are_what_they_look_like(ag, fused):
+    """In the stash (saved by a product), through bitmap_relu, and as the gradient that comes back to it."""
+    h = torch.relu(torch.randn(8192, device="cuda"))
+    w = torch.ones(8192, device="cuda", requires_grad=True)
+    with ag.BitmapStash():
+        loss = (torch._neg_view(h) * w).sum()
+    loss.backward()
+    assert torch.equal(w.grad, -h)
+    x = torch.randn(8192, device="cuda").requires_grad_()
+    y = ag.bitmap_relu(torch._neg_view(x), fused=fused)
+    assert torch.equal(y, torch.relu(-x))
+    y.backward(torch._neg_view(h))
+    assert torch.equal(x.grad, torch.where(x < 0, h, 0))
