@@ -2098,9 +2098,16 @@ uint64_t tiles_for(uint64_t n, int s, int rows = kRows) {
 
 constexpr uint64_t kReluCachedBytes = (uint64_t)48 << 20;      // largest gradient that is read through the caches
 
-uint64_t relu_blocks_for(uint64_t n, int s) {
-    const uint64_t t = (uint64_t)kBlock * kReluRows * (kVecBytes / s);
-    return (n + t - 1) / t;
+// A stream over n elements, `per_block` (a multiple of 32) a workgroup: go(first element, elements, workgroups) for one launch, or
+// for several, since a grid holds less than 2^32 threads.
+template <class Go> bt_status stream_launches(uint64_t n, uint64_t per_block, Go go) {
+    const uint64_t most = per_block << 23;      // 2^31 threads
+    for (uint64_t first = 0; first < n; first += most) {
+        const uint64_t count = n - first < most ? n - first : most;
+        const bt_status st = go(first, count, (count + per_block - 1) / per_block);
+        if (st != BT_OK) return st;
+    }
+    return BT_OK;
 }
 
 bool misaligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
@@ -2460,7 +2467,12 @@ bt_status bt_relu_backward_from_bitmap(const uint32_t *d_bitmap, const void *d_g
     // 5.3 / 4.3, 25.7 M 18.6 / 16.1, 60 M 39.5 / 41.1.  With eight sets, which push each other out of it: fp32 5.5 M 9.4 / 7.9, 9 M 13.9 /
     // 13.5, 16 M 22.5 / 23.0, 25.7 M 34.4 / 35.2.  In a step (compress, restore, this) fp32 5.5 M 32.4 / 30.7, 12 M 51.3 / 49.7, bf16 32.2 M 66.4 / 68.4.
     const bool cached = n * (uint64_t)s <= kReluCachedBytes;
-    const auto go = [&](auto kernel) { return launch(kernel, relu_blocks_for(n, s), kBlock, hs, d_bitmap, d_grad_out, n, d_grad_in); };
+    const auto go = [&](auto kernel) {
+        return stream_launches(n, (uint64_t)kBlock * kReluRows * (kVecBytes / s), [&](uint64_t first, uint64_t count, uint64_t blocks) {
+            return launch(kernel, blocks, kBlock, hs, d_bitmap + first / 32, static_cast<const char *>(d_grad_out) + first * s, count,
+                          static_cast<char *>(d_grad_in) + first * s);
+        });
+    };
     if (s == 8) return go(cached ? relu_backward_kernel<8, false> : relu_backward_kernel<8, true>);
     if (s == 4) return go(cached ? relu_backward_kernel<4, false> : relu_backward_kernel<4, true>);
     return go(cached ? relu_backward_kernel<2, false> : relu_backward_kernel<2, true>);
@@ -2474,9 +2486,13 @@ bt_status bt_relu_forward(const void *d_in, uint64_t n, bt_dtype dtype, void *d_
     if (d_in == nullptr || d_out == nullptr || d_bitmap == nullptr) return BT_ERR_NULL;
     if (misaligned(d_in, 16) || misaligned(d_out, 16) || misaligned(d_bitmap, 4)) return BT_ERR_ALIGN;
     hipStream_t hs = (hipStream_t)stream;
-    const uint64_t per_block = (uint64_t)kBlock * (kVecBytes / s);
     const bool cached = n * (uint64_t)s <= kReluCachedBytes;      // written just before, like a gradient
-    const auto go = [&](auto kernel) { return launch(kernel, (n + per_block - 1) / per_block, kBlock, hs, d_in, n, d_out, d_bitmap); };
+    const auto go = [&](auto kernel) {
+        return stream_launches(n, (uint64_t)kBlock * (kVecBytes / s), [&](uint64_t first, uint64_t count, uint64_t blocks) {
+            return launch(kernel, blocks, kBlock, hs, static_cast<const char *>(d_in) + first * s, count, static_cast<char *>(d_out) + first * s,
+                          d_bitmap + first / 32);
+        });
+    };
     if (dtype == BT_F64) return go(cached ? relu_forward_kernel<8, kKeepAboveF64, false> : relu_forward_kernel<8, kKeepAboveF64, true>);
     if (dtype == BT_F32) return go(cached ? relu_forward_kernel<4, kKeepAboveF32, false> : relu_forward_kernel<4, kKeepAboveF32, true>);
     if (dtype == BT_F16) return go(cached ? relu_forward_kernel<2, kKeepAboveF16, false> : relu_forward_kernel<2, kKeepAboveF16, true>);

@@ -510,3 +510,76 @@ def test_binding_takes_every_stream_that_makes_a_pointer(bt, handle):
     for stream in (Stream(),) if handle is None else (Stream(), handle):
         assert bt.bt_relu_backward_from_bitmap(w, f, f, stream=stream) is None
         assert bt.bt_decompress_batch((bt.DecompressItem * 1)(), 0, torch.float32, _FakeTensor(64, torch.uint8), stream=stream) is None
+
+
+_RECORDER = r"""
+#include <stdint.h>
+#include <string.h>
+typedef struct { uint32_t x, y, z; } dim3;
+uint64_t launches[32][6];
+int count;
+int hipLaunchKernel(const void *kernel, dim3 grid, dim3 block, void **args, size_t shared, void *stream) {
+    (void)kernel, (void)shared, (void)stream;
+    if (count == 32) return 1;
+    launches[count][0] = grid.x;
+    launches[count][1] = block.x;
+    for (int i = 0; i < 4; ++i) memcpy(&launches[count][2 + i], args[i], 8);
+    ++count;
+    return 0;
+}
+"""
+
+_RECORD = r"""
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # before the library: its launches come here
+lib = ctypes.CDLL(sys.argv[2])
+rows = ((ctypes.c_uint64 * 6) * 32).in_dll(stub, "launches")
+count = ctypes.c_int.in_dll(stub, "count")
+u64, vp = ctypes.c_uint64, ctypes.c_void_p
+lib.bt_relu_forward.argtypes = [vp, u64, ctypes.c_int, vp, vp, vp]
+for f in (lib.bt_relu_backward_from_bitmap, lib.bt_mask_apply):
+    f.argtypes = [vp, vp, u64, ctypes.c_int, vp, vp]
+IN, OUT, BITMAP = 1 << 44, 1 << 45, 1 << 46
+for dtype in range(4):
+    for n in [int(a) for a in sys.argv[3:]]:
+        for name in ("bt_relu_forward", "bt_relu_backward_from_bitmap", "bt_mask_apply"):
+            count.value = 0
+            forward = name == "bt_relu_forward"
+            status = getattr(lib, name)(*((IN, n, dtype, OUT, BITMAP, None) if forward else (BITMAP, IN, n, dtype, OUT, None)))
+            print(name, dtype, n, status)
+            for r in rows[:count.value]:
+                grid, block, a, b, c, d = r
+                at_in, length, out, bitmap = (a, b, c, d) if forward else (b, c, d, a)
+                print("launch", grid, block, at_in - IN, length, out - OUT, bitmap - BITMAP)
+"""
+
+
+def test_streams_over_more_than_a_grid_holds_are_cut(bt, tmp_path):
+    """A grid holds less than 2^32 threads, and these calls take 16 bytes a thread: from 64 GiB on in several launches, which
+    cover the tensor from its first element to its last, each beginning at a word of the bitmap.  What is launched is
+    recorded in the place of the runtime's launch, so nothing needs memory or a GPU."""
+    import subprocess
+    import sys
+    src, stub, script = tmp_path / "stub.c", tmp_path / "libstub.so", tmp_path / "record.py"
+    src.write_text(_RECORDER)
+    script.write_text(_RECORD)
+    subprocess.check_call(["gcc", "-O1", "-fPIC", "-shared", str(src), "-o", str(stub)])
+    sizes = [1, 12345, 1 << 30, (1 << 33) - 1, 1 << 33, (1 << 34) - 4096, 1 << 34, (1 << 34) + 5, (1 << 36) + 777]
+    out = subprocess.run([sys.executable, str(script), str(stub), bt.LIB_PATH] + [str(n) for n in sizes], check=True, capture_output=True, text=True).stdout
+    calls, width = [], {bt.BT_F32: 4, bt.BT_F16: 2, bt.BT_BF16: 2, bt.BT_F64: 8}
+    for line in out.splitlines():
+        word, *numbers = line.split()
+        if word == "launch":
+            calls[-1][-1].append([int(v) for v in numbers])
+        else:
+            calls.append((word, *[int(v) for v in numbers], []))
+    assert len(calls) == 3 * 4 * len(sizes)
+    for name, dtype, n, status, launches in calls:
+        s, at = width[dtype], 0
+        assert status == 0 and launches, (name, dtype, n)
+        assert len(launches) == 1 or n * s > 1 << 35, (name, dtype, n)
+        for grid, block, at_in, length, at_out, at_bitmap in launches:
+            assert grid * block < 1 << 32 and grid == -(-length * s // (16 * block)), (name, dtype, n)
+            assert at % 32 == 0 and (at_in, at_out, at_bitmap) == (at * s, at * s, at // 8), (name, dtype, n)
+            at += length
+        assert at == n, (name, dtype, n)

@@ -82,3 +82,29 @@ def test_tensor_of_more_than_2_to_32_elements(oracle):
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int16), x.view(torch.int16))
     assert int(ws[8:12].cpu().numpy().view(np.uint32)[0]) == 0, "a bounded wait ran out"
+
+
+def test_streams_of_more_than_one_launch():
+    """ReLU with its bitmap and its backward, in place, on a little more than 32 GiB, which is where a second launch begins: every
+    element against torch, in slices made again from their seeds."""
+    import paper_2110_15362_amd.bittrain as bt
+    n, chunk = (1 << 34) + 4101, 1 << 28
+    bounds = [(lo, min(n, lo + chunk)) for lo in range(0, n, chunk)]
+
+    def bits(seed, lo, hi):
+        g = torch.Generator(device="cuda").manual_seed(seed + lo // chunk)
+        return torch.randint(-(1 << 15), 1 << 15, (hi - lo,), generator=g, device="cuda", dtype=torch.int16)
+    x = torch.empty(n, dtype=torch.int16, device="cuda")
+    bitmap = torch.full(((n + 31) // 32 + 1,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    for lo, hi in bounds:
+        x[lo:hi] = bits(1000, lo, hi)
+    h = x.view(torch.bfloat16)
+    bt.bt_relu_forward(h, h, bitmap[:-1])
+    for lo, hi in bounds:
+        assert torch.equal(x[lo:hi], torch.relu(bits(1000, lo, hi).view(torch.bfloat16)).view(torch.int16)), lo
+        x[lo:hi] = bits(5000, lo, hi)
+    bt.bt_relu_backward_from_bitmap(bitmap[:-1], h, h)
+    for lo, hi in bounds:
+        kept = torch.relu(bits(1000, lo, hi).view(torch.bfloat16)).view(torch.int16) != 0
+        assert torch.equal(x[lo:hi], torch.where(kept, bits(5000, lo, hi), 0)), lo
+    assert int(bitmap[-1].item()) == 0x5A5A5A5A
