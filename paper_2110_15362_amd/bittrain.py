@@ -103,6 +103,9 @@ def lib():
         L.bt_workspace_status.restype = ci
         L.bt_workspace_status.argtypes = [vp, vp, vp]
         from . import _call as call
+        built_for = getattr(call, "torch_version", "unknown")
+        if built_for != str(torch.__version__):      # it reads tensor objects by that torch's layouts
+            raise ImportError("_call.so was built for torch %s, this is %s: build it again" % (built_for, torch.__version__))
         call.bind(tuple(ctypes.cast(getattr(L, f), vp).value for f in _CALLS), _DTYPES, dtype_code, BitTrainError, _stream_handle,
                   hasattr(torch._C, "_cuda_getCurrentRawStream"))
         _call = call      # first: other threads go by _lib

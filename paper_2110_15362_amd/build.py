@@ -1,6 +1,7 @@
 """Build libbittrain.so for gfx950 with hipcc (cross-compiles without a GPU), and the binding's call module with g++."""
 import importlib.util
 import os
+import re
 import subprocess
 import sysconfig
 
@@ -46,7 +47,10 @@ def build_bench_aids(verbose=False, extra_flags=()):
 def build_call(verbose=False):
     torch = os.path.dirname(importlib.util.find_spec("torch").origin)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    with open(os.path.join(torch, "version.py")) as f:      # (the module tells which torch it was compiled with)
+        version = re.search(r"^__version__\s*=\s*['\"]([^'\"]+)", f.read(), re.M).group(1)
     cmd = ["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           '-DBT_TORCH_VERSION="%s"' % version,
            "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(torch, "include"),
            "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
            CALL_SRC, "-o", CALL_LIB, "-L", os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]

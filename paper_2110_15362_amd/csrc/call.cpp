@@ -9,7 +9,8 @@
  *   any     else: the attributes of the tensors are read as any Python caller would read them (1.1 to 1.5 us a call), so
  *           subclasses, wrappers and modes see what they have always seen.  Whatever is wrong with a tensor is
  *           reported from here.
- * The library itself is loaded by bittrain.py, which hands over the addresses of the calls (bind).
+ * The library itself is loaded by bittrain.py, which hands over the addresses of the calls (bind), once it has compared the torch
+ * that this file was compiled with (torch_version) to the one that is there.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -411,5 +412,10 @@ PyMODINIT_FUNC PyInit__call(void) {
     s_element_size = PyUnicode_InternFromString("element_size");
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     if (!s_is_cuda || !s_is_contiguous || !s_dtype || !s_numel || !s_element_size || !s_data_ptr) return NULL;
-    return PyModule_Create(&module);
+    PyObject *const m = PyModule_Create(&module);
+    if (m != NULL && PyModule_AddStringConstant(m, "torch_version", BT_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return NULL;
+    }
+    return m;
 }

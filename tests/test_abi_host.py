@@ -583,3 +583,14 @@ def test_streams_over_more_than_a_grid_holds_are_cut(bt, tmp_path):
             assert at % 32 == 0 and (at_in, at_out, at_bitmap) == (at * s, at * s, at // 8), (name, dtype, n)
             at += length
         assert at == n, (name, dtype, n)
+
+
+def test_a_call_module_built_for_another_torch_is_refused(bt, monkeypatch):
+    """It reads tensor objects by the layouts of the torch it was compiled with."""
+    import torch
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + ".1")
+    monkeypatch.setattr(bt, "_lib", None)
+    monkeypatch.setattr(bt, "_call", None)
+    with pytest.raises(ImportError, match="built for torch"):
+        bt.lib()
+    assert bt._lib is None and bt._call is None
