@@ -131,6 +131,16 @@ def test_argument_errors_are_found_on_the_host(bt):
     assert relu(bm=None) == 1 and relu(g=None) == 1 and relu(gi=None) == 1
     assert relu(g=A + 2) == 3 and relu(gi=A + 8) == 3 and relu(bm=A + 1) == 3
     assert relu(n=0, bm=None, g=None, gi=None) == 0
+    assert relu(n=(1 << 37) + 1) == 6
+
+    def relu_forward(x=A, n=1000, dt=bt.BT_F16, out=A, bm=A):
+        return L.bt_relu_forward(x, n, dt, out, bm, None)
+
+    assert relu_forward(dt=4) == 2
+    assert relu_forward(x=None) == 1 and relu_forward(out=None) == 1 and relu_forward(bm=None) == 1
+    assert relu_forward(x=A + 2) == 3 and relu_forward(out=A + 8) == 3 and relu_forward(bm=A + 1) == 3
+    assert relu_forward(n=0, x=None, out=None, bm=None) == 0
+    assert relu_forward(n=(1 << 37) + 1) == 6
     assert L.bt_workspace_init(None, 100, None) == 1
     assert L.bt_workspace_init(A + 1, 100, None) == 3
 
@@ -412,7 +422,7 @@ def _binding_calls():
             "bt_decompress": (("bitmap", "values", "out", "workspace"), None),
             "bt_decompress_indexed": (("bitmap", "values", "index", "out"), None),
             "bt_relu_backward_from_bitmap": (("bitmap", "grad_out", "grad_in"), None),
-            "bt_mask_apply": (("bitmap", "x", "out"), None)}
+            "bt_mask_apply": (("bitmap", "x", "out"), None), "bt_relu_forward": (("x", "out", "bitmap"), None)}
 
 
 @pytest.mark.parametrize("name", sorted(_binding_calls()))
@@ -450,7 +460,7 @@ def test_binding_refuses_what_does_not_fit(bt, name):
            ("dense_out", _FakeTensor(n, torch.float16), TypeError, "must match x"),
            ("grad_in", _FakeTensor(n - 1, torch.float32), TypeError, "grad_in must match"),
            ("grad_in", _FakeTensor(n, torch.bfloat16), TypeError, "grad_in must match")]
-    if name == "bt_mask_apply":
+    if name in ("bt_mask_apply", "bt_relu_forward"):
         bad += [("out", _FakeTensor(n - 1, torch.float32), TypeError, "out must match x"),
                 ("out", _FakeTensor(n, torch.float16), TypeError, "out must match x")]
     for a, t_bad, error, text in bad:
@@ -495,6 +505,7 @@ def test_binding_takes_empty_tensors_and_keywords(bt):
     assert bt.bt_decompress(bitmap=w, values=f, out=f, workspace=_FakeTensor(1 << 16, torch.uint8), stream=0) is None
     assert bt.bt_relu_backward_from_bitmap(w, grad_out=f, grad_in=f, stream=0) is None
     assert bt.bt_mask_apply(w, f, f, stream=0) is None
+    assert bt.bt_relu_forward(f, out=f, bitmap=w, stream=0) is None
     assert bt.bt_decompress_indexed(w, f, _FakeTensor(0, torch.int64, ptr=0), f, stream=0) is None
 
 

@@ -127,7 +127,7 @@ def test_relu_forward_is_torch_relu_with_its_bitmap(ag, dt):
         top = -(1 << (8 * width - 1))      # the sign
         special = torch.tensor([0, 1, inf - 1, inf, inf + 1, top - 1 & 0x7FFFFFFF, top, top + 1, top + inf - 1, top + inf, top + inf + 1, -1],
                                dtype=torch.int64, device="cuda").to(iv)
-    bits = torch.randint(torch.iinfo(iv).min, torch.iinfo(iv).max, (last + 5,), generator=g, device="cuda", dtype=iv)
+    bits = torch.randint(torch.iinfo(iv).min, torch.iinfo(iv).max, (last + 5 + 16,), generator=g, device="cuda", dtype=iv)
     bits[:special.numel()] = special
     block = 4096 // width
     for n in (1, 31, 33, block - 1, block, block + 1, 65 * block + 7, 70000, last, last + 5):
@@ -136,6 +136,7 @@ def test_relu_forward_is_torch_relu_with_its_bitmap(ag, dt):
             x = bits[:n + 16].clone()
             out = x if inplace else torch.full_like(x, 0x5A)
             guard = out[n:].clone()
+            assert guard.numel() == 16
             bitmap = torch.full((words + 2,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
             want = torch.relu(x[:n].clone().view(dt)).view(iv)
             bt.bt_relu_forward(x[:n].view(dt), out[:n].view(dt), bitmap[:words])
@@ -180,10 +181,14 @@ def test_stash_keeps_what_a_failed_compression_was_given(ag, deferred, monkeypat
         return stash.stats
     assert step(0)["compressed"] == 1
     places = len(st.places)
+
+    def distinct():
+        return len({p.address for p in st.places}) == len(st.places)
     with pytest.warns(UserWarning, match="gave up"):
         assert step(1)["failed"] == 1
+    assert len(st.places) == places and distinct()
     stats = step(0)
-    assert stats["compressed"] == 1 and stats["failed"] == 0 and len(st.places) == places
+    assert stats["compressed"] == 1 and stats["failed"] == 0 and len(st.places) == places and distinct()
 
 
 def test_bitmap_relu_in_a_concatenation(ag):

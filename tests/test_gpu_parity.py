@@ -841,35 +841,40 @@ def test_binding_sees_the_same_in_every_kind_of_tensor(gpu, oracle):
 
 
 @pytest.mark.parametrize("dt", DTYPES)
-@pytest.mark.parametrize("rows", [2, 4, 8])
-def test_last_tiles_that_end_anywhere(gpu, oracle, dt, rows):
-    """The last tile of a tensor, in every plan (tiles of two and four rows, of eight with a grid scan), ending around vectors, rows,
-    waves' quarters and the tile: compressed, pruned with a threshold below zero (nothing beyond the end is kept, although
-    what lies there in memory would be), with a dense output beside, restored."""
+@pytest.mark.parametrize("rows,tiles", [(2, 3), (4, 70), (8, 200), (8, 261)])
+def test_last_tiles_that_end_anywhere(gpu, oracle, dt, rows, tiles):
+    """The last tile of a tensor, in every plan (tiles of two and four rows, of eight without and with a grid scan), ending around
+    vectors, rows, waves' quarters and the tile: compressed, pruned with a threshold below zero (nothing beyond the end is kept,
+    although what lies there in memory would be), with a dense output beside, restored."""
     import paper_2110_15362_amd.bittrain as bt
     dtype = wl.DTYPES[dt]
     vec, row = 16 // dtype.itemsize, 1024 // dtype.itemsize
     quarter, tile = rows * row, 4 * rows * row
-    whole = {2: 3, 4: 70, 8: 261}[rows] * tile
+    whole = tiles * tile
     ws = bt.new_workspace(whole + tile, dtype)
     for i, r in enumerate((1, vec - 1, vec, vec + 1, 2 * vec + 1, row - 1, row, row + 1, quarter - 1, quarter, quarter + vec + 1, 3 * quarter + 5, tile - 1)):
         n = whole + r
         x = wl.random_sparse(n, dt, 0.4, seed=9100 + i)
         buf = torch.ones(n + 64, dtype=dtype, device="cuda")      # what a read beyond the end would find
         buf[:n] = x.cuda()
-        for thr in (None, -0.5):
-            want = wl.bits(x) if thr is None else oracle.prune(wl.bits(x), dt, thr)
+        want = wl.bits(x)
+        for call in ("compress", "pruned", "activation"):
+            if call == "pruned":
+                want = oracle.prune(want, dt, -0.5)
             o_bitmap, o_values, o_nnz = oracle.compress(want)
             bitmap = torch.full((o_bitmap.size + 2,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
             values, dense = torch.zeros(n, dtype=dtype, device="cuda"), torch.full((n + 64,), 7, dtype=dtype, device="cuda")
             nnz = torch.zeros(1, dtype=torch.int64, device="cuda")
-            if thr is None:
+            if call == "compress":
                 bt.bt_compress(buf[:n], bitmap[:o_bitmap.size], values, nnz, ws)
-                bt.bt_decompress(bitmap[:o_bitmap.size], values, dense[:n], ws)
+            elif call == "pruned":
+                bt.bt_compress_pruned(buf[:n], -0.5, bitmap[:o_bitmap.size], values, nnz, ws)
             else:
-                bt.bt_activation_compress(buf[:n], thr, dense[:n], bitmap[:o_bitmap.size], values, nnz, ws)
+                bt.bt_activation_compress(buf[:n], -0.5, dense[:n], bitmap[:o_bitmap.size], values, nnz, ws)
+            if call != "activation":
+                bt.bt_decompress(bitmap[:o_bitmap.size], values, dense[:n], ws)
             torch.cuda.synchronize()
-            assert int(nnz.item()) == o_nnz, (n, thr)
-            assert np.array_equal(bitmap.cpu().numpy().view(np.uint32)[:-2], o_bitmap) and bool((bitmap[-2:] == 0x5A5A5A5A).all()), (n, thr)
-            assert np.array_equal(wl.bits(values[:o_nnz].cpu()), o_values[:o_nnz]), (n, thr)
-            assert np.array_equal(wl.bits(dense[:n].cpu()), want) and bool((dense[n:] == 7).all()), (n, thr)
+            assert int(nnz.item()) == o_nnz, (n, call)
+            assert np.array_equal(bitmap.cpu().numpy().view(np.uint32)[:-2], o_bitmap) and bool((bitmap[-2:] == 0x5A5A5A5A).all()), (n, call)
+            assert np.array_equal(wl.bits(values[:o_nnz].cpu()), o_values[:o_nnz]), (n, call)
+            assert np.array_equal(wl.bits(dense[:n].cpu()), want) and bool((dense[n:] == 7).all()), (n, call)
