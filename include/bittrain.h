@@ -19,7 +19,8 @@
  *   - a cleared bit restores +0 (all-zero bits) of the element width.
  *   - tensors are flat, contiguous buffers; the shape stays with the caller.
  *
- * Every pointer named d_* is DEVICE memory owned by the caller.  The library
+ * Every pointer named d_* is DEVICE memory owned by the caller (d_nnz may also be pinned
+ * host memory, see bt_compress).  The library
  * allocates nothing, frees nothing and never synchronises: each device call
  * enqueues its kernel(s) on `stream` and returns.  Argument errors are found on
  * the host before anything is launched; nothing is written in that case.
@@ -150,7 +151,10 @@ bt_status bt_workspace_init(void *d_workspace, size_t workspace_bytes, bt_stream
  *               complete, and the caller sees the overflow as *d_nnz > values_cap.
  *               The worst case is n.
  *   d_nnz       one uint64, 8-byte aligned, written by the kernel: valid once
- *               `stream` has reached this call.
+ *               `stream` has reached this call.  It may also be pinned host memory that the
+ *               device can address (hipHostMalloc): the host may read it once it has waited for the
+ *               stream or for an event behind the call.  A call that gives up a wait, or finds a
+ *               workspace on which one was given up, leaves it as it was.
  *   d_workspace bt_workspace_bytes(n, dtype) bytes, 128-byte aligned, initialised
  *               once with bt_workspace_init.  A workspace must not be shared by
  *               two calls that can be in flight at the same time: calls that use

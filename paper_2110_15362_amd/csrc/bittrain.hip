@@ -349,7 +349,7 @@ __device__ __forceinline__ uint32_t bitmap_bits(const uint32_t *bitmap, uint64_t
 // end in a numbering of SLOTS (= workspace entries): a call on one tensor has slot == tile,
 // in a batched call a tensor's first tile has the slot behind the previous tensor's last one.  Prefixes restart
 // at 0 with every tensor and each tensor's total goes to its nnz.  The kernels see the call through a
-// small interface (count, start, tiles, at, and the per-tensor pointers) that the
+// small interface (slots, at, and the per-tensor pointers) that the
 // single-tensor and the batched argument structs both provide; the per-tensor pointers of a
 // batched call travel as kernel arguments and are read with scalar loads.
 
@@ -395,9 +395,7 @@ struct CompressOne {
     uint64_t *index_;
     void *dense_;
     uint32_t tiles_;
-    __device__ __forceinline__ uint32_t count() const { return 1; }
     __device__ __forceinline__ uint32_t slots() const { return tiles_; }
-    __device__ __forceinline__ uint32_t tiles(uint32_t) const { return tiles_; }
     __device__ __forceinline__ Slot at(uint32_t slot) const { return Slot{0, slot}; }
     __device__ __forceinline__ const void *in(uint32_t) const { return in_; }
     __device__ __forceinline__ uint64_t n(uint32_t) const { return n_; }
@@ -424,7 +422,6 @@ struct CompressMany {
     __device__ __forceinline__ uint32_t count() const { return lay.count; }
     __device__ __forceinline__ uint32_t start(uint32_t i) const { return lay.start[i]; }
     __device__ __forceinline__ uint32_t slots() const { return lay.start[lay.count]; }
-    __device__ __forceinline__ uint32_t tiles(uint32_t i) const { return lay.start[i + 1] - lay.start[i]; }
     __device__ __forceinline__ Slot at(uint32_t slot) const { return lay.at(slot); }
     __device__ __forceinline__ const void *in(uint32_t i) const { return in_[i]; }
     __device__ __forceinline__ uint64_t n(uint32_t i) const { return n_[i]; }
@@ -447,9 +444,7 @@ struct DecompressOne {
     uint64_t n_;
     void *out_;
     uint32_t tiles_;
-    __device__ __forceinline__ uint32_t count() const { return 1; }
     __device__ __forceinline__ uint32_t slots() const { return tiles_; }
-    __device__ __forceinline__ uint32_t tiles(uint32_t) const { return tiles_; }
     __device__ __forceinline__ Slot at(uint32_t slot) const { return Slot{0, slot}; }
     __device__ __forceinline__ const uint32_t *bitmap(uint32_t) const { return bitmap_; }
     __device__ __forceinline__ const void *values(uint32_t) const { return values_; }
@@ -469,10 +464,7 @@ struct DecompressMany {
     const uint64_t *index_[kMaxBatchDecompress];
     uint64_t n_[kMaxBatchDecompress];
     void *out_[kMaxBatchDecompress];
-    __device__ __forceinline__ uint32_t count() const { return lay.count; }
-    __device__ __forceinline__ uint32_t start(uint32_t i) const { return lay.start[i]; }
     __device__ __forceinline__ uint32_t slots() const { return lay.start[lay.count]; }
-    __device__ __forceinline__ uint32_t tiles(uint32_t i) const { return lay.start[i + 1] - lay.start[i]; }
     __device__ __forceinline__ Slot at(uint32_t slot) const { return lay.at(slot); }
     __device__ __forceinline__ const uint32_t *bitmap(uint32_t i) const { return bitmap_[i]; }
     __device__ __forceinline__ const void *values(uint32_t i) const { return values_[i]; }
