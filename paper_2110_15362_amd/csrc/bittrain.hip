@@ -1292,22 +1292,22 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
 // vectors: the inner ones (at most 255, all fully inside the range) go PHASE to a
 // lane; of the first and the last vector, lane j < E takes element j of the first
 // and lane E + j element j of the last, each only if it lies inside the range.
-template <int S, int R> struct Fetched {
-    uint4 inner[Geo<S, R>::PHASE];
+template <int S> struct Fetched {
+    uint4 inner[Geo<S>::PHASE];
     typename std::conditional<S == 8, uint64_t, uint32_t>::type edge;
 };
 
-template <int S, int R>
+template <int S>
 __device__ __forceinline__ void strip_fetch(const char *g0_ptr, const uint32_t pad, const uint32_t cnt, const int lane,
-                                            Fetched<S, R> &f) {
-    constexpr int E = Geo<S, R>::E;
-    constexpr int PHASE = Geo<S, R>::PHASE;
-    static_assert(PHASE * Geo<S, R>::ROW / E + 1 <= 2 + PHASE * kWaveSize, "a phase must fit PHASE inner vectors per lane");
+                                            Fetched<S> &f) {
+    constexpr int E = Geo<S>::E;
+    constexpr int PHASE = Geo<S>::PHASE;
+    static_assert(PHASE * Geo<S>::ROW / E + 1 <= 2 + PHASE * kWaveSize, "a phase must fit PHASE inner vectors per lane");
     const char *gvec = g0_ptr - (size_t)pad * S;
     const uint32_t hi_valid = pad + cnt;
     const uint32_t n_vec = cnt ? (hi_valid + E - 1) / E : 0;
 #pragma unroll
-    for (int i = 0; i < Geo<S, R>::PHASE; ++i) {
+    for (int i = 0; i < Geo<S>::PHASE; ++i) {
         const uint32_t v = 1u + (uint32_t)lane + (uint32_t)kWaveSize * i;
         f.inner[i] = make_uint4(0, 0, 0, 0);
         if (v + 1 < n_vec) f.inner[i] = stream_load<kDecompressNtLoad>(reinterpret_cast<const uint4 *>(gvec + (size_t)v * kVecBytes));
@@ -1324,14 +1324,14 @@ __device__ __forceinline__ void strip_fetch(const char *g0_ptr, const uint32_t p
     }
 }
 
-template <int S, int R>
+template <int S>
 __device__ __forceinline__ void strip_commit(unsigned char *strip, const uint32_t pad, const uint32_t cnt, const int lane,
-                                             const Fetched<S, R> &f) {
-    constexpr int E = Geo<S, R>::E;
+                                             const Fetched<S> &f) {
+    constexpr int E = Geo<S>::E;
     const uint32_t hi_valid = pad + cnt;
     const uint32_t n_vec = cnt ? (hi_valid + E - 1) / E : 0;
 #pragma unroll
-    for (int i = 0; i < Geo<S, R>::PHASE; ++i) {
+    for (int i = 0; i < Geo<S>::PHASE; ++i) {
         const uint32_t v = 1u + (uint32_t)lane + (uint32_t)kWaveSize * i;
         if (v + 1 < n_vec) *reinterpret_cast<uint4 *>(strip + (size_t)v * kVecBytes) = f.inner[i];
     }
@@ -1356,17 +1356,21 @@ __device__ __forceinline__ void strip_commit(unsigned char *strip, const uint32_
 // (Read once per row by the lanes that share a word, and ranked by row sums, they cost a wave eight loads of 32 bytes,
 // which keep the address units busy before anything else can start, and four times the DPP steps.  Measured, before /
 // after, us: fp32 25.7 M 27.0 / 26.7, 206 M 214 / 212, fp16 206 M at 5 % 142.8 / 141.7.)
-template <int S, int R> struct Quarter { uint32_t w[Geo<S, R>::QPL]; };
+// (fetch_values, commit_values and expand_row of the restoration without the scan are three of these steps again, for a workgroup
+// instead of a wave.  As one set of functions for both, or with the expansion alone shared, this kernel is scheduled otherwise and
+// mostly slower.  Measured, us, as it is / one set / expansion shared: bf16 3 M elements at 50 % zeros 6.75 / 6.81 / 6.79, the 49 tensors
+// of a ResNet-50 at one image in bf16, 70 % zeros, 10.89 / 10.97 / 10.98, fp64 25.7 M 59.0 / 59.6 / 59.1, fp32 100 M 105.6 / 105.5 / 105.8.)
+template <int S> struct Quarter { uint32_t w[Geo<S>::QPL]; };
 
 // Words at or beyond the bitmap's end read as 0, bits at or beyond n are cleared (Algorithm 2 visits n bits).
-template <int S, int R>
-__device__ __forceinline__ Quarter<S, R> quarter_load(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane, const int wave) {
-    using G = Geo<S, R>;
+template <int S>
+__device__ __forceinline__ Quarter<S> quarter_load(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane, const int wave) {
+    using G = Geo<S>;
     static_assert(G::QPL <= 2, "one load");
     typedef uint32_t word2 __attribute__((ext_vector_type(2), aligned(4)));      // (the bitmap is 4-byte aligned)
     const uint64_t first = (uint64_t)tile * G::TILE_WORDS + (uint64_t)wave * G::WAVE_WORDS;
     const bool full = (uint64_t)(tile + 1) * G::TILE <= n;
-    Quarter<S, R> q;
+    Quarter<S> q;
 #pragma unroll
     for (int j = 0; j < G::QPL; ++j) q.w[j] = 0;
     if (__builtin_expect(full, 1)) {
@@ -1394,19 +1398,19 @@ __device__ __forceinline__ Quarter<S, R> quarter_load(const uint32_t *bitmap, co
     return q;
 }
 
-template <int S, int R> struct Restoring {            // a quarter tile between restore_ranks and restore_store
-    static constexpr int PHASES = R / Geo<S, R>::PHASE;
-    uint32_t mp[Geo<S, R>::MW], rank2[R / 2];          // ranks inside the quarter, two rows to a register
+template <int S> struct Restoring {            // a quarter tile between restore_ranks and restore_store
+    static constexpr int PHASES = kRows / Geo<S>::PHASE;
+    uint32_t mp[Geo<S>::MW], rank2[kRows / 2];          // ranks inside the quarter, two rows to a register
     uint32_t before[PHASES + 1];                       // set bits of the quarter before each phase, and all of them
-    Fetched<S, R> fetched[PHASES];
+    Fetched<S> fetched[PHASES];
     uint32_t pads[PHASES], cnts[PHASES];
 };
 
 // (1) this lane's bits of the bitmap (G lanes take E bits each of one word), and Algorithm 2's counter j as ranks.  Returns the
 //     set bits of this wave's quarter of the tile.  `strip`: the wave's LDS, free until the values are put into it.
-template <int S, int R>
-__device__ __forceinline__ uint32_t restore_ranks(const Quarter<S, R> &q, unsigned char *strip, const int lane, Restoring<S, R> &r) {
-    using G = Geo<S, R>;
+template <int S>
+__device__ __forceinline__ uint32_t restore_ranks(const Quarter<S> &q, unsigned char *strip, const int lane, Restoring<S> &r) {
+    using G = Geo<S>;
     constexpr int E = G::E;
     static_assert(8 * G::WAVE_WORDS <= G::LDS_WAVE && G::WAVE < 65536, "a word and its rank per entry; ranks in 16 bits");
     uint32_t mine = 0;
@@ -1415,10 +1419,10 @@ __device__ __forceinline__ uint32_t restore_ranks(const Quarter<S, R> &q, unsign
     const uint32_t incl = wave_inclusive_sum(mine);
     uint32_t rank = incl - mine;
 #pragma unroll
-    for (int ph = 0; ph < Restoring<S, R>::PHASES; ++ph)       // the lane that holds the phase's first word
+    for (int ph = 0; ph < Restoring<S>::PHASES; ++ph)       // the lane that holds the phase's first word
         r.before[ph] = (uint32_t)__builtin_amdgcn_readlane((int)rank, ph * G::PHASE * G::WPR / G::QPL);
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-    r.before[Restoring<S, R>::PHASES] = total;
+    r.before[Restoring<S>::PHASES] = total;
     bt_u2 *const entries = reinterpret_cast<bt_u2 *>(strip);
     if (G::WAVE_WORDS >= kWaveSize || lane < G::WAVE_WORDS) {
 #pragma unroll
@@ -1433,7 +1437,7 @@ __device__ __forceinline__ uint32_t restore_ranks(const Quarter<S, R> &q, unsign
     const uint32_t shift = (uint32_t)E * (uint32_t)(lane % G::G);
     const uint32_t below = (1u << shift) - 1u;
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
+    for (int k = 0; k < kRows; ++k) {
         const bt_u2 e = entries[k * G::WPR + lane / G::G];
         r.mp[k / G::RPM] |= ((e.x >> shift) & ((1u << E) - 1u)) << (E * (k % G::RPM));
         const uint32_t at = e.y + (uint32_t)__popc(e.x & below);
@@ -1444,13 +1448,13 @@ __device__ __forceinline__ uint32_t restore_ranks(const Quarter<S, R> &q, unsign
 }
 
 // (2) ask for the values of every phase (PHASE rows each), so that all of them are in flight together
-template <int S, int R>
+template <int S>
 __device__ __forceinline__ void restore_fetch(const void *__restrict__ values, const uint64_t values_cap, const uint64_t tile_j,
-                                              const uint32_t before_wave, const int lane, Restoring<S, R> &r) {
-    using G = Geo<S, R>;
+                                              const uint32_t before_wave, const int lane, Restoring<S> &r) {
+    using G = Geo<S>;
     uint64_t g0 = tile_j + before_wave;                                   // Algorithm 2's j for this wave
 #pragma unroll
-    for (int ph = 0; ph < R / G::PHASE; ++ph) {
+    for (int ph = 0; ph < Restoring<S>::PHASES; ++ph) {
         r.cnts[ph] = r.before[ph + 1] - r.before[ph];
         const char *gsrc = static_cast<const char *>(values) + g0 * S;
         r.pads[ph] = (uint32_t)(reinterpret_cast<uintptr_t>(gsrc) & (kVecBytes - 1)) / S;
@@ -1458,22 +1462,22 @@ __device__ __forceinline__ void restore_fetch(const void *__restrict__ values, c
         // nothing at or beyond the capacity is read (an index that does not belong to the bitmap, a wait that ran out)
         if (g0 >= values_cap) r.cnts[ph] = 0;
         else if (values_cap - g0 < r.cnts[ph]) r.cnts[ph] = (uint32_t)(values_cap - g0);
-        strip_fetch<S, R>(gsrc, r.pads[ph], r.cnts[ph], lane, r.fetched[ph]);
+        strip_fetch<S>(gsrc, r.pads[ph], r.cnts[ph], lane, r.fetched[ph]);
         g0 += phase_total;
     }
 }
 
-template <int S, int R>
-__device__ __forceinline__ void restore_store(const Restoring<S, R> &r, const uint64_t n, void *__restrict__ out, const uint32_t tile,
+template <int S>
+__device__ __forceinline__ void restore_store(const Restoring<S> &r, const uint64_t n, void *__restrict__ out, const uint32_t tile,
                                               unsigned char *strip, const int lane, const int wave) {
-    using G = Geo<S, R>;
+    using G = Geo<S>;
     constexpr int E = G::E;
     const uint64_t wave_e0 = (uint64_t)tile * G::TILE + (uint64_t)wave * G::WAVE;
     const bool full = (uint64_t)(tile + 1) * G::TILE <= n;
 #pragma unroll
-    for (int ph = 0; ph < R / G::PHASE; ++ph) {
+    for (int ph = 0; ph < Restoring<S>::PHASES; ++ph) {
         if (ph != 0) wave_lds_sync();   // the previous phase's reads are done before the strip is reused
-        strip_commit<S, R>(strip, r.pads[ph], r.cnts[ph], lane, r.fetched[ph]);
+        strip_commit<S>(strip, r.pads[ph], r.cnts[ph], lane, r.fetched[ph]);
         wave_lds_sync();
         const uint32_t base = r.pads[ph] - r.before[ph];
 #pragma unroll
@@ -1523,9 +1527,9 @@ __device__ __forceinline__ void restore_store(const Restoring<S, R> &r, const ui
 // What a restoring wave does when the scanner's answer for its tile does not come: it counts the set
 // bits of the tensor's bitmap before the tile itself.  Slow (the whole bitmap up to the tile), but it
 // needs nothing from any other workgroup.  Every bit before a tile is a bit of the tensor, so no mask.
-template <int S, int R>
+template <int S>
 __device__ __noinline__ uint64_t prefix_from_bitmap(const uint32_t *__restrict__ bitmap, const uint32_t tile, const int lane) {
-    const uint64_t words = (uint64_t)tile * Geo<S, R>::TILE_WORDS;
+    const uint64_t words = (uint64_t)tile * Geo<S>::TILE_WORDS;
     uint64_t mine = 0;
     for (uint64_t w = (uint32_t)lane; w < words; w += kWaveSize) mine += (uint32_t)__popc(bitmap[w]);
 #pragma unroll
@@ -1552,8 +1556,7 @@ __device__ __noinline__ uint64_t prefix_from_bitmap(const uint32_t *__restrict__
 // started ends, whatever the others do, and every workgroup is started in the end.
 template <int S, class Job>
 __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(const Job job, char *ws) {
-    constexpr int R = kRows;
-    using G = Geo<S, R>;
+    using G = Geo<S>;
     __shared__ __attribute__((aligned(16))) unsigned char s_stage[kWaves * G::LDS_WAVE];
     __shared__ uint64_t s_tile_j;
     __shared__ uint32_t s_wave_total[kWaves];
@@ -1579,12 +1582,12 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
     // the bitmap words first: everything else waits for them
     const uint32_t *const bitmap = job.bitmap(sl.item);
     const uint64_t n = job.n(sl.item);
-    const Quarter<S, R> quarter = quarter_load<S, R>(bitmap, n, sl.tile, lane, wave);
+    const Quarter<S> quarter = quarter_load<S>(bitmap, n, sl.tile, lane, wave);
     BT_TL(slot, 0);
     // masks and ranks; what they add up to is this wave's share of the tile's count
-    Restoring<S, R> r;
+    Restoring<S> r;
     unsigned char *const strip = s_stage + wave * G::LDS_WAVE;
-    const uint32_t wave_total = restore_ranks<S, R>(quarter, strip, lane, r);
+    const uint32_t wave_total = restore_ranks<S>(quarter, strip, lane, r);
     const Epoch ep = epoch_of(header);
     if (lane == 0) s_wave_total[wave] = ep.failed ? kWaveFailed : wave_total;
     lds_barrier();                      // also: every wave has read the header before the first wave publishes anything
@@ -1604,14 +1607,14 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
     // Algorithm 2's counter j at the start of the tile: the first wave asks (one poller a tile keeps the
     // traffic on the workspace's few lines low) and passes the answer on through LDS
     if (wave == 0) {
-        const uint64_t v = wait_for_prefix(ws, slot, n_slots, ep.cur, polls, [&]() { return prefix_from_bitmap<S, R>(bitmap, sl.tile, lane); });
+        const uint64_t v = wait_for_prefix(ws, slot, n_slots, ep.cur, polls, [&]() { return prefix_from_bitmap<S>(bitmap, sl.tile, lane); });
         if (lane == 0) s_tile_j = v;
     }
     lds_barrier();
     const uint64_t tile_j = uniform64(s_tile_j);
     BT_TL(slot, 2);
-    restore_fetch<S, R>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
-    restore_store<S, R>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
+    restore_fetch<S>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
+    restore_store<S>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
     BT_TL(slot, 3);
     BT_TL_VALUE(slot, 5, polls);
 }
