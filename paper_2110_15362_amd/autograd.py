@@ -119,11 +119,11 @@ class _Packed:
 
 class _Pending:
     """What a deferred packing still waits for: nnz on its way to pinned host memory, the event behind the
-    compression, and the dense tensor, kept until the result is known to be good."""
-    __slots__ = ("packed", "dense", "place", "event", "ws", "lock", "taken")
+    compression on its stream, and the dense tensor, kept until the result is known to be good."""
+    __slots__ = ("packed", "dense", "place", "event", "ws", "stream", "lock", "taken")
 
-    def __init__(self, packed, dense, place, event, ws):
-        self.packed, self.dense, self.place, self.event, self.ws = packed, dense, place, event, ws
+    def __init__(self, packed, dense, place, event, ws, stream):
+        self.packed, self.dense, self.place, self.event, self.ws, self.stream = packed, dense, place, event, ws, stream
         self.lock, self.taken = threading.RLock(), False       # one thread may pack while another unpacks: the first settles it
 
 
@@ -186,7 +186,13 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
                 w.event.synchronize()
                 nnz = w.place.read()
                 w.place.give_back()
-                kept = self._settle(w.packed, nnz, w.packed.values, w.ws)
+                here = torch.cuda.current_stream()
+                if here == w.stream:
+                    kept = self._settle(w.packed, nnz, w.packed.values, w.ws)
+                else:                     # where backward unpacks it, and where the next call on the workspace is
+                    with torch.cuda.stream(w.stream):
+                        kept = self._settle(w.packed, nnz, w.packed.values, w.ws)
+                    here.wait_stream(w.stream)      # (who unpacks it here is behind the copy too)
             finally:
                 if not kept:
                     w.packed.dense, w.packed.bitmap, w.packed.values, w.packed.index = w.dense, None, None, None
@@ -219,7 +225,7 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
             event = torch.cuda.Event()
             event.record(stream)
             packed.pending = True
-            self._waiting.append(_Pending(packed, t.detach(), place, event, ws))
+            self._waiting.append(_Pending(packed, t.detach(), place, event, ws, stream))
             return packed
         scratch = st.take_scratch(n, t.dtype)
         try:

@@ -1,5 +1,6 @@
 """What BitmapStash does on the host around its compressions, without a GPU: the compressions, the events behind them and
 pinned memory are stand-ins, so every order of events and every failure can be had."""
+import contextlib
 import gc
 import threading
 import weakref
@@ -11,13 +12,26 @@ N = 4096
 NNZ = 100
 
 
+class _Stream(str):
+    def wait_stream(self, other):
+        self.__dict__.setdefault("waited", []).append(other)
+
+
 @pytest.fixture
 def ag(monkeypatch):
-    """The module, with ordinary host memory for pinned memory."""
+    """The module, with ordinary host memory for pinned memory and names for streams."""
     from paper_2110_15362_amd import autograd, bittrain
     bittrain.lib()
-    empty = torch.empty
+    empty, current = torch.empty, [_Stream("default")]
+
+    @contextlib.contextmanager
+    def stream(other):
+        current.append(other)
+        yield
+        current.pop()
     monkeypatch.setattr(torch, "empty", lambda *a, pin_memory=False, **k: empty(*a, **k))
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: current[-1])
+    monkeypatch.setattr(torch.cuda, "stream", stream)
     return autograd
 
 
@@ -38,8 +52,8 @@ class _Event:
 class _Values:
     """The worst-case buffer of a packing, which is cut to size by a copy."""
 
-    def __init__(self, failures=0):
-        self.failures = failures
+    def __init__(self, failures=0, on_copy=None):
+        self.failures, self.on_copy = failures, on_copy
 
     def __getitem__(self, cut):
         self.length = cut.stop
@@ -49,16 +63,18 @@ class _Values:
         if self.failures:
             self.failures -= 1
             raise torch.OutOfMemoryError("out of memory")
+        if self.on_copy is not None:
+            self.on_copy()
         return torch.zeros(self.length)
 
 
-def _waiting(ag, stash, st, values, event=None):
+def _waiting(ag, stash, st, values, event=None, stream="default"):
     """A packing of N elements, of which NNZ are stored, that `stash` has not settled yet."""
     p = ag._Packed(torch.zeros(N // 32, dtype=torch.int32), values, torch.zeros(1, dtype=torch.int64), torch.Size([N]), torch.float32, st.device)
     p.pending = True
     place = st.place()
     place.word[0] = NNZ
-    stash._waiting.append(ag._Pending(p, torch.ones(N), place, event or _Event(), None))
+    stash._waiting.append(ag._Pending(p, torch.ones(N), place, event or _Event(), None, stream))
     return p
 
 
@@ -104,6 +120,26 @@ def test_two_threads_settle_a_packing_once(ag):
     assert len(waits) == 1 and stash._waiting == []
     assert not p.pending and p.values.numel() == NNZ and stash.stats["compressed"] == 1
     assert len(st.places) == 8 and _distinct(st.places)
+
+
+@pytest.mark.parametrize("gave_up", [False, True])
+def test_a_packing_is_settled_on_the_stream_it_was_packed_on(ag, monkeypatch, gave_up):
+    """Wherever the host is by then (leaving the stash, packing on another stream): its values are read there in the backward pass,
+    which nothing else orders behind their copy, and so is its workspace used by the next call.  Work here is ordered behind it too."""
+    st = ag._StreamState(torch.device("cpu"))
+    stash, used = ag.BitmapStash(deferred=True), []
+
+    def note(*args):
+        used.append(torch.cuda.current_stream())
+    monkeypatch.setattr(ag.bt, "bt_workspace_init", note)
+    for stream in ("side", "default", "other"):
+        _waiting(ag, stash, st, _Values(on_copy=note), stream=_Stream(stream))
+        if gave_up:
+            stash._waiting[-1].place.word[0] = -1
+    with pytest.warns(UserWarning) if gave_up else contextlib.nullcontext():
+        stash._finish_waiting(block=True)
+    here = torch.cuda.current_stream()
+    assert used == ["side", "default", "other"] and here == "default" and here.waited == ["side", "other"]
 
 
 def test_leaving_the_stash_takes_its_hooks_off_though_settling_failed(ag):

@@ -191,6 +191,26 @@ def test_stash_keeps_what_a_failed_compression_was_given(ag, deferred, monkeypat
     assert stats["compressed"] == 1 and stats["failed"] == 0 and len(st.places) == places and distinct()
 
 
+def test_deferred_packings_of_another_stream(ag):
+    """Packed on one stream, settled where the host leaves the stash, on another, and unpacked on the first."""
+    x, ws = _mlp(4, torch.float32)
+    _forward(x, ws, torch.relu).backward()
+    ref = [t.grad.clone() for t in (x,) + ws]
+    for t in (x,) + ws:
+        t.grad = None
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    stash = ag.BitmapStash(min_numel=1024, deferred=True)
+    with stash:
+        with torch.cuda.stream(side):
+            loss = _forward(x, ws, torch.relu)
+    loss.backward()
+    torch.cuda.synchronize()
+    for r, t in zip(ref, (x,) + ws):
+        assert torch.equal(r, t.grad)
+    assert stash.stats["compressed"] >= 2 and stash.stats["failed"] == 0
+
+
 def test_bitmap_relu_in_a_concatenation(ag):
     """Its gradient is a view that begins where the other part ends, off every 16-byte boundary."""
     x = torch.randn(4099, device="cuda", requires_grad=True)
