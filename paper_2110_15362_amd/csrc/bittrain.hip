@@ -791,6 +791,10 @@ __device__ __forceinline__ bool any_wave_failed(const uint32_t (&totals)[kWaves]
 // (With thousands of tiles the same few lines would be polled by all of them at once.)
 constexpr uint32_t kDirectSlots = 256;
 static_assert(kDirectSlots % 128 == 0, "a lane takes two neighbouring slots of each 128");
+// Up to kQuarterSlots tiles all four waves of a tile read the counts, a quarter of the slots each (wait_for_quarter): one wave's
+// load of 128 counts and the registers for it, four times in a row, would cost more than the scanner's two hops.
+constexpr uint32_t kQuarterSlots = 512;
+static_assert(kQuarterSlots == 128 * kWaves, "two neighbouring slots a lane");
 
 // The number of values before `slot`, summed from the published counts by one wave, or false if they are not all there.
 __device__ __forceinline__ bool sum_counts(char *ws, const uint32_t slot, const uint32_t cur, uint64_t &sum) {
@@ -862,6 +866,41 @@ __device__ __forceinline__ uint64_t wait_for_counts(char *ws, const uint32_t slo
     }
     complete = last;
     return v;
+}
+
+// A wave's share of the wait in a launch of up to kQuarterSlots tiles: the number of values in the tiles before `slot` among the
+// wave's quarter of the slots, or kWaveFailed if the counts have not all been there for too many polls.
+__device__ __forceinline__ uint32_t wait_for_quarter(char *ws, const uint32_t slot, const bool last, const uint32_t cur, const int wave, uint32_t &polls) {
+    uint32_t *const hdr = reinterpret_cast<uint32_t *>(ws);
+    const bool deaf = told_nothing(hdr, last ? 2 : 1);
+    for (;;) {
+        const uint32_t at = 128u * (uint32_t)wave + 2u * (uint32_t)lane_number();
+        uint64_t two = 0;
+        if (at < slot) two = ws_load64(ws_count(ws, at, cur));
+        const uint32_t ca = at < slot ? (uint32_t)two : 1u, cb = at + 1 < slot ? (uint32_t)(two >> 32) : 1u;
+        if (__ballot(deaf || ca == 0 || cb == 0) == 0) return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(ca + cb - 2u), 63);
+        ++polls;
+        if (last ? polls >= wait_limit(hdr) : (polls & 255u) == 0 && polls > patience_of(hdr)) return kWaveFailed;
+        __builtin_amdgcn_s_sleep(kScannerSleep);
+    }
+}
+
+// What the four waves have found, added up.  If one has given up, every wave counts what precedes the tile from the call's input
+// (`itself`), and the call has failed if this is the last tile, which was to end it.
+template <class Itself>
+__device__ __forceinline__ uint64_t add_quarters(char *ws, const uint32_t (&found)[kWaves], const bool last, bool &complete, const Itself &itself) {
+    uint32_t sum = 0;
+    bool gave_up = false;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const uint32_t q = uniform32(found[w]);
+        gave_up = gave_up || q == kWaveFailed;
+        sum += q;
+    }
+    complete = last && !gave_up;
+    if (__builtin_expect(!gave_up, 1)) return sum;
+    if (last && threadIdx.x == 0) __hip_atomic_store(&reinterpret_cast<uint32_t *>(ws)[kHdrError], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return itself();
 }
 
 // Zero what the previous call left in the other copy of the workspace entries: the blocks of slots
@@ -999,9 +1038,9 @@ __device__ __forceinline__ uint64_t prefix_from_input(const void *__restrict__ i
     return wave_total_of(share);
 }
 
-// bt_compress and its relatives (pruning, dense output, tile index, batches).  Tiles of R rows a lane; without DIRECT
-// workgroup 0 is the scanner (one wave of it) and workgroup 1 + t compresses slot t, with it (small tensors, see
-// compress_common) workgroup t does and sums the counts before its tile itself.
+// bt_compress and its relatives (pruning, dense output, tile index, batches).  Tiles of R rows a lane; with DIRECT = 0
+// workgroup 0 is the scanner (one wave of it) and workgroup 1 + t compresses slot t, otherwise (launches on one tensor of up to
+// DIRECT tiles, see compress_common) workgroup t does and sums the counts before its tile itself.
 // 1. load: lane l of row k owns elements wave_e0 + k * ROW + l * E ... + E - 1 of its wave's quarter of the
 //    tile; all R rows are asked for at once.
 // 2. the test of Algorithm 1 (on the bit pattern), or the pruning test; masks packed RPM rows to a register;
@@ -1025,13 +1064,14 @@ __device__ __forceinline__ uint64_t prefix_from_input(const void *__restrict__ i
 // of this kernel -- as many workgroups as are resident, each taking tiles w, w + G, ..., the next tile's loads
 // asked for before the current tile's prefix wait, compacted values parked in rings in LDS -- was built and
 // measured: 1 % faster on a 25.7 M element fp32 tensor, 5 to 15 % slower on 16-bit and on larger tensors.)
-template <int S, int R, bool DIRECT, int KEEP, bool DENSE, class Job>
+template <int S, int R, int DIRECT, int KEEP, bool DENSE, class Job>
 __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Job job, char *ws, const double threshold, const float threshold_f) {
     using G = Geo<S, R>;
     constexpr int E = G::E;
     __shared__ __attribute__((aligned(16))) unsigned char s_stage[G::STAGE + kVecBytes];
     __shared__ uint64_t s_tile_prefix;
-    __shared__ uint32_t s_wave_total[kWaves];
+    __shared__ uint32_t s_wave_total[kWaves], s_found[kWaves];
+    constexpr bool kQuarters = DIRECT > (int)kDirectSlots;
     const uint32_t n_slots = gridDim.x - (DIRECT ? 0u : 1u);
     if (!DIRECT && blockIdx.x == 0) {
         if (threadIdx.x < kWaveSize && !epoch_of(read_header(ws)).failed) scan_counts<3>(ws, job);
@@ -1199,7 +1239,7 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
     const bool dense_early = DENSE && n_slots <= kDenseEarlySlots<S>;
     // The bitmap words; the wave that polls keeps its own until afterwards, because a store in flight delays the polling
     // loads, which share its completion counter.  (For 16-bit elements in tiles of eight rows it has no register to keep them in.)
-    const bool words_early = (S == 2 && R == kRows) || dense_early || wave != 0;
+    const bool words_early = (S == 2 && R == kRows) || dense_early || (!kQuarters && wave != 0);
     if (words_early) store_words();
 
     // The values: if the tile's fit LDS together (62 % of its elements: most activations), all of them are compacted into
@@ -1228,23 +1268,36 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
 
     if (dense_early) store_dense();
 
-    // The first wave waits for the tile's prefix.
+    // The wait for the tile's prefix, the index in the value array of its first value: by the first wave, or by all.
     uint32_t polls = 0;
     bool complete = false;
-    if (wave == 0) {
-        const auto itself = [&]() { return prefix_from_input<S, R, KEEP>(in, tile, threshold_f, threshold, lane_number()); };
-        const uint64_t v = DIRECT ? wait_for_counts(ws, slot, n_slots, ep.cur, polls, complete, itself)
-                                  : wait_for_prefix(ws, slot, n_slots, ep.cur, polls, itself);
-        if (lane_number() == 0) {
-            s_tile_prefix = v;
-            uint64_t *const index = job.index(sl.item);
-            // Algorithm 2's j at the start of this tile, for bt_decompress_indexed; the index has the tiles of kRows rows
-            constexpr uint32_t kPerEntry = kRows / R;
-            if (index != nullptr && tile % kPerEntry == 0) index[tile / kPerEntry] = v;
+    uint64_t tile_g0;
+    const auto itself = [&]() { return prefix_from_input<S, R, KEEP>(in, tile, threshold_f, threshold, lane_number()); };
+    // Algorithm 2's j at the start of this tile, for bt_decompress_indexed; the index has the tiles of kRows rows
+    const auto store_index = [&](const uint64_t j) __attribute__((always_inline)) {
+        uint64_t *const index = job.index(sl.item);
+        constexpr uint32_t kPerEntry = kRows / R;
+        if (index != nullptr && tile % kPerEntry == 0) index[tile / kPerEntry] = j;
+    };
+    if constexpr (kQuarters) {
+        const bool last = slot + 1 == n_slots;
+        const uint32_t mine = wait_for_quarter(ws, slot, last, ep.cur, wave, polls);
+        if (lane_number() == 0) s_found[wave] = mine;
+        lds_barrier();
+        tile_g0 = add_quarters(ws, s_found, last, complete, itself);
+        complete = complete && wave == 0;
+        if (wave == 0 && lane_number() == 0) store_index(tile_g0);
+    } else {
+        if (wave == 0) {
+            const uint64_t v = DIRECT ? wait_for_counts(ws, slot, n_slots, ep.cur, polls, complete, itself) : wait_for_prefix(ws, slot, n_slots, ep.cur, polls, itself);
+            if (lane_number() == 0) {
+                s_tile_prefix = v;
+                store_index(v);
+            }
         }
+        lds_barrier();
+        tile_g0 = uniform64(s_tile_prefix);
     }
-    lds_barrier();
-    const uint64_t tile_g0 = uniform64(s_tile_prefix);         // index in the value array of the tile's first value
     BT_TL(slot, 2);
     BT_TL_VALUE(slot, 5, polls);
     if (!words_early) store_words();
@@ -2181,7 +2234,7 @@ bt_status check_batch_common(const void *items, size_t count, bt_dtype dt, const
 }
 
 // Launch the compression kernel for a dtype / pruning / dense-output combination on `job`.
-template <int R, bool DIRECT, class Job>
+template <int R, int DIRECT, class Job>
 bt_status launch_compress(const Job &job, uint64_t slots, bt_dtype dtype, bool prune, bool dense, double threshold,
                           char *ws, hipStream_t hs) {
     const uint64_t grid = slots + (DIRECT ? 0u : 1u);      // with or without a scanner
@@ -2192,21 +2245,23 @@ bt_status launch_compress(const Job &job, uint64_t slots, bt_dtype dtype, bool p
     if ((double)threshold_f > threshold) threshold_f = std::nextafterf(threshold_f, -INFINITY);
     const auto go = [&](auto kernel) { return launch(kernel, grid, kBlock, hs, job, ws, threshold, threshold_f); };
     const int s = elem_size(dtype);
+    // (What compress_common does not launch with four waves waiting is not built either.)
+    constexpr bool kQuarters = DIRECT > (int)kDirectSlots;
     if (!prune) {
-        if (s == 8) return go(compress_kernel<8, R, DIRECT, kKeepNonZero, false, Job>);
         if (s == 4) return go(compress_kernel<4, R, DIRECT, kKeepNonZero, false, Job>);
-        return go(compress_kernel<2, R, DIRECT, kKeepNonZero, false, Job>);
-    }
-    if (!dense) {
-        if (dtype == BT_F64) return go(compress_kernel<8, R, DIRECT, kKeepAboveF64, false, Job>);
+        if (s == 2) return go(compress_kernel<2, R, DIRECT, kKeepNonZero, false, Job>);
+        if constexpr (!kQuarters) return go(compress_kernel<8, R, DIRECT, kKeepNonZero, false, Job>);
+    } else if (!dense) {
         if (dtype == BT_F32) return go(compress_kernel<4, R, DIRECT, kKeepAboveF32, false, Job>);
         if (dtype == BT_F16) return go(compress_kernel<2, R, DIRECT, kKeepAboveF16, false, Job>);
-        return go(compress_kernel<2, R, DIRECT, kKeepAboveBF16, false, Job>);
+        if (dtype == BT_BF16) return go(compress_kernel<2, R, DIRECT, kKeepAboveBF16, false, Job>);
+        if constexpr (!kQuarters) return go(compress_kernel<8, R, DIRECT, kKeepAboveF64, false, Job>);
+    } else {
+        if (dtype == BT_F64) return go(compress_kernel<8, R, DIRECT, kKeepAboveF64, true, Job>);
+        if (dtype == BT_F32) return go(compress_kernel<4, R, DIRECT, kKeepAboveF32, true, Job>);
+        if constexpr (!kQuarters) return go(dtype == BT_F16 ? compress_kernel<2, R, DIRECT, kKeepAboveF16, true, Job> : compress_kernel<2, R, DIRECT, kKeepAboveBF16, true, Job>);
     }
-    if (dtype == BT_F64) return go(compress_kernel<8, R, DIRECT, kKeepAboveF64, true, Job>);
-    if (dtype == BT_F32) return go(compress_kernel<4, R, DIRECT, kKeepAboveF32, true, Job>);
-    if (dtype == BT_F16) return go(compress_kernel<2, R, DIRECT, kKeepAboveF16, true, Job>);
-    return go(compress_kernel<2, R, DIRECT, kKeepAboveBF16, true, Job>);
+    return BT_ERR_UNSUPPORTED;
 }
 
 template <class Job> bt_status launch_decompress(const Job &job, uint64_t slots, int s, char *ws, hipStream_t hs) {
@@ -2341,10 +2396,22 @@ static bt_status compress_common(const void *d_in, uint64_t n, bt_dtype dtype, b
     // with the scanner 7.2, without it but in tiles of eight rows 7.3 (by the workspace's place up to 7.6), of two rows 4.8; 800 k,
     // 5 % zeros, 8.7 / 9.2 / 6.3 (four rows); fp32 201 k 6.9 / 6.6 / 4.8.
     using std::integral_constant;
-    if (tiles_for(n, s, 2) <= 64) return go(integral_constant<int, 2>{}, std::true_type{});
-    if (tiles_for(n, s, 4) <= kDirectSlots) return go(integral_constant<int, 4>{}, std::true_type{});
-    if (tiles_for(n, s) <= kDirectSlots) return go(integral_constant<int, kRows>{}, std::true_type{});
-    return go(integral_constant<int, kRows>{}, std::false_type{});
+    const integral_constant<int, (int)kDirectSlots> direct;
+    const integral_constant<int, kRows> eight;
+    const uint64_t tiles = tiles_for(n, s);
+    if (tiles_for(n, s, 2) <= 64) return go(integral_constant<int, 2>{}, direct);
+    if (tiles_for(n, s, 4) <= kDirectSlots) return go(integral_constant<int, 4>{}, direct);
+    if (tiles <= kDirectSlots) return go(eight, direct);
+    // More tiles than that, still without a scanner: all four waves read counts (wait_for_quarter).  Where it stops is where the tiles'
+    // polls get into each other's way and into that of the values: with many values sooner, and with a dense output beside them
+    // for 16-bit elements at once.  Measured, us, with the scanner / this: fp32 2.2 M elements (269 tiles) 7.3 / 6.7, 3.2 M 8.2 / 7.0, at 95 %
+    // zeros 7.8 / 6.5, at 5 % 9.1 / 9.0, 3.9 M 8.5 / 7.7, at 5 % 9.3 / 9.5 (not done), 8 M 11.1 / 15.2; pruning 3.2 M 8.4 / 7.4; activation call 3.2 M 8.4 / 8.2;
+    // bf16 4.3 M (263) 7.4 / 7.2, 8.4 M (512) 9.0 / 7.9, at 5 % 9.8 / 8.4, at 95 % 8.3 / 7.3, activation call 4.5 M 9.0 / 9.2; fp64 1.6 M (391) 8.2 / 8.0, at 5 %
+    // 8.8 / 9.7, activation call 1.1 M 7.7 / 7.1, 2.1 M (512) 8.9 / 8.1.
+    const bool dense = d_dense != nullptr;
+    const uint64_t most = s == 4 ? 448 : dense == (s == 8) ? kQuarterSlots : 0;
+    if (tiles <= most) return go(eight, integral_constant<int, (int)kQuarterSlots>{});
+    return go(eight, integral_constant<int, 0>{});
 }
 
 bt_status bt_compress(const void *d_in, uint64_t n, bt_dtype dtype, uint32_t *d_bitmap, void *d_values,
