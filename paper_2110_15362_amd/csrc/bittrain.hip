@@ -869,18 +869,22 @@ __device__ __forceinline__ uint64_t wait_for_counts(char *ws, const uint32_t slo
 }
 
 // A wave's share of the wait in a launch of up to kQuarterSlots tiles: the number of values in the tiles before `slot` among the
-// wave's quarter of the slots, or kWaveFailed if the counts have not all been there for too many polls.
+// wave's quarter of the slots, or kWaveFailed if the counts have not all been there for too many polls.  The last tile's wait is bounded
+// like the scanner's, fruitful or not: a limit of one poll makes every such call fail.
 __device__ __forceinline__ uint32_t wait_for_quarter(char *ws, const uint32_t slot, const bool last, const uint32_t cur, const int wave, uint32_t &polls) {
     uint32_t *const hdr = reinterpret_cast<uint32_t *>(ws);
     const bool deaf = told_nothing(hdr, last ? 2 : 1);
+    uint32_t limit = 0;
+    if (last) limit = uniform32(wait_limit(hdr));
     for (;;) {
         const uint32_t at = 128u * (uint32_t)wave + 2u * (uint32_t)lane_number();
         uint64_t two = 0;
         if (at < slot) two = ws_load64(ws_count(ws, at, cur));
         const uint32_t ca = at < slot ? (uint32_t)two : 1u, cb = at + 1 < slot ? (uint32_t)(two >> 32) : 1u;
-        if (__ballot(deaf || ca == 0 || cb == 0) == 0) return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(ca + cb - 2u), 63);
         ++polls;
-        if (last ? polls >= wait_limit(hdr) : (polls & 255u) == 0 && polls > patience_of(hdr)) return kWaveFailed;
+        if (last && polls >= limit) return kWaveFailed;
+        if (__ballot(deaf || ca == 0 || cb == 0) == 0) return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(ca + cb - 2u), 63);
+        if (!last && (polls & 255u) == 0 && polls > patience_of(hdr)) return kWaveFailed;
         __builtin_amdgcn_s_sleep(kScannerSleep);
     }
 }
