@@ -6,7 +6,7 @@ Two pieces, both thin: every byte of codec work is done by libbittrain's kernels
 
 * ``BitmapStash`` -- a ``torch.autograd.graph.saved_tensors_hooks`` context.  Packing a
   saved activation runs ``bt_compress_indexed`` into a reusable worst-case scratch buffer, waits for
-  nnz, which the kernel writes straight to the host (one synchronisation per tensor: the price of right-sizing), and keeps
+  nnz, which the kernel writes straight to the host (one wait per tensor: the price of right-sizing), and keeps
   only ``values[:nnz]`` and the bitmap; if that is not smaller than the dense tensor the
   tensor is kept as it is.  Packing also keeps the tile index (8 bytes per 32 KiB of
   dense data) that compression produces on the way, so unpacking runs
@@ -27,6 +27,13 @@ from . import bittrain as bt
 _SUPPORTED = (torch.float32, torch.float16, torch.bfloat16, torch.float64)
 
 
+def _native():
+    """The steps in C++ (csrc/call.cpp)."""
+    if bt._lib is None:
+        bt.lib()
+    return bt._call
+
+
 class _StreamState:
     """Reusable buffers of one (device, stream): workspace, worst-case value scratch, and places in pinned host memory
     that compressions write their nnz to (a call that gave up a wait, or found a workspace on which one was given up, writes
@@ -36,6 +43,7 @@ class _StreamState:
     def __init__(self, device):
         self.device = device
         self.ws = None
+        self.fits = {}        # dtype -> the most elements that `ws` is known to serve
         self.scratch = {}
         self.nnz = torch.zeros(1, dtype=torch.int64, device=device)
         self.places = []      # free ones
@@ -53,12 +61,15 @@ class _StreamState:
         return p
 
     def workspace(self, n, dtype):
-        need = bt.bt_workspace_bytes(n, dtype)
         ws = self.ws
+        if n <= self.fits.get(dtype, -1):     # (a workspace is only ever replaced by a larger one)
+            return ws
+        need = bt.bt_workspace_bytes(n, dtype)
         if ws is None or ws.numel() < need:
             ws = torch.empty(max(need, 1 << 16), dtype=torch.uint8, device=self.device)
             bt.bt_workspace_init(ws)
             self.ws = ws                      # (only now: another thread on this stream may look for one in between)
+        self.fits[dtype] = n
         return ws
 
     def take_scratch(self, n, dtype):
@@ -99,7 +110,7 @@ _states = {}
 
 
 def _state(device):
-    key = (device, torch.cuda.current_stream(device).cuda_stream)
+    key = (device, torch._C._cuda_getCurrentRawStream(device.index))
     st = _states.get(key)
     if st is None:
         st = _states[key] = _StreamState(device)
@@ -205,10 +216,67 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
         finally:
             super().__exit__(*exc)
 
+    def _pack_plain(self, t):
+        """_pack of an ordinary tensor, around one call that allocates, compresses and, unless deferred, waits and copies (see
+        csrc/call.cpp); None if it is no such tensor after all.  (A packing of fp32 [500, 1024], waiting included, 35 -> 19 us; a step of four
+        layers of 1024 features, on fp32 with 8192 rows 1903 -> 1833 us, with 500 rows 897 -> 660, on bf16 with 8192 rows 965 -> 809, deferred
+        875 -> 719.)"""
+        st = _state(t.device)
+        n, dtype = t.numel(), t.dtype
+        ws = st.workspace(n, dtype)
+        if self.deferred:
+            self._finish_waiting(most=self.max_waiting - 1)        # bounds what the unsettled packings hold
+            values = torch.empty(n, dtype=dtype, device=t.device)  # its own: it outlives this call
+        else:
+            values = st.take_scratch(n, dtype)
+        place = st.place()
+        try:
+            got = _native().pack(t, values, ws, place.address, not self.deferred)
+        except BaseException:
+            if place.read() != -1:            # (over as far as the place is concerned: it was the copy that failed)
+                place.give_back()
+            raise
+        finally:
+            if not self.deferred:
+                st.give_scratch(values)
+        if got is None:
+            place.give_back()
+            return None
+        self.stats["tensors"] += 1
+        self.stats["dense_bytes"] += n * t.element_size()
+        packed = _Packed(got[0], None, got[1], t.shape, dtype, t.device)
+        if self.deferred:
+            packed.values = values
+            self._defer(packed, t, place, ws, torch.cuda.current_stream())
+            return packed
+        nnz, kept = got[2], got[3]
+        place.give_back()
+        if nnz < 0:
+            self._settle(packed, nnz, None, ws)
+            return t
+        if kept is None:
+            self.stats["stored_bytes"] += n * t.element_size()
+            return t
+        packed.values = kept
+        self.stats["compressed"] += 1
+        self.stats["stored_bytes"] += 4 * got[0].numel() + nnz * t.element_size() + 8 * got[1].numel()
+        return packed
+
+    def _defer(self, packed, t, place, ws, stream):
+        """`packed` is settled later (see _finish_waiting)."""
+        event = torch.cuda.Event()
+        event.record(stream)
+        packed.pending = True
+        self._waiting.append(_Pending(packed, t.detach(), place, event, ws, stream))
+
     def _pack(self, t):
         if (not t.is_cuda or t.dtype not in _SUPPORTED or t.numel() < self.min_numel or not t.is_contiguous()
                 or isinstance(t, torch.nn.Parameter) or t.is_neg() or t._is_zerotensor() or t.data_ptr() % 16 != 0):
             return t                      # (the library takes memory from a 16-byte boundary on that holds the values)
+        if type(t) is torch.Tensor:
+            packed = self._pack_plain(t)
+            if packed is not None:
+                return packed
         st = _state(t.device)
         n = t.numel()
         self.stats["tensors"] += 1
@@ -222,10 +290,7 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
             self._finish_waiting(most=self.max_waiting - 1)        # bounds what the unsettled packings hold
             packed.values = torch.empty(n, dtype=t.dtype, device=t.device)     # its own: it outlives this call
             place = self._compress(t, packed, packed.values, st, ws, stream)
-            event = torch.cuda.Event()
-            event.record(stream)
-            packed.pending = True
-            self._waiting.append(_Pending(packed, t.detach(), place, event, ws, stream))
+            self._defer(packed, t, place, ws, stream)
             return packed
         scratch = st.take_scratch(n, t.dtype)
         try:
@@ -240,9 +305,7 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
     @staticmethod
     def _compress(t, packed, values, st, ws, stream):
         """bt_compress_indexed of `t`, nnz to a place on the host, which is returned.  (Through device memory it took a kernel for
-        the status and a copy.  With this and the one-pass ReLU a step of four layers on fp32 [8192, 1024] takes 1.91 ms instead of 2.01,
-        deferred 1.70 instead of 1.82; two layers on bf16 [2021, 672], deferred, 0.40 instead of 0.68.  Looking at the word in a
-        loop instead of waiting in the runtime is up to 10 % slower.)"""
+        the status and a copy.)"""
         place = st.place()
         bt._check("bt_compress_indexed", bt.lib().bt_compress_indexed(
             t.data_ptr(), t.numel(), bt.dtype_code(t.dtype), packed.bitmap.data_ptr(), values.data_ptr(), values.numel(), place.address,
@@ -256,8 +319,10 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
             self._finish_waiting(only=obj)
         if obj.dense is not None:
             return obj.dense
-        out = torch.empty(obj.shape, dtype=obj.dtype, device=obj.device)
-        bt.bt_decompress_indexed(obj.bitmap, obj.values, obj.index, out)
+        out = _native().unpack(obj.bitmap, obj.values, obj.index, obj.shape)
+        if out is None:
+            out = torch.empty(obj.shape, dtype=obj.dtype, device=obj.device)
+            bt.bt_decompress_indexed(obj.bitmap, obj.values, obj.index, out)
         return out
 
 
@@ -269,6 +334,11 @@ def _held(t):
 class _BitmapReLU(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, fused):
+        if not fused:
+            done = _native().relu(x)
+            if done is not None:
+                y, ctx.bitmap = done
+                return y
         if not (x.is_cuda and x.dtype in _SUPPORTED and x.is_contiguous()):
             raise TypeError("bitmap_relu needs a contiguous float64/float32/float16/bfloat16 device tensor")
         n = x.numel()
@@ -290,6 +360,9 @@ class _BitmapReLU(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, grad_out):
+        grad_in = _native().relu_gradient(ctx.bitmap, grad_out)
+        if grad_in is not None:
+            return grad_in, None
         grad_out = _held(grad_out.contiguous())
         if grad_out.data_ptr() % 16 != 0:      # (a part of a concatenation's gradient)
             grad_out = grad_out.clone()

@@ -29,7 +29,8 @@ _lib = None
 _call = None      # the single-tensor calls, checked and marshalled in C++; bound to the library that lib() has loaded
 # the library's functions behind it, in the order of the table in csrc/call.cpp
 _CALLS = ("bt_compress", "bt_compress_static", "bt_compress_pruned", "bt_activation_compress", "bt_compress_indexed",
-          "bt_decompress", "bt_decompress_indexed", "bt_relu_backward_from_bitmap", "bt_mask_apply", "bt_relu_forward", "bt_index_bytes")
+          "bt_decompress", "bt_decompress_indexed", "bt_relu_backward_from_bitmap", "bt_mask_apply", "bt_relu_forward", "bt_index_bytes",
+          "bt_compressed_size")
 
 
 class BitTrainError(RuntimeError):

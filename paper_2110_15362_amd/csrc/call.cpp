@@ -16,9 +16,13 @@
 #include <Python.h>
 #include <stdint.h>
 
+#include <chrono>
+
+#include <ATen/Functions.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "bittrain.h"
@@ -38,6 +42,7 @@ static struct {
     bt_status (*mask_apply)(const uint32_t *, const void *, uint64_t, bt_dtype, void *, bt_stream);
     bt_status (*relu_forward)(const void *, uint64_t, bt_dtype, void *, uint32_t *, bt_stream);
     size_t (*index_bytes)(uint64_t, bt_dtype);
+    size_t (*compressed_size)(uint64_t, uint64_t, bt_dtype);
 } lib;
 
 /* Python objects handed over by bind: {dtype: code}, the function that refuses other dtypes, the error class, the
@@ -373,6 +378,148 @@ static PyObject *py_relu_forward(PyObject *self, PyObject *const *args, Py_ssize
     CALL("bt_relu_forward", lib.relu_forward(a[0].ptr, a[0].numel, code, a[1].ptr, a[2].ptr, stream));
 }
 
+/* ---- steps of autograd.py on plain tensors --------------------------------------------------------
+ *
+ * What autograd.py does around a call, allocations included, in one go: written in Python, packing took the host 35 us beside the
+ * compression, and while it waits for nnz all of that is time in which the GPU has nothing to do.  Each returns None for tensors that are not
+ * plain, which autograd.py then takes the general way.  The GIL is released from the first allocation on. */
+
+static at::TensorOptions like(const at::Tensor &t, const at::ScalarType type) { return at::TensorOptions().dtype(type).device(t.device()); }
+
+static bool aligned(const tensor *a) { return (reinterpret_cast<uintptr_t>(a->ptr.p) & 15) == 0; }
+
+static PyObject *wrap(const at::Tensor &t) {
+    if (t.defined()) return THPVariable_Wrap(t);
+    Py_RETURN_NONE;
+}
+
+/* The nnz of a compression on `stream`, which replaces the -1 at `word` in pinned memory as soon as it is known, a little before the last
+ * values are written.  One that failed leaves the -1 there, which is known when the stream has come past it. */
+static int64_t wait_for_nnz(const volatile int64_t *word, const c10::hip::HIPStream &stream) {
+    using clock = std::chrono::steady_clock;
+    const clock::time_point end = clock::now() + std::chrono::milliseconds(2);      /* a host that waits longer sleeps */
+    do {
+        for (int i = 0; i < 64; ++i) {
+            const int64_t nnz = *word;
+            if (nnz != -1) return nnz;
+            __builtin_ia32_pause();
+        }
+    } while (clock::now() < end);
+    stream.synchronize();
+    return *word;
+}
+
+/* (x, scratch, workspace, address of the place, wait?) -> None, or (bitmap, index) of the compression that has been started;
+ * or, having waited for it, (bitmap, index, nnz, values cut to size): nnz -1 if it failed, values None if it is not worth keeping. */
+static PyObject *py_pack(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    HANDLE_TH_ERRORS
+    (void)self;
+    tensor a[3];
+    uint64_t place;
+    if (expect(nargs, 5) != 0) return NULL;
+    if (!has_device || !all_plain(a, args, 3) || a[0].code < 0 || !aligned(&a[0])) Py_RETURN_NONE;
+    if (a[1].dtype != a[0].dtype || a[1].numel < a[0].numel) return fail(PyExc_TypeError, "scratch must have the dtype of x and room for it"), nullptr;
+    Py_INCREF(args[3]);
+    if (to_u64(args[3], &place) != 0) return NULL;
+    const int wait = PyObject_IsTrue(args[4]);
+    if (wait < 0) return NULL;
+    const at::Tensor x = THPVariable_Unpack(args[0]), scratch = THPVariable_Unpack(args[1]);
+    const bt_dtype code = (bt_dtype)a[0].code;
+    at::Tensor bitmap, index, values;
+    int64_t nnz = -1;
+    bt_status st;
+    {
+        pybind11::gil_scoped_release no_gil;
+        const uint64_t n = a[0].numel;
+        bitmap = at::empty({(int64_t)((n + 31) / 32)}, like(x, at::kInt));
+        index = at::empty({(int64_t)(lib.index_bytes(n, code) / 8)}, like(x, at::kLong));
+        const c10::hip::HIPStream stream = c10::hip::getCurrentHIPStream();
+        st = lib.compress_indexed(a[0].ptr, n, code, (uint32_t *)bitmap.data_ptr(), a[1].ptr, a[1].numel, (uint64_t *)(uintptr_t)place,
+                                  (uint64_t *)index.data_ptr(), a[2].ptr, a[2].numel * a[2].width, (bt_stream)stream.stream());
+        if (st == BT_OK && wait) {
+            nnz = wait_for_nnz((const volatile int64_t *)(uintptr_t)place, stream);
+            if (nnz >= 0 && lib.compressed_size(n, (uint64_t)nnz, code) + 8 * (uint64_t)index.numel() < n * a[0].width) values = scratch.narrow(0, 0, nnz).clone();
+        }
+    }
+    if (st != BT_OK) return done("bt_compress_indexed", st);
+    if (!wait) return Py_BuildValue("(NN)", wrap(bitmap), wrap(index));
+    return Py_BuildValue("(NNLN)", wrap(bitmap), wrap(index), (long long)nnz, wrap(values));
+    END_HANDLE_TH_ERRORS
+}
+
+/* (bitmap, values, index, shape) -> None or the dense tensor */
+static PyObject *py_unpack(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    HANDLE_TH_ERRORS
+    (void)self;
+    tensor a[3];
+    if (expect(nargs, 4) != 0) return NULL;
+    if (!has_device || !PyTuple_Check(args[3]) || !all_plain(a, args, 3) || a[1].code < 0) Py_RETURN_NONE;
+    std::vector<int64_t> shape;
+    uint64_t n = 1;
+    for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(args[3]); ++i) {
+        shape.push_back(PyLong_AsLongLong(PyTuple_GET_ITEM(args[3], i)));
+        if (shape.back() == -1 && PyErr_Occurred()) return NULL;
+        n *= (uint64_t)shape.back();
+    }
+    if (a[0].width != 4 || a[0].numel < (n + 31) / 32 || a[2].width != 8 || a[2].numel * 8 < lib.index_bytes(n, (bt_dtype)a[1].code))
+        return fail(PyExc_ValueError, "bitmap and index must be those of a tensor of this shape"), nullptr;
+    const at::Tensor values = THPVariable_Unpack(args[1]);
+    at::Tensor out;
+    bt_status st;
+    {
+        pybind11::gil_scoped_release no_gil;
+        out = at::empty(shape, like(values, values.scalar_type()));
+        st = lib.decompress_indexed(a[0].ptr, a[1].ptr, a[1].numel, a[2].ptr, n, (bt_dtype)a[1].code, out.data_ptr(),
+                                    (bt_stream)c10::hip::getCurrentHIPStream().stream());
+    }
+    if (st != BT_OK) return done("bt_decompress_indexed", st);
+    return wrap(out);
+    END_HANDLE_TH_ERRORS
+}
+
+/* (x) -> None or (ReLU(x), its bitmap) */
+static PyObject *py_relu(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    HANDLE_TH_ERRORS
+    (void)self;
+    tensor a[1];
+    if (expect(nargs, 1) != 0) return NULL;
+    if (!has_device || !all_plain(a, args, 1) || a[0].code < 0 || !aligned(&a[0])) Py_RETURN_NONE;
+    const at::Tensor x = THPVariable_Unpack(args[0]);
+    at::Tensor y, bitmap;
+    bt_status st;
+    {
+        pybind11::gil_scoped_release no_gil;
+        bitmap = at::empty({(int64_t)((a[0].numel + 31) / 32)}, like(x, at::kInt));
+        y = at::empty_like(x);
+        st = lib.relu_forward(a[0].ptr, a[0].numel, (bt_dtype)a[0].code, y.data_ptr(), (uint32_t *)bitmap.data_ptr(),
+                              (bt_stream)c10::hip::getCurrentHIPStream().stream());
+    }
+    if (st != BT_OK) return done("bt_relu_forward", st);
+    return Py_BuildValue("(NN)", wrap(y), wrap(bitmap));
+    END_HANDLE_TH_ERRORS
+}
+
+/* (bitmap, gradient) -> None or the gradient behind the ReLU */
+static PyObject *py_relu_gradient(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
+    HANDLE_TH_ERRORS
+    (void)self;
+    tensor a[2];
+    if (expect(nargs, 2) != 0) return NULL;
+    if (!has_device || !all_plain(a, args, 2) || a[1].code < 0 || !aligned(&a[1])) Py_RETURN_NONE;
+    if (check_bitmap(&a[0], a[1].numel) != 0) return NULL;
+    const at::Tensor grad = THPVariable_Unpack(args[1]);
+    at::Tensor out;
+    bt_status st;
+    {
+        pybind11::gil_scoped_release no_gil;
+        out = at::empty_like(grad);
+        st = lib.relu_backward(a[0].ptr, a[1].ptr, a[1].numel, (bt_dtype)a[1].code, out.data_ptr(), (bt_stream)c10::hip::getCurrentHIPStream().stream());
+    }
+    if (st != BT_OK) return done("bt_relu_backward_from_bitmap", st);
+    return wrap(out);
+    END_HANDLE_TH_ERRORS
+}
+
 /* (addresses of the calls in the order of `lib`, the objects above in their order) */
 static PyObject *py_bind(PyObject *self, PyObject *args) {
     (void)self;
@@ -401,6 +548,7 @@ static PyObject *py_bind(PyObject *self, PyObject *args) {
 static PyMethodDef methods[] = {
     FAST(compress), FAST(compress_static), FAST(compress_pruned), FAST(activation_compress), FAST(compress_indexed),
     FAST(decompress), FAST(decompress_indexed), FAST(relu_backward), FAST(mask_apply), FAST(relu_forward),
+    FAST(pack), FAST(unpack), FAST(relu), FAST(relu_gradient),
     {"bind", py_bind, METH_VARARGS, NULL}, {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", NULL, -1, methods, NULL, NULL, NULL, NULL};
 
