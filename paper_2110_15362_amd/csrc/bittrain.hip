@@ -90,22 +90,22 @@ constexpr uint32_t kPatience = 1u << 12;  // polls before a workgroup counts wha
 template <int S> constexpr uint32_t kDenseEarlySlots = S == 2 ? 1280 : 1000;
 constexpr int kScannerSleep = BT_SCANNER_SLEEP;   // pause between two polls, in units of 64 clocks
 
-// S: element bytes; R: rows (16-byte loads) per lane per tile.
-template <int S, int R = kRows> struct Geo {
+// S: element bytes; R: rows (16-byte loads) per lane per tile; W: waves of the workgroup that a tile belongs to.
+template <int S, int R = kRows, int W = kWaves> struct Geo {
     static constexpr int E = kVecBytes / S;          // elements per lane per load
     static constexpr int G = 32 / E;                 // lanes that share a bitmap word
     static constexpr int WPR = kWaveSize / G;        // bitmap words per row
     static constexpr int ROW = kWaveSize * E;        // elements per wave-wide load
     static constexpr int WAVE = R * ROW;             // elements per wave per tile
     static constexpr int PHASE = R < 4 ? R : 4;      // rows that are compacted / expanded through LDS at a time
-    static constexpr int TILE = kWaves * WAVE;       // elements per tile
+    static constexpr int TILE = W * WAVE;            // elements per tile
     static constexpr int TILE_WORDS = TILE / 32;     // bitmap words per tile
-    static constexpr int WAVE_WORDS = TILE_WORDS / kWaves;      // of which a wave's quarter of the tile has this many
+    static constexpr int WAVE_WORDS = TILE_WORDS / W;      // of which a wave's quarter of the tile has this many
     static constexpr int QPL = WAVE_WORDS > kWaveSize ? WAVE_WORDS / kWaveSize : 1;   // and a lane reads this many (of a quarter)
     static constexpr int WPL = TILE_WORDS > kWaveSize ? TILE_WORDS / kWaveSize : 1;   // or this many (of the whole tile)
     static constexpr int LDS_WAVE = PHASE * ROW * S + 2 * kVecBytes;  // restoration's staging bytes per wave: the rows of a phase, the
                                                                           // shift to a 16-byte boundary, and what a read past the last value may touch
-    static constexpr int LDS_TILE = PHASE * kBlock * kVecBytes + 2 * kVecBytes;      // and per workgroup, where its waves stage together
+    static constexpr int LDS_TILE = PHASE * W * kWaveSize * kVecBytes + 2 * kVecBytes;      // and per workgroup, where its waves stage together
     static constexpr int STAGE = TILE * S <= kStageBytes - kVecBytes ? TILE * S : kStageBytes - kVecBytes;   // compression: bytes of a tile's
                                                                           // values that fit LDS together (then a vector nobody reads)
     static constexpr int RPM = 32 / E;               // rows whose E-bit lane masks share one register
@@ -778,10 +778,10 @@ __device__ __forceinline__ Epoch epoch_of(const HeaderWords h) {
     return Epoch{entries >> 31, entries & 0x7fffffffu, uniform32(h.calls), uniform32(h.error) != 0};
 }
 
-__device__ __forceinline__ bool any_wave_failed(const uint32_t (&totals)[kWaves]) {
+template <int W> __device__ __forceinline__ bool any_wave_failed(const uint32_t (&totals)[W]) {
     bool any = false;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) any = any || uniform32(totals[w]) == kWaveFailed;
+    for (int w = 0; w < W; ++w) any = any || uniform32(totals[w]) == kWaveFailed;
     return any;
 }
 
@@ -1694,15 +1694,15 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_kernel(cons
 // 7.9 / 8.3, fp64 25.7 M 58.2 / 63.5.)
 
 // Bits of words at or beyond the bitmap's end, and bits at or beyond n, are 0 (Algorithm 2 visits n bits).
-template <int S, int R> struct TileBits { uint32_t w[Geo<S, R>::WPL]; };
+template <int S, int R, int W = kWaves> struct TileBits { uint32_t w[Geo<S, R, W>::WPL]; };
 
-template <int S, int R>
-__device__ __forceinline__ TileBits<S, R> load_bits(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane) {
-    using G = Geo<S, R>;
+template <int S, int R, int W = kWaves>
+__device__ __forceinline__ TileBits<S, R, W> load_bits(const uint32_t *bitmap, const uint64_t n, const uint32_t tile, const int lane) {
+    using G = Geo<S, R, W>;
     constexpr int WPL = G::WPL;
     typedef uint32_t words __attribute__((ext_vector_type(WPL), aligned(4)));      // (the bitmap is 4-byte aligned)
     const uint64_t first = (uint64_t)tile * G::TILE_WORDS;
-    TileBits<S, R> b;
+    TileBits<S, R, W> b;
 #pragma unroll
     for (int j = 0; j < WPL; ++j) b.w[j] = 0;
     if (__builtin_expect((uint64_t)(tile + 1) * G::TILE <= n, 1)) {
@@ -1728,24 +1728,24 @@ __device__ __forceinline__ TileBits<S, R> load_bits(const uint32_t *bitmap, cons
 }
 
 // Set bits of the tile before the lane's first word, and before each phase and after the last one.
-template <int S, int R> struct TileRanks {
-    static constexpr int PHASES = R / Geo<S, R>::PHASE;
+template <int S, int R, int W = kWaves> struct TileRanks {
+    static constexpr int PHASES = R / Geo<S, R, W>::PHASE;
     uint32_t mine;
     uint32_t before[PHASES + 1];
 };
 
-template <int S, int R> __device__ __forceinline__ TileRanks<S, R> rank_words(const TileBits<S, R> &b) {
-    using G = Geo<S, R>;
+template <int S, int R, int W = kWaves> __device__ __forceinline__ TileRanks<S, R, W> rank_words(const TileBits<S, R, W> &b) {
+    using G = Geo<S, R, W>;
     uint32_t sum = 0;
 #pragma unroll
     for (int j = 0; j < G::WPL; ++j) sum += (uint32_t)__popc(b.w[j]);
     const uint32_t incl = wave_inclusive_sum(sum);
-    TileRanks<S, R> r;
+    TileRanks<S, R, W> r;
     r.mine = incl - sum;
 #pragma unroll
-    for (int ph = 0; ph < TileRanks<S, R>::PHASES; ++ph)       // (the lane that holds the phase's first word)
-        r.before[ph] = (uint32_t)__builtin_amdgcn_readlane((int)r.mine, ph * kWaves * G::PHASE * G::WPR / G::WPL);
-    r.before[TileRanks<S, R>::PHASES] = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    for (int ph = 0; ph < TileRanks<S, R, W>::PHASES; ++ph)       // (the lane that holds the phase's first word)
+        r.before[ph] = (uint32_t)__builtin_amdgcn_readlane((int)r.mine, ph * W * G::PHASE * G::WPR / G::WPL);
+    r.before[TileRanks<S, R, W>::PHASES] = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     return r;
 }
 
@@ -1756,9 +1756,9 @@ template <int S, int K> struct Rows {
 
 // The wave's rows among the tile's rows [first, first + 4 K).  `entries`: room for their words, a pair each; a wave writes and reads
 // those of its own rows only.
-template <int S, int R, int K>
-__device__ __forceinline__ Rows<S, K> rows_of(const TileBits<S, R> &b, const TileRanks<S, R> &r, const int first, bt_u2 *entries, const int lane, const int wave) {
-    using G = Geo<S, R>;
+template <int S, int R, int K, int W = kWaves>
+__device__ __forceinline__ Rows<S, K> rows_of(const TileBits<S, R, W> &b, const TileRanks<S, R, W> &r, const int first, bt_u2 *entries, const int lane, const int wave) {
+    using G = Geo<S, R, W>;
     constexpr int E = G::E;
     static_assert(G::TILE < 65536, "ranks in 16 bits");
     uint32_t rank = r.mine;
@@ -1766,8 +1766,8 @@ __device__ __forceinline__ Rows<S, K> rows_of(const TileBits<S, R> &b, const Til
     for (int j = 0; j < G::WPL; ++j) {
         const int i = lane * G::WPL + j;
         const int row = i / G::WPR;
-        const bool asked = K == R || (unsigned)(row - first) < (unsigned)(kWaves * K);
-        if (asked && row % kWaves == wave && (G::TILE_WORDS >= kWaveSize || lane < G::TILE_WORDS)) entries[i - first * G::WPR] = bt_u2{b.w[j], rank};
+        const bool asked = K == R || (unsigned)(row - first) < (unsigned)(W * K);
+        if (asked && row % W == wave && (G::TILE_WORDS >= kWaveSize || lane < G::TILE_WORDS)) entries[i - first * G::WPR] = bt_u2{b.w[j], rank};
         rank += (uint32_t)__popc(b.w[j]);
     }
     wave_lds_sync();
@@ -1778,7 +1778,7 @@ __device__ __forceinline__ Rows<S, K> rows_of(const TileBits<S, R> &b, const Til
     const uint32_t below = (1u << shift) - 1u;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const bt_u2 e = entries[(k * kWaves + wave) * G::WPR + lane / G::G];
+        const bt_u2 e = entries[(k * W + wave) * G::WPR + lane / G::G];
         rows.mp[k / G::RPM] |= ((e.x >> shift) & ((1u << E) - 1u)) << (E * (k % G::RPM));
         const uint32_t at = e.y + (uint32_t)__popc(e.x & below);
         rows.rank2[k / 2] = (k & 1) == 0 ? at : rows.rank2[k / 2] | (at << 16);
@@ -1787,18 +1787,18 @@ __device__ __forceinline__ Rows<S, K> rows_of(const TileBits<S, R> &b, const Til
 }
 
 // The values of one phase on their way to LDS, whose element pad + i is the phase's i-th (pad lines LDS byte 0 up with a 16-byte
-// boundary of the value array).  They are at most PHASE * kBlock + 1 aligned vectors: the inner ones, all fully inside the
+// boundary of the value array).  They are at most PHASE * W * kWaveSize + 1 aligned vectors: the inner ones, all fully inside the
 // range, go PHASE to a thread; of the first and the last vector, thread j < E takes element j of the first and thread
 // E + j element j of the last, each only if it lies inside the range.
-template <int S, int R> struct TileValues {
-    uint4 inner[Geo<S, R>::PHASE];
+template <int S, int R, int W = kWaves> struct TileValues {
+    uint4 inner[Geo<S, R, W>::PHASE];
     typename std::conditional<S == 8, uint64_t, uint32_t>::type edge;
     uint32_t pad, end;      // elements of LDS [pad, end) are values
 };
 
 // Is there an edge element for thread `tid`, and which?
-template <int S, int R> __device__ __forceinline__ bool edge_of(const TileValues<S, R> &f, const int tid, uint32_t &at) {
-    constexpr int E = Geo<S, R>::E;
+template <int S, int R, int W = kWaves> __device__ __forceinline__ bool edge_of(const TileValues<S, R, W> &f, const int tid, uint32_t &at) {
+    constexpr int E = Geo<S, R, W>::E;
     const uint32_t vecs = (f.end + E - 1) / E;
     at = tid < E ? (uint32_t)tid : (vecs - 1) * E + (uint32_t)(tid - E);
     return tid < 2 * E && f.end != f.pad && at >= f.pad && at < f.end && (tid < E || vecs > 1);
@@ -1806,26 +1806,26 @@ template <int S, int R> __device__ __forceinline__ bool edge_of(const TileValues
 
 // j: position of the phase's first value; nothing at or beyond the capacity is read (an index that does not belong to the
 // bitmap, a wait that ran out).
-template <int S, int R>
-__device__ __forceinline__ TileValues<S, R> fetch_values(const void *__restrict__ values, const uint64_t values_cap, const uint64_t j, uint32_t count, const int tid) {
-    using G = Geo<S, R>;
+template <int S, int R, int W = kWaves>
+__device__ __forceinline__ TileValues<S, R, W> fetch_values(const void *__restrict__ values, const uint64_t values_cap, const uint64_t j, uint32_t count, const int tid) {
+    using G = Geo<S, R, W>;
     constexpr int E = G::E;
     if (j >= values_cap) count = 0;
     else if (values_cap - j < count) count = (uint32_t)(values_cap - j);
     const char *const src = static_cast<const char *>(values) + j * S;
-    TileValues<S, R> f;
+    TileValues<S, R, W> f;
     f.pad = (uint32_t)(reinterpret_cast<uintptr_t>(src) & (kVecBytes - 1)) / S;
     f.end = f.pad + count;
     const char *const vec = src - (size_t)f.pad * S;
 #pragma unroll
     for (int i = 0; i < G::PHASE; ++i) {
-        const uint32_t v = 1u + (uint32_t)tid + (uint32_t)kBlock * i;
+        const uint32_t v = 1u + (uint32_t)tid + (uint32_t)(W * kWaveSize) * i;
         f.inner[i] = make_uint4(0, 0, 0, 0);
         if ((v + 1) * E < f.end) f.inner[i] = stream_load<kDecompressNtLoad>(reinterpret_cast<const uint4 *>(vec + (size_t)v * kVecBytes));
     }
     f.edge = 0;
     uint32_t at;
-    if (edge_of<S, R>(f, tid, at)) {
+    if (edge_of<S, R, W>(f, tid, at)) {
         if (S == 8) f.edge = reinterpret_cast<const uint64_t *>(vec)[at];
         else if (S == 4) f.edge = reinterpret_cast<const uint32_t *>(vec)[at];
         else f.edge = reinterpret_cast<const uint16_t *>(vec)[at];
@@ -1833,17 +1833,17 @@ __device__ __forceinline__ TileValues<S, R> fetch_values(const void *__restrict_
     return f;
 }
 
-template <int S, int R>
-__device__ __forceinline__ void commit_values(unsigned char *stage, const TileValues<S, R> &f, const int tid) {
-    using G = Geo<S, R>;
+template <int S, int R, int W = kWaves>
+__device__ __forceinline__ void commit_values(unsigned char *stage, const TileValues<S, R, W> &f, const int tid) {
+    using G = Geo<S, R, W>;
     constexpr int E = G::E;
 #pragma unroll
     for (int i = 0; i < G::PHASE; ++i) {
-        const uint32_t v = 1u + (uint32_t)tid + (uint32_t)kBlock * i;
+        const uint32_t v = 1u + (uint32_t)tid + (uint32_t)(W * kWaveSize) * i;
         if ((v + 1) * E < f.end) *reinterpret_cast<uint4 *>(stage + (size_t)v * kVecBytes) = f.inner[i];
     }
     uint32_t at;
-    if (edge_of<S, R>(f, tid, at)) {
+    if (edge_of<S, R, W>(f, tid, at)) {
         if (S == 8) reinterpret_cast<uint64_t *>(stage)[at] = f.edge;
         else if (S == 4) reinterpret_cast<uint32_t *>(stage)[at] = (uint32_t)f.edge;
         else reinterpret_cast<uint16_t *>(stage)[at] = (uint16_t)f.edge;
@@ -1887,17 +1887,17 @@ template <int S> __device__ __forceinline__ uint4 expand_row(const unsigned char
 }
 
 // The wave's rows [k0, k0 + PHASE) of `rows`, which are rows first + k * 4 + wave of the tile; `before`: set bits of the tile before the phase.
-template <int S, int R, int K>
-__device__ __forceinline__ void expand_phase(const Rows<S, K> &rows, const int k0, const int first, const TileValues<S, R> &f, const uint32_t before,
+template <int S, int R, int K, int W = kWaves>
+__device__ __forceinline__ void expand_phase(const Rows<S, K> &rows, const int k0, const int first, const TileValues<S, R, W> &f, const uint32_t before,
                                              const unsigned char *stage, void *__restrict__ out, const uint64_t n, const uint32_t tile, const int lane,
                                              const int wave) {
-    using G = Geo<S, R>;
+    using G = Geo<S, R, W>;
     const uint64_t tile_e0 = (uint64_t)tile * G::TILE;
     const bool full = tile_e0 + G::TILE <= n;
 #pragma unroll
     for (int k = k0; k < k0 + G::PHASE; ++k) {
         const uint4 o = expand_row<S>(stage, f.pad - before + BT_FIELD(rows.rank2, k), BT_MASK(S, rows.mp, k));
-        const uint64_t e0 = tile_e0 + (uint64_t)((uint32_t)(first + k * kWaves + wave) * G::ROW + (uint32_t)lane * G::E);
+        const uint64_t e0 = tile_e0 + (uint64_t)((uint32_t)(first + k * W + wave) * G::ROW + (uint32_t)lane * G::E);
         if (full) stream_store<kDecompressNtStore>(reinterpret_cast<uint4 *>(static_cast<char *>(out) + e0 * S), o);
         else store_vec_guarded<S>(out, e0, n, o);
     }
@@ -1905,15 +1905,16 @@ __device__ __forceinline__ void expand_phase(const Rows<S, K> &rows, const int k
 
 // One thread's share of the set bits in the first `words` words of the bitmap (a whole number of 16-byte vectors), the
 // workgroup's threads taking a vector each in turn.  kAhead loads are in flight together.
+template <int THREADS>
 __device__ __forceinline__ uint32_t count_share(const uint32_t *__restrict__ bitmap, const uint32_t words, const int tid) {
     typedef uint32_t word4 __attribute__((ext_vector_type(4), aligned(4)));      // (the bitmap is 4-byte aligned)
     constexpr uint32_t kAhead = 8;
     uint32_t count = 0;
-    for (uint32_t first = 0; first < words; first += 4u * kBlock * kAhead) {
+    for (uint32_t first = 0; first < words; first += 4u * THREADS * kAhead) {
         word4 v[kAhead];
 #pragma unroll
         for (uint32_t i = 0; i < kAhead; ++i) {
-            const uint32_t w = first + 4u * (kBlock * i + (uint32_t)tid);
+            const uint32_t w = first + 4u * (THREADS * i + (uint32_t)tid);
             v[i] = word4{0, 0, 0, 0};
             if (w < words) v[i] = *reinterpret_cast<const word4 *>(bitmap + w);
         }
@@ -1925,17 +1926,18 @@ __device__ __forceinline__ uint32_t count_share(const uint32_t *__restrict__ bit
 }
 
 
-// Small tensors (see bt_decompress): no scanner and nothing published.  Every workgroup counts the bitmap before
-// its tile itself, all its threads together while its own words are on their way: a few KiB that sit in the caches, against
-// four hops through memory.  The call leaves the workspace's entries alone.  (With each wave restoring a quarter of the tile,
+// Small tensors (see bt_decompress): no scanner and nothing published.  Every workgroup of W waves counts the bitmap before
+// its tile itself, all its threads together while its own words are on their way: what sits in the caches, against
+// four hops through memory.  Bound by that count, a compute unit's reads through its first-level cache: eight waves halve what is
+// read for a tensor, and ask for twice as much at once.  The call leaves the workspace's entries alone.  (With each wave restoring a quarter of the tile,
 // us: fp32 30 k elements 3.1, 201 k 3.1, 700 k 4.5, bf16 201 k 3.2; now 2.9, 2.9, 4.3, 3.1.)
-template <int S, int R>
-__global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_small_kernel(const DecompressOne job, char *ws) {
-    using G = Geo<S, R>;
-    static_assert(TileRanks<S, R>::PHASES == 1, "one phase");
+template <int S, int R, int W = kWaves>
+__global__ __launch_bounds__(W * kWaveSize, kDecompressOcc) void decompress_small_kernel(const DecompressOne job, char *ws) {
+    using G = Geo<S, R, W>;
+    static_assert(TileRanks<S, R, W>::PHASES == 1, "one phase");
     __shared__ __attribute__((aligned(16))) unsigned char s_stage[G::LDS_TILE];
     __shared__ bt_u2 s_entries[G::TILE_WORDS];
-    __shared__ uint32_t s_wave_before[kWaves], s_wave_total[kWaves];
+    __shared__ uint32_t s_wave_before[W], s_wave_total[W];
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1944,10 +1946,10 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_small_kerne
     const uint32_t calls = hdr[kHdrCalls], error = hdr[kHdrError];
     const uint32_t *const bitmap = job.bitmap(0);
     const uint64_t n = job.n(0);
-    const TileBits<S, R> bits = load_bits<S, R>(bitmap, n, tile, lane);
-    const uint32_t before_share = count_share(bitmap, tile * G::TILE_WORDS, tid);
-    const TileRanks<S, R> ranks = rank_words<S, R>(bits);
-    const Rows<S, R> rows = rows_of<S, R, R>(bits, ranks, 0, s_entries, lane, wave);
+    const TileBits<S, R, W> bits = load_bits<S, R, W>(bitmap, n, tile, lane);
+    const uint32_t before_share = count_share<W * kWaveSize>(bitmap, tile * G::TILE_WORDS, tid);
+    const TileRanks<S, R, W> ranks = rank_words<S, R, W>(bits);
+    const Rows<S, R> rows = rows_of<S, R, R, W>(bits, ranks, 0, s_entries, lane, wave);
     const uint32_t incl = wave_inclusive_sum(before_share);
     if (lane == kWaveSize - 1) s_wave_before[wave] = incl;
     if (lane == 0) s_wave_total[wave] = uniform32(error) != 0 ? kWaveFailed : 0u;
@@ -1955,13 +1957,13 @@ __global__ __launch_bounds__(kBlock, kDecompressOcc) void decompress_small_kerne
     if (any_wave_failed(s_wave_total)) return;
     uint64_t tile_j = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) tile_j += s_wave_before[w];
+    for (int w = 0; w < W; ++w) tile_j += s_wave_before[w];
     tile_j = uniform64(tile_j);
     if (tile == 0 && tid == 0) hdr[kHdrCalls] = calls + 1u;
-    const TileValues<S, R> f = fetch_values<S, R>(job.values(0), job.cap(0), tile_j, ranks.before[1], tid);
-    commit_values<S, R>(s_stage, f, tid);
+    const TileValues<S, R, W> f = fetch_values<S, R, W>(job.values(0), job.cap(0), tile_j, ranks.before[1], tid);
+    commit_values<S, R, W>(s_stage, f, tid);
     lds_barrier();
-    expand_phase<S, R, R>(rows, 0, 0, f, 0, s_stage, job.out(0), n, tile, lane, wave);
+    expand_phase<S, R, R, W>(rows, 0, 0, f, 0, s_stage, job.out(0), n, tile, lane, wave);
 }
 
 // bt_decompress_indexed and its batched form: two workgroups per slot, one for each phase of its tile, and nothing else.
@@ -2273,9 +2275,9 @@ template <class Job> bt_status launch_decompress(const Job &job, uint64_t slots,
     return s == 8 ? go(decompress_kernel<8, Job>) : s == 4 ? go(decompress_kernel<4, Job>) : go(decompress_kernel<2, Job>);
 }
 
-template <int R> bt_status launch_decompress_small(const DecompressOne &job, uint64_t tiles, int s, char *ws, hipStream_t hs) {
-    const auto go = [&](auto kernel) { return launch(kernel, tiles, kBlock, hs, job, ws); };
-    return s == 8 ? go(decompress_small_kernel<8, R>) : s == 4 ? go(decompress_small_kernel<4, R>) : go(decompress_small_kernel<2, R>);
+template <int R, int W> bt_status launch_decompress_small(const DecompressOne &job, uint64_t tiles, int s, char *ws, hipStream_t hs) {
+    const auto go = [&](auto kernel) { return launch(kernel, tiles, W * kWaveSize, hs, job, ws); };
+    return s == 8 ? go(decompress_small_kernel<8, R, W>) : s == 4 ? go(decompress_small_kernel<4, R, W>) : go(decompress_small_kernel<2, R, W>);
 }
 
 template <class Job> bt_status launch_decompress_indexed(const Job &job, uint64_t slots, int s, hipStream_t hs) {
@@ -2507,14 +2509,17 @@ bt_status bt_decompress(const uint32_t *d_bitmap, const void *d_values, uint64_t
     char *const ws = static_cast<char *>(d_workspace);
     hipStream_t hs = (hipStream_t)stream;
     const auto job = [&](uint64_t tiles) { return DecompressOne{d_bitmap, d_values, ~(uint64_t)0, nullptr, n, d_out, (uint32_t)tiles}; };
-    const uint64_t tiles2 = tiles_for(n, s, 2), tiles4 = tiles_for(n, s, 4), tiles = tiles_for(n, s);
-    // Small tensors: every workgroup counts the bitmap before its tile itself, in tiles of two or four rows a lane.
-    // What it reads grows with the tensor: with 256 tiles of four rows 128 KiB at the end of an fp32 tensor, 256 KiB of a
-    // 16-bit one, which is where the scanner is as fast.  Measured, us per call on the GPU, before / after: fp32 5 k elements
-    // 6.0 / 2.9, 201 k 6.5 / 3.2, 500 k 6.7 / 3.8, 1 M 6.6 / 5.2 (1.5 M with eight rows 6.9 / 7.6: not done); bf16 1 M 7.9 / 5.0,
-    // 2 M 7.9 / 7.6.
-    if (tiles2 <= 256) return launch_decompress_small<2>(job(tiles2), tiles2, s, ws, hs);
-    if (tiles4 <= 256) return launch_decompress_small<4>(job(tiles4), tiles4, s, ws, hs);
+    // Small tensors: every workgroup counts the bitmap before its tile itself, in tiles of two rows a lane or, with eight waves, of four
+    // (the tiles of the index).  What a workgroup reads grows with the tensor, to the whole bitmap at its end: 256 KiB at 2 M elements, which
+    // is where the scanner is as fast (224 KiB for wider elements: at 5 % zeros fp32 2.09 M 6.6 with it, 7.0 without).  Measured, us per call on
+    // the GPU, before / after: fp32 5 k elements 6.0 / 2.9, 201 k 6.5 / 3.2, 500 k 6.7 / 3.6.  Two rows up to 320 tiles, against four rows above 256:
+    // fp32 560 k 4.4 / 4.1, bf16 1.06 M 5.5 / 5.3, with eight waves 5.9.  Eight waves, against tiles of four rows and four waves up to 256 of them
+    // and the scanner beyond: fp32 800 k 4.8 / 4.5, 1.05 M 5.0 / 4.6, 1.3 M 6.2 / 5.1, 1.6 M 6.1 / 5.5, 2.6 M 7.2 / 7.5; bf16 1.6 M 6.4 / 5.7, 2.09 M
+    // 7.3 / 6.6, 3.2 M 6.6 / 7.6; fp64 600 k 5.9 / 4.3, 800 k 6.2 / 4.4, 1.2 M 6.8 / 5.6, 1.8 M 7.5 / 7.3, 2.09 M 7.7 / 7.9.  (Sixteen waves: fp32 1.3 M 5.7,
+    // fp64 1.2 M 6.7.)
+    const uint64_t tiles2 = tiles_for(n, s, 2), tiles = tiles_for(n, s);
+    if (tiles2 <= 320) return launch_decompress_small<2, kWaves>(job(tiles2), tiles2, s, ws, hs);
+    if (n <= (s == 2 ? 1u << 21 : 7u << 18)) return launch_decompress_small<4, 2 * kWaves>(job(tiles), tiles, s, ws, hs);
     return launch_decompress(job(tiles), tiles, s, ws, hs);
 }
 
