@@ -40,9 +40,39 @@ def test_sizes_on_both_sides_of_every_line(bt, oracle, dt):
     assert status.tolist() == [0, len(sizes)]
 
 
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16", "f64"])
+def test_launches_whose_waves_read_a_quarter_of_the_counts(bt, oracle, dt):
+    tile = bt.bt_tile_elems(wl.DTYPES[dt])
+    sizes = [257 * tile, 256 * tile, 512 * tile, 256 * tile + 1, 512 * tile + 1, 511 * tile + 3, 384 * tile - 29]
+    ws = bt.new_workspace(max(sizes), wl.DTYPES[dt])
+    for i, n in enumerate(sizes):
+        _check(bt, oracle, dt, n, (0.5, 0.03, 0.97)[i % 3], 800 + i, ws, i % 4)
+    status = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+    bt.bt_workspace_status(ws, status)
+    assert status.tolist() == [0, len(sizes)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_a_launch_whose_last_tile_gives_up_says_so(bt, oracle, dt):
+    """The limit of one poll fails every such call; what it writes stays inside its buffers, and the workspace works again once initialised."""
+    n = 260 * bt.bt_tile_elems(wl.DTYPES[dt]) + 5
+    x = wl.random_sparse(n, dt, 0.5, 4)
+    o_bitmap, o_values, _ = oracle.compress(wl.bits(x))
+    ws = bt.new_workspace(n, x.dtype)
+    words = ws.view(torch.int32)
+    words[bt.BT_WS_WAIT_LIMIT_WORD] = 1
+    _, guard_ok = gpu.gpu_decompress(o_bitmap, o_values, n, x.dtype, ws=ws)
+    assert guard_ok and int(words[bt.BT_WS_ERROR_WORD].item()) == 1
+    out, guard_ok = gpu.gpu_decompress(o_bitmap, o_values, n, x.dtype, ws=ws)
+    assert guard_ok and (out.view(np.uint8) == gpu.SENTINEL).all()
+    bt.bt_workspace_init(ws)
+    _check(bt, oracle, dt, n, 0.5, 5, ws, 1)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
-def test_tiles_that_stop_waiting_count_the_bitmap_themselves(bt, oracle, dt):
-    n = (1 << 21) + 5 * 16384 + 4321
+@pytest.mark.parametrize("tiles", [300, 600])      # without and with a scanner
+def test_tiles_that_stop_waiting_count_the_bitmap_themselves(bt, oracle, dt, tiles):
+    n = tiles * bt.bt_tile_elems(wl.DTYPES[dt]) + 4321
     ws = bt.new_workspace(n, wl.DTYPES[dt])
     words = ws.view(torch.int32)
     words[bt.BT_WS_MUTE_WORD], words[bt.BT_WS_PATIENCE_WORD] = 1, 1
