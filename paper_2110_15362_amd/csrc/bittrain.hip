@@ -791,6 +791,7 @@ template <int W> __device__ __forceinline__ bool any_wave_failed(const uint32_t 
 // (With thousands of tiles the same few lines would be polled by all of them at once.)
 constexpr uint32_t kDirectSlots = 256;
 static_assert(kDirectSlots % 128 == 0, "a lane takes two neighbouring slots of each 128");
+constexpr uint32_t kLog2Xcds = 3;         // consecutive workgroups go to the eight XCDs in turn
 // Up to kQuarterSlots tiles all four waves of a tile read the counts, a quarter of the slots each (wait_for_quarter): one wave's
 // load of 128 counts and the registers for it, four times in a row, would cost more than the scanner's two hops.
 constexpr uint32_t kQuarterSlots = 512;
@@ -1076,7 +1077,11 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
     __shared__ uint64_t s_tile_prefix;
     __shared__ uint32_t s_wave_total[kWaves], s_found[kWaves];
     constexpr bool kQuarters = DIRECT > (int)kDirectSlots;
-    const uint32_t n_slots = gridDim.x - (DIRECT ? 0u : 1u);
+    // (of the launches of few tiles of two rows one workgroup in eight works, see kOneXcdSlots)
+    constexpr bool kMayBeApart = R == 2 && !DENSE;
+    const uint32_t n_slots = kMayBeApart ? job.slots() : gridDim.x - (DIRECT ? 0u : 1u);
+    const uint32_t apart = kMayBeApart && gridDim.x != n_slots ? kLog2Xcds : 0u;
+    if (kMayBeApart && (blockIdx.x & ((1u << apart) - 1u)) != 0) return;
     if (!DIRECT && blockIdx.x == 0) {
         if (threadIdx.x < kWaveSize && !epoch_of(read_header(ws)).failed) scan_counts<3>(ws, job);
         return;
@@ -1085,7 +1090,7 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it in a scalar register
-    const uint32_t slot = blockIdx.x - (DIRECT ? 0u : 1u);
+    const uint32_t slot = kMayBeApart ? blockIdx.x >> apart : blockIdx.x - (DIRECT ? 0u : 1u);
     const Slot sl = job.at(slot);
     const uint32_t tile = sl.tile;
     const uint64_t n = job.n(sl.item);
@@ -2257,11 +2262,20 @@ bt_status check_batch_common(const void *items, size_t count, bt_dtype dt, const
     return BT_OK;
 }
 
+// Tiles of two rows that one XCD takes by itself, its share of a launch of eight times as many workgroups of which the others end at once.
+// XCDs begin a launch up to a microsecond one after the other, and a tile waits for the counts of all before it: with all of
+// them on the one that begins first there is nothing to wait for but the counts, as long as one XCD's memory paths do for the tensor.
+// Nothing rests on where the workgroups really go.  Measured, us, on all XCDs / on one: fp32 12.5 k elements 3.75 / 3.41, 25 k 3.98 / 3.51, 50 k
+// (25 tiles) 3.99 / 3.50, 75 k 4.08 / 3.98, 100 k 4.25 / 4.32; bf16 12.5 k 3.64 / 3.36, 65 k 3.95 / 3.51, 130 k 4.12 / 3.90; fp64 12.5 k 3.97 / 3.44; activation
+// calls, which store more, fp32 12.5 k 3.79 / 3.60, 50 k 3.96 / 4.07, fp64 12.5 k 3.88 / 3.97: not done.
+constexpr uint64_t kOneXcdSlots = 28;
+
 // Launch the compression kernel for a dtype / pruning / dense-output combination on `job`.
 template <int R, int DIRECT, class Job>
 bt_status launch_compress(const Job &job, uint64_t slots, bt_dtype dtype, bool prune, bool dense, double threshold,
                           char *ws, hipStream_t hs) {
-    const uint64_t grid = slots + (DIRECT ? 0u : 1u);      // with or without a scanner
+    static_assert(R != 2 || DIRECT != 0, "tiles of two rows have no scanner");
+    const uint64_t grid = R == 2 && !dense && slots <= kOneXcdSlots ? slots << kLog2Xcds : slots + (DIRECT ? 0u : 1u);      // with or without a scanner
     // Elements narrower than a double are compared in single precision.  For a single x, x > threshold exactly when
     // x > the largest single at or below the threshold, so that is what the kernel gets (a NaN stays one: nothing
     // exceeds it).

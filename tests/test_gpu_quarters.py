@@ -85,3 +85,16 @@ def test_a_launch_whose_last_tile_gives_up_says_so(bt, oracle, dt):
     assert nnz == -7 and int(words[bt.BT_WS_ERROR_WORD].item()) == 1
     bt.bt_workspace_init(ws)
     _check(bt, oracle, x, dt, ws)
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16", "f64"])
+def test_few_tiles_on_one_xcd_and_on_all(bt, oracle, dt):
+    """One workgroup in eight works in the smallest launches, of up to 28 tiles of two rows, without a dense output."""
+    two = 8192 // wl.DTYPES[dt].itemsize
+    sizes = [1, two - 1, two, two + 1, 8 * two, 8 * two + 1, 27 * two + 5, 28 * two, 28 * two + 1, 29 * two, 64 * two, 64 * two + 1]
+    ws = bt.new_workspace(max(sizes), wl.DTYPES[dt])
+    for i, n in enumerate(sizes):
+        _check(bt, oracle, wl.random_sparse(n, dt, (0.5, 0.05, 0.95)[i % 3], seed=140 + i), dt, ws)
+    status = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+    bt.bt_workspace_status(ws, status)
+    assert status.tolist() == [0, 4 * len(sizes)]
