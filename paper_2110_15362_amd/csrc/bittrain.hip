@@ -1617,18 +1617,23 @@ __device__ __noinline__ uint64_t prefix_from_bitmap(const uint32_t *__restrict__
 // stops waiting and counts the bitmap itself (prefix_from_bitmap): so every workgroup that has been
 // started ends, whatever the others do, and every workgroup is started in the end.
 //
-// QUARTERS: launches on one tensor of up to kQuarterSlots tiles, without a scanner, whose tiles' waves read a quarter of the counts each
+// MODE kScannedSoon: the header is asked for behind the bitmap words instead of waited for before them.  That takes a round trip off the
+// chain of launches that the GPU holds at once; in larger ones a workgroup that starts sooner only adds to what the stores compete with.
+// Measured, us, kScanned / this: fp32 3.2 M elements 7.6 / 7.3, 4.5 M 8.9 / 8.6, at 95 % zeros 3.2 M 7.8 / 7.3, fp64 3.2 M 11.0 / 10.5, bf16 33 M (2015
+// tiles) 19.5 / 20.0, 67 M at 65 % zeros 29.7 / 30.1.
+// MODE kQuartered: launches on one tensor of up to kQuarterSlots tiles, without a scanner, whose tiles' waves read a quarter of the counts each
 // as in compression (wait_for_quarter); the last tile ends the call.  Two workgroups a compute unit at most, so there are registers.
 // Measured, us, with the scanner / this: fp32 2.2 M elements 7.1 / 6.7, 3.2 M 7.5 / 7.0, 4.2 M 7.9 / 7.3, at 5 % zeros 9.3 / 8.5; bf16 4.5 M
 // 7.8 / 7.3, 6.4 M 8.0 / 7.4, 8.4 M 8.4 / 7.8, at 5 % 9.7 / 9.2; bf16 3.2 M (196 tiles) 6.6 / 6.6; fp64 2.1 M 7.4 / 8.4 (not done).
-template <int S, bool QUARTERS, class Job>
-__global__ __launch_bounds__(kBlock, QUARTERS ? 7 : kDecompressOcc) void decompress_kernel(const Job job, char *ws) {
+enum { kScanned, kScannedSoon, kQuartered };
+template <int S, int MODE, class Job>
+__global__ __launch_bounds__(kBlock, MODE == kQuartered ? 7 : kDecompressOcc) void decompress_kernel(const Job job, char *ws) {
     using G = Geo<S>;
     __shared__ __attribute__((aligned(16))) unsigned char s_stage[kWaves * G::LDS_WAVE];
     __shared__ uint64_t s_tile_j;
     __shared__ uint32_t s_wave_total[kWaves], s_found[kWaves];
-    const uint32_t n_slots = gridDim.x - (QUARTERS ? 0u : 1u);
-    if (!QUARTERS && blockIdx.x == 0) {
+    const uint32_t n_slots = gridDim.x - (MODE == kQuartered ? 0u : 1u);
+    if (MODE != kQuartered && blockIdx.x == 0) {
         if (threadIdx.x < kWaveSize && !epoch_of(read_header(ws)).failed) scan_counts<2>(ws, job);
         return;
     }
@@ -1636,16 +1641,26 @@ __global__ __launch_bounds__(kBlock, QUARTERS ? 7 : kDecompressOcc) void decompr
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t slot = blockIdx.x - (QUARTERS ? 0u : 1u);
+    const uint32_t slot = blockIdx.x - (MODE == kQuartered ? 0u : 1u);
+    // The header while the bitmap words are on their way, as in compression, or (MODE = kScanned) before them.
+    HeaderWords header;
+    if (MODE == kScanned) {
+        header = read_header(ws);
+        if (__builtin_expect(epoch_of(header).failed, 0)) {
+            if (lane == 0) s_wave_total[wave] = kWaveFailed;
+            lds_barrier();
+            return;
+        }
+    }
     const Slot sl = job.at(slot);
-    // the bitmap words first: everything else waits for them
+    // everything else waits for these
     const uint32_t *const bitmap = job.bitmap(sl.item);
     const uint64_t n = job.n(sl.item);
     const Quarter<S> quarter = quarter_load<S>(bitmap, n, sl.tile, lane, wave);
-    // The header while they are on their way, as in compression.  (Waited for before them, us: fp32 3.2 M elements 7.6 / 7.3, 4.5 M 8.9 / 8.6, 12.8 M
-    // 16.3 / 16.0, at 95 % zeros 3.2 M 7.8 / 7.3, bf16 6.4 M 8.1 / 7.8, fp64 3.2 M 11.0 / 10.4; batches and large tensors the same.)
-    asm volatile("" ::: "memory");
-    const HeaderWords header = read_header(ws);
+    if (MODE != kScanned) {
+        asm volatile("" ::: "memory");
+        header = read_header(ws);
+    }
     BT_TL(slot, 0);
     // masks and ranks; what they add up to is this wave's share of the tile's count
     Restoring<S> r;
@@ -1671,7 +1686,7 @@ __global__ __launch_bounds__(kBlock, QUARTERS ? 7 : kDecompressOcc) void decompr
     // traffic on the workspace's few lines low) and passes the answer on through LDS
     uint64_t tile_j;
     bool complete = false;
-    if constexpr (QUARTERS) {
+    if constexpr (MODE == kQuartered) {
         const bool last = slot + 1 == n_slots;
         const uint32_t mine = wait_for_quarter(ws, slot, last, ep.cur, wave, polls);
         if (lane == 0) s_found[wave] = mine;
@@ -1694,7 +1709,7 @@ __global__ __launch_bounds__(kBlock, QUARTERS ? 7 : kDecompressOcc) void decompr
     BT_TL(slot, 2);
     restore_fetch<S>(job.values(sl.item), job.cap(sl.item), tile_j, before_wave, lane, r);
     restore_store<S>(r, n, job.out(sl.item), sl.tile, strip, lane, wave);
-    if (QUARTERS && complete && wave == 0 && lane == 0) header_finish(reinterpret_cast<uint32_t *>(ws), n_slots, ep.cur, ep.calls);
+    if (MODE == kQuartered && complete && wave == 0 && lane == 0) header_finish(reinterpret_cast<uint32_t *>(ws), n_slots, ep.cur, ep.calls);
     BT_TL(slot, 3);
     BT_TL_VALUE(slot, 5, polls);
 }
@@ -2302,9 +2317,12 @@ bt_status launch_compress(const Job &job, uint64_t slots, bt_dtype dtype, bool p
     return BT_ERR_UNSUPPORTED;
 }
 
-template <class Job> bt_status launch_decompress(const Job &job, uint64_t slots, int s, char *ws, hipStream_t hs) {
-    const auto go = [&](auto kernel) { return launch(kernel, slots + 1, kBlock, hs, job, ws); };      // and the scanner
-    return s == 8 ? go(decompress_kernel<8, false, Job>) : s == 4 ? go(decompress_kernel<4, false, Job>) : go(decompress_kernel<2, false, Job>);
+template <int MODE, class Job> bt_status launch_decompress(const Job &job, uint64_t slots, int s, char *ws, hipStream_t hs) {
+    const auto go = [&](auto kernel) { return launch(kernel, slots + (MODE == kQuartered ? 0 : 1), kBlock, hs, job, ws); };      // with or without a scanner
+    if (s == 4) return go(decompress_kernel<4, MODE, Job>);
+    if (s == 2) return go(decompress_kernel<2, MODE, Job>);
+    if constexpr (MODE == kQuartered) return BT_ERR_UNSUPPORTED;      // (bt_decompress has none of these)
+    else return go(decompress_kernel<8, MODE, Job>);
 }
 
 template <int R, int W> bt_status launch_decompress_small(const DecompressOne &job, uint64_t tiles, int s, char *ws, hipStream_t hs) {
@@ -2552,11 +2570,10 @@ bt_status bt_decompress(const uint32_t *d_bitmap, const void *d_values, uint64_t
     const uint64_t tiles2 = tiles_for(n, s, 2), tiles = tiles_for(n, s);
     if (tiles2 <= 320) return launch_decompress_small<2, kWaves>(job(tiles2), tiles2, s, ws, hs);
     if (n <= (s == 2 ? 1u << 21 : 7u << 18)) return launch_decompress_small<4, 2 * kWaves>(job(tiles), tiles, s, ws, hs);
-    // More tiles than a compression without a scanner has with one wave waiting, but not many: without a scanner here too (see decompress_kernel).
-    if (s != 8 && tiles > kDirectSlots && tiles <= kQuarterSlots)
-        return s == 4 ? launch(decompress_kernel<4, true, DecompressOne>, tiles, kBlock, hs, job(tiles), ws)
-                      : launch(decompress_kernel<2, true, DecompressOne>, tiles, kBlock, hs, job(tiles), ws);
-    return launch_decompress(job(tiles), tiles, s, ws, hs);
+    // (see decompress_kernel)
+    if (s != 8 && tiles > kDirectSlots && tiles <= kQuarterSlots) return launch_decompress<kQuartered>(job(tiles), tiles, s, ws, hs);
+    if (tiles <= 1024) return launch_decompress<kScannedSoon>(job(tiles), tiles, s, ws, hs);
+    return launch_decompress<kScanned>(job(tiles), tiles, s, ws, hs);
 }
 
 bt_status bt_relu_backward_from_bitmap(const uint32_t *d_bitmap, const void *d_grad_out, uint64_t n, bt_dtype dtype,
@@ -2710,7 +2727,7 @@ bt_status bt_decompress_batch(const bt_decompress_item *items, size_t count, bt_
             b.n_[i] = it.n;
             b.out_[i] = it.d_out;
         }
-        const bt_status ls = launch_decompress(b, b.lay.start[c], s, ws, hs);
+        const bt_status ls = launch_decompress<kScanned>(b, b.lay.start[c], s, ws, hs);
         if (ls != BT_OK) return ls;
     }
     return BT_OK;
