@@ -61,8 +61,9 @@ class _StreamState:
         return p
 
     def workspace(self, n, dtype):
-        ws = self.ws
-        if n <= self.fits.get(dtype, -1):     # (a workspace is only ever replaced by a larger one)
+        fits = self.fits.get(dtype, -1)
+        ws = self.ws                          # (after `fits`: another thread may replace it, by a larger one only, between the two)
+        if n <= fits:
             return ws
         need = bt.bt_workspace_bytes(n, dtype)
         if ws is None or ws.numel() < need:

@@ -237,6 +237,20 @@ def test_a_new_workspace_is_seen_by_others_only_once_it_is_initialised(ag, packi
     assert seen == [False, False]
 
 
+def test_a_workspace_that_another_thread_replaces_meanwhile_is_not_the_small_one(ag, packing):
+    """The larger one is there between this thread's two looks, at what the workspace serves and at the workspace."""
+    st = packing.state
+    st.workspace(N, torch.float32)
+    large = torch.empty(ag.bt.bt_workspace_bytes(1 << 28, torch.float32), dtype=torch.uint8)
+
+    class Fits(dict):
+        def get(self, dtype, default):
+            st.ws = large
+            return 1 << 28
+    st.fits = Fits()
+    assert st.workspace(1 << 28, torch.float32) is large
+
+
 @pytest.fixture
 def relu_backward(ag, monkeypatch):
     """bitmap_relu's backward with the kernel's work done by torch on what it is handed: the memory at an address."""
