@@ -42,8 +42,9 @@ class _StreamState:
 
     def __init__(self, device):
         self.device = device
-        self.ws = None
-        self.fits = {}        # dtype -> the most elements that `ws` is known to serve
+        self.ws = None        # replaced by a larger one only
+        self.fits = {}        # dtype -> elements that `ws`, and so whatever replaces it, is known to serve
+        self.lock = threading.RLock()
         self.scratch = {}
         self.nnz = torch.zeros(1, dtype=torch.int64, device=device)
         self.places = []      # free ones
@@ -62,15 +63,17 @@ class _StreamState:
 
     def workspace(self, n, dtype):
         fits = self.fits.get(dtype, -1)
-        ws = self.ws                          # (after `fits`: another thread may replace it, by a larger one only, between the two)
+        ws = self.ws                          # (after `fits`: another thread may replace it between the two)
         if n <= fits:
             return ws
         need = bt.bt_workspace_bytes(n, dtype)
         if ws is None or ws.numel() < need:
             ws = torch.empty(max(need, 1 << 16), dtype=torch.uint8, device=self.device)
             bt.bt_workspace_init(ws)
-            self.ws = ws                      # (only now: another thread on this stream may look for one in between)
-        self.fits[dtype] = n
+            with self.lock:                   # (only now: another thread on this stream may look for one in between, or make one too)
+                if self.ws is None or self.ws.numel() < ws.numel():
+                    self.ws = ws
+        self.fits[dtype] = n                  # (behind a workspace that serves them: this one, or a larger one)
         return ws
 
     def take_scratch(self, n, dtype):

@@ -251,6 +251,47 @@ def test_a_workspace_that_another_thread_replaces_meanwhile_is_not_the_small_one
     assert st.workspace(1 << 28, torch.float32) is large
 
 
+@pytest.mark.parametrize("last", ["small", "large"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_of_two_new_workspaces_the_larger_one_stays(ag, packing, monkeypatch, dtype, last):
+    """Two threads on one stream find no workspace, both make one, and whichever is through last puts its own there.  From then on
+    everything that either has asked for is served."""
+    st, both, first_is_through = packing.state, threading.Barrier(2), threading.Event()
+    asked = {"small": (N, dtype), "large": (1 << 28, torch.float32)}
+
+    def init(ws):
+        both.wait(10)
+        if threading.current_thread().name == last:
+            first_is_through.wait(10)
+    monkeypatch.setattr(ag.bt, "bt_workspace_init", init)
+
+    def ask(who):
+        got[who] = st.workspace(*asked[who])
+        if who != last:
+            first_is_through.set()
+    got = {}
+    threads = [threading.Thread(target=ask, args=(who,), name=who) for who in asked]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(20)
+    monkeypatch.setattr(ag.bt, "bt_workspace_init", lambda ws: None)
+    for who, (n, dtype) in asked.items():
+        need = ag.bt.bt_workspace_bytes(n, dtype)
+        assert got[who].numel() >= need and st.workspace(n, dtype).numel() >= need
+
+
+def test_a_larger_workspace_that_comes_while_a_smaller_one_is_initialised_stays(ag, packing, monkeypatch):
+    st = packing.state
+
+    def init(ws):
+        if ws.numel() == 1 << 16:
+            st.workspace(1 << 28, torch.float32)
+    monkeypatch.setattr(ag.bt, "bt_workspace_init", init)
+    st.workspace(N, torch.bfloat16)
+    assert st.workspace(1 << 28, torch.float32).numel() >= ag.bt.bt_workspace_bytes(1 << 28, torch.float32)
+
+
 @pytest.fixture
 def relu_backward(ag, monkeypatch):
     """bitmap_relu's backward with the kernel's work done by torch on what it is handed: the memory at an address."""
