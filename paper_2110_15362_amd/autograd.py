@@ -34,6 +34,11 @@ def _native():
     return bt._call
 
 
+def _elsewhere(device):
+    """Whether a tensor on `device` needs it made the current one: calls and allocations go to the current device's stream."""
+    return device.index is not None and device.index != torch.cuda.current_device()
+
+
 class _StreamState:
     """Reusable buffers of one (device, stream): workspace, worst-case value scratch, and places in pinned host memory
     that compressions write their nnz to (a call that gave up a wait, or found a workspace on which one was given up, writes
@@ -277,6 +282,9 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
         if (not t.is_cuda or t.dtype not in _SUPPORTED or t.numel() < self.min_numel or not t.is_contiguous()
                 or isinstance(t, torch.nn.Parameter) or t.is_neg() or t._is_zerotensor() or t.data_ptr() % 16 != 0):
             return t                      # (the library takes memory from a 16-byte boundary on that holds the values)
+        if _elsewhere(t.device):
+            with torch.cuda.device(t.device):
+                return self._pack(t)
         if type(t) is torch.Tensor:
             packed = self._pack_plain(t)
             if packed is not None:
@@ -319,6 +327,9 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
     def _unpack(self, obj):
         if not isinstance(obj, _Packed):
             return obj
+        if _elsewhere(obj.device):
+            with torch.cuda.device(obj.device):
+                return self._unpack(obj)
         if obj.pending:
             self._finish_waiting(only=obj)
         if obj.dense is not None:
@@ -345,6 +356,9 @@ class _BitmapReLU(torch.autograd.Function):
                 return y
         if not (x.is_cuda and x.dtype in _SUPPORTED and x.is_contiguous()):
             raise TypeError("bitmap_relu needs a contiguous float64/float32/float16/bfloat16 device tensor")
+        if _elsewhere(x.device):
+            with torch.cuda.device(x.device):
+                return _BitmapReLU.forward(ctx, x, fused)
         n = x.numel()
         bitmap = torch.empty((n + 31) // 32, dtype=torch.int32, device=x.device)
         if fused:
@@ -367,6 +381,9 @@ class _BitmapReLU(torch.autograd.Function):
         grad_in = _native().relu_gradient(ctx.bitmap, grad_out)
         if grad_in is not None:
             return grad_in, None
+        if _elsewhere(grad_out.device):
+            with torch.cuda.device(grad_out.device):
+                return _BitmapReLU.backward(ctx, grad_out)
         grad_out = _held(grad_out.contiguous())
         if grad_out.data_ptr() % 16 != 0:      # (a part of a concatenation's gradient)
             grad_out = grad_out.clone()

@@ -21,6 +21,7 @@
 #include <ATen/Functions.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -382,9 +383,18 @@ static PyObject *py_relu_forward(PyObject *self, PyObject *const *args, Py_ssize
  *
  * What autograd.py does around a call, allocations included, in one go: written in Python, packing took the host 35 us beside the
  * compression, and while it waits for nnz all of that is time in which the GPU has nothing to do.  Each returns None for tensors that are not
- * plain, which autograd.py then takes the general way.  The GIL is released from the first allocation on. */
+ * plain or not on the current device, whose stream the calls go to and the copies must be behind them on; autograd.py then takes the
+ * general way, or makes their device the current one.  The GIL is released from the first allocation on. */
 
 static at::TensorOptions like(const at::Tensor &t, const at::ScalarType type) { return at::TensorOptions().dtype(type).device(t.device()); }
+
+static bool all_here(tensor *a, PyObject *const *args, const int count) {
+    if (!has_device || !all_plain(a, args, count)) return false;
+    const c10::DeviceIndex current = c10::hip::current_device();
+    for (int i = 0; i < count; ++i)
+        if (THPVariable_Unpack(args[i]).device().index() != current) return false;
+    return true;
+}
 
 static bool aligned(const tensor *a) { return (reinterpret_cast<uintptr_t>(a->ptr.p) & 15) == 0; }
 
@@ -417,7 +427,7 @@ static PyObject *py_pack(PyObject *self, PyObject *const *args, Py_ssize_t nargs
     tensor a[3];
     uint64_t place;
     if (expect(nargs, 5) != 0) return NULL;
-    if (!has_device || !all_plain(a, args, 3) || a[0].code < 0 || !aligned(&a[0])) Py_RETURN_NONE;
+    if (!all_here(a, args, 3) || a[0].code < 0 || !aligned(&a[0])) Py_RETURN_NONE;
     if (a[1].dtype != a[0].dtype || a[1].numel < a[0].numel) return fail(PyExc_TypeError, "scratch must have the dtype of x and room for it"), nullptr;
     Py_INCREF(args[3]);
     if (to_u64(args[3], &place) != 0) return NULL;
@@ -453,7 +463,7 @@ static PyObject *py_unpack(PyObject *self, PyObject *const *args, Py_ssize_t nar
     (void)self;
     tensor a[3];
     if (expect(nargs, 4) != 0) return NULL;
-    if (!has_device || !PyTuple_Check(args[3]) || !all_plain(a, args, 3) || a[1].code < 0) Py_RETURN_NONE;
+    if (!PyTuple_Check(args[3]) || !all_here(a, args, 3) || a[1].code < 0) Py_RETURN_NONE;
     std::vector<int64_t> shape;
     uint64_t n = 1;
     for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(args[3]); ++i) {
@@ -483,7 +493,7 @@ static PyObject *py_relu(PyObject *self, PyObject *const *args, Py_ssize_t nargs
     (void)self;
     tensor a[1];
     if (expect(nargs, 1) != 0) return NULL;
-    if (!has_device || !all_plain(a, args, 1) || a[0].code < 0 || !aligned(&a[0])) Py_RETURN_NONE;
+    if (!all_here(a, args, 1) || a[0].code < 0 || !aligned(&a[0])) Py_RETURN_NONE;
     const at::Tensor x = THPVariable_Unpack(args[0]);
     at::Tensor y, bitmap;
     bt_status st;
@@ -505,7 +515,7 @@ static PyObject *py_relu_gradient(PyObject *self, PyObject *const *args, Py_ssiz
     (void)self;
     tensor a[2];
     if (expect(nargs, 2) != 0) return NULL;
-    if (!has_device || !all_plain(a, args, 2) || a[1].code < 0 || !aligned(&a[1])) Py_RETURN_NONE;
+    if (!all_here(a, args, 2) || a[1].code < 0 || !aligned(&a[1])) Py_RETURN_NONE;
     if (check_bitmap(&a[0], a[1].numel) != 0) return NULL;
     const at::Tensor grad = THPVariable_Unpack(args[1]);
     at::Tensor out;

@@ -335,3 +335,75 @@ def test_tensors_whose_memory_does_not_hold_their_values(ag, packing, relu_backw
     x = torch._neg_view(grad[:32])
     ag._BitmapReLU.forward(torch.autograd.function.FunctionCtx(), x.as_subclass(_OnDevice), True)
     assert not handed[0].is_neg() and torch.equal(handed[0], -grad[:32])
+
+
+class _Elsewhere(torch.Tensor):
+    """A tensor of the second of two devices, as far as one can ask it."""
+    is_cuda = True
+    device = torch.device("cuda", 1)
+
+
+@pytest.fixture
+def two_devices(ag, monkeypatch):
+    """The first of two devices is the current one.  `calls`: (what was called, the device that was current then)."""
+    current, calls = [0], []
+    empty, empty_like = torch.empty, torch.empty_like
+
+    @contextlib.contextmanager
+    def device(d):
+        current.append(torch.device(d).index)
+        yield
+        current.pop()
+
+    class Stream(_Stream):
+        cuda_stream = 0
+
+        def synchronize(self):
+            note("wait")
+
+    def note(name):
+        calls.append((name, current[-1]))
+
+    def compress(t, packed, values, st, ws, stream):
+        note("compress")
+        assert stream == "stream of %d" % current[-1]
+        place = st.place()
+        place.word[0] = NNZ
+        return place
+
+    class Event(_Event):
+        def record(self, stream):
+            note("record")
+    monkeypatch.setattr(torch, "empty", lambda *a, pin_memory=False, device=None, **k: empty(*a, **k))
+    monkeypatch.setattr(torch, "empty_like", lambda t: empty_like(t.as_subclass(torch.Tensor)))
+    monkeypatch.setattr(torch.cuda, "device", device)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: current[-1])
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d=None: Stream("stream of %d" % current[-1]))
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    states = {}
+    monkeypatch.setattr(ag, "_state", lambda device: states.setdefault(device, ag._StreamState(torch.device("cpu"))))
+    monkeypatch.setattr(ag.BitmapStash, "_compress", staticmethod(compress))
+    for name in ("bt_workspace_init", "bt_decompress_indexed", "bt_relu_forward", "bt_relu_backward_from_bitmap", "bt_activation_compress"):
+        monkeypatch.setattr(ag.bt, name, lambda *a, name=name: note(name))
+    return calls
+
+
+@pytest.mark.parametrize("deferred", [False, True])
+def test_a_tensor_off_the_current_device_is_packed_on_its_own(ag, two_devices, deferred):
+    """Its values are copied, and it is unpacked and used, on its device's stream, which nothing else orders behind a compression on
+    another device's."""
+    stash = ag.BitmapStash(deferred=deferred)
+    packed = stash._pack(_sparse(N, 1).as_subclass(_Elsewhere))
+    assert isinstance(packed, ag._Packed)
+    stash._unpack(packed)
+    assert {"compress", "bt_workspace_init", "bt_decompress_indexed"} <= {name for name, _ in two_devices}
+    assert {device for _, device in two_devices} == {1} and torch.cuda.current_device() == 0
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_bitmap_relu_off_the_current_device(ag, two_devices, fused):
+    ctx = torch.autograd.function.FunctionCtx()
+    ag._BitmapReLU.forward(ctx, _sparse(N, 1).as_subclass(_Elsewhere), fused)
+    ag._BitmapReLU.backward(ctx, _sparse(N, 2).as_subclass(_Elsewhere))
+    assert {"bt_activation_compress" if fused else "bt_relu_forward", "bt_relu_backward_from_bitmap"} <= {name for name, _ in two_devices}
+    assert {device for _, device in two_devices} == {1} and torch.cuda.current_device() == 0
