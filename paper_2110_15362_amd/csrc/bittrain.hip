@@ -2290,6 +2290,9 @@ template <int R, int DIRECT, class Job>
 bt_status launch_compress(const Job &job, uint64_t slots, bt_dtype dtype, bool prune, bool dense, double threshold,
                           char *ws, hipStream_t hs) {
     static_assert(R != 2 || DIRECT != 0, "tiles of two rows have no scanner");
+    // A workspace is sized in tiles of kRows rows (bt_workspace_bytes) and has one block at the least: that one is all that a launch
+    // of smaller tiles can count on, whose counts would lie behind the workspace beyond it.
+    static_assert(R == kRows || (DIRECT != 0 && DIRECT <= kSlotsPerBlock), "smaller tiles have the slots of one block");
     const uint64_t grid = R == 2 && !dense && slots <= kOneXcdSlots ? slots << kLog2Xcds : slots + (DIRECT ? 0u : 1u);      // with or without a scanner
     // Elements narrower than a double are compared in single precision.  For a single x, x > threshold exactly when
     // x > the largest single at or below the threshold, so that is what the kernel gets (a NaN stays one: nothing
