@@ -57,13 +57,14 @@ class _StreamState:
                               # may still be written to, and not be something else by then
 
     def place(self):
-        """A place for one compression's nnz, holding -1; back to `places` when that compression is over."""
+        """A place for one compression's nnz, holding -2 until that compression is queued and -1 from then on; back to `places` when it
+        is over."""
         try:
             p = self.places.pop()
         except IndexError:                # (not asked before: another thread may take the last one)
             self.places += [_Place(self) for _ in range(7)]
             p = _Place(self)
-        p.word[0] = -1
+        p.word[0] = -2
         return p
 
     def workspace(self, n, dtype):
@@ -107,7 +108,7 @@ class _Place:
         state.words.append(self.memory)
 
     def read(self):
-        """nnz, or -1 from a compression that failed; only after the compression is over."""
+        """nnz, or -1 from a compression that failed; only after the compression is over, or -2 if none has been queued."""
         return int(self.word[0])
 
     def give_back(self):
@@ -242,7 +243,7 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
         try:
             got = _native().pack(t, values, ws, place.address, not self.deferred)
         except BaseException:
-            if place.read() != -1:            # (over as far as the place is concerned: it was the copy that failed)
+            if place.read() != -1:            # (not queued at all, or over as far as the place is concerned: it was the copy that failed)
                 place.give_back()
             raise
         finally:
@@ -319,9 +320,13 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
         """bt_compress_indexed of `t`, nnz to a place on the host, which is returned.  (Through device memory it took a kernel for
         the status and a copy.)"""
         place = st.place()
-        bt._check("bt_compress_indexed", bt.lib().bt_compress_indexed(
+        place.word[0] = -1
+        status = bt.lib().bt_compress_indexed(
             t.data_ptr(), t.numel(), bt.dtype_code(t.dtype), packed.bitmap.data_ptr(), values.data_ptr(), values.numel(), place.address,
-            packed.index.data_ptr(), ws.data_ptr(), ws.numel(), stream.cuda_stream))
+            packed.index.data_ptr(), ws.data_ptr(), ws.numel(), stream.cuda_stream)
+        if status not in (bt.BT_OK, bt.BT_ERR_HIP):                # refused: nothing is queued that could write to it
+            place.give_back()
+        bt._check("bt_compress_indexed", status)
         return place
 
     def _unpack(self, obj):

@@ -403,6 +403,9 @@ static PyObject *wrap(const at::Tensor &t) {
     Py_RETURN_NONE;
 }
 
+/* What a place holds while nothing is queued that could write to it. */
+static const int64_t kNotQueued = -2;
+
 /* The nnz of a compression on `stream`, which replaces the -1 at `word` in pinned memory as soon as it is known, a little before the last
  * values are written.  One that failed leaves the -1 there, which is known when the stream has come past it. */
 static int64_t wait_for_nnz(const volatile int64_t *word, const c10::hip::HIPStream &stream) {
@@ -420,7 +423,8 @@ static int64_t wait_for_nnz(const volatile int64_t *word, const c10::hip::HIPStr
 }
 
 /* (x, scratch, workspace, address of the place, wait?) -> None, or (bitmap, index) of the compression that has been started;
- * or, having waited for it, (bitmap, index, nnz, values cut to size): nnz -1 if it failed, values None if it is not worth keeping. */
+ * or, having waited for it, (bitmap, index, nnz, values cut to size): nnz -1 if it failed, values None if it is not worth keeping.
+ * The place holds -1 from when the compression may have been queued: whoever catches an error can tell whether it may still be written to. */
 static PyObject *py_pack(PyObject *self, PyObject *const *args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     (void)self;
@@ -444,10 +448,13 @@ static PyObject *py_pack(PyObject *self, PyObject *const *args, Py_ssize_t nargs
         bitmap = at::empty({(int64_t)((n + 31) / 32)}, like(x, at::kInt));
         index = at::empty({(int64_t)(lib.index_bytes(n, code) / 8)}, like(x, at::kLong));
         const c10::hip::HIPStream stream = c10::hip::getCurrentHIPStream();
+        volatile int64_t *const word = (volatile int64_t *)(uintptr_t)place;
+        *word = -1;
         st = lib.compress_indexed(a[0].ptr, n, code, (uint32_t *)bitmap.data_ptr(), a[1].ptr, a[1].numel, (uint64_t *)(uintptr_t)place,
                                   (uint64_t *)index.data_ptr(), a[2].ptr, a[2].numel * a[2].width, (bt_stream)stream.stream());
+        if (st != BT_OK && st != BT_ERR_HIP) *word = kNotQueued;      /* refused */
         if (st == BT_OK && wait) {
-            nnz = wait_for_nnz((const volatile int64_t *)(uintptr_t)place, stream);
+            nnz = wait_for_nnz(word, stream);
             if (nnz >= 0 && lib.compressed_size(n, (uint64_t)nnz, code) + 8 * (uint64_t)index.numel() < n * a[0].width) values = scratch.narrow(0, 0, nnz).clone();
         }
     }

@@ -292,6 +292,39 @@ def test_a_larger_workspace_that_comes_while_a_smaller_one_is_initialised_stays(
     assert st.workspace(1 << 28, torch.float32).numel() >= ag.bt.bt_workspace_bytes(1 << 28, torch.float32)
 
 
+@pytest.mark.parametrize("deferred", [False, True])
+@pytest.mark.parametrize("started", [False, True])
+def test_a_packing_that_raises_gives_its_place_back_unless_its_compression_may_still_write_to_it(ag, packing, monkeypatch, deferred, started):
+    """Out of memory for the bitmap, or a refused call, before anything is queued; and an error met while the host waits."""
+    import ctypes
+    import types
+
+    def pack(t, scratch, ws, place, wait):
+        if started:
+            ctypes.c_int64.from_address(place).value = -1
+        raise torch.OutOfMemoryError("out of memory")
+    st = packing.state
+    monkeypatch.setattr(ag, "_native", lambda: types.SimpleNamespace(pack=pack))
+    for lost in range(1, 4):
+        with pytest.raises(torch.OutOfMemoryError):
+            ag.BitmapStash(deferred=deferred)._pack_plain(_sparse(N, 1))
+        assert len(st.places) == (8 - lost if started else 8) and _distinct(st.places)
+    assert len(st.words) == 8
+
+
+def test_a_refused_compression_gives_its_place_back(ag, monkeypatch):
+    """The general way: the library refuses (here, a workspace that is none), so nothing is queued that could write to the place."""
+    st = ag._StreamState(torch.device("cpu"))
+    x = _sparse(N, 1)
+    packed = ag._Packed(torch.zeros(N // 32, dtype=torch.int32), None, torch.zeros(1, dtype=torch.int64), x.shape, x.dtype, st.device)
+
+    class Stream:
+        cuda_stream = 0
+    with pytest.raises(ag.bt.BitTrainError):
+        ag.BitmapStash._compress(x, packed, torch.empty(N), st, torch.empty(0, dtype=torch.uint8), Stream())
+    assert len(st.places) == 8 and _distinct(st.places)
+
+
 @pytest.fixture
 def relu_backward(ag, monkeypatch):
     """bitmap_relu's backward with the kernel's work done by torch on what it is handed: the memory at an address."""

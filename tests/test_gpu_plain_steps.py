@@ -73,3 +73,20 @@ def test_what_is_refused_stays_refused(ag):
     for t in (x.t()[:, 1:], x.int(), x.cpu(), x.view(-1)[1:], torch.nn.Parameter(x)):
         assert stash._pack(t) is t
     assert stash.stats["tensors"] == 0
+
+
+@pytest.mark.parametrize("deferred", [False, True])
+def test_a_refused_packing_gives_its_place_back(ag, deferred, monkeypatch):
+    """The library's host checks refuse the workspace: nothing is queued, and no place on the host is lost."""
+    from paper_2110_15362_amd import bittrain as bt
+    x = torch.randn(5000, device="cuda").relu()
+    st = ag._state(x.device)
+    assert ag.BitmapStash(min_numel=1)._pack(x) is not None
+    places = len(st.places)
+    with monkeypatch.context() as m:
+        m.setattr(st, "workspace", lambda n, dtype: torch.empty(128, dtype=torch.uint8, device="cuda"))
+        with pytest.raises(bt.BitTrainError, match="workspace"):
+            ag.BitmapStash(deferred=deferred)._pack(x)
+    assert len(st.places) == places and len({p.address for p in st.places}) == places
+    stash = ag.BitmapStash()
+    assert torch.equal(stash._unpack(stash._pack(x)), x)
