@@ -155,8 +155,9 @@ bt_status bt_workspace_init(void *d_workspace, size_t workspace_bytes, bt_stream
  *               device can address (hipHostMalloc): the host may read it once it has waited for the
  *               stream or for an event behind the call.  A call that gives up a wait, or finds a
  *               workspace on which one was given up, leaves it as it was; others write it with one 8-byte
- *               store, so a host that has put a number there which no nnz is may also look for the change:
- *               it then has nnz, but not yet the rest of the call's outputs.
+ *               store that is visible to the whole system.  So a host that has put a number there which no nnz
+ *               is may also look for the change, if the memory is coherent (hipHostMalloc's is unless asked
+ *               otherwise): it then has nnz, but not yet the rest of the call's outputs.
  *   d_workspace bt_workspace_bytes(n, dtype) bytes, 128-byte aligned, initialised
  *               once with bt_workspace_init.  A workspace must not be shared by
  *               two calls that can be in flight at the same time: calls that use

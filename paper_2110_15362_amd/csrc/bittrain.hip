@@ -533,6 +533,8 @@ __device__ __forceinline__ void ws_store64(void *p, uint64_t v) {
 __device__ __forceinline__ void ws_store32(void *p, uint32_t v) {
     __hip_atomic_store(static_cast<uint32_t *>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// nnz, which a host may be looking at while the kernel runs: one store that everybody sees
+__device__ __forceinline__ void store_nnz(uint64_t *nnz, const uint64_t v) { __hip_atomic_store(nnz, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
 // count + 1 of `tile` in copy c
 __device__ __forceinline__ char *ws_count(char *ws, uint32_t tile, uint32_t copy) {
     return ws + kHeaderBytes + (size_t)(tile >> 8) * kBlockBytes + 1024u * copy + 4u * (tile & 255u);
@@ -744,9 +746,9 @@ template <int kRowScan, class Job> __device__ __forceinline__ void scan_counts(c
         static_assert(kMaxBatchCompress < kWaveSize, "a lane per tensor and one behind the last");
         if (my_start >= n_slots) my_sum = all;      // (empty tensors at the end, and the lane behind the last tensor)
         const uint64_t next = __shfl_down((unsigned long long)my_sum, 1, kWaveSize);
-        if (lane < job.count()) *job.nnz(lane) = next - my_sum;
+        if (lane < job.count()) store_nnz(job.nnz(lane), next - my_sum);
     } else if constexpr (Job::kTotals) {
-        if (lane == 0) *job.nnz(0) = all;
+        if (lane == 0) store_nnz(job.nnz(0), all);
     }
     if (lane == 0) {
         // every slot's workgroup has published its count by now, hence has read the header: advance it
@@ -1337,7 +1339,7 @@ __global__ __launch_bounds__(kBlock, kCompressOcc) void compress_kernel(const Jo
     // written, with the header's count of calls read only then, it was a microsecond behind the others.  With both, us: fp32 12.5 k
     // elements 4.3 -> 3.9, 60 k 4.5 -> 4.1, 201 k 5.0 -> 4.7, bf16 60 k 4.8 -> 4.3, fp64 60 k 5.0 -> 4.4, fp32 activation call on 12.5 k 4.5 -> 4.2.)
     if (DIRECT && complete && lane_number() == 0) {
-        *job.nnz(0) = tile_g0 + tile_total;
+        store_nnz(job.nnz(0), tile_g0 + tile_total);
         // every slot's workgroup has published its count by now, hence has read the header: advance it
         header_finish(reinterpret_cast<uint32_t *>(ws), n_slots, ep.cur, ep.calls);
     }
@@ -2161,6 +2163,11 @@ __global__ void fill_u64_kernel(uint64_t *p, uint64_t count, uint64_t value) {
     if (i < count) p[i] = value;
 }
 
+// Compression of no elements.
+__global__ void no_values_kernel(uint64_t *nnz) {
+    if (threadIdx.x == 0) store_nnz(nnz, 0);
+}
+
 // bt_workspace_status: d_status[0] = 1 if a wait was given up on the workspace (else 0), d_status[1] = calls completed.
 __global__ void copy_status_kernel(const uint32_t *ws, uint32_t *d_status) {
     if (threadIdx.x == 0) {
@@ -2433,7 +2440,7 @@ static bt_status compress_common(const void *d_in, uint64_t n, bt_dtype dtype, b
     const int s = elem_size(dtype);
     hipStream_t hs = (hipStream_t)stream;
     if (n == 0) {
-        return launch(fill_u64_kernel, 1, 64, hs, d_nnz, (uint64_t)1, (uint64_t)0);
+        return launch(no_values_kernel, 1, 64, hs, d_nnz);
     }
     if (d_in == nullptr || d_bitmap == nullptr) return BT_ERR_NULL;
     if (d_values == nullptr && values_cap != 0) return BT_ERR_NULL;

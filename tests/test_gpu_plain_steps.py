@@ -1,5 +1,7 @@
 """The autograd steps on ordinary tensors, which one call in C++ takes with its allocations, against the same steps on a subclass, which
 go the general way call by call: the same bytes, the same decisions and the same statistics."""
+import time
+
 import pytest
 import torch
 
@@ -90,3 +92,39 @@ def test_a_refused_packing_gives_its_place_back(ag, deferred, monkeypatch):
     assert len(st.places) == places and len({p.address for p in st.places}) == places
     stash = ag.BitmapStash()
     assert torch.equal(stash._unpack(stash._pack(x)), x)
+
+
+def test_a_host_that_looks_at_nnz_sees_it_change_once(ag):
+    """In pinned memory that held -1, without waiting for the stream, from every way to end a compression: no elements, the last of
+    two-row, four-row and eight-row tiles and of those whose four waves read the counts, the scanner, and a batch with an empty tensor."""
+    from paper_2110_15362_amd import bittrain as bt
+    g = torch.Generator(device="cuda").manual_seed(6)
+    tile, L = bt.bt_tile_elems(torch.float32), bt.lib()
+    sizes = [0, 1, 5 * tile + 3, 100 * tile, 250 * tile, 300 * tile, 1000 * tile + 1]
+    xs = [torch.randn(n, generator=g, device="cuda").relu() for n in sizes]
+    bitmaps = [torch.empty((n + 31) // 32, dtype=torch.int32, device="cuda") for n in sizes]
+    values = [torch.empty_like(x) for x in xs]
+    word = torch.empty(len(sizes), dtype=torch.int64, pin_memory=True)
+    ws, wsb = bt.new_workspace(max(sizes), torch.float32), bt.new_batch_workspace(sizes, torch.float32)
+    want = [int(torch.count_nonzero(x)) for x in xs]
+    torch.cuda.synchronize()
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def seen(count):
+        end = time.monotonic() + 10
+        while (word[:count] == -1).any() and time.monotonic() < end:
+            pass
+        got = word[:count].tolist()
+        torch.cuda.synchronize()
+        assert word[:count].tolist() == got
+        return got
+    for x, b, v, k in zip(xs, bitmaps, values, want):
+        word.fill_(-1)
+        bt._check("bt_compress", L.bt_compress(x.data_ptr(), x.numel(), bt.BT_F32, b.data_ptr(), v.data_ptr(), v.numel(), word.data_ptr(),
+                                               ws.data_ptr(), ws.numel(), stream))
+        assert seen(1) == [k]
+    word.fill_(-1)
+    items = (bt.CompressItem * len(sizes))(*[bt.CompressItem(x.data_ptr(), x.numel(), b.data_ptr(), v.data_ptr(), v.numel(), word[i:].data_ptr(), None, None)
+                                             for i, (x, b, v) in enumerate(zip(xs, bitmaps, values))])
+    bt.bt_compress_batch(items, len(sizes), torch.float32, wsb)
+    assert seen(len(sizes)) == want
