@@ -29,10 +29,14 @@ def _bytes(t):
 @pytest.mark.parametrize("dtype", DTYPES)
 def test_packing(ag, dtype, deferred):
     g = torch.Generator(device="cuda").manual_seed(5)
-    for shape, zeros in (((4096,), 0.5), ((3, 7, 411), 0.9), ((260 * 8192 + 13,), 0.5), ((64, 64), 1.0), ((10, 1000), 0.0), ((1001, 1003), 0.02)):
+    for shape, zeros, nan in (((4096,), 0.5, True), ((3, 7, 411), 0.9, True), ((260 * 8192 + 13,), 0.5, True), ((64, 64), 1.0, True),
+                              ((10, 1000), 0.0, True), ((1001, 1003), 0.02, True), ((64, 64), 1.0, False), ((260 * 8192 + 13,), 1.0, False)):
         x = torch.randn(shape, generator=g, device="cuda").to(dtype)
         x[torch.rand(shape, generator=g, device="cuda") < zeros] = 0
-        x.view(-1)[7] = float("nan")
+        if nan:
+            x.view(-1)[7] = float("nan")
+        else:
+            assert not x.any()             # no value at all
         got = []
         for t in (x, x.as_subclass(_Sub)):
             stash = ag.BitmapStash(deferred=deferred)
@@ -42,8 +46,9 @@ def test_packing(ag, dtype, deferred):
         (s0, p0, u0), (s1, p1, u1) = got
         assert s0.stats == s1.stats and u0.shape == x.shape and u0.dtype == dtype
         assert torch.equal(_bytes(u0), _bytes(x)) and torch.equal(_bytes(u1), _bytes(x))
-        assert isinstance(p0, ag._Packed) == isinstance(p1, ag._Packed)
+        assert isinstance(p0, ag._Packed) == isinstance(p1, ag._Packed) and (nan or (isinstance(p0, ag._Packed) and p0.dense is None))
         if isinstance(p0, ag._Packed) and p0.dense is None:
+            assert nan or (p0.values.numel() == 0 and s0.stats["compressed"] == 1)
             assert p0.values.untyped_storage().nbytes() == p1.values.untyped_storage().nbytes()
             assert torch.equal(p0.bitmap, p1.bitmap) and torch.equal(p0.index, p1.index) and torch.equal(_bytes(p0.values), _bytes(p1.values))
 

@@ -69,8 +69,8 @@ def test_a_launch_whose_last_tile_gives_up_says_so(bt, oracle, dt):
     _check(bt, oracle, dt, n, 0.5, 5, ws, 1)
 
 
-@pytest.mark.parametrize("dt", ["f32", "bf16", "f64"])
-@pytest.mark.parametrize("tiles", [300, 600])      # without and with a scanner
+# without a scanner (of doubles no launch that waits is) and with one
+@pytest.mark.parametrize("dt,tiles", [("f32", 300), ("bf16", 300), ("f32", 600), ("bf16", 600), ("f64", 460), ("f64", 600)])
 def test_tiles_that_stop_waiting_count_the_bitmap_themselves(bt, oracle, dt, tiles):
     n = tiles * bt.bt_tile_elems(wl.DTYPES[dt]) + 4321
     ws = bt.new_workspace(n, wl.DTYPES[dt])
