@@ -825,10 +825,10 @@ __device__ __forceinline__ bool sum_counts(char *ws, const uint32_t slot, const 
 
 // Pause between two polls of a tile for its prefix.  A launch that the GPU swallows in one go wants the answer soon; where
 // thousands of workgroups come and go, the polls of the two thousand resident ones stand in the way of the scanner's
-// and of the values'.  Measured with pauses of 4 / 16 / 32 x 64 clocks, us: fp32 at 50 % zeros, restore 2 M elements (245
-// tiles) 6.5 / 6.8 / 7.0, 4 M 8.0 / 8.1 / 8.4, 25.7 M (3136 tiles) 26.8 / 26.7 / 26.8; compress 25.7 M 28.3 / 28.3 / 28.8, 4 M
-// 8.6 / 8.9 / 9.0; restore fp16 206 M (12,544 tiles, 5 % zeros) - / 141.4 / 140.7, fp32 206 M - / 211.3 / 209.7; the 49 tensors of
-// a ResNet-50 (79,488 slots) restore - / 610 / 572, compress - / 519 / 514 (48: 568 / 515; 100: 581 / 518).
+// and of the values'.  Measured with pauses of 4 / 16 / 32 x 64 clocks, us: fp32 at 50 % zeros, restore 4.5 M elements (549
+// tiles) 8.5 / 8.7 / 8.9, 8 M 11.4 / 11.6 / 12.0, 12.8 M (1563) 16.3 / 16.2 / 16.5, 25.7 M (3136) 26.9 / 26.7 / 27.0; compress 4 M (489)
+// 8.5 / 8.7 / 8.9, 8 M 11.2 / 11.3 / 11.4, 25.7 M 28.4 / 28.2 / 29.1; restore fp64 2.1 M (513) 8.1 / 8.5 / 8.5, fp16 206 M (12,544 tiles, 5 % zeros)
+// 141.4 / 141.3 / 141.2; the 49 tensors of a ResNet-50 (75,068 slots) restore 611 / 603 / 570, compress 530 / 519 / 515.
 __device__ __forceinline__ void poll_pause(const uint32_t n_slots) {
     if (n_slots >= 8192) __builtin_amdgcn_s_sleep(32);
     else if (n_slots > 1536) __builtin_amdgcn_s_sleep(16);
@@ -1620,9 +1620,11 @@ __device__ __noinline__ uint64_t prefix_from_bitmap(const uint32_t *__restrict__
 // started ends, whatever the others do, and every workgroup is started in the end.
 //
 // MODE kScannedSoon: the header is asked for behind the bitmap words instead of waited for before them.  That takes a round trip off the
-// chain of launches that the GPU holds at once; in larger ones a workgroup that starts sooner only adds to what the stores compete with.
-// Measured, us, kScanned / this: fp32 3.2 M elements 7.6 / 7.3, 4.5 M 8.9 / 8.6, at 95 % zeros 3.2 M 7.8 / 7.3, fp64 3.2 M 11.0 / 10.5, bf16 33 M (2015
-// tiles) 19.5 / 20.0, 67 M at 65 % zeros 29.7 / 30.1.
+// start of a launch; where workgroups come and go, one that starts sooner also adds to what the stores compete with.  The line, at 1024
+// tiles for all elements, is where the 16-bit ones stop to gain; wider ones gain a little beyond it too.  Measured, us, kScanned / this: fp32
+// 4.5 M elements (549 tiles) 8.9 / 8.7, 8 M 11.9 / 11.7, fp64 3.2 M 10.9 / 10.4, bf16 9 M 9.5 / 9.2, 15 M (916) 11.9 / 11.9; beyond the line bf16 21 M
+// (1282) 14.2 / 14.6, 33 M 19.6 / 19.9, 25.7 M at 95 % zeros 14.0 / 13.8, fp32 9 M (1099) 12.9 / 12.7, 12.8 M 16.2 / 16.0, 20 M 22.4 / 22.0, 25.7 M 26.6 / 26.7,
+// fp64 4.5 M (1099) 13.0 / 12.5, 6.4 M 16.4 / 15.9, 12.8 M 26.7 / 26.4.
 // MODE kQuartered: launches on one tensor of up to kQuarterSlots tiles, without a scanner, whose tiles' waves read a quarter of the counts each
 // as in compression (wait_for_quarter); the last tile ends the call.  Two workgroups a compute unit at most, so there are registers.
 // Measured, us, with the scanner / this: fp32 2.2 M elements 7.1 / 6.7, 3.2 M 7.5 / 7.0, 4.2 M 7.9 / 7.3, at 5 % zeros 9.3 / 8.5; bf16 4.5 M
@@ -1726,7 +1728,7 @@ __global__ __launch_bounds__(kBlock, MODE == kQuartered ? 7 : kDecompressOcc) vo
 //   fetch_values  given j at the start of the tile, asks for the values of one phase (PHASE rows of every wave), a contiguous run;
 //   commit_values puts them into LDS, where all waves find them;
 //   expand_row    a value where the bit is set, +0 where it is clear, by rank; 16-byte dense stores.
-// The waves take the tile's rows in turn (wave w rows w, w + 4, ...): a phase is one contiguous piece of the tensor and of the
+// The waves take the tile's rows in turn (of W waves, wave w rows w, w + W, ...): a phase is one contiguous piece of the tensor and of the
 // values, and it is written from front to back.  When every wave had a quarter of the tile with a strip of LDS of its own, a phase
 // was eight pieces, each with element-wise edges and partial cache lines of its own, written at four places at once.
 // (With the scan it is the other way round: quarters publish their counts from a fourth of the loads, and the waves of a tile that
@@ -1794,7 +1796,7 @@ template <int S, int K> struct Rows {
     uint32_t mp[Geo<S, K>::MW], rank2[K / 2];          // two rows' ranks to a register
 };
 
-// The wave's rows among the tile's rows [first, first + 4 K).  `entries`: room for their words, a pair each; a wave writes and reads
+// The wave's rows among the tile's rows [first, first + W * K).  `entries`: room for their words, a pair each; a wave writes and reads
 // those of its own rows only.
 template <int S, int R, int K, int W = kWaves>
 __device__ __forceinline__ Rows<S, K> rows_of(const TileBits<S, R, W> &b, const TileRanks<S, R, W> &r, const int first, bt_u2 *entries, const int lane, const int wave) {
@@ -1926,7 +1928,7 @@ template <int S> __device__ __forceinline__ uint4 expand_row(const unsigned char
     return make_uint4(d[0], d[1], d[2], d[3]);
 }
 
-// The wave's rows [k0, k0 + PHASE) of `rows`, which are rows first + k * 4 + wave of the tile; `before`: set bits of the tile before the phase.
+// The wave's rows [k0, k0 + PHASE) of `rows`, which are rows first + k * W + wave of the tile; `before`: set bits of the tile before the phase.
 template <int S, int R, int K, int W = kWaves>
 __device__ __forceinline__ void expand_phase(const Rows<S, K> &rows, const int k0, const int first, const TileValues<S, R, W> &f, const uint32_t before,
                                              const unsigned char *stage, void *__restrict__ out, const uint64_t n, const uint32_t tile, const int lane,
@@ -2458,7 +2460,7 @@ static bt_status compress_common(const void *d_in, uint64_t n, bt_dtype dtype, b
     // as long as no more than kDirectSlots workgroups poll each other's counts; two rows only up to 64 tiles, beyond which
     // the polling costs more than they save.  An index entry comes from every second or fourth of these tiles.  Measured,
     // us per call on the GPU, before / after: fp32 5 k elements 6.1 / 3.6, 50 k 5.9 / 4.1, 201 k 6.5 / 4.5 (with two rows 4.7), 500 k
-    // 6.3 / 4.9, 1 M 6.6 / 5.2, 2 M (eight rows) 7.3 / 6.2, 3 M (scanner) 8.7 / 8.3; bf16 2 M 7.0 / 5.3.  With an index: bf16 100 k elements
+    // 6.3 / 4.9, 1 M 6.6 / 5.2, 2 M (eight rows) 7.3 / 6.2; bf16 2 M 7.0 / 5.3.  With an index: bf16 100 k elements
     // with the scanner 7.2, without it but in tiles of eight rows 7.3 (by the workspace's place up to 7.6), of two rows 4.8; 800 k,
     // 5 % zeros, 8.7 / 9.2 / 6.3 (four rows); fp32 201 k 6.9 / 6.6 / 4.8.
     using std::integral_constant;
@@ -2473,7 +2475,9 @@ static bt_status compress_common(const void *d_in, uint64_t n, bt_dtype dtype, b
     // for 16-bit elements at once.  Measured, us, with the scanner / this: fp32 2.2 M elements (269 tiles) 7.3 / 6.7, 3.2 M 8.2 / 7.0, at 95 %
     // zeros 7.8 / 6.5, at 5 % 9.1 / 9.0, 3.9 M 8.5 / 7.7, at 5 % 9.3 / 9.5 (not done), 8 M 11.1 / 15.2; pruning 3.2 M 8.4 / 7.4; activation call 3.2 M 8.4 / 8.2;
     // bf16 4.3 M (263) 7.4 / 7.2, 8.4 M (512) 9.0 / 7.9, at 5 % 9.8 / 8.4, at 95 % 8.3 / 7.3, activation call 4.5 M 9.0 / 9.2; fp64 1.6 M (391) 8.2 / 8.0, at 5 %
-    // 8.8 / 9.7, activation call 1.1 M 7.7 / 7.1, 2.1 M (512) 8.9 / 8.1.
+    // 8.8 / 9.7, activation call 1.1 M 7.7 / 7.1, 2.1 M (512) 8.9 / 8.1.  The lines hold for pruning and with an index as well, us, at 50 / 5 / 95 %
+    // zeros: pruning fp32 3.7 M (448) 8.5 / 7.3, 9.1 / 8.6, 7.9 / 6.8, bf16 4.3 M 7.8 / 7.8, 8.9 / 8.3, -, 8.4 M 9.1 / 8.4, 10.0 / 8.8, 8.3 / 7.6, fp16 8.4 M 9.2 / 8.6,
+    // 10.0 / 8.9, 8.5 / 7.8; indexed fp32 3.7 M 8.5 / 7.1, 9.3 / 8.9, 7.8 / 6.5, bf16 8.4 M 8.8 / 7.9, 9.5 / 8.4, 8.1 / 7.1, fp16 8.4 M 8.8 / 7.8, 9.5 / 8.5, -.
     const bool dense = d_dense != nullptr;
     const uint64_t most = s == 4 ? 448 : dense == (s == 8) ? kQuarterSlots : 0;
     if (tiles <= most) return go(eight, integral_constant<int, (int)kQuarterSlots>{});
