@@ -229,8 +229,8 @@ class BitmapStash(torch.autograd.graph.saved_tensors_hooks):
     def _pack_plain(self, t):
         """_pack of an ordinary tensor, around one call that allocates, compresses and, unless deferred, waits and copies (see
         csrc/call.cpp); None if it is no such tensor after all.  (A packing of fp32 [500, 1024], waiting included, 35 -> 19 us; a step of four
-        layers of 1024 features, on fp32 with 8192 rows 1903 -> 1833 us, with 500 rows 897 -> 660, on bf16 with 8192 rows 965 -> 809, deferred
-        875 -> 719.)"""
+        layers of 1024 features, on fp32 with 8192 rows 1915 -> 1830 us, with 500 rows 850 -> 675, on bf16 with 8192 rows 960 -> 820, deferred
+        865 -> 770.)"""
         st = _state(t.device)
         n, dtype = t.numel(), t.dtype
         ws = st.workspace(n, dtype)
